@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "xc_common.h"
+#include "xc_mine.h"
 
 namespace xc {
 
@@ -1225,10 +1226,12 @@ static int rows_slices_per_xcd(int64_t nQT, int sx_max) {
 // bytes of W per flop; they are taken where padding the pool to a multiple of 512 costs no more than
 // padding it to a multiple of 256, or less than a sixteenth of the pool.  XC_MINE_ROWS=narrow or wide
 // in the environment (read at every call) overrides the rule, for A/B timing and for tests.
-static bool rows_wide_items(int64_t Zq) {
+static bool force_rows_layout() {
     const char* e = getenv("XC_MINE_ROWS");
-    if (e != nullptr && e[0] == 'n') return false;
-    if (e != nullptr && e[0] == 'w') return true;
+    return e != nullptr && (e[0] == 'n' || e[0] == 'w');
+}
+static bool rows_wide_items(int64_t Zq) {
+    if (force_rows_layout()) return getenv("XC_MINE_ROWS")[0] == 'w';
     const int64_t pad_w = (Zq + 2 * kBN - 1) / (2 * kBN) * (2 * kBN) - Zq;
     const int64_t pad_n = (Zq + kBN - 1) / kBN * kBN - Zq;
     return pad_w <= pad_n || pad_w * 16 <= Zq;
@@ -1307,6 +1310,14 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     a.zeros = w8 + p.off_zero;
     a.cond = nullptr;
     int32_t* flag = reinterpret_cast<int32_t*>(w8 + p.off_flag);
+
+    // few queries: W is read once and the group maxima take the place of thresholds and lists.  A warm search of one
+    // query tile has nothing to gain there and nothing to repeat; of more, its one sweep is the better way.
+    FewPlan few;
+    if (!(warm && Zq > kBN) && !force_general_kernel() && !force_rows_layout() &&
+        plan_few(Zq, L, a.row_bytes, k_h, t, p.off_glist - p.off_lists, &few))
+        return run_mine_few(few, Z, W, Zq, L, a.row_bytes, k_h, t, w8 + p.off_lists, tau_g,
+                            warm ? flag : nullptr, static_cast<int>(p.nQT) + 1, shortlist, scores, st);
 
     // raise the dynamic LDS limit of the tile kernels: once per device and process (the attribute
     // belongs to the device's copy of the kernel)

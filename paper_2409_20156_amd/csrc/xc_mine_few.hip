@@ -1,0 +1,535 @@
+// The search for few queries: the same exact top-k as xc_mine.hip (score of Sec. 2.1) where the work is
+// reading W once, not the products.  Inference over a handful of queries, small pools.
+//
+//   few_max_kernel     streams W once.  A wave multiplies 32 labels with all queries of the workgroup, whose
+//       rows lie in LDS as MFMA operands, and keeps of every group of 16 << gshift labels the largest score per
+//       query: the only thing written, 1 / (16 << gshift) of the score matrix.
+//   few_finish_kernel  one workgroup per query: the k-th largest group maximum tau (radix select).  At least k
+//       labels score tau or more, so every label of the answer does, and it lies in a group whose maximum is
+//       above tau or, for scores equal to tau, in one of the first groups (in label order) whose maximum is tau:
+//       of equal scores the smaller ids win, and each of these groups holds one.  So k groups in all hold the
+//       answer.  Their scores are formed again, with the same instructions in the same order (hence the same
+//       bits), what is below tau is dropped, the rest sorted.
+// Bound: HBM, one read of W.  131 072 x 768 bf16, 32 queries, k = 5: 72 us in all (first kernel 44 us, 4.5 TB/s of the 5.1
+// a plain copy reaches), where the general kernel took 378; 30 M x 256 bf16, 32 queries: 3.3 ms (4.7 TB/s) against 8.5.  In
+// fp32 with many queries the matrix pipe: 1000 queries x 50 021 x 300, 368 us against 782 (the products alone take 195).
+// No thresholds to find in phases, no lists that could overflow, two launches.  The general kernel pads the
+// pool to 256 queries and sweeps the labels in four or more serial phases, of which the first have fewer work
+// items than the chip has compute units.
+#include "xc_mine.h"
+
+namespace xc {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 few_bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int kFewThreads = 512;
+constexpr int kFewWaves = kFewThreads / kWave;
+constexpr int kFewRing = 8;              // 64-byte steps in flight per wave (two rows of 16 B per lane each: 16 KiB)
+constexpr int kFewTile = 32;             // labels a wave multiplies at a time
+// The second kernel: 1024 threads per query while there are few queries, 256 (and a quarter of the key list, so that
+// eight queries are in flight per compute unit) from 512 queries on: 1000 queries x 50 021 x 300 fp32, k = 32: 118 -> 102 us.
+constexpr int64_t kSmallFinishQueries = 512;
+template <int NT> struct Finish {
+    static constexpr int kWaves = NT / kWave;
+    static constexpr int kKeys = 4 * NT;                // candidate keys of a query in LDS
+};
+constexpr int kRankSort = 512;           // up to so many candidates are sorted by counting
+constexpr int kMaxSplit = 8;             // workgroups per query of the second kernel at most
+constexpr int kPartKeys = Finish<1024>::kKeys / kMaxSplit;      // candidates one of them hands over at most
+static_assert(kPartKeys >= XC_MAX_K_MINE, "a workgroup hands over at least its best k");
+
+template <typename T> struct FewMma;
+template <> struct FewMma<bf16_t> {
+    static __device__ __forceinline__ f32x4 mma(const uint4& a, const uint4& b, f32x4 c) {
+        few_bf16x8 av, bv;
+        __builtin_memcpy(&av, &a, 16);
+        __builtin_memcpy(&bv, &b, 16);
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
+    }
+};
+template <> struct FewMma<float> {
+    static __device__ __forceinline__ f32x4 mma(const uint4& a, const uint4& b, f32x4 c) {
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+        return c;
+    }
+};
+
+struct FewArgs {
+    const unsigned char* Z;
+    const unsigned char* W;
+    int64_t Zq, L, row_bytes;
+    int ks, n_qb, gshift, k;
+    int64_t n_groups;
+    uint32_t* gmax;              // [Zq][n_groups] ordered image of the largest score, 0 = no score that is a number
+    uint32_t* tau_g;
+    int32_t* flag;
+    int n_flag;
+    int32_t* shortlist;
+    float* scores;
+    int n_split;                 // workgroups that share a query in the second kernel
+    uint64_t* part;              // [Zq][n_split][kPartKeys] their candidates
+    int32_t* part_n;             // [Zq][n_split]
+    int32_t* done;               // [Zq] how many of them are through (cleared by the first kernel)
+};
+
+// ordered image of a score; 0 (below every number) for NaN.  -0 counts as +0, as in the result.
+__device__ __forceinline__ uint32_t score_image(float v) { return v == v ? float_to_ordered(v + 0.0f) : 0u; }
+
+// MFMA operands: lane (r, g) = (lane & 15, lane >> 4) holds 16 bytes of row r: chunk 4 s + g of the row in step s, for
+// labels and queries alike.  (Which k a chunk stands for does not matter as long as both sides agree.)
+template <typename T, int NB, bool KTAIL>
+__global__ __launch_bounds__(kFewThreads)
+void few_max_kernel(const FewArgs a) {
+    extern __shared__ __align__(16) unsigned char zlds[];       // [ks][NB] operands of 1 KiB
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int KS = a.ks;
+    // workgroups of one XCD (id % 8) that differ in the query block only are neighbours: they read the same rows of W
+    // at about the same time, and all but the first find them in that XCD's L2
+    const int id = blockIdx.x;
+    const int qb = (id / 8) % a.n_qb;
+    const int wg = (id % 8) + 8 * (id / (8 * a.n_qb));
+    const int n_wg = gridDim.x / a.n_qb;                        // (a multiple of 8, see the launch)
+    const int64_t q0 = static_cast<int64_t>(qb) * NB * 16;
+
+    for (int e = tid; e < KS * NB * 64; e += kFewThreads) {
+        const int l = e & 63, blk = e >> 6;
+        const int s = blk / NB, n = blk % NB;
+        const int64_t q = q0 + n * 16 + (l & 15);
+        const int64_t off = static_cast<int64_t>(s) * 64 + (l >> 4) * 16;
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (q < a.Zq && off < a.row_bytes) v = *reinterpret_cast<const uint4*>(a.Z + q * a.row_bytes + off);
+        *reinterpret_cast<uint4*>(zlds + static_cast<size_t>(e) * 16) = v;
+    }
+    if (id == 0)
+        for (int64_t i = tid; i < a.Zq; i += kFewThreads) a.done[i] = 0;
+    __syncthreads();
+
+    // a unit is the tiles whose maxima one wave combines: a tile of two groups (gshift 0), or 2^(gshift-1) tiles of one
+    const int comb = a.gshift > 0 ? 1 << (a.gshift - 1) : 1;
+    const int64_t n_tiles = (a.L + kFewTile - 1) / kFewTile;
+    const int64_t n_units = (n_tiles + comb - 1) / comb;
+    const int64_t u_step = static_cast<int64_t>(n_wg) * kFewWaves;
+    int64_t unit = static_cast<int64_t>(wg) * kFewWaves + wave;
+    if (unit >= n_units) return;                                // (no barrier below)
+
+    // ---- the load stream: ring of kFewRing steps, running ahead across tiles and units
+    int64_t ld_unit = unit;
+    int ld_t = 0;
+    int ld_off = 0;                                             // bytes into the rows
+    const unsigned char *p0, *p1;
+    auto set_rows = [&]() {
+        const int64_t l = (ld_unit * comb + ld_t) * kFewTile + r;
+        const int64_t l0 = l < a.L ? l : a.L - 1, l1 = l + 16 < a.L ? l + 16 : a.L - 1;      // rows past the end: dropped later
+        p0 = a.W + l0 * a.row_bytes;
+        p1 = a.W + l1 * a.row_bytes;
+    };
+    set_rows();
+    uint4 ra[kFewRing][2];
+    auto load_step = [&](int j) {
+        int64_t off = ld_off + g * 16;
+        if (KTAIL) off = off < a.row_bytes ? off : 0;           // (zeroed where it is used)
+        ra[j][0] = *reinterpret_cast<const uint4*>(p0 + off);
+        ra[j][1] = *reinterpret_cast<const uint4*>(p1 + off);
+        ld_off += 64;
+        if (ld_off == KS * 64) {                                // uniform
+            ld_off = 0;
+            ++ld_t;
+            if (ld_t == comb || ld_unit * comb + ld_t >= n_tiles) { ld_t = 0; ld_unit += u_step; }
+            if (ld_unit < n_units) set_rows();                  // else: the last tile again, never used
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < kFewRing; ++j) load_step(j);
+
+    const bool tail_chunk = static_cast<int64_t>(KS - 1) * 64 + g * 16 >= a.row_bytes;       // this lane's chunk of the last step
+    f32x4 acc[2][NB];
+    // maxima are taken as floats: fmaxf passes over NaN, so a group is NaN only if all its scores are
+    const float nan = __builtin_nanf("");
+    float run[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        run[n] = nan;
+        acc[0][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        acc[1][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    int t = 0, s = 0;
+    for (;;) {
+#pragma unroll
+        for (int j = 0; j < kFewRing; ++j) {
+            uint4 a0 = ra[j][0], a1 = ra[j][1];
+            if (KTAIL && s == KS - 1 && tail_chunk) { a0 = make_uint4(0, 0, 0, 0); a1 = make_uint4(0, 0, 0, 0); }
+            const unsigned char* zb = zlds + static_cast<size_t>(s) * NB * 1024 + lane * 16;
+#pragma unroll
+            for (int n = 0; n < NB; ++n) {
+                const uint4 b = *reinterpret_cast<const uint4*>(zb + n * 1024);
+                acc[0][n] = FewMma<T>::mma(a0, b, acc[0][n]);
+                acc[1][n] = FewMma<T>::mma(a1, b, acc[1][n]);
+            }
+            load_step(j);
+            if (++s == KS) {                                    // uniform: a tile is complete
+                s = 0;
+                const int64_t tile = unit * comb + t;
+                const int64_t lab = tile * kFewTile + 4 * g;    // accumulator i of block b: label lab + 16 b + i, query r
+                const bool full = (tile + 1) * kFewTile <= a.L;
+                const bool unit_done = t + 1 == comb || tile + 1 >= n_tiles;
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    float m[2];
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        if (!full)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                if (lab + 16 * b + i >= a.L) acc[b][n][i] = nan;
+                        m[b] = fmaxf(fmaxf(acc[b][n][0], acc[b][n][1]), fmaxf(acc[b][n][2], acc[b][n][3]));
+                    }
+                    acc[0][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    acc[1][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    const int64_t q = q0 + n * 16 + r;
+                    if (a.gshift == 0) {
+#pragma unroll
+                        for (int b = 0; b < 2; ++b) {
+                            m[b] = fmaxf(m[b], __shfl_xor(m[b], 16, kWave));
+                            m[b] = fmaxf(m[b], __shfl_xor(m[b], 32, kWave));
+                        }
+                        // lanes 0..15 store the first group's maxima, lanes 16..31 the second's
+                        const int64_t grp = 2 * tile + g;
+                        if (g < 2 && q < a.Zq && grp < a.n_groups) a.gmax[q * a.n_groups + grp] = score_image(g == 0 ? m[0] : m[1]);
+                    } else {
+                        run[n] = fmaxf(run[n], fmaxf(m[0], m[1]));
+                        if (unit_done) {
+                            run[n] = fmaxf(run[n], __shfl_xor(run[n], 16, kWave));
+                            run[n] = fmaxf(run[n], __shfl_xor(run[n], 32, kWave));
+                            if (g == 0 && q < a.Zq) a.gmax[q * a.n_groups + unit] = score_image(run[n]);
+                            run[n] = nan;
+                        }
+                    }
+                }
+                ++t;
+                if (unit_done) { t = 0; unit += u_step; if (unit >= n_units) return; }
+            }
+        }
+    }
+}
+
+// Bitonic sort of keys[0..n), n <= Finish<NT>::kKeys, by the whole workgroup (ascending; padded with sentinels).
+template <int NT>
+__device__ void block_sort(uint64_t* keys, int n) {
+    int n2 = 64;
+    while (n2 < n) n2 <<= 1;
+    for (int e = n + static_cast<int>(threadIdx.x); e < n2; e += NT) keys[e] = kKeySentinel;
+    __syncthreads();
+    for (int size = 2; size <= n2; size <<= 1)
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            for (int e = threadIdx.x; e < n2 / 2; e += NT) {
+                const int lo = 2 * e - (e & (stride - 1));
+                const int hi = lo + stride;
+                const bool up = (lo & size) == 0;
+                const uint64_t x = keys[lo], y = keys[hi];
+                if ((x > y) == up) { keys[lo] = y; keys[hi] = x; }
+            }
+            __syncthreads();
+        }
+}
+
+// Exclusive prefix sum over the workgroup; `total` gets the sum.  `sh` holds a value per wave.
+template <int NT>
+__device__ __forceinline__ int block_excl_scan(int v, int* sh, int* total) {
+    const int incl = wave_incl_scan(v);
+    const int w = threadIdx.x >> 6;
+    __syncthreads();
+    if (lane_id() == kWave - 1) sh[w] = incl;
+    __syncthreads();
+    int before = 0, all = 0;
+#pragma unroll
+    for (int i = 0; i < Finish<NT>::kWaves; ++i) { before += i < w ? sh[i] : 0; all += sh[i]; }
+    *total = all;
+    return before + incl - v;
+}
+
+template <typename T, int NT>
+__global__ __launch_bounds__(NT)
+void few_finish_kernel(const FewArgs a) {
+    __shared__ uint64_t keys[Finish<NT>::kKeys];
+    __shared__ int hist[2048];
+    __shared__ int sh[Finish<NT>::kWaves];
+    __shared__ int32_t groups[XC_MAX_K_MINE];
+    __shared__ int n_sel, n_key, sel_bin, sel_need, sel_have;
+    __shared__ uint32_t tau_sh;
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t q = blockIdx.x / a.n_split;
+    const int split = blockIdx.x % a.n_split;
+    const uint32_t* gm = a.gmax + q * a.n_groups;
+    if (a.flag != nullptr && blockIdx.x == 0)
+        for (int i = tid; i < a.n_flag; i += NT) a.flag[i] = 0;
+
+    // ---- the k-th largest group maximum: digits of 11, 11, 10 bits, from the top
+    uint32_t prefix = 0;           // the digits found so far
+    int bits = 32;                 // bits below them
+    int need = a.k;                // groups still to take among those that share the prefix
+    bool all = false, exact = false;
+    for (int pass = 0; pass < 3; ++pass) {
+        const int width = pass < 2 ? 11 : 10;
+        for (int d = tid; d < 2048; d += NT) hist[d] = 0;
+        __syncthreads();
+        for (int64_t i = tid; i < a.n_groups; i += NT) {
+            const uint32_t o = gm[i];
+            if (o != 0 && (pass == 0 || (o >> bits) == prefix))
+                atomicAdd(&hist[(o >> (bits - width)) & ((1u << width) - 1u)], 1);
+        }
+        __syncthreads();
+        constexpr int kPer = 2048 / NT;                                        // digits per thread, largest first
+        int c[kPer], local = 0, total;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) { c[j] = hist[2047 - kPer * tid - j]; local += c[j]; }
+        int before = block_excl_scan<NT>(local, sh, &total);
+        if (pass == 0 && total <= a.k) { all = true; break; }                  // uniform: no more groups than wanted
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            if (before < need && need <= before + c[j]) { sel_bin = 2047 - kPer * tid - j; sel_need = need - before; sel_have = c[j]; }
+            before += c[j];
+        }
+        __syncthreads();
+        bits -= width;
+        prefix = (prefix << width) | static_cast<uint32_t>(sel_bin);
+        need = sel_need;
+        if (sel_have == need) { exact = true; break; }                         // uniform: all that share the prefix
+        __syncthreads();
+    }
+    // taken: every group above the prefix, and `need` of those that share it (all of them if `exact`; else the
+    // prefix is a whole score and the first `need` in label order are taken)
+    if (tid == 0) { n_sel = 0; n_key = 0; tau_sh = 0xffffffffu; }
+    __syncthreads();
+    const uint32_t bound = all ? 1u : (exact ? prefix << bits : prefix + 1u);  // (prefix + 1 cannot wrap: that is a NaN image)
+    for (int64_t i = tid; i < a.n_groups; i += NT) {
+        const uint32_t o = gm[i];
+        if (o >= bound) {
+            groups[atomicAdd(&n_sel, 1)] = static_cast<int32_t>(i);
+            atomicMin(&tau_sh, o);
+        }
+    }
+    if (!all && !exact) {
+        __syncthreads();
+        const int first = n_sel;
+        int got = 0;
+        for (int64_t i0 = 0; got < need; i0 += NT) {               // uniform (need <= their number)
+            const int64_t i = i0 + tid;
+            const bool tie = i < a.n_groups && gm[i] == prefix;
+            int total;
+            const int at = got + block_excl_scan<NT>(tie ? 1 : 0, sh, &total);
+            if (tie && at < need) groups[first + at] = static_cast<int32_t>(i);
+            got += total;
+        }
+        __syncthreads();
+        if (tid == 0) { n_sel = first + need; tau_sh = prefix; }
+    }
+    __syncthreads();
+    // in label order: the workgroups that share the query have to agree on whose block is whose
+    {
+        int32_t mine = 0;
+        int rank = 0;
+        if (tid < n_sel) {
+            mine = groups[tid];
+            for (int e = 0; e < n_sel; ++e) rank += groups[e] < mine ? 1 : 0;
+        }
+        __syncthreads();
+        if (tid < n_sel) groups[rank] = mine;
+        __syncthreads();
+    }
+    const int n_blocks = n_sel << a.gshift;                    // blocks of 16 labels
+    const uint32_t tau = all ? 1u : tau_sh;
+
+    // ---- the scores of these groups again: one query in all 16 columns of the product
+    const int r = lane & 15, g = lane >> 4;
+    const bool may_overflow = (n_blocks / a.n_split + 1) * 16 > Finish<NT>::kKeys;
+    const unsigned char* zrow = a.Z + q * a.row_bytes;
+    const int n_mine = (n_blocks - split + a.n_split - 1) / a.n_split;          // blocks split, split + n_split, ...
+    for (int b0 = 0; b0 < n_mine; b0 += Finish<NT>::kWaves) {
+        const int b = split + (b0 + wave) * a.n_split;
+        if (b < n_blocks) {
+            const int64_t l0 = ((static_cast<int64_t>(groups[b >> a.gshift]) << a.gshift) + (b & ((1 << a.gshift) - 1))) * 16;
+            const int64_t lr = l0 + r < a.L ? l0 + r : a.L - 1;
+            const unsigned char* wrow = a.W + lr * a.row_bytes;
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            const int full = static_cast<int>(a.row_bytes / 64);
+#pragma unroll 8
+            for (int s = 0; s < full; ++s) {
+                const uint4 w = *reinterpret_cast<const uint4*>(wrow + s * 64 + g * 16);
+                const uint4 z = *reinterpret_cast<const uint4*>(zrow + s * 64 + g * 16);
+                acc = FewMma<T>::mma(w, z, acc);
+            }
+            if (full < a.ks) {
+                uint4 w = make_uint4(0, 0, 0, 0), z = make_uint4(0, 0, 0, 0);
+                if (full * 64 + g * 16 < a.row_bytes) {
+                    w = *reinterpret_cast<const uint4*>(wrow + full * 64 + g * 16);
+                    z = *reinterpret_cast<const uint4*>(zrow + full * 64 + g * 16);
+                }
+                acc = FewMma<T>::mma(w, z, acc);
+            }
+            const float v = (r & 2) ? ((r & 1) ? acc[3] : acc[2]) : ((r & 1) ? acc[1] : acc[0]);
+            const int64_t lab = l0 + 4 * g + r;
+            if (r < 4 && lab < a.L && score_image(v) >= tau)
+                keys[atomicAdd(&n_key, 1)] = make_key(v + 0.0f, static_cast<int32_t>(lab));
+        }
+        if (may_overflow) {                                    // uniform
+            __syncthreads();
+            if (n_key > Finish<NT>::kKeys - Finish<NT>::kWaves * 16) {     // the next round might not fit: keep the best k
+                const int n = n_key;
+                block_sort<NT>(keys, n);
+                if (tid == 0) n_key = n < a.k ? n : a.k;
+            }
+            __syncthreads();
+        }
+    }
+    __syncthreads();
+    int n = n_key;
+    if (a.n_split > 1) {
+        // hand the candidates over; whoever comes last has all of them and finishes the query (nobody waits)
+        if (n > kPartKeys) { block_sort<NT>(keys, n); n = a.k; }
+        // (stores at agent scope, acknowledged before the count goes up: no cache has to be written back for them, which
+        // a fence at that scope would do for the whole XCD - with it, 64 queries of 512-byte rows took 134 us, not 33)
+        uint64_t* part = a.part + (q * a.n_split + split) * kPartKeys;
+        for (int e = tid; e < n; e += NT)
+            __hip_atomic_store(&part[e], keys[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_store(&a.part_n[q * a.n_split + split], n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0);                         // this wave's stores have arrived ...
+        __syncthreads();                                       // ... and everyone's
+        if (tid == 0) sel_have = __hip_atomic_fetch_add(&a.done[q], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __syncthreads();
+        if (sel_have != a.n_split - 1) return;                 // uniform
+        n = 0;
+        for (int sp = 0; sp < a.n_split; ++sp) {
+            const int np = __hip_atomic_load(&a.part_n[q * a.n_split + sp], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const uint64_t* from = a.part + (q * a.n_split + sp) * kPartKeys;
+            for (int e = tid; e < np; e += NT)
+                keys[n + e] = __hip_atomic_load(&from[e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            n += np;
+        }
+        __syncthreads();
+    }
+    int32_t* ids = a.shortlist + q * a.k;
+    float* sc = a.scores != nullptr ? a.scores + q * a.k : nullptr;
+    auto put = [&](int rank, uint64_t key) {
+        ids[rank] = key_id(key);
+        if (sc != nullptr) sc[rank] = key_score(key);
+        if (rank == a.k - 1) a.tau_g[q] = float_to_ordered(key_score(key));
+    };
+    if (n <= kRankSort) {                                      // a key's place is the number of smaller keys
+        for (int m = tid; m < n; m += NT) {
+            const uint64_t mine = keys[m];
+            int rank = 0;
+            for (int e = 0; e < n; ++e) rank += keys[e] < mine ? 1 : 0;
+            if (rank < a.k) put(rank, mine);
+        }
+    } else {
+        block_sort<NT>(keys, n);
+        if (tid < a.k) put(tid, keys[tid]);
+    }
+    if (tid < a.k && tid >= n) {
+        ids[tid] = -1;
+        if (sc != nullptr) sc[tid] = -INFINITY;
+    }
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+constexpr size_t kFewLds = 144u << 10;       // LDS for the query block at most
+constexpr int64_t kFewQueries = 256;         // up to so many queries always
+constexpr int64_t kFewMaxQueries = 2048;     // beyond that never
+
+// Which searches come here.  Up to 256 queries (one query tile of the general kernel, mostly padding) all whose query
+// block fits LDS: 131 072 x 768 bf16, k = 5: 57 us against 397 at 64 queries, 121 against 328 at 256; 4 M x 256 bf16,
+// k = 50: 0.67 ms against 1.57 at 64 queries, 1.60 against 1.84 at 256.  More queries cost this path time in proportion
+// (it reads W once per 64 queries), the general kernels almost nothing until their tiles of 256 x 256 fill the chip
+// several times over; the line lies where that many tiles per compute unit were measured equal:
+//   bf16  768 x 131 072:  512 queries (4 tiles per CU) 222 : 328 us, 1024 (8) 426 : 371
+//         256 x 131 072: 1024 queries (8 tiles per CU) 243 : 467 us, 2048 (16) 468 : 595;  4 M labels, 384 (122) 2.6 : 1.9 ms
+//         768 x 16 000, k = 100: 512 queries 217 : 249 us, 1024 419 : 251 - there the rows read again by the second
+//         kernel (16 k per query) are the cost, hence the second line at 1.3 GB of them
+//   fp32  300 x 50 021:  1024 queries (3 tiles per CU) 394 : 775 us;  128 x 500 000: 512 (15) 0.70 : 1.32 ms, 1024 (30) 1.39 : 1.34
+bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, size_t scratch, FewPlan* p) {
+    if (Zq > kFewQueries) {
+        const int64_t tiles = ((Zq + 255) / 256) * ((L + 255) / 256);
+        if (Zq > kFewMaxQueries || tiles > (t == XC_F32 ? 16 : 6) * 256) return false;
+        if (static_cast<double>(Zq) * k * 16.0 * static_cast<double>(row_bytes) > 1.3e9) return false;
+    }
+    const int64_t ks = (row_bytes + 63) / 64;
+    if (ks * 1024 > static_cast<int64_t>(kFewLds)) return false;
+    p->ks = static_cast<int>(ks);
+    int nb = 1;
+    while (nb < 4 && nb * 16 < Zq && static_cast<size_t>(2 * nb * ks) * 1024 <= kFewLds) nb <<= 1;
+    p->nb = nb;
+    p->n_qb = static_cast<int>((Zq + nb * 16 - 1) / (nb * 16));
+    p->lds = static_cast<size_t>(nb) * ks * 1024;
+    // groups of 16 labels (least to compute again) while a query has at most 2^17 of them
+    int gs = 0;
+    while (gs < 4 && (L >> (4 + gs)) > (1 << 17)) ++gs;
+    p->gshift = gs;
+    p->n_groups = (L + (16LL << gs) - 1) / (16LL << gs);
+    // the second kernel: as many workgroups per query as give each wave one block of 16 labels, within what the chip holds
+    int ns = 1;
+    while (ns < kMaxSplit && Zq * ns * 2 <= 256 && (static_cast<int64_t>(k) << gs) > ns * Finish<1024>::kWaves) ns <<= 1;
+    p->n_split = ns;
+    const size_t q = static_cast<size_t>(Zq);
+    return round_up(q * p->n_groups * 4, 256) + q * ns * kPartKeys * 8 + round_up(q * ns * 4, 256) + q * 4 <= scratch;
+}
+
+template <typename T>
+static int launch_few(const FewPlan& p, const FewArgs& a, hipStream_t st) {
+    const bool ktail = a.row_bytes % 64 != 0;
+    // workgroups: two per compute unit where two query blocks fit its LDS, as many label ranges as that leaves per
+    // query block, in multiples of the 8 XCDs, and no more than there are tiles
+    int64_t per_qb = (p.lds <= (76u << 10) ? 512 : 256) / p.n_qb;
+    const int64_t tiles = (a.L + kFewTile - 1) / kFewTile;
+    const int64_t enough = (tiles + kFewWaves - 1) / kFewWaves;
+    per_qb = per_qb < enough ? per_qb : (enough + 7) / 8 * 8;
+    per_qb = per_qb < 8 ? 8 : per_qb / 8 * 8;                 // (never more workgroups than are resident at once)
+    const dim3 grid(static_cast<unsigned>(per_qb * p.n_qb));
+    typedef void (*Fn)(const FewArgs);
+    const Fn fn = p.nb == 1 ? (ktail ? &few_max_kernel<T, 1, true> : &few_max_kernel<T, 1, false>)
+                : p.nb == 2 ? (ktail ? &few_max_kernel<T, 2, true> : &few_max_kernel<T, 2, false>)
+                            : (ktail ? &few_max_kernel<T, 4, true> : &few_max_kernel<T, 4, false>);
+    if (p.lds > (64u << 10))
+        XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         static_cast<int>(kFewLds)));
+    XC_LAUNCH(K_MINE_TILE, st, (fn<<<grid, kFewThreads, p.lds, st>>>(a)));
+    XC_HIP_CHECK(hipGetLastError());
+    if (a.Zq >= kSmallFinishQueries)
+        XC_LAUNCH(K_MINE_SELECT, st, (few_finish_kernel<T, 256><<<static_cast<unsigned>(a.Zq * a.n_split), 256, 0, st>>>(a)));
+    else
+        XC_LAUNCH(K_MINE_SELECT, st, (few_finish_kernel<T, 1024><<<static_cast<unsigned>(a.Zq * a.n_split), 1024, 0, st>>>(a)));
+    XC_HIP_CHECK(hipGetLastError());
+    return XC_OK;
+}
+
+int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int64_t L, int64_t row_bytes, int k,
+                 xc_dtype t, unsigned char* scratch, uint32_t* tau_g, int32_t* flag, int n_flag, int32_t* shortlist,
+                 float* scores, hipStream_t st) {
+    FewArgs a;
+    a.Z = static_cast<const unsigned char*>(Z);
+    a.W = static_cast<const unsigned char*>(W);
+    a.Zq = Zq; a.L = L; a.row_bytes = row_bytes;
+    a.ks = p.ks; a.n_qb = p.n_qb; a.gshift = p.gshift; a.k = k;
+    a.n_groups = p.n_groups;
+    a.tau_g = tau_g; a.flag = flag; a.n_flag = n_flag;
+    a.shortlist = shortlist; a.scores = scores;
+    a.n_split = p.n_split;
+    unsigned char* s = scratch;
+    a.gmax = reinterpret_cast<uint32_t*>(s); s += round_up(static_cast<size_t>(Zq) * p.n_groups * 4, 256);
+    a.part = reinterpret_cast<uint64_t*>(s); s += static_cast<size_t>(Zq) * p.n_split * kPartKeys * 8;
+    a.part_n = reinterpret_cast<int32_t*>(s); s += round_up(static_cast<size_t>(Zq) * p.n_split * 4, 256);
+    a.done = reinterpret_cast<int32_t*>(s);
+    return t == XC_BF16 ? launch_few<bf16_t>(p, a, st) : launch_few<float>(p, a, st);
+}
+
+}  // namespace xc
