@@ -222,3 +222,23 @@ def test_pps_pipeline_from_mined_scores():
     ref = orc.xc_step(Z64, W64, pos, neg_o, logq_o, 0.3, storage="f32")
     assert abs(float(out["loss"].item()) - ref["loss"]) <= TOL["f32"] * abs(ref["loss"])
     check_rows_close(out["dZ"].cpu().numpy(), ref["dZ"], TOL["f32"], "dZ")
+
+
+@pytest.mark.parametrize("k_h", [1, 3, 4, 5, 64, 65, 255, 256, 257, 300])
+def test_sample_orders_short_rows_by_counting(k_h):
+    """Rows of up to 256 ids are ordered by counting, longer ones sorted: rows without repeats, with repeats, with padding,
+    of one id only, next to each other."""
+    import paper_2409_20156_amd as xc
+    L, k_r, seed = 1000, 77, 5
+    rng = np.random.default_rng(k_h)
+    sl = np.stack([rng.permutation(L)[:k_h] for _ in range(6)]).astype(np.int32)
+    sl[1, k_h // 2:] = sl[1, 0]                       # repeats
+    sl[2, ::3] = -1                                   # padding
+    sl[3] = 999                                       # one id
+    sl[4] = -1                                        # none
+    sl[5, -1] = L                                     # out of range
+    neg, logq = xc.sample_negatives(torch.tensor(sl, device="cuda:0"), k_h, k_r, L, seed)
+    torch.cuda.synchronize()
+    neg_o, logq_o = orc.sample_negatives(sl, 6, k_h, k_r, L, seed=seed)
+    assert (neg.cpu().numpy() == neg_o).all()
+    assert np.allclose(logq.cpu().numpy(), logq_o, rtol=2e-7, atol=1e-7)
