@@ -274,3 +274,19 @@ def test_step_wide_keys_in_a_narrow_label_range():
     neg[:, -5:] = L - 1 - np.arange(5)                       # and a few at the far end of the label range
     logq = np.log(rng.uniform(0.05, 1.0, size=(B, n_neg))).astype(np.float32)
     _run_and_check(Z, W, pos, neg, logq, f64(Z), f64(W), 0.2, orc.LOSS_BCE)
+
+
+@pytest.mark.parametrize("B,n_neg,L", [
+    (1, 1, 300), (31, 32, 50), (32, 31, 4096), (41, 24, 4096),                  # 2, 1023, 1024, 1025 pairs
+    (32, 63, 4096), (683, 2, 4096), (64, 63, 700), (64, 63, 3000000),           # 2048, 2049, 4096 pairs; 64-bit elements
+    (241, 16, 3000000), (30, 30, 3000000), (1, 4095, 40),                       # 4097 pairs: the general sort; few labels
+])
+def test_step_small_pair_sort(B, n_neg, L):
+    """Steps of up to 4096 pairs sort them in one workgroup: both element widths, one to four elements per thread, a
+    last one partly filled, masked pairs among them; labels with one and with many pairs."""
+    print("case", B, n_neg, L, flush=True)
+    Z, W, pos, neg, logq, Z64, W64 = _inputs(31, B, L, 8, torch.float32, 1, 0, n_neg)
+    neg[0, n_neg // 2] = -1
+    neg[B // 2, 0] = pos[B // 2, 0]
+    for kind in (orc.LOSS_BCE, orc.LOSS_SOFTMAX):
+        _run_and_check(Z, W, pos, neg, logq, Z64, W64, 0.2, kind)
