@@ -1223,18 +1223,23 @@ static int rows_slices_per_xcd(int64_t nQT, int sx_max) {
 }
 
 // Work items of 512 queries (the row kernel with all eight waves along the queries) stage half the
-// bytes of W per flop; they are taken where padding the pool to a multiple of 512 costs no more than
-// padding it to a multiple of 256, or less than a sixteenth of the pool.  XC_MINE_ROWS=narrow or wide
-// in the environment (read at every call) overrides the rule, for A/B timing and for tests.
+// bytes of W per flop, but there are half as many of them: they are taken where they keep the 32 compute
+// units of an XCD busy with one label slice, as well as items of 256 would.  Measured, 256 against 512:
+// 4 M x 256, k = 50: 512 queries 1.90 : 3.43 ms, 2048 4.25 : 4.53, 8192 14.9 : 14.9, 16 384 28.8 : 28.0;
+// 1.3 M x 128: 4096 queries 2.31 : 2.46 ms, 16 384 8.2 : 7.6.  XC_MINE_ROWS=narrow or wide in the
+// environment (read at every call) overrides the rule, for A/B timing and for tests.
 static bool force_rows_layout() {
     const char* e = getenv("XC_MINE_ROWS");
     return e != nullptr && (e[0] == 'n' || e[0] == 'w');
 }
 static bool rows_wide_items(int64_t Zq) {
     if (force_rows_layout()) return getenv("XC_MINE_ROWS")[0] == 'w';
-    const int64_t pad_w = (Zq + 2 * kBN - 1) / (2 * kBN) * (2 * kBN) - Zq;
-    const int64_t pad_n = (Zq + kBN - 1) / kBN * kBN - Zq;
-    return pad_w <= pad_n || pad_w * 16 <= Zq;
+    const int64_t wide = (Zq + 2 * kBN - 1) / (2 * kBN), narrow = (Zq + kBN - 1) / kBN;
+    if (wide < kCusPerXcd) return false;
+    // compute units that a full set of rounds would have busy, against those that are: wide / its rounds >= narrow / its
+    // rounds, crosswise
+    const int64_t rw = (wide + kCusPerXcd - 1) / kCusPerXcd, rn = (narrow + kCusPerXcd - 1) / kCusPerXcd;
+    return 17 * wide * rn >= 16 * narrow * rw;
 }
 
 static int plan_mine(int64_t Zq, int64_t L, int d, int k_h, xc_dtype t, MinePlan* p) {
