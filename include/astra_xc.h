@@ -69,7 +69,12 @@ int xc_version(void);
  * Two environment variables, read at every call, only choose between kernels
  * that return the same result (for A/B timing and tests): XC_MINE_GENERAL=1
  * sends every shape through the general tile kernel; XC_MINE_ROWS=narrow or
- * wide fixes the work-item width of the kernel for bf16 rows of 128..512 bytes.
+ * wide fixes the work-item width of the kernel for bf16 rows of 128..512 bytes
+ * (with either set, the kernels for few queries and the 8-bit filter stay out).
+ * xc_mine_workspace includes room for the 8-bit filter where a search takes it
+ * (bf16 rows of 256 or 512 bytes, at least 4096 queries and 2^20 labels: up to
+ * 545 MB); a workspace without that room is accepted as before, and the search
+ * then runs in bf16 throughout.
  * ------------------------------------------------------------------------- */
 int xc_mine_workspace(int64_t Zq, int64_t L, int d, int k_h, xc_dtype t, size_t* bytes);
 int xc_mine_negatives(const void* Z, const void* W, int64_t Zq, int64_t L, int d, int k_h,

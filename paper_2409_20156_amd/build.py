@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB_PATH = os.path.join(HERE, "libastra_xc.so")
-SOURCES = ["xc_api.hip", "xc_mine.hip", "xc_mine_few.hip", "xc_sample.hip", "xc_step.hip"]
+SOURCES = ["xc_api.hip", "xc_mine.hip", "xc_mine_few.hip", "xc_mine_q8.hip", "xc_sample.hip", "xc_step.hip"]
 
 
 def build(verbose: bool = False) -> str:

@@ -1,9 +1,78 @@
-// What the two search files share: the search of few queries (xc_mine_few.hip), called by xc_mine.hip.
+// What the search files share: tile geometry, the direct global->LDS loads, and the two other searches that xc_mine.hip
+// calls (few queries: xc_mine_few.hip; the 8-bit filter of long label ranges: xc_mine_q8.hip).
 #pragma once
+
+#include <type_traits>
 
 #include "xc_common.h"
 
 namespace xc {
+
+constexpr int kBM = 256;            // labels per tile   (MFMA M)
+constexpr int kBN = 256;            // queries per tile  (MFMA N)
+constexpr int kStageBytes = 128;    // bytes of a row staged in LDS per K step (= LDS row pitch; the
+                                    // 16-byte chunks of a row are stored swizzled, see lds_chunk_swizzle)
+constexpr int kCandCap = 1024;      // keys per query candidate list
+constexpr int kPool = 320;          // passing scores a wave parks in LDS before it empties them into the lists
+constexpr int kPoolCheck = 4;       // accumulators between two looks at the pool's fill (each adds <= 64 entries)
+constexpr int kPoolKeep = kPool - kPoolCheck * 64;      // entries a wave may carry from one tile to the next
+constexpr int kMineThreads = 512;   // 8 waves: 2 along labels x 4 along queries
+constexpr int kMineWaves = kMineThreads / kWave;
+static_assert(kPoolKeep >= 0, "the pool holds what can arrive between two looks at its fill");
+constexpr int kMineGrid = 256;      // persistent workgroups, one per compute unit
+constexpr int kXcds = 8;            // workgroup w runs on XCD w % 8
+constexpr int kCusPerXcd = kMineGrid / kXcds;
+constexpr int kPhaseGrowth = 8;     // labels of a phase / labels before it
+constexpr int kMaxSlices = 64;      // label slices of a phase at most (one lane per slice in the select)
+constexpr int kSelectRegs = 16;     // keys per lane held in registers by the phase select
+constexpr uint32_t kTauInit = 0x007fffffu;   // ordered image of -inf
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+constexpr int kRing = 8;            // stages in LDS (8 or 16 KiB each)
+static_assert(kRing >= 4 && (kRing & (kRing - 1)) == 0, "stage slots are indexed modulo a power of two, and the two halves of the workgroup fill them in turn");
+
+__device__ __forceinline__ void lds_dma16(const void* gptr, uint32_t lds_addr /* wave-uniform */) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+                 :: "v"(gptr), "s"(lds_addr) : "memory");
+}
+// The same with a wave-uniform 64-bit base and a 32-bit lane offset: no vector arithmetic is needed
+// to form the address, so issuing the load never competes with another wave's MFMAs for the VALU.
+template <int V> using IC = std::integral_constant<int, V>;
+
+template <int kLdsOffset>
+__device__ __forceinline__ void lds_dma16_sbase(const void* sbase /* wave-uniform */, uint32_t voff,
+                                                uint32_t lds_addr /* wave-uniform; kLdsOffset is added */) {
+    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                 :: "v"(voff), "s"(sbase), "s"(lds_addr), "n"(kLdsOffset) : "memory", "scc");
+}
+__device__ __forceinline__ void wait_all_vmem() {
+    __builtin_amdgcn_s_waitcnt(0x0070 | 0x0f00);      // vmcnt(0); expcnt and lgkmcnt untouched
+}
+
+// The lane number, computed where it is asked for (the compiler can neither hoist nor keep it).
+__device__ __forceinline__ uint32_t lane_now() {
+    uint32_t l;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
+    return l;
+}
+
+template <int N>
+__device__ __forceinline__ void wait_vmem_at_most() {   // until at most N vector memory operations are outstanding
+    __builtin_amdgcn_s_waitcnt((N & 0xf) | ((N >> 4) << 14) | 0x0070 | 0x0f00);
+}
+
+// Stage fill of the last, ragged label tile: per-lane addresses, rows past the end repeat the last row.
+__device__ __noinline__ void issue_stage_ragged(const unsigned char* W, int64_t L, int64_t row, int row_bytes, int kbyte,
+                                                uint32_t dcol0, uint32_t dcol1, uint32_t dst, int n_instr) {
+#pragma unroll 1
+    for (int t = 0; t < n_instr; ++t) {
+        int64_t r = row + 8 * t;
+        r = r < L ? r : L - 1;
+        lds_dma16(W + r * row_bytes + kbyte + ((t & 1) ? dcol1 : dcol0), __builtin_amdgcn_readfirstlane(dst + t * 1024));
+    }
+}
 
 struct FewPlan {
     int ks;                  // 64-byte steps of a row
@@ -22,5 +91,32 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, size_
 int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int64_t L, int64_t row_bytes, int k,
                  xc_dtype t, unsigned char* scratch, uint32_t* tau_g, int32_t* flag /* null: leave alone */, int n_flag,
                  int32_t* shortlist, float* scores, hipStream_t st);
+
+// ---- the 8-bit filter (xc_mine_q8.hip)
+constexpr int64_t kQ8MinQueries = 4096, kQ8MinLabels = 1 << 20;
+constexpr int64_t kQ8ChunkBytes = 512ll << 20;       // 8-bit rows held at a time
+constexpr int64_t kQ8FirstTile = 512;                // label tiles that the bf16 phases cover first (a threshold to filter with)
+constexpr int kQ8Growth = 3;                         // labels of a chunk / labels before it, at most
+
+struct Q8Plan {
+    int nk;                                          // row bytes / 256; 0 = not used
+    int64_t chunk;                                   // labels at a time
+    size_t off_rows, off_meta, off_z, off_zpar, off_base, off_flag, bytes;      // within its part of the workspace
+};
+struct Q8Chunk {
+    const void *Z, *W;
+    int64_t Zq, lab0, lab1;
+    int kcap, glist_cap, max_slices;
+    uint64_t *lists, *glist;
+    int32_t* gcnt;
+    const uint32_t* tau_g;
+};
+
+bool plan_q8(int64_t Zq, int64_t L, int64_t row_bytes, xc_dtype t, Q8Plan* p);
+int q8_begin(const Q8Plan& p, unsigned char* ws, const void* Z, int64_t Zq, hipStream_t st);
+// Filters labels [lab0, lab1) and appends the keys of those that reach the thresholds to the queries' global lists, except
+// for query tiles qt whose flag q8_flags()[1 + qt] is set afterwards (then [0] is too): for these the caller searches the range itself.
+int q8_chunk(const Q8Plan& p, unsigned char* ws, const Q8Chunk& c, hipStream_t st);
+const int32_t* q8_flags(const Q8Plan& p, const unsigned char* ws);
 
 }  // namespace xc

@@ -33,28 +33,6 @@
 
 namespace xc {
 
-constexpr int kBM = 256;            // labels per tile   (MFMA M)
-constexpr int kBN = 256;            // queries per tile  (MFMA N)
-constexpr int kStageBytes = 128;    // bytes of a row staged in LDS per K step (= LDS row pitch; the
-                                    // 16-byte chunks of a row are stored swizzled, see lds_chunk_swizzle)
-constexpr int kCandCap = 1024;      // keys per query candidate list
-constexpr int kPool = 320;          // passing scores a wave parks in LDS before it empties them into the lists
-constexpr int kPoolCheck = 4;       // accumulators between two looks at the pool's fill (each adds <= 64 entries)
-constexpr int kPoolKeep = kPool - kPoolCheck * 64;      // entries a wave may carry from one tile to the next
-constexpr int kMineThreads = 512;   // 8 waves: 2 along labels x 4 along queries
-constexpr int kMineWaves = kMineThreads / kWave;
-static_assert(kPoolKeep >= 0, "the pool holds what can arrive between two looks at its fill");
-constexpr int kMineGrid = 256;      // persistent workgroups, one per compute unit
-constexpr int kXcds = 8;            // workgroup w runs on XCD w % 8
-constexpr int kCusPerXcd = kMineGrid / kXcds;
-constexpr int kPhaseGrowth = 8;     // labels of a phase / labels before it
-constexpr int kMaxSlices = 64;      // label slices of a phase at most (one lane per slice in the select)
-constexpr int kSelectRegs = 16;     // keys per lane held in registers by the phase select
-constexpr uint32_t kTauInit = 0x007fffffu;   // ordered image of -inf
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-
 // ---------------------------------------------------------------------------
 // Reduce a candidate list of n > k keys to its k smallest keys (best scores).
 // One wave; n <= 64*R keys, fetched by load(index) and held in registers.  Radix select, most significant byte first, with a
@@ -196,24 +174,6 @@ struct MineArgs {
 // that the compiler does not serialise later LDS reads behind them; they are awaited with an
 // explicit vmcnt wait followed by a workgroup barrier.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ void lds_dma16(const void* gptr, uint32_t lds_addr /* wave-uniform */) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
-                 :: "v"(gptr), "s"(lds_addr) : "memory");
-}
-// The same with a wave-uniform 64-bit base and a 32-bit lane offset: no vector arithmetic is needed
-// to form the address, so issuing the load never competes with another wave's MFMAs for the VALU.
-template <int V> using IC = std::integral_constant<int, V>;
-
-template <int kLdsOffset>
-__device__ __forceinline__ void lds_dma16_sbase(const void* sbase /* wave-uniform */, uint32_t voff,
-                                                uint32_t lds_addr /* wave-uniform; kLdsOffset is added */) {
-    asm volatile("s_add_u32 m0, %2, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(voff), "s"(sbase), "s"(lds_addr), "n"(kLdsOffset) : "memory", "scc");
-}
-__device__ __forceinline__ void wait_all_vmem() {
-    __builtin_amdgcn_s_waitcnt(0x0070 | 0x0f00);      // vmcnt(0); expcnt and lgkmcnt untouched
-}
-
 // Stage fill of a ragged tile (rows past the end repeat the last row) or of rows whose length is
 // not a multiple of the stage (chunks past the end come from the zero block): lane addresses are
 // formed one by one.  Kept out of line so that its registers do not burden the main loop.
@@ -640,8 +600,6 @@ void mine_tile_kernel(const MineArgs a) {
 //   * At the end of the slice the lists of a query are appended to its global list, cut to
 //     the best k of them all first if they hold more than a slice may append.
 // ---------------------------------------------------------------------------
-constexpr int kRing = 8;            // stages in LDS (8 or 16 KiB each)
-static_assert(kRing >= 4 && (kRing & (kRing - 1)) == 0, "stage slots are indexed modulo a power of two, and the two halves of the workgroup fill them in turn");
 constexpr int kSubCap = kCandCap / 4;            // keys of a lane's own list
 constexpr int kSubFull = kSubCap - 32;           // above this a tile could overflow it (a lane adds <= 32 per column)
 constexpr size_t rows_lds_bytes(int wm) {     // ring, list fills at the end of a slice, select histograms
@@ -653,29 +611,6 @@ constexpr size_t rows_lds_bytes(int wm) {     // ring, list fills at the end of 
 static bool force_general_kernel() {
     const char* e = getenv("XC_MINE_GENERAL");
     return e != nullptr && e[0] == '1';
-}
-
-// The lane number, computed where it is asked for (the compiler can neither hoist nor keep it).
-__device__ __forceinline__ uint32_t lane_now() {
-    uint32_t l;
-    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(l));
-    return l;
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmem_at_most() {   // until at most N vector memory operations are outstanding
-    __builtin_amdgcn_s_waitcnt((N & 0xf) | ((N >> 4) << 14) | 0x0070 | 0x0f00);
-}
-
-// Stage fill of the last, ragged label tile: per-lane addresses, rows past the end repeat the last row.
-__device__ __noinline__ void issue_stage_ragged(const unsigned char* W, int64_t L, int64_t row, int row_bytes, int kbyte,
-                                                uint32_t dcol0, uint32_t dcol1, uint32_t dst, int n_instr) {
-#pragma unroll 1
-    for (int t = 0; t < n_instr; ++t) {
-        int64_t r = row + 8 * t;
-        r = r < L ? r : L - 1;
-        lds_dma16(W + r * row_bytes + kbyte + ((t & 1) ? dcol1 : dcol0), __builtin_amdgcn_readfirstlane(dst + t * 1024));
-    }
 }
 
 template <int NK, int WM>
@@ -1175,7 +1110,9 @@ void mine_select_kernel(uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt
 struct MinePlan {
     int64_t nQT, nLT;
     int kcap, nkb, glist_cap;
-    size_t off_flag, off_lists, off_glist, off_gcnt, off_tau, off_zero, ws_bytes;
+    size_t off_flag, off_lists, off_glist, off_gcnt, off_tau, off_zero;
+    size_t ws_min, ws_bytes;         // with ws_min the 8-bit filter, which needs the rest, stays out
+    Q8Plan q8;
     size_t lds_tile;
 };
 
@@ -1266,6 +1203,8 @@ static int plan_mine(int64_t Zq, int64_t L, int d, int k_h, xc_dtype t, MinePlan
     p->off_gcnt = take(nq * sizeof(int32_t));
     p->off_tau = take(nq * sizeof(uint32_t));
     p->off_zero = take(256);
+    p->ws_min = off;
+    if (plan_q8(Zq, L, row_bytes, t, &p->q8)) off += p->q8.bytes;
     p->ws_bytes = off;
     p->lds_tile = 2 * static_cast<size_t>(kBM + kBN) * kStageBytes + kBN * 8 + kMineWaves * 256 * 4 +
                   static_cast<size_t>(kMineWaves) * kPool * 8 + 16;
@@ -1296,7 +1235,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     if (!Z || !W || !shortlist || !ws) return XC_EINVAL;
     if (warm && !(rel_margin >= 0.0f)) return XC_EINVAL;
     if (!aligned16(Z) || !aligned16(W) || !aligned16(ws)) return XC_EINVAL;
-    if (ws_bytes < p.ws_bytes) return XC_EWORKSPACE;
+    if (ws_bytes < p.ws_min) return XC_EWORKSPACE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     unsigned char* w8 = static_cast<unsigned char*>(ws);
     MineArgs a;
@@ -1353,7 +1292,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     uint32_t* zeros32 = reinterpret_cast<uint32_t*>(w8 + p.off_zero);
 
     // one phase: the tile kernel over label tiles [lo, hi), then the select
-    auto phase = [&](int64_t lo, int64_t hi, const int32_t* cond, int32_t* short_flag) -> int {
+    auto sweep = [&](int64_t lo, int64_t hi, const int32_t* cond) -> int {
         const int64_t nT = hi - lo;
         // bf16 rows of whole stages whose queries fit a wave's registers take the row kernel: work items of
         // 512 queries where the pool fills them about as well as items of 256
@@ -1393,11 +1332,19 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
         }
         XC_HIP_CHECK(hipGetLastError());
+        return XC_OK;
+    };
+    auto select = [&](int64_t hi, const int32_t* cond, int32_t* short_flag) -> int {
         const int final_phase = hi == p.nLT ? 1 : 0;
         XC_LAUNCH(K_MINE_SELECT, st, (mine_select_kernel<<<select_grid, kSelectWaves * kWave, 0, st>>>(
             a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h, final_phase, shortlist, scores, cond, short_flag)));
         XC_HIP_CHECK(hipGetLastError());
         return XC_OK;
+    };
+
+    auto phase = [&](int64_t lo, int64_t hi, const int32_t* cond, int32_t* short_flag) -> int {
+        const int rcs = sweep(lo, hi, cond);
+        return rcs != XC_OK ? rcs : select(hi, cond, short_flag);
     };
 
     const int32_t* cond = nullptr;
@@ -1411,7 +1358,28 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     mine_init_kernel<<<init_grid, 256, 0, st>>>(tau_g, a.gcnt, nq, zeros32, cond);
     XC_HIP_CHECK(hipGetLastError());
     int64_t lo = 0;
+    const bool q8 = p.q8.nk > 0 && !warm && ws_bytes >= p.ws_bytes && !force_general_kernel() && !force_rows_layout();
+    unsigned char* q8_ws = w8 + p.ws_min;
+    if (q8) { const int rcq = q8_begin(p.q8, q8_ws, Z, Zq, st); if (rcq != XC_OK) return rcq; }
     while (lo < p.nLT) {
+        if (q8 && lo >= kQ8FirstTile) {
+            // a chunk through the 8-bit filter, what that gave up through the bf16 kernel, the select
+            int64_t hi = lo + p.q8.chunk / kBM;
+            if (hi > lo + kQ8Growth * lo) hi = lo + kQ8Growth * lo;
+            if (hi > p.nLT) hi = p.nLT;
+            Q8Chunk c;
+            c.Z = Z; c.W = W; c.Zq = Zq;
+            c.lab0 = lo * kBM;
+            c.lab1 = hi * kBM < L ? hi * kBM : L;
+            c.kcap = p.kcap; c.glist_cap = p.glist_cap; c.max_slices = slices_cap(p.kcap);
+            c.lists = a.lists; c.glist = a.glist; c.gcnt = a.gcnt; c.tau_g = tau_g;
+            int rcp = q8_chunk(p.q8, q8_ws, c, st);
+            if (rcp == XC_OK) rcp = sweep(lo, hi, q8_flags(p.q8, q8_ws));
+            if (rcp == XC_OK) rcp = select(hi, nullptr, nullptr);
+            if (rcp != XC_OK) return rcp;
+            lo = hi;
+            continue;
+        }
         // phases end at about 1, 8, 64, ... tiles: each sees about 8x the labels seen before it
         int64_t hi = lo + phase_tiles(lo, p.nQT);
         if (hi > p.nLT || p.nLT - hi < hi / 4) hi = p.nLT;      // fold a short remainder into this phase

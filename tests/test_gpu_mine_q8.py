@@ -1,0 +1,135 @@
+"""The 8-bit filter in front of the search of large pools over long ranges of short bf16 rows: the result has to be that
+of the bf16 kernels (forced through XC_MINE_ROWS) on everything the filter can meet - rows that 8 bits describe well and
+badly, rows that are no numbers, scores that rise along the label range so that its lists run over - and, on sampled
+queries, that of 64-bit scores."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2409_20156_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _search(Z, W, k, ws=None):
+    import paper_2409_20156_amd as xc
+    ids, sc = xc.mine_negatives(Z, W, k, want_scores=True, workspace=ws)
+    torch.cuda.synchronize()
+    return ids, sc
+
+
+def _same_as_bf16(monkeypatch, Z, W, k, ties=1e-4):
+    ids, sc = _search(Z, W, k)
+    monkeypatch.setenv("XC_MINE_ROWS", "narrow")
+    ids_b, sc_b = _search(Z, W, k)
+    monkeypatch.delenv("XC_MINE_ROWS")
+    fin = torch.isfinite(sc_b)
+    assert torch.equal(fin, torch.isfinite(sc)) and torch.equal(sc[~fin], sc_b[~fin])
+    # fp32 sums of d products in another order: well under 1e-5 of the score, or of the row lengths where it cancels
+    scale = sc_b[fin].abs().clamp(min=1e-3 * float(Z.float().norm(dim=1).max()))
+    assert float(((sc[fin] - sc_b[fin]).abs() / scale).max()) <= 1e-5
+    assert float((ids != ids_b).float().mean()) <= ties            # labels whose scores differ by less than that
+    return ids, sc
+
+
+def _check_exact(Z, W, ids, sc, k, n=24):
+    """Sampled queries against 64-bit scores over all labels."""
+    q = torch.linspace(0, Z.shape[0] - 1, n, device=DEV).long()
+    best = None
+    for r in range(0, W.shape[0], 1 << 20):
+        s = Z[q].double() @ W[r:r + (1 << 20)].double().T
+        v = torch.topk(s, min(k, s.shape[1]), dim=1)[0]
+        best = v if best is None else torch.topk(torch.cat([best, v], 1), k, dim=1)[0]
+    assert float(((sc[q].double() - best).abs() / best.abs().clamp(min=1e-3)).max()) <= 1e-5
+    own = (Z[q].double()[:, None, :] * W[ids[q].long()].double()).sum(-1)
+    assert float(((own - best).abs() / best.abs().clamp(min=1e-3)).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("Zq,L,d,k", [
+    (4096, 1 << 20, 256, 50),              # the smallest it takes; whole tiles
+    (4100, 1050001, 128, 100),             # ragged queries and labels
+    (5000, 2300007, 256, 64),              # two chunks and a remainder
+    (9001, 1100000, 128, 1),
+    (4097, 1048577, 256, 128),             # one label beyond a whole tile, maximum k
+])
+def test_q8_matches_bf16_search(monkeypatch, Zq, L, d, k):
+    print("case", Zq, L, d, k, flush=True)
+    W = synth.make_matrix(41, synth.TAG_W, L, d, torch.bfloat16, DEV)
+    Z = synth.make_matrix(41, synth.TAG_Z, Zq, d, torch.bfloat16, DEV)
+    ids, sc = _same_as_bf16(monkeypatch, Z, W, k)
+    _check_exact(Z, W, ids, sc, k)
+
+
+def _base(seed=43, Zq=4300, L=1100000, d=256):
+    return (synth.make_matrix(seed, synth.TAG_Z, Zq, d, torch.bfloat16, DEV),
+            synth.make_matrix(seed, synth.TAG_W, L, d, torch.bfloat16, DEV))
+
+
+def test_q8_uneven_rows(monkeypatch):
+    """Outliers that cost their tile its resolution, rows of very different lengths, zero rows and tiles, elements near
+    the ends of the range, and queries of the same kinds."""
+    Z, W = _base()
+    L = W.shape[0]
+    W[::1000, 7] = 3.0                                              # a spike in every 16th tile
+    W[200000:300000] *= torch.logspace(-3, 1.5, 100000, device=DEV)[:, None].to(torch.bfloat16)
+    W[400000:420000] = 0.0
+    W[500000:500064] = 1e-20
+    W[600000] = 1e18
+    W[L - 1] = W[5] * 4
+    Z[3, 0] = 9.0
+    Z[17] *= 1e-3
+    Z[18] = 0.0
+    Z[19] = 1e-20
+    Z[20] = 1e16
+    ids, sc = _same_as_bf16(monkeypatch, Z, W, 50)
+    ok = torch.ones(Z.shape[0], dtype=torch.bool, device=DEV)
+    ok[[18, 19, 20]] = False
+    _check_exact(Z[ok], W, ids[ok], sc[ok], 50)
+
+
+def test_q8_rows_that_are_no_numbers(monkeypatch):
+    Z, W = _base(44)
+    W[300000:300100] = float("nan")
+    W[700001, 3] = float("inf")
+    W[800002, 4] = -float("inf")
+    Z[9, 1] = float("nan")
+    Z[4200, 0] = float("inf")
+    ids, _ = _same_as_bf16(monkeypatch, Z, W, 50, ties=1e-3)
+    assert bool((ids[9] == -1).all())
+    good = torch.arange(Z.shape[0], device=DEV) != 9
+    assert not bool(((ids[good] >= 300000) & (ids[good] < 300100)).any())
+
+
+def test_q8_scores_that_rise_along_the_labels(monkeypatch):
+    """Every label beats the threshold of those before it: the lists run over, the query tiles are given up and searched in
+    bf16, for some of them (the odd half of the queries prefers small ids) or for all."""
+    L, d, Zq, k = 1100000, 128, 4200, 60
+    W = (torch.arange(L, dtype=torch.float32, device=DEV)[:, None] / 65536.0 * torch.ones(d, device=DEV)[None, :]).to(torch.bfloat16)
+    Z = torch.ones((Zq, d), dtype=torch.bfloat16, device=DEV)
+    Z[2000:3000] *= -1.0
+    _same_as_bf16(monkeypatch, Z, W, k, ties=0.0)                   # (these products are exact)
+    Z[:] = synth.make_matrix(5, synth.TAG_Z, Zq, d, torch.bfloat16, DEV)
+    Z[256:300] = 1.0
+    _same_as_bf16(monkeypatch, Z, W, k, ties=1.0)                   # bf16 rows of equal value: ties everywhere
+
+
+def test_q8_needs_its_room_and_is_reproducible(monkeypatch):
+    import paper_2409_20156_amd as xc
+    Z, W = _base(45)
+    need = xc.mine_workspace(Z.shape[0], W.shape[0], 256, 50, xc.XC_BF16)
+    ws = torch.empty(need, dtype=torch.uint8, device=DEV)
+    ws.random_(0, 255)
+    a = _search(Z, W, 50, ws)
+    ws.random_(0, 255)
+    b = _search(Z, W, 50, ws)
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    c = _search(Z, W, 50, ws[:need - 256])                          # without the filter's room: the bf16 search
+    assert float((a[0] != c[0]).float().mean()) <= 1e-4
+    # a warm search after it starts from its thresholds
+    ids, sc = xc.mine_negatives(Z, W, 50, want_scores=True, workspace=ws, warm_margin=0.05)
+    xc.mine_negatives(Z, W, 50, workspace=ws)
+    ids, sc = xc.mine_negatives(Z, W, 50, want_scores=True, workspace=ws, warm_margin=0.05)
+    torch.cuda.synchronize()
+    assert int(ws[:4].view(torch.int32).item()) == 0
+    assert float((a[0] != ids).float().mean()) <= 1e-4
