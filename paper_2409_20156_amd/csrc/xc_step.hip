@@ -14,8 +14,9 @@ namespace xc {
 
 constexpr int kStepThreads = 256;
 constexpr int kMaxRowFloats = XC_MAX_ROW_BYTES / 2;     // bf16 rows hold the most elements
-constexpr int kSortTile = 256;                          // keys ranked together in the scatter
-constexpr int kSortMaxBlocks = 2048;
+constexpr int kSortTile = 256;                          // keys ranked together in a bucket's sort
+constexpr int kRoundThreads = 1024;                     // threads of a sort round's blocks = keys ranked together there
+constexpr int kSortMaxBlocks = 512;                     // blocks of a sort round: two per compute unit
 constexpr int kSortCountEntries = 1 << 19;              // digit values x sort blocks at most (2 MiB of counts)
 constexpr int kUpdateMaxGrid = 256 * 8;                 // workgroups of the update kernel
 constexpr int kMaxRadixBits = 11;
@@ -140,8 +141,8 @@ __device__ __forceinline__ int lane_of_row(int u, int G) {      // lowest lane o
 // ---------------------------------------------------------------------------
 // FULL: every lane's CPL chunks exist (d / kPerChunk == G * CPL), so no load needs a bounds test; a masked
 // pair then reads the query's own row (finite, and weighted zero) instead of branching around the loads.
-// FUSE (BCE only): the pair sort has run before this kernel and single_slot[pair] says whether the pair's label
-// occurs in no other unmasked pair of the batch (then: its position in the touched list, else -1).  Such a row
+// FUSE (BCE only): the pair sort has run before this kernel and single_flag[pair] says whether the pair's label
+// occurs in no other unmasked pair of the batch (single_slot[pair]: its position in the touched list, for rows_out).  Such a row
 // is read by this pair alone, its gradient is g z_i with both factors at hand, so it is updated here, while it
 // is in registers (w - lr g z, rounded once), and the row update kernel never sees it: one read and one write of
 // the row in the whole step instead of two reads, a read of z_i and a write.
@@ -150,7 +151,7 @@ __global__ __launch_bounds__(kStepThreads)
 void gather_kernel(const T* __restrict__ Z, T* W, int64_t L, int d,
                    const int32_t* __restrict__ pos, int k_p, const int32_t* __restrict__ neg,
                    const float* __restrict__ logq, int n_neg, int G, int SQ, int64_t B, float inv_B,
-                   const int32_t* __restrict__ single_slot, float lr, T* rows_out,
+                   const uint8_t* __restrict__ single_flag, const int32_t* __restrict__ single_slot, float lr, T* rows_out,
                    float* __restrict__ gco, float* __restrict__ loss_q, float* __restrict__ dZ) {
     constexpr int EPC = Elem<T>::kPerChunk;       // U = candidate rows in flight per group
     __shared__ float red[kStepThreads / kWave][kMaxRowFloats];
@@ -210,7 +211,7 @@ void gather_kernel(const T* __restrict__ Z, T* W, int64_t L, int d,
     // iteration that uses it begins: nothing waits for them where they are issued, behind the row loads.
     int32_t id_nx[U];
     float lq_nx[U];
-    int32_t sl_nx[FUSE ? U : 1];
+    uint8_t sl_nx[FUSE ? U : 1];
     auto fetch_ids = [&](int c0) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -222,7 +223,7 @@ void gather_kernel(const T* __restrict__ Z, T* W, int64_t L, int d,
             if (FUSE) {
                 int ca = c0 + u * NG;
                 ca = ca < n ? ca : n - 1;
-                sl_nx[u] = single_slot[p_base + ca];
+                sl_nx[u] = single_flag[p_base + ca];
             }
         }
     };
@@ -239,7 +240,7 @@ void gather_kernel(const T* __restrict__ Z, T* W, int64_t L, int d,
         int32_t id[U];
         float lq[U];
         bool ok[U], isp[U];
-        int32_t slot[FUSE ? U : 1];
+        uint8_t slot[FUSE ? U : 1];
         uint4 rw[U][CPL];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
@@ -345,11 +346,11 @@ void gather_kernel(const T* __restrict__ Z, T* W, int64_t L, int d,
                         for (int e = 0; e < EPC; ++e) pz[j][e] += wf[j][e];
                 }
                 if (FUSE) {
-                    if (ok[u] && slot[u] >= 0) {           // the only pair of its label: the row is updated here
+                    if (ok[u] && slot[u] != 0) {           // the only pair of its label: the row is updated here
                         const float cg = -lr * g;
                         unsigned char* wrow = Wb + static_cast<int64_t>(id[u]) * row_bytes;
                         unsigned char* orow = rows_out ? reinterpret_cast<unsigned char*>(rows_out) +
-                                                             static_cast<int64_t>(slot[u]) * row_bytes : nullptr;
+                                                             static_cast<int64_t>(single_slot[p_base + c]) * row_bytes : nullptr;
 #pragma unroll
                         for (int j = 0; j < CPL; ++j) {
                             const int ch = gl + j * G;
@@ -468,6 +469,9 @@ void gather_kernel(const T* __restrict__ Z, T* W, int64_t L, int d,
 // bucket_sort (5 launches with the segment heads instead of 8); wider keys take
 // least-significant-digit-first rounds of count/prefix/scatter.
 // A key >= inv_key (the marker of a masked pair) is given the digit inv_digit.
+// Blocks of 1024 threads, two per compute unit: a block's pairs of one digit form longer runs (fewer lines written in
+// parts), and the [digit][block] matrix is small.  Against blocks of 256 threads with four barriers per 256 keys, per
+// scatter round of 8.6 M pairs over 512 digits 88 -> 66 us, of 2.3 M over 2048 61 -> 31; count 19 -> 14 and 53 -> 29.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int digit_of(uint32_t key, int shift, int radix, uint32_t inv_key, int inv_digit) {
     return key >= inv_key ? inv_digit : static_cast<int>((key >> shift) & static_cast<uint32_t>(radix - 1));
@@ -528,30 +532,33 @@ __device__ __forceinline__ uint32_t pair_key(const KeySource& k, uint32_t p) {
 // MAKE: this is the first kernel of the step; it forms the (key, pair index) pairs, writes them to `pairs_out`
 // and counts their digits.  Otherwise the pairs are read.
 template <bool MAKE>
-__global__ __launch_bounds__(256)
+__global__ __launch_bounds__(kRoundThreads)
 void radix_count_kernel(const uint2* __restrict__ pairs, int64_t P, int64_t chunk, int shift, int rb,
                         int nb, int* __restrict__ counts /* [radix][nb] */, uint32_t inv_key, int inv_digit,
-                        const KeySource ks, uint2* __restrict__ pairs_out, int32_t* __restrict__ stats) {
+                        const KeySource ks, uint2* __restrict__ pairs_out, uint8_t* __restrict__ single /* or null */,
+                        int32_t* __restrict__ stats) {
     __shared__ int hist[kMaxRadix];
     const int radix = 1 << rb;
-    for (int d = threadIdx.x; d < radix; d += 256) hist[d] = 0;
+    for (int d = threadIdx.x; d < radix; d += kRoundThreads) hist[d] = 0;
     if (MAKE && blockIdx.x == 0 && threadIdx.x == 0) stats[0] = 0;      // rows updated inside the gather: counted later
     __syncthreads();
     const int64_t p0 = blockIdx.x * chunk;
     int64_t p1 = p0 + chunk;
     p1 = p1 < P ? p1 : P;
-    for (int64_t p = p0 + threadIdx.x; p < p1; p += 256) {
+#pragma unroll 4
+    for (int64_t p = p0 + threadIdx.x; p < p1; p += kRoundThreads) {
         uint32_t key;
         if (MAKE) {
             key = pair_key(ks, static_cast<uint32_t>(p));
             pairs_out[p] = make_uint2(key, static_cast<uint32_t>(p));
+            if (single != nullptr) single[p] = 1;                       // until the segment heads say otherwise
         } else {
             key = pairs[p].x;
         }
         atomicAdd(&hist[digit_of(key, shift, radix, inv_key, inv_digit)], 1);
     }
     __syncthreads();
-    for (int d = threadIdx.x; d < radix; d += 256) counts[d * nb + blockIdx.x] = hist[d];
+    for (int d = threadIdx.x; d < radix; d += kRoundThreads) counts[d * nb + blockIdx.x] = hist[d];
 }
 
 __global__ __launch_bounds__(kWave)
@@ -570,14 +577,15 @@ void radix_prefix_kernel(int* __restrict__ counts /* [radix][nb], in place */, i
     if (lane == 0) totals[blockIdx.x] = run;
 }
 
-// One tile of kSortTile keys: key/val of thread tid (valid or not) goes to offs[digit] + its rank among
-// the tile's keys of the same digit, and offs moves on.  whist must be zero on entry and is zero on exit.
+// One tile of 64 NW keys: key/val of thread tid (valid or not) goes to offs[digit] + its rank among the tile's keys of the
+// same digit, and offs moves on.  A wave's count of a digit is one byte (64 at most), the NW bytes of a digit lie side by
+// side: one read gives every wave the counts of all.  whist must be zero on entry and is zero on exit.  Two barriers: a
+// wave writes and clears only its own bytes, and what it does behind the second one is ordered before the next tile's reads by the first.
+template <int NW>
 __device__ __forceinline__ void place_tile(bool valid, uint32_t key, uint32_t val, int digit, int rb,
-                                           int* offs /* [radix] */, int* whist /* [waves][radix] */,
+                                           int* offs /* [radix] */, uint8_t* whist /* [radix][NW] */,
                                            uint2* __restrict__ out) {
-    const int tid = threadIdx.x;
-    const int wave = tid >> 6;
-    const int radix = 1 << rb;
+    const int wave = threadIdx.x >> 6;
     // lanes of this wave holding the same digit
     uint64_t same = __ballot(valid);
     for (int b = 0; b < rb; ++b) {
@@ -586,43 +594,43 @@ __device__ __forceinline__ void place_tile(bool valid, uint32_t key, uint32_t va
         same &= bit ? bal : ~bal;
     }
     const int rank = __popcll(same & lanemask_lt());
-    if (valid && rank == 0) whist[wave * radix + digit] = __popcll(same);
+    if (valid && rank == 0) whist[digit * NW + wave] = static_cast<uint8_t>(__popcll(same));
     lds_barrier();
+    uint32_t before = 0, total = 0;
     if (valid) {
-        int before = offs[digit];
-        for (int w = 0; w < wave; ++w) before += whist[w * radix + digit];
-        out[before + rank] = make_uint2(key, val);       // one 8-byte store: key and payload share a line
-    }
-    lds_barrier();
-    // only digits present in this tile need their running offset advanced
-    if (valid && rank == 0) {
-        int add = 0;
+        const uint32_t* w4 = reinterpret_cast<const uint32_t*>(whist + digit * NW);
 #pragma unroll
-        for (int w = 0; w < kSortTile / kWave; ++w) add += whist[w * radix + digit];
-        // one lane per (wave, digit); the wave holding the lowest index among the waves
-        // that saw the digit applies the update
-        bool first = true;
-        for (int w = 0; w < wave; ++w) first = first && whist[w * radix + digit] == 0;
-        if (first) offs[digit] += add;
+        for (int i = 0; i < NW / 4; ++i) {
+            const uint32_t w = w4[i];
+            const int lower = wave - 4 * i;                      // waves of this word before mine
+            const uint32_t mask = lower >= 4 ? 0xffffffffu : (lower <= 0 ? 0u : (1u << (8 * lower)) - 1u);
+            before = __builtin_amdgcn_sad_u8(w & mask, 0u, before);
+            total = __builtin_amdgcn_sad_u8(w, 0u, total);
+        }
+        out[offs[digit] + static_cast<int>(before) + rank] = make_uint2(key, val);      // one 8-byte store: key and payload share a line
     }
     lds_barrier();
-    if (valid && rank == 0) whist[wave * radix + digit] = 0;
-    lds_barrier();
+    // only digits present in this tile need their running offset advanced: by the first wave that saw the digit
+    if (valid && rank == 0) {
+        if (before == 0) offs[digit] += static_cast<int>(total);
+        whist[digit * NW + wave] = 0;
+    }
 }
 
-__global__ __launch_bounds__(kSortTile)
+__global__ __launch_bounds__(kRoundThreads)
 void radix_scatter_kernel(const uint2* __restrict__ in, uint2* __restrict__ out, int64_t P,
                           int64_t chunk, int shift, int rb, int nb, const int* __restrict__ prefix,
                           const int* __restrict__ totals, uint32_t inv_key, int inv_digit,
                           int* __restrict__ bases_out /* [radix] or null: where each digit's pairs start */) {
-    extern __shared__ int sort_lds[];                  // offs[radix], whist[waves][radix]: sized by the launch
-    __shared__ int wsum[kSortTile / kWave];
+    constexpr int NW = kRoundThreads / kWave;
+    extern __shared__ int sort_lds[];                  // offs[radix], whist[radix][NW] bytes: sized by the launch
+    __shared__ int wsum[NW];
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
     const int radix = 1 << rb;
     int* offs = sort_lds;
-    int* whist = sort_lds + radix;
-    const int per = (radix + kSortTile - 1) / kSortTile;     // digits per thread, contiguous
+    uint8_t* whist = reinterpret_cast<uint8_t*>(sort_lds + radix);
+    const int per = (radix + kRoundThreads - 1) / kRoundThreads;     // digits per thread, contiguous
     // digit bases: exclusive scan of the totals
     {
         int local = 0;
@@ -641,9 +649,7 @@ void radix_scatter_kernel(const uint2* __restrict__ in, uint2* __restrict__ out,
             }
         }
     }
-    for (int d = tid; d < radix; d += kSortTile)
-#pragma unroll
-        for (int w = 0; w < kSortTile / kWave; ++w) whist[w * radix + d] = 0;
+    for (int d = tid; d < radix * NW / 4; d += kRoundThreads) reinterpret_cast<uint32_t*>(whist)[d] = 0;
     __syncthreads();
     const int64_t p0 = blockIdx.x * chunk;
     int64_t p1 = p0 + chunk;
@@ -651,12 +657,12 @@ void radix_scatter_kernel(const uint2* __restrict__ in, uint2* __restrict__ out,
     // the next tile's pairs are fetched while the current tile is placed
     uint32_t key_n = 0, val_n = 0;
     if (p0 + tid < p1) { const uint2 kv = in[p0 + tid]; key_n = kv.x; val_n = kv.y; }
-    for (int64_t t0 = p0; t0 < p1; t0 += kSortTile) {
+    for (int64_t t0 = p0; t0 < p1; t0 += kRoundThreads) {
         const bool valid = t0 + tid < p1;
         const uint32_t key = key_n, val = val_n;
-        const int64_t pn = t0 + kSortTile + tid;
+        const int64_t pn = t0 + kRoundThreads + tid;
         if (pn < p1) { const uint2 kv = in[pn]; key_n = kv.x; val_n = kv.y; }
-        place_tile(valid, key, val, digit_of(key, shift, radix, inv_key, inv_digit), rb, offs, whist, out);
+        place_tile<NW>(valid, key, val, digit_of(key, shift, radix, inv_key, inv_digit), rb, offs, whist, out);
     }
 }
 
@@ -676,21 +682,21 @@ void bucket_sort_kernel(const uint2* __restrict__ in, uint2* __restrict__ out,
                         const int* __restrict__ bases /* [gridDim.x] first pair of each bucket */, int rb,
                         int* __restrict__ head_cnt /* [gridDim.x] */,
                         int* __restrict__ multi_cnt /* [gridDim.x] labels of the bucket with several pairs */) {
-    extern __shared__ int sort_lds[];                  // offs[radix], whist[waves][radix]: sized by the launch
+    constexpr int NW = kSortTile / kWave;
+    extern __shared__ int sort_lds[];                  // offs[radix], whist[radix][NW] bytes: sized by the launch
     __shared__ int wsum[kSortTile / kWave];
     __shared__ int red[kSortTile / kWave];
     const int tid = threadIdx.x;
     const int wave = tid >> 6;
     const int radix = 1 << rb;
     int* offs = sort_lds;
-    int* whist = sort_lds + radix;
+    uint8_t* whist = reinterpret_cast<uint8_t*>(sort_lds + radix);
     const int b = blockIdx.x;
     const int p0 = bases[b];
     const int p1 = p0 + sizes[b];
     for (int d = tid; d < radix; d += kSortTile) {
         offs[d] = 0;
-#pragma unroll
-        for (int w = 0; w < kSortTile / kWave; ++w) whist[w * radix + d] = 0;
+        reinterpret_cast<uint32_t*>(whist)[d] = 0;
     }
     __syncthreads();
     const bool in_regs = p1 - p0 <= kBucketRegTiles * kSortTile;        // uniform
@@ -736,7 +742,7 @@ void bucket_sort_kernel(const uint2* __restrict__ in, uint2* __restrict__ out,
         for (int u = 0; u < kBucketRegTiles; ++u) {
             if (p0 + u * kSortTile >= p1) break;                       // uniform
             const bool valid = p0 + u * kSortTile + tid < p1;
-            place_tile(valid, rk[u], rv[u], static_cast<int>(rk[u] & static_cast<uint32_t>(radix - 1)), rb, offs, whist,
+            place_tile<NW>(valid, rk[u], rv[u], static_cast<int>(rk[u] & static_cast<uint32_t>(radix - 1)), rb, offs, whist,
                        out);
         }
     } else {
@@ -747,7 +753,7 @@ void bucket_sort_kernel(const uint2* __restrict__ in, uint2* __restrict__ out,
             const uint32_t key = key_n, val = val_n;
             const int pn = t0 + kSortTile + tid;
             if (pn < p1) { const uint2 kv = in[pn]; key_n = kv.x; val_n = kv.y; }
-            place_tile(valid, key, val, static_cast<int>(key & static_cast<uint32_t>(radix - 1)), rb, offs, whist,
+            place_tile<NW>(valid, key, val, static_cast<int>(key & static_cast<uint32_t>(radix - 1)), rb, offs, whist,
                        out);
         }
     }
@@ -789,7 +795,8 @@ void heads_write_kernel(const uint2* __restrict__ pairs, int64_t P, int64_t chun
                         int32_t* __restrict__ n_touched,
                         const int* __restrict__ bucket_sizes /* not null: block b covers bucket b ... */,
                         const int* __restrict__ bucket_bases /* ... which starts at pair bucket_bases[b] */,
-                        int32_t* __restrict__ single_slot /* [P] by pair index, or null */,
+                        uint8_t* __restrict__ single_flag /* [P] by pair index, all ones so far; or null */,
+                        int32_t* __restrict__ single_slot /* [P] by pair index, or null: nobody asks for the rows */,
                         const int* __restrict__ multi_cnt, int32_t* __restrict__ multi_list /* segments with several pairs */,
                         int32_t* __restrict__ stats) {
     __shared__ int sh[4];
@@ -839,11 +846,12 @@ void heads_write_kernel(const uint2* __restrict__ pairs, int64_t P, int64_t chun
                 seg_start[s] = static_cast<int32_t>(p);
                 seg_idx0[s] = kv.y;                  // first pair of the segment, saves the update a hop
             }
-            if (single_slot != nullptr) {
-                // a label with one pair only: the gather updates its row itself and needs the row's place in the
-                // touched list (for the copy of the updated rows); every other pair is told -1.  The other
-                // labels are listed for the row update kernel.
-                single_slot[kv.y] = single ? s : -1;
+            if (single_flag != nullptr) {
+                // a label with one pair only: the gather updates its row itself, and needs the row's place in the
+                // touched list if a copy of the updated rows is wanted.  The pairs of other labels - the rarer ones where
+                // this is done - are told so (a scattered write each), and these labels are listed for the row update kernel.
+                if (!single) single_flag[kv.y] = 0;
+                else if (single_slot != nullptr) single_slot[kv.y] = s;
                 singles += single ? 1 : 0;
                 if (head && !single) multi_list[before_m + __popcll(bal_m & lanemask_lt())] = s;
             }
@@ -855,7 +863,7 @@ void heads_write_kernel(const uint2* __restrict__ pairs, int64_t P, int64_t chun
         }
         lds_barrier();
     }
-    if (single_slot != nullptr) {
+    if (single_flag != nullptr) {
         singles = block_sum<int, 4>(singles, sh);
         if (tid == 0 && singles > 0) atomicAdd(&stats[0], singles);      // an integer sum: the same in every run
     }
@@ -883,8 +891,8 @@ template <typename K, int E>
 __global__ __launch_bounds__(kSmallThreads)
 void sort_small_kernel(const KeySource ks, int P, int ib, uint2* __restrict__ pairs, int32_t* __restrict__ touched,
                        int32_t* __restrict__ seg_start, uint32_t* __restrict__ seg_idx0, int32_t* __restrict__ n_touched,
-                       int32_t* __restrict__ single_slot /* or null */, int32_t* __restrict__ multi_list,
-                       int32_t* __restrict__ stats) {
+                       uint8_t* __restrict__ single_flag /* or null */, int32_t* __restrict__ single_slot /* or null */,
+                       int32_t* __restrict__ multi_list, int32_t* __restrict__ stats) {
     constexpr int N = kSmallThreads * E;
     constexpr int kW = kSmallThreads / kWave;
     __shared__ K arr[N];
@@ -975,8 +983,9 @@ void sort_small_kernel(const KeySource ks, int P, int ib, uint2* __restrict__ pa
                 seg_start[s] = e;
                 seg_idx0[s] = idx;
             }
-            if (single_slot != nullptr) {
-                single_slot[idx] = single ? s : -1;
+            if (single_flag != nullptr) {
+                single_flag[idx] = single ? 1 : 0;
+                if (single && single_slot != nullptr) single_slot[idx] = s;
                 if (head && !single) multi_list[m] = s;
             }
         }
@@ -984,7 +993,7 @@ void sort_small_kernel(const KeySource ks, int P, int ib, uint2* __restrict__ pa
     if (tid == 0) {
         n_touched[0] = run_h;
         seg_start[run_h] = n_valid;
-        stats[0] = single_slot != nullptr ? n_single : 0;
+        stats[0] = single_flag != nullptr ? n_single : 0;
         stats[1] = run_m;
     }
 }
@@ -1265,16 +1274,16 @@ void update_kernel(const T* __restrict__ Z, T* __restrict__ W, int d, uint32_t n
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-static size_t sort_lds_bytes(int rb) {      // offs + one histogram per wave, for digits of rb bits
-    return (static_cast<size_t>(1) + kSortTile / kWave) * (static_cast<size_t>(1) << rb) * sizeof(int);
+static size_t sort_lds_bytes(int rb, int threads) {      // an offset and a byte per wave for each digit of rb bits
+    return (sizeof(int) + threads / kWave) * (static_cast<size_t>(1) << rb);
 }
 struct StepPlan {
     int64_t P;
-    int n, G, cpl, nb, passes, rb, key_bits, sq, n_shift;
+    int n, G, cpl, nb, nb_heads, passes, rb, key_bits, sq, n_shift;
     int low_bits, n_buckets, high_rb;       // n_buckets > 0: one round on the high digit, then bucket_sort
     bool stream_update, stream_gather;      // rows of W go through the caches with the non-temporal hint
     uint32_t n_magic;
-    int64_t chunk;
+    int64_t chunk, chunk_heads;
     size_t off_stats, off_single, off_multi, off_multicnt, off_pairs0, off_pairs1, off_g, off_lossq, off_dzpart, off_counts, off_totals, off_bases, off_headcnt,
         off_validcnt, off_segstart, off_segidx0, total;
 };
@@ -1334,19 +1343,22 @@ static int plan_step(int64_t B, int64_t L, int d, int k_p, int n_neg, xc_dtype t
             p->high_rb = hb;
         }
     }
-    // blocks of the sort: two 256-key tiles per block at least; the [digit][block] count matrix, which is
+    // blocks of the sort: one tile per block at least; the [digit][block] count matrix, which is
     // written and read across its rows, stays within kSortCountEntries
     const int radix_max = 1 << (p->n_buckets > 0 ? p->high_rb : p->rb);
     int nb_cap = kSortCountEntries / radix_max;
     if (nb_cap > kSortMaxBlocks) nb_cap = kSortMaxBlocks;
-    int nb = static_cast<int>((p->P + 511) / 512);
+    int nb = static_cast<int>((p->P + kRoundThreads - 1) / kRoundThreads < nb_cap ? (p->P + kRoundThreads - 1) / kRoundThreads : nb_cap);
     if (nb > nb_cap) nb = nb_cap;
     if (nb < 1) nb = 1;
     int64_t chunk = (p->P + nb - 1) / nb;
-    chunk = (chunk + kSortTile - 1) / kSortTile * kSortTile;
+    chunk = (chunk + kRoundThreads - 1) / kRoundThreads * kRoundThreads;
     nb = static_cast<int>((p->P + chunk - 1) / chunk);
     p->nb = nb;
     p->chunk = chunk;
+    // blocks of the segment-head kernels behind the rounds of wide keys
+    p->nb_heads = p->P < 2048 * 1024 ? static_cast<int>((p->P + 1023) / 1024) : kMaxRadix;
+    p->chunk_heads = ((p->P + p->nb_heads - 1) / p->nb_heads + 255) / 256 * 256;
     size_t off = 0;
     auto take = [&off](size_t bytes) { size_t o = off; off += round_up(bytes, 256); return o; };
     const size_t P = static_cast<size_t>(p->P);
@@ -1360,13 +1372,13 @@ static int plan_step(int64_t B, int64_t L, int d, int k_p, int n_neg, xc_dtype t
     p->off_counts = take(static_cast<size_t>(kSortCountEntries) * 4);      // whatever L: the layout does not depend on it
     p->off_totals = take(static_cast<size_t>(kMaxRadix) * 4);
     p->off_bases = take(static_cast<size_t>(kMaxRadix) * 4);
-    p->off_headcnt = take(static_cast<size_t>(kSortMaxBlocks > kMaxRadix ? kSortMaxBlocks : kMaxRadix) * 4);
-    p->off_validcnt = take(static_cast<size_t>(kSortMaxBlocks) * 4);
+    p->off_headcnt = take(static_cast<size_t>(kMaxRadix) * 4);
+    p->off_validcnt = take(static_cast<size_t>(kMaxRadix) * 4);
     p->off_segstart = take((P + 1) * 4);
     p->off_segidx0 = take(P * 4);
     p->off_single = take(P * 4);
     p->off_multi = take(P * 4);
-    p->off_multicnt = take(static_cast<size_t>(kSortMaxBlocks > kMaxRadix ? kSortMaxBlocks : kMaxRadix) * 4);
+    p->off_multicnt = take(static_cast<size_t>(kMaxRadix) * 4);
     p->total = off;
     return XC_OK;
 }
@@ -1374,16 +1386,16 @@ static int plan_step(int64_t B, int64_t L, int d, int k_p, int n_neg, xc_dtype t
 template <typename T, int KIND>
 static void launch_gather(const StepPlan& pl, hipStream_t st, const void* Z, void* W, int64_t B,
                           int64_t L, int d, const int32_t* pos, int k_p, const int32_t* neg,
-                          const float* logq, int n_neg, const int32_t* single_slot /* null: no row updates here */,
-                          float lr, void* rows_out, float* gco, float* loss_q, float* dZ, int SQ) {
+                          const float* logq, int n_neg, const uint8_t* single_flag /* null: no row updates here */,
+                          const int32_t* single_slot, float lr, void* rows_out, float* gco, float* loss_q, float* dZ, int SQ) {
     const float inv_B = 1.0f / static_cast<float>(B);
     const dim3 grid(static_cast<unsigned>(B * SQ));
     // (the soft-max coefficient needs the whole query first: no fused row updates there)
-    const bool fuse = KIND == XC_LOSS_BCE && single_slot != nullptr;
+    const bool fuse = KIND == XC_LOSS_BCE && single_flag != nullptr;
 #define XC_GATHER3(CPL, UU, FF, SS, FU)                                                                \
     XC_LAUNCH(K_GATHER, st, (gather_kernel<T, CPL, KIND, UU, FF, SS, FU><<<grid, kStepThreads, 0, st>>>( \
         static_cast<const T*>(Z), static_cast<T*>(W), L, d, pos, k_p, neg, logq, n_neg,                \
-        pl.G, SQ, B, inv_B, single_slot, lr, static_cast<T*>(rows_out), gco, loss_q, dZ)))
+        pl.G, SQ, B, inv_B, single_flag, single_slot, lr, static_cast<T*>(rows_out), gco, loss_q, dZ)))
 #define XC_GATHER2(CPL, UU, FF, SS)                                                                    \
     do {                                                                                               \
         if (KIND == XC_LOSS_BCE && fuse) XC_GATHER3(CPL, UU, FF, SS, (KIND == XC_LOSS_BCE));           \
@@ -1507,6 +1519,9 @@ static int step_impl(const void* Z, void* W, int64_t B, int64_t L, int d, const 
     // them with a row written from a kernel that is bound by instruction issue.  Measured: 2.3 M pairs over
     // 1.3 M labels (a third single) loses 8 % of the step, 8.6 M over 120 M (96 % single) gains 30 %.
     const bool fuse = kind == XC_LOSS_BCE && 2 * pl.P <= L;
+    // (a label with several pairs has two at least: the list needs half of its room, the flags live in the other half)
+    uint8_t* flags = fuse ? reinterpret_cast<uint8_t*>(multi_list + pl.P / 2 + 1) : nullptr;
+    int32_t* slots = fuse && W_rows_out != nullptr ? single_slot : nullptr;
     KeySource ks;
     ks.pos = pos; ks.neg = neg; ks.k_p = k_p; ks.n_neg = n_neg; ks.n = pl.n; ks.n_shift = pl.n_shift;
     ks.n_magic = pl.n_magic; ks.softmax = kind == XC_LOSS_SOFTMAX ? 1 : 0; ks.L = L;
@@ -1518,11 +1533,10 @@ static int step_impl(const void* Z, void* W, int64_t B, int64_t L, int d, const 
         // one workgroup does it all; 32-bit elements where key and pair index fit them
         int ib = 0;
         while ((static_cast<int64_t>(1) << ib) < pl.P) ++ib;
-        int32_t* slots = fuse ? single_slot : nullptr;
         const int n = static_cast<int>(pl.P);
 #define XC_SORT_SMALL(K, E)                                                                                      \
     XC_LAUNCH(K_BUCKET_SORT, st, (sort_small_kernel<K, E><<<1, kSmallThreads, 0, st>>>(                           \
-        ks, n, ib, kin, touched, seg_start, seg_idx0, n_touched, slots, multi_list, stats)))
+        ks, n, ib, kin, touched, seg_start, seg_idx0, n_touched, flags, slots, multi_list, stats)))
         const bool narrow = pl.key_bits + ib < 32;           // (below 32: the padding element stays larger than every pair)
         if (n <= kSmallThreads) { if (narrow) XC_SORT_SMALL(uint32_t, 1); else XC_SORT_SMALL(uint64_t, 1); }
         else if (n <= 2 * kSmallThreads) { if (narrow) XC_SORT_SMALL(uint32_t, 2); else XC_SORT_SMALL(uint64_t, 2); }
@@ -1533,30 +1547,30 @@ static int step_impl(const void* Z, void* W, int64_t B, int64_t L, int d, const 
         // one round on the high digit (masked pairs behind every label), then each bucket by its low digit
         const int radix = 1 << pl.high_rb;
         const uint32_t Lk = static_cast<uint32_t>(L);
-        XC_LAUNCH(K_RADIX_COUNT, st, (radix_count_kernel<true><<<pl.nb, 256, 0, st>>>(nullptr, pl.P, pl.chunk, pl.low_bits, pl.high_rb, pl.nb, counts, Lk, pl.n_buckets, ks, kin, stats)));
+        XC_LAUNCH(K_RADIX_COUNT, st, (radix_count_kernel<true><<<pl.nb, kRoundThreads, 0, st>>>(nullptr, pl.P, pl.chunk, pl.low_bits, pl.high_rb, pl.nb, counts, Lk, pl.n_buckets, ks, kin, flags, stats)));
         XC_LAUNCH(K_RADIX_SCAN, st, (radix_prefix_kernel<<<radix, kWave, 0, st>>>(counts, pl.nb, totals)));
-        XC_LAUNCH(K_RADIX_SCATTER, st, (radix_scatter_kernel<<<pl.nb, kSortTile, sort_lds_bytes(pl.high_rb), st>>>(kin, kout, pl.P, pl.chunk, pl.low_bits, pl.high_rb, pl.nb, counts, totals, Lk, pl.n_buckets, bases)));
-        XC_LAUNCH(K_BUCKET_SORT, st, (bucket_sort_kernel<<<pl.n_buckets, kSortTile, sort_lds_bytes(pl.low_bits), st>>>(kout, kin, totals, bases, pl.low_bits, head_cnt, multi_cnt)));
+        XC_LAUNCH(K_RADIX_SCATTER, st, (radix_scatter_kernel<<<pl.nb, kRoundThreads, sort_lds_bytes(pl.high_rb, kRoundThreads), st>>>(kin, kout, pl.P, pl.chunk, pl.low_bits, pl.high_rb, pl.nb, counts, totals, Lk, pl.n_buckets, bases)));
+        XC_LAUNCH(K_BUCKET_SORT, st, (bucket_sort_kernel<<<pl.n_buckets, kSortTile, sort_lds_bytes(pl.low_bits, kSortTile), st>>>(kout, kin, totals, bases, pl.low_bits, head_cnt, multi_cnt)));
         // the sizes of the label buckets add up to the number of unmasked pairs
         XC_LAUNCH(K_HEADS_WRITE, st, (heads_write_kernel<<<pl.n_buckets + 1, 256, 0, st>>>(kin, pl.P, pl.chunk, Lk, pl.n_buckets, head_cnt,
                                                                                      totals, touched, seg_start, seg_idx0, n_touched, totals, bases,
-                                                                                     fuse ? single_slot : nullptr, multi_cnt, multi_list, stats)));
+                                                                                     flags, slots, multi_cnt, multi_list, stats)));
         XC_HIP_CHECK(hipGetLastError());
     } else {
         for (int pass = 0; pass < pl.passes; ++pass) {
             const int shift = pass * pl.rb;
             const int radix = 1 << pl.rb;
-            if (pass == 0) XC_LAUNCH(K_RADIX_COUNT, st, (radix_count_kernel<true><<<pl.nb, 256, 0, st>>>(nullptr, pl.P, pl.chunk, shift, pl.rb, pl.nb, counts, 0xffffffffu, 0, ks, kin, stats)));
-            else XC_LAUNCH(K_RADIX_COUNT, st, (radix_count_kernel<false><<<pl.nb, 256, 0, st>>>(kin, pl.P, pl.chunk, shift, pl.rb, pl.nb, counts, 0xffffffffu, 0, ks, nullptr, stats)));
+            if (pass == 0) XC_LAUNCH(K_RADIX_COUNT, st, (radix_count_kernel<true><<<pl.nb, kRoundThreads, 0, st>>>(nullptr, pl.P, pl.chunk, shift, pl.rb, pl.nb, counts, 0xffffffffu, 0, ks, kin, flags, stats)));
+            else XC_LAUNCH(K_RADIX_COUNT, st, (radix_count_kernel<false><<<pl.nb, kRoundThreads, 0, st>>>(kin, pl.P, pl.chunk, shift, pl.rb, pl.nb, counts, 0xffffffffu, 0, ks, nullptr, nullptr, stats)));
             XC_LAUNCH(K_RADIX_SCAN, st, (radix_prefix_kernel<<<radix, kWave, 0, st>>>(counts, pl.nb, totals)));
-            XC_LAUNCH(K_RADIX_SCATTER, st, (radix_scatter_kernel<<<pl.nb, kSortTile, sort_lds_bytes(pl.rb), st>>>(kin, kout, pl.P, pl.chunk, shift, pl.rb, pl.nb, counts, totals, 0xffffffffu, 0, nullptr)));
+            XC_LAUNCH(K_RADIX_SCATTER, st, (radix_scatter_kernel<<<pl.nb, kRoundThreads, sort_lds_bytes(pl.rb, kRoundThreads), st>>>(kin, kout, pl.P, pl.chunk, shift, pl.rb, pl.nb, counts, totals, 0xffffffffu, 0, nullptr)));
             XC_HIP_CHECK(hipGetLastError());
             uint2* tk = kin; kin = kout; kout = tk;
         }
-        XC_LAUNCH(K_HEADS_COUNT, st, (heads_count_kernel<<<pl.nb, 256, 0, st>>>(kin, pl.P, pl.chunk, static_cast<uint32_t>(L), head_cnt, valid_cnt, multi_cnt)));
-        XC_LAUNCH(K_HEADS_WRITE, st, (heads_write_kernel<<<pl.nb + 1, 256, 0, st>>>(kin, pl.P, pl.chunk, static_cast<uint32_t>(L), pl.nb, head_cnt,
+        XC_LAUNCH(K_HEADS_COUNT, st, (heads_count_kernel<<<pl.nb_heads, 256, 0, st>>>(kin, pl.P, pl.chunk_heads, static_cast<uint32_t>(L), head_cnt, valid_cnt, multi_cnt)));
+        XC_LAUNCH(K_HEADS_WRITE, st, (heads_write_kernel<<<pl.nb_heads + 1, 256, 0, st>>>(kin, pl.P, pl.chunk_heads, static_cast<uint32_t>(L), pl.nb_heads, head_cnt,
                                                                                 valid_cnt, touched, seg_start, seg_idx0, n_touched, nullptr, nullptr,
-                                                                                fuse ? single_slot : nullptr, multi_cnt, multi_list, stats)));
+                                                                                flags, slots, multi_cnt, multi_list, stats)));
         XC_HIP_CHECK(hipGetLastError());
     }
 
@@ -1565,14 +1579,14 @@ static int step_impl(const void* Z, void* W, int64_t B, int64_t L, int d, const 
     float* dz_target = SQ > 1 ? reinterpret_cast<float*>(w8 + pl.off_dzpart) : dZ;
     if (t == XC_BF16) {
         if (kind == XC_LOSS_BCE)
-            launch_gather<bf16_t, XC_LOSS_BCE>(pl, st, Z, W, B, L, d, pos, k_p, neg, logq, n_neg, fuse ? single_slot : nullptr, lr, W_rows_out, gco, loss_q, dz_target, SQ);
+            launch_gather<bf16_t, XC_LOSS_BCE>(pl, st, Z, W, B, L, d, pos, k_p, neg, logq, n_neg, flags, slots, lr, W_rows_out, gco, loss_q, dz_target, SQ);
         else
-            launch_gather<bf16_t, XC_LOSS_SOFTMAX>(pl, st, Z, W, B, L, d, pos, k_p, neg, logq, n_neg, fuse ? single_slot : nullptr, lr, W_rows_out, gco, loss_q, dz_target, SQ);
+            launch_gather<bf16_t, XC_LOSS_SOFTMAX>(pl, st, Z, W, B, L, d, pos, k_p, neg, logq, n_neg, flags, slots, lr, W_rows_out, gco, loss_q, dz_target, SQ);
     } else {
         if (kind == XC_LOSS_BCE)
-            launch_gather<float, XC_LOSS_BCE>(pl, st, Z, W, B, L, d, pos, k_p, neg, logq, n_neg, fuse ? single_slot : nullptr, lr, W_rows_out, gco, loss_q, dz_target, SQ);
+            launch_gather<float, XC_LOSS_BCE>(pl, st, Z, W, B, L, d, pos, k_p, neg, logq, n_neg, flags, slots, lr, W_rows_out, gco, loss_q, dz_target, SQ);
         else
-            launch_gather<float, XC_LOSS_SOFTMAX>(pl, st, Z, W, B, L, d, pos, k_p, neg, logq, n_neg, fuse ? single_slot : nullptr, lr, W_rows_out, gco, loss_q, dz_target, SQ);
+            launch_gather<float, XC_LOSS_SOFTMAX>(pl, st, Z, W, B, L, d, pos, k_p, neg, logq, n_neg, flags, slots, lr, W_rows_out, gco, loss_q, dz_target, SQ);
     }
     XC_HIP_CHECK(hipGetLastError());
 
