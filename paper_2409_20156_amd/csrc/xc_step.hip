@@ -1401,11 +1401,17 @@ static void launch_gather(const StepPlan& pl, hipStream_t st, const void* Z, voi
         if (KIND == XC_LOSS_BCE && fuse) XC_GATHER3(CPL, UU, FF, SS, (KIND == XC_LOSS_BCE));           \
         else XC_GATHER3(CPL, UU, FF, SS, false);                                                       \
     } while (0)
+    // Four rows in flight per group.  Eight cost half of the waves that fit a SIMD and pay only where there is less than
+    // one workgroup per compute unit, which the soft-max (a workgroup per query) meets in small batches: 100 queries x 1078
+    // candidates x 768 soft-max 100 against 109 us; 1024 x 628 x 768 soft-max 260 against 182, 100 x 1078 x 768 BCE 91
+    // against 66 (its queries are shared by up to four workgroups).
+    constexpr int kFewU = KIND == XC_LOSS_SOFTMAX ? 8 : 4;     // (4: no instance of its own)
 #define XC_GATHER(CPL)                                                                                 \
     do {                                                                                               \
         const bool full = (d / Elem<T>::kPerChunk) == pl.G * CPL && d % Elem<T>::kPerChunk == 0;       \
-        if (B * SQ <= 1024) {   /* few workgroups: more rows in flight per group */                   \
-            if (full) XC_GATHER2(CPL, 8, true, false); else XC_GATHER2(CPL, 8, false, false);          \
+        if (KIND == XC_LOSS_SOFTMAX && B <= 256) {                                                     \
+            if (full) XC_GATHER3(CPL, kFewU, true, false, false);                                      \
+            else XC_GATHER3(CPL, kFewU, false, false, false);                                          \
         } else if (full && pl.stream_gather) {                                                         \
             XC_GATHER2(CPL, 4, true, true);                                                            \
         } else {                                                                                       \
