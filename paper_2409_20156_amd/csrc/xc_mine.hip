@@ -24,6 +24,7 @@
 //   mine_select_kernel  after each phase, one wave per query cuts the global
 //       candidate list to its best k and publishes the new tau; after the last
 //       phase it sorts the winners by (score descending, id ascending).
+#include <cmath>
 #include <cstdlib>
 #include <mutex>
 #include <type_traits>
@@ -160,6 +161,8 @@ struct MineArgs {
     int32_t* gcnt;           // [nQT*kBN] fill of glist
     const uint32_t* tau_g;   // [nQT*kBN] ordered image of the phase threshold
     const unsigned char* zeros;   // 256 zero bytes (source of the chunks past the end of a row)
+    float* dense;            // first phase, all scores of its tiles: [nQT*kBN][dense_ld]
+    int dense_ld;
     const int32_t* cond;     // not null: repeat of a warm search; cond[0] != 0 if any query tile needs it,
                              // cond[1 + qt] != 0 if query tile qt does
 };
@@ -191,7 +194,8 @@ __device__ __noinline__ void issue_stage_slow(const unsigned char* base, int64_t
     }
 }
 
-template <typename T, bool KTAIL>
+// DENSE: the first phase, where no threshold exists yet: a work item is one tile, and all its scores are written.
+template <typename T, bool KTAIL, bool DENSE>
 __global__ __launch_bounds__(kMineThreads, 1)
 void mine_tile_kernel(const MineArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -424,6 +428,22 @@ void mine_tile_kernel(const MineArgs a) {
             }
 
 
+            if constexpr (DENSE) {
+                // accumulators 4 j .. 4 j + 3 of a block are four labels in a row of the lane's query
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt) {
+                    const int64_t q = q0 + wn * 64 + nt * 32 + (lane & 31);
+                    float* out = a.dense + q * a.dense_ld + static_cast<int>(t_begin - a.tile_lo + tile) * kBM + wm * 128 + 4 * (lane >> 5);
+#pragma unroll
+                    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                        for (int j = 0; j < 4; ++j)
+                            *reinterpret_cast<float4*>(out + mt * 32 + 8 * j) =
+                                make_float4(acc[mt][nt][4 * j], acc[mt][nt][4 * j + 1], acc[mt][nt][4 * j + 2], acc[mt][nt][4 * j + 3]);
+                }
+                continue;
+            }
+
             // ---- threshold filter: lane owns query column (lane & 31) of each N tile
             const bool last = tile + 1 == n_tiles;
             // The flag this tile may set shares its slot with the flag of two tiles back, which the waves
@@ -435,12 +455,17 @@ void mine_tile_kernel(const MineArgs a) {
                 constexpr int nt = decltype(ntc)::value;
                 const int qloc = wn * 64 + nt * 32 + (lane & 31);
                 const float t = (q0 + qloc) < a.Zq ? tau[qloc] : INFINITY;
-                float mx = acc[0][nt][0];
+                // the largest score of each 32-label block, then of all: a block is looked through only if its own passes
+                // (late phases let through about one score per four blocks: 10 M x 120 bf16, 18 834 queries 69.4 -> 65.9 ms
+                // together with the smaller growth of these phases)
+                float mb[4];
 #pragma unroll
-                for (int mt = 0; mt < 4; ++mt)
+                for (int mt = 0; mt < 4; ++mt) {
+                    mb[mt] = acc[mt][nt][0];
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc[mt][nt][i]);
-                if (__ballot(mx >= t) != 0ull) {
+                    for (int i = 1; i < 16; ++i) mb[mt] = fmaxf(mb[mt], acc[mt][nt][i]);
+                }
+                if (__ballot(fmaxf(fmaxf(mb[0], mb[1]), fmaxf(mb[2], mb[3])) >= t) != 0ull) {
                     // entry: score bits, query << 24 | label offset from the pool's first tile
                     auto row_word = [&]() {
                         uint32_t w = (static_cast<uint32_t>(qloc) << 24) |
@@ -451,6 +476,7 @@ void mine_tile_kernel(const MineArgs a) {
                     uint32_t qrow = row_word();
 #pragma unroll
                     for (int mt = 0; mt < 4; ++mt) {
+                        if (__ballot(mb[mt] >= t) == 0ull) continue;
 #pragma unroll
                         for (int i0 = 0; i0 < 16; i0 += kPoolCheck) {
 #pragma unroll
@@ -1105,6 +1131,118 @@ void mine_select_kernel(uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt
 }
 
 // ---------------------------------------------------------------------------
+// After the dense first phase: one wave per query takes the best k of its R * 256 scores (label = position) and publishes
+// the threshold.  The k-th largest of the 128 maxima that the lanes hold over halves of their scores bounds the k-th score from
+// below (k of the scores reach it); what passes that - about 1.3 k - goes through the radix select.  If too many pass
+// (equal scores), the k-th largest score is found by bisection over all of them, ties by the smaller label.
+// ---------------------------------------------------------------------------
+constexpr int kDenseTiles = 16;                 // tiles of the dense phase at most (one float4 per tile and lane)
+constexpr int kDenseMin = 4;                    // and at least: k <= 128 halves of the lanes' scores have a maximum
+constexpr int kDenseList = 512;                 // keys of a wave's list
+
+__device__ __forceinline__ uint32_t dense_image(float v) { return v == v ? float_to_ordered(v + 0.0f /* -0 -> +0 */) : 0u; }
+
+template <int R>
+__global__ __launch_bounds__(kSelectWaves * kWave)
+void mine_dense_select_kernel(const float* __restrict__ dense, int dense_ld, uint64_t* __restrict__ glist,
+                              int32_t* __restrict__ gcnt, uint32_t* __restrict__ tau_g, int64_t Zq, int glist_cap, int k) {
+    static_assert(R % 2 == 0 && R <= kDenseTiles, "");
+    __shared__ int hist[kSelectWaves][256];
+    __shared__ uint64_t picked[kSelectWaves][kDenseList];
+    const int lane = lane_id();
+    const int wave = threadIdx.x >> 6;
+    const int64_t q = static_cast<int64_t>(blockIdx.x) * kSelectWaves + wave;
+    if (q >= Zq) return;                               // wave-uniform; no workgroup barrier below
+    uint64_t* list = glist + static_cast<size_t>(q) * glist_cap;
+    // label of v[r][j]: 256 r + 4 lane + j; rows past dense_ld do not exist (image 0, as a score that is no number)
+    uint32_t v[R][4];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        float4 f = make_float4(NAN, NAN, NAN, NAN);
+        if (r * 256 < dense_ld) f = *reinterpret_cast<const float4*>(dense + q * dense_ld + r * 256 + lane * 4);
+        v[r][0] = dense_image(f.x); v[r][1] = dense_image(f.y); v[r][2] = dense_image(f.z); v[r][3] = dense_image(f.w);
+    }
+    uint32_t m[2] = {0, 0};
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m[r & 1] = v[r][j] > m[r & 1] ? v[r][j] : m[r & 1];
+    // k-th largest of the 128 maxima, bit by bit (k <= 128)
+    uint32_t t0 = 0;
+    for (int b = 31; b >= 0; --b) {
+        const uint32_t c = t0 | (1u << b);
+        if (__popcll(__ballot(m[0] >= c)) + __popcll(__ballot(m[1] >= c)) >= k) t0 = c;
+    }
+    t0 = t0 > 0 ? t0 : 1u;                             // (fewer than k maxima that are numbers: everything that is one)
+    uint64_t* keys = picked[wave];
+    int n = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool hit = v[r][j] >= t0;
+            const uint64_t bal = __ballot(hit);
+            if (hit) {
+                const int at = n + __popcll(bal & lanemask_lt());
+                if (at < kDenseList)
+                    keys[at] = (static_cast<uint64_t>(~v[r][j]) << 32) | static_cast<uint32_t>(r * 256 + lane * 4 + j);
+            }
+            n += __popcll(bal);
+        }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    if (n <= k) {                                      // all there are
+        for (int e = lane; e < n; e += kWave) list[e] = keys[e];
+        uint32_t lowest = 0xffffffffu;
+        if (n == k) {
+            for (int e = lane; e < n; e += kWave) { const uint32_t o = ~static_cast<uint32_t>(keys[e] >> 32); lowest = o < lowest ? o : lowest; }
+            for (int off = 32; off > 0; off >>= 1) { const uint32_t o = __shfl_xor(lowest, off, kWave); lowest = o < lowest ? o : lowest; }
+        }
+        if (lane == 0) { gcnt[q] = n; if (n == k) tau_g[q] = lowest; }
+        return;
+    }
+    if (n <= kDenseList) {
+        const float t = wave_select_k<kDenseList / kWave>(list, [keys](int idx) { return keys[idx]; }, n, k, hist[wave]);
+        if (lane == 0) { gcnt[q] = k; tau_g[q] = float_to_ordered(t); }
+        return;
+    }
+    uint32_t t = 0;                                    // the k-th largest score of all
+    for (int b = 31; b >= 0; --b) {
+        const uint32_t c = t | (1u << b);
+        int have = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) have += __popcll(__ballot(v[r][j] >= c));
+        if (have >= k) t = c;
+    }
+    int above = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) above += __popcll(__ballot(v[r][j] > t));
+    int out = 0, tie = 0;                              // written, and ties seen so far (labels ascend with r, lane, j)
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        uint64_t eq[4];
+        int lower = tie;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { eq[j] = __ballot(v[r][j] == t); lower += __popcll(eq[j] & lanemask_lt()); }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const bool mine = v[r][j] == t;
+            const bool take = v[r][j] > t || (mine && lower < k - above);
+            lower += mine ? 1 : 0;
+            const uint64_t bal = __ballot(take);
+            if (take)
+                list[out + __popcll(bal & lanemask_lt())] = (static_cast<uint64_t>(~v[r][j]) << 32) | static_cast<uint32_t>(r * 256 + lane * 4 + j);
+            out += __popcll(bal);
+            tie += __popcll(eq[j]);
+        }
+    }
+    if (lane == 0) { gcnt[q] = out; tau_g[q] = t; }
+}
+
+// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 struct MinePlan {
@@ -1138,6 +1276,53 @@ static int64_t phase_tiles(int64_t lo, int64_t nQT) {
         if (fill >= best_fill) { best_fill = fill; best = n; }
     }
     return best;
+}
+
+// Label tiles of a dense first phase (0: none).  Every score of it is written and read once (kBM floats per query and tile, in
+// `room` bytes), none goes through the filter, whose cost is that of the scores that pass: 0.37 us per score that every query
+// of 10 240 lets through, and thresholds found in phases of 1, 7 and 56 tiles let through 256, 384 and 448 of them, from work
+// items too few or too short to fill the chip.  About 48 k scores per query (the threshold costs memory traffic in proportion
+// to the scores, the passes it saves go with k), of these numbers of tiles the one whose items fill their last round best.
+// Measured, without : with, 131 072 x 768 bf16: k = 64, 1024 queries 435 : 279 us, 4096 1043 : 894, 10 240 2308 : 2180;
+// k = 5, 4096 873 : 783, 20 000 3782 : 3781; 300 000 x 768, k = 128, 40 000 19.8 : 19.4 ms; 60 000 x 128 fp32, k = 100,
+// 30 000 5.44 : 4.71.  Many queries with a short list have nothing to gain (131 072 x 392, k = 20, 20 000 3.47 : 3.55 ms).
+static int dense_tiles(int64_t nQT, int64_t full_tiles, int k, size_t room) {
+    if (k < 32 && nQT > 64) return 0;
+    int64_t most = (48 * k + kBM - 1) / kBM;
+    most = most < kDenseMin ? kDenseMin : (most > kDenseTiles ? kDenseTiles : most);
+    const int64_t fits = static_cast<int64_t>(room / (static_cast<size_t>(nQT) * kBN * kBM * sizeof(float)));
+    most = most < fits ? most : fits;
+    most = most < full_tiles / 2 ? most : full_tiles / 2;       // (and a range long enough to use the threshold on)
+    if (most < kDenseMin) return 0;
+    const int64_t least = 2 * most / 3 > kDenseMin ? 2 * most / 3 : kDenseMin;
+    int best = 0;
+    double best_fill = 0.0;
+    for (int64_t n = least; n <= most; ++n) {
+        const int64_t items = nQT * n;
+        const int64_t rounds = (items + kMineGrid - 1) / kMineGrid;
+        const double fill = static_cast<double>(items) / static_cast<double>(rounds * kMineGrid);
+        if (fill >= best_fill - 0.02) { best_fill = fill > best_fill ? fill : best_fill; best = static_cast<int>(n); }
+    }
+    return best;
+}
+
+// Label tiles of a phase behind a dense one, which starts at tile `lo` of nLT: equal growth to the end by at most 8.5, and so
+// that the candidates of a query stay within what the select holds in registers (1024), in whole multiples of the slices, so
+// that every slice of the phase has the same number of tiles.  By at most 3 where the tiles so far were 512 per compute unit:
+// a phase then lasts many times what the select between two of them takes, and every score that passes makes its wave look
+// through a block of accumulators (45.6 M x 120 bf16, 18 834 queries, k = 50, growth 7: the last phase alone 8 ms longer
+// than with a threshold that lets through 221 scores per query instead of 300).
+static int64_t even_phase_tiles(int64_t lo, int64_t nLT, int64_t nQT, int k, int slices) {
+    const double ratio = static_cast<double>(nLT) / static_cast<double>(lo);
+    double most = 960.0 / k;
+    most = most > 8.5 ? 8.5 : most;
+    if (lo * nQT >= 512 * kMineGrid && most > 3.0) most = 3.0;
+    const int m = static_cast<int>(ceil(log(ratio) / log(most) - 0.01));
+    if (m <= 1) return nLT - lo;
+    const double want = static_cast<double>(lo) * (pow(ratio, 1.0 / m) - 1.0);
+    int64_t n = static_cast<int64_t>(want / slices + 0.5) * slices;
+    if (n < slices) n = slices;
+    return n < nLT - lo ? n : nLT - lo;
 }
 
 // Slices per XCD for the kernel that keeps the query tile in registers.  The compute units of an XCD
@@ -1253,6 +1438,8 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     a.tau_g = tau_g;
     a.zeros = w8 + p.off_zero;
     a.cond = nullptr;
+    a.dense = nullptr;
+    a.dense_ld = 0;
     int32_t* flag = reinterpret_cast<int32_t*>(w8 + p.off_flag);
 
     // few queries: W is read once and the group maxima take the place of thresholds and lists.  A warm search of one
@@ -1272,10 +1459,14 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         XC_HIP_CHECK(hipGetDevice(&dev));
         std::lock_guard<std::mutex> lock(attr_mu);
         if (dev < 0 || dev >= 64 || !(attr_done_mask & (1ull << dev))) {
-            const void* fns[4] = {reinterpret_cast<const void*>(&mine_tile_kernel<bf16_t, false>),
-                                  reinterpret_cast<const void*>(&mine_tile_kernel<bf16_t, true>),
-                                  reinterpret_cast<const void*>(&mine_tile_kernel<float, false>),
-                                  reinterpret_cast<const void*>(&mine_tile_kernel<float, true>)};
+            const void* fns[8] = {reinterpret_cast<const void*>(&mine_tile_kernel<bf16_t, false, true>),
+                                  reinterpret_cast<const void*>(&mine_tile_kernel<bf16_t, true, true>),
+                                  reinterpret_cast<const void*>(&mine_tile_kernel<float, false, true>),
+                                  reinterpret_cast<const void*>(&mine_tile_kernel<float, true, true>),
+                                  reinterpret_cast<const void*>(&mine_tile_kernel<bf16_t, false, false>),
+                                  reinterpret_cast<const void*>(&mine_tile_kernel<bf16_t, true, false>),
+                                  reinterpret_cast<const void*>(&mine_tile_kernel<float, false, false>),
+                                  reinterpret_cast<const void*>(&mine_tile_kernel<float, true, false>)};
             for (const void* fn : fns)
                 XC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  static_cast<int>(p.lds_tile)));
@@ -1291,16 +1482,17 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     const dim3 select_grid(static_cast<unsigned>((Zq + kSelectWaves - 1) / kSelectWaves));
     uint32_t* zeros32 = reinterpret_cast<uint32_t*>(w8 + p.off_zero);
 
+    // bf16 rows of whole stages whose queries fit a wave's registers take the row kernel: work items of
+    // 512 queries where the pool fills them about as well as items of 256
+    const RowsKernel* rk = nullptr;
+    if (t == XC_BF16 && a.row_bytes % kStageBytes == 0 && !force_general_kernel()) {
+        const int nk = static_cast<int>(a.row_bytes / kStageBytes);
+        rk = find_rows_kernel(nk, rows_wide_items(Zq) ? 1 : 2);
+    }
+
     // one phase: the tile kernel over label tiles [lo, hi), then the select
     auto sweep = [&](int64_t lo, int64_t hi, const int32_t* cond) -> int {
         const int64_t nT = hi - lo;
-        // bf16 rows of whole stages whose queries fit a wave's registers take the row kernel: work items of
-        // 512 queries where the pool fills them about as well as items of 256
-        const RowsKernel* rk = nullptr;
-        if (t == XC_BF16 && a.row_bytes % kStageBytes == 0 && !force_general_kernel()) {
-            const int nk = static_cast<int>(a.row_bytes / kStageBytes);
-            rk = find_rows_kernel(nk, rows_wide_items(Zq) ? 1 : 2);
-        }
         const bool rows_kernel = rk != nullptr;
         a.nQT = rows_kernel ? (Zq + 2 * kBN / rk->wm - 1) / (2 * kBN / rk->wm) : p.nQT;
         if (nT >= kXcds) {
@@ -1325,11 +1517,11 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             // the query tile stays in registers, only W is streamed
             XC_LAUNCH(K_MINE_TILE, st, (rk->fn<<<kMineGrid, kMineThreads, rows_lds_bytes(rk->wm), st>>>(a)));
         } else if (t == XC_BF16) {
-            if (ktail) XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<bf16_t, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
-            else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<bf16_t, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            if (ktail) XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<bf16_t, true, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<bf16_t, false, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
         } else {
-            if (ktail) XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
-            else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            if (ktail) XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, true, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, false, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
         }
         XC_HIP_CHECK(hipGetLastError());
         return XC_OK;
@@ -1360,6 +1552,38 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     int64_t lo = 0;
     const bool q8 = p.q8.nk > 0 && !warm && ws_bytes >= p.ws_bytes && !force_general_kernel() && !force_rows_layout();
     unsigned char* q8_ws = w8 + p.ws_min;
+    if (cond == nullptr && rk == nullptr) {
+        // the first phase dense, by the general kernel: as many tiles as one or a few full rounds of the compute units take
+        const int n0 = dense_tiles(p.nQT, L / kBM, k_h, p.off_glist - p.off_lists);
+        if (n0 > 0) {
+            a.nQT = p.nQT;
+            a.tile_lo = 0; a.tile_hi = n0; a.tiles_per_slice = 1;
+            a.S = n0; a.Qx = 0;
+            a.dense = reinterpret_cast<float*>(w8 + p.off_lists);
+            a.dense_ld = n0 * kBM;
+            a.cond = nullptr;
+            const bool ktail = (a.row_bytes % kStageBytes) != 0;
+            if (t == XC_BF16) {
+                if (ktail) XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<bf16_t, true, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+                else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<bf16_t, false, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            } else {
+                if (ktail) XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, true, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+                else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, false, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            }
+            XC_HIP_CHECK(hipGetLastError());
+            if (n0 <= kDenseMin)
+                XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<kDenseMin><<<select_grid, kSelectWaves * kWave, 0, st>>>(
+                    a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
+            else if (n0 <= 8)
+                XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<8><<<select_grid, kSelectWaves * kWave, 0, st>>>(
+                    a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
+            else
+                XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<kDenseTiles><<<select_grid, kSelectWaves * kWave, 0, st>>>(
+                    a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
+            XC_HIP_CHECK(hipGetLastError());
+            lo = n0;
+        }
+    }
     if (q8) { const int rcq = q8_begin(p.q8, q8_ws, Z, Zq, st); if (rcq != XC_OK) return rcq; }
     while (lo < p.nLT) {
         if (q8 && lo >= kQ8FirstTile) {
@@ -1381,7 +1605,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             continue;
         }
         // phases end at about 1, 8, 64, ... tiles: each sees about 8x the labels seen before it
-        int64_t hi = lo + phase_tiles(lo, p.nQT);
+        int64_t hi = lo + (a.dense != nullptr ? even_phase_tiles(lo, p.nLT, p.nQT, k_h, slices_cap(p.kcap)) : phase_tiles(lo, p.nQT));
         if (hi > p.nLT || p.nLT - hi < hi / 4) hi = p.nLT;      // fold a short remainder into this phase
         const int rcp = phase(lo, hi, cond, nullptr);
         if (rcp != XC_OK) return rcp;
