@@ -4,13 +4,14 @@
 //   few_max_kernel     streams W once.  A wave multiplies 32 labels with all queries of the workgroup, whose
 //       rows lie in LDS as MFMA operands, and keeps of every group of 16 << gshift labels the largest score per
 //       query: the only thing written, 1 / (16 << gshift) of the score matrix.
-//   few_finish_kernel  one workgroup per query: the k-th largest group maximum tau (radix select).  At least k
+//   few_finish_kernel  one workgroup per query: the k-th largest group maximum tau (one radix digit or more, then by
+//       counting).  At least k
 //       labels score tau or more, so every label of the answer does, and it lies in a group whose maximum is
 //       above tau or, for scores equal to tau, in one of the first groups (in label order) whose maximum is tau:
 //       of equal scores the smaller ids win, and each of these groups holds one.  So k groups in all hold the
 //       answer.  Their scores are formed again, with the same instructions in the same order (hence the same
 //       bits), what is below tau is dropped, the rest sorted.
-// Bound: HBM, one read of W.  131 072 x 768 bf16, 32 queries, k = 5: 72 us in all (first kernel 44 us, 4.5 TB/s of the 5.1
+// Bound: HBM, one read of W.  131 072 x 768 bf16, 32 queries, k = 5: 70 us in all (first kernel 44 us, 4.5 TB/s of the 5.1
 // a plain copy reaches), where the general kernel took 378; 30 M x 256 bf16, 32 queries: 3.3 ms (4.7 TB/s) against 8.5.  In
 // fp32 with many queries the matrix pipe: 1000 queries x 50 021 x 300, 368 us against 782 (the products alone take 195).
 // No thresholds to find in phases, no lists that could overflow, two launches.  The general kernel pads the
@@ -272,27 +273,45 @@ void few_finish_kernel(const FewArgs a) {
     if (a.flag != nullptr && blockIdx.x == 0)
         for (int i = tid; i < a.n_flag; i += NT) a.flag[i] = 0;
 
-    // ---- the k-th largest group maximum: digits of 11, 11, 10 bits, from the top
+    // ---- the k groups: digits of 11, 11, 10 bits of the maxima, from the top, until the groups at or above the digit of the
+    // k-th are few enough to be ordered by counting (after the first digit where k is small).  The maxima are read once
+    // where the threads can hold them.
+    constexpr int kHold = 8;
+    const bool held = a.n_groups <= NT * kHold;                // uniform
+    uint32_t hv[kHold];
+    if (held) {
+#pragma unroll
+        for (int j = 0; j < kHold; ++j) hv[j] = tid + j * NT < a.n_groups ? gm[tid + j * NT] : 0u;
+    }
+    // f(value, group) for every group, in no order
+    auto for_groups = [&](auto f) {
+        if (held) {
+#pragma unroll
+            for (int j = 0; j < kHold; ++j) f(hv[j], static_cast<int32_t>(tid + j * NT));
+        } else {
+            for (int64_t i = tid; i < a.n_groups; i += NT) f(gm[i], static_cast<int32_t>(i));
+        }
+    };
+    if (tid == 0) { n_sel = 0; n_key = 0; tau_sh = 0xffffffffu; }
     uint32_t prefix = 0;           // the digits found so far
     int bits = 32;                 // bits below them
     int need = a.k;                // groups still to take among those that share the prefix
-    bool all = false, exact = false;
+    uint32_t bound = 0;            // the groups at or above it are ordered by counting; 0: too many with the same maximum
     for (int pass = 0; pass < 3; ++pass) {
         const int width = pass < 2 ? 11 : 10;
         for (int d = tid; d < 2048; d += NT) hist[d] = 0;
         __syncthreads();
-        for (int64_t i = tid; i < a.n_groups; i += NT) {
-            const uint32_t o = gm[i];
+        for_groups([&](uint32_t o, int32_t) {
             if (o != 0 && (pass == 0 || (o >> bits) == prefix))
                 atomicAdd(&hist[(o >> (bits - width)) & ((1u << width) - 1u)], 1);
-        }
+        });
         __syncthreads();
         constexpr int kPer = 2048 / NT;                                        // digits per thread, largest first
         int c[kPer], local = 0, total;
 #pragma unroll
         for (int j = 0; j < kPer; ++j) { c[j] = hist[2047 - kPer * tid - j]; local += c[j]; }
         int before = block_excl_scan<NT>(local, sh, &total);
-        if (pass == 0 && total <= a.k) { all = true; break; }                  // uniform: no more groups than wanted
+        if (pass == 0 && total <= kRankSort) { bound = 1u; break; }            // uniform
 #pragma unroll
         for (int j = 0; j < kPer; ++j) {
             if (before < need && need <= before + c[j]) { sel_bin = 2047 - kPer * tid - j; sel_need = need - before; sel_have = c[j]; }
@@ -302,51 +321,44 @@ void few_finish_kernel(const FewArgs a) {
         bits -= width;
         prefix = (prefix << width) | static_cast<uint32_t>(sel_bin);
         need = sel_need;
-        if (sel_have == need) { exact = true; break; }                         // uniform: all that share the prefix
+        if (a.k - need + sel_have <= kRankSort) { bound = prefix << bits; break; }      // uniform
         __syncthreads();
     }
-    // taken: every group above the prefix, and `need` of those that share it (all of them if `exact`; else the
-    // prefix is a whole score and the first `need` in label order are taken)
-    if (tid == 0) { n_sel = 0; n_key = 0; tau_sh = 0xffffffffu; }
+    // (bound 0: the prefix is a whole score.  Taken are the groups above it and the first `need` in label order of those
+    // that share it; adding 1 cannot wrap: the largest image is that of a NaN)
+    const uint32_t least = bound != 0 ? bound : prefix + 1u;
+    for_groups([&](uint32_t o, int32_t i) {
+        if (o >= least) keys[atomicAdd(&n_key, 1)] = (static_cast<uint64_t>(~o) << 32) | static_cast<uint32_t>(i);
+    });
     __syncthreads();
-    const uint32_t bound = all ? 1u : (exact ? prefix << bits : prefix + 1u);  // (prefix + 1 cannot wrap: that is a NaN image)
-    for (int64_t i = tid; i < a.n_groups; i += NT) {
-        const uint32_t o = gm[i];
-        if (o >= bound) {
-            groups[atomicAdd(&n_sel, 1)] = static_cast<int32_t>(i);
-            atomicMin(&tau_sh, o);
-        }
+    const int n_cand = n_key;
+    for (int m = tid; m < n_cand; m += NT) {                   // larger maxima first, of equal ones the smaller labels
+        const uint64_t mine = keys[m];
+        int rank = 0;
+        for (int e = 0; e < n_cand; ++e) rank += keys[e] < mine ? 1 : 0;
+        if (rank < a.k) groups[rank] = static_cast<int32_t>(mine & 0xffffffffu);
+        if (rank == a.k - 1) tau_sh = ~static_cast<uint32_t>(mine >> 32);
     }
-    if (!all && !exact) {
-        __syncthreads();
-        const int first = n_sel;
+    if (tid == 0) n_sel = n_cand < a.k ? n_cand : a.k;
+    if (bound == 0) {
         int got = 0;
-        for (int64_t i0 = 0; got < need; i0 += NT) {               // uniform (need <= their number)
+        for (int64_t i0 = 0; got < need; i0 += NT) {           // uniform (need <= their number)
             const int64_t i = i0 + tid;
             const bool tie = i < a.n_groups && gm[i] == prefix;
             int total;
             const int at = got + block_excl_scan<NT>(tie ? 1 : 0, sh, &total);
-            if (tie && at < need) groups[first + at] = static_cast<int32_t>(i);
+            if (tie && at < need) groups[n_cand + at] = static_cast<int32_t>(i);
             got += total;
         }
         __syncthreads();
-        if (tid == 0) { n_sel = first + need; tau_sh = prefix; }
+        if (tid == 0) { n_sel = a.k; tau_sh = prefix; }
     }
     __syncthreads();
-    // in label order: the workgroups that share the query have to agree on whose block is whose
-    {
-        int32_t mine = 0;
-        int rank = 0;
-        if (tid < n_sel) {
-            mine = groups[tid];
-            for (int e = 0; e < n_sel; ++e) rank += groups[e] < mine ? 1 : 0;
-        }
-        __syncthreads();
-        if (tid < n_sel) groups[rank] = mine;
-        __syncthreads();
-    }
+    const uint32_t tau = n_sel < a.k ? 1u : tau_sh;            // (fewer groups with a score than k: every score counts)
+    __syncthreads();
+    if (tid == 0) n_key = 0;
+    __syncthreads();
     const int n_blocks = n_sel << a.gshift;                    // blocks of 16 labels
-    const uint32_t tau = all ? 1u : tau_sh;
 
     // ---- the scores of these groups again: one query in all 16 columns of the product
     const int r = lane & 15, g = lane >> 4;
