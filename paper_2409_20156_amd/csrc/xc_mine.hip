@@ -1332,13 +1332,18 @@ static int64_t even_phase_tiles(int64_t lo, int64_t nLT, int64_t nQT, int k, int
 // delivered W, with one slice 19 % faster).  The other side: 32 / slices query tiles are in flight per
 // XCD, and compute units without a query tile idle.  Among the counts the phase allows (<= sx_max) take
 // the one that keeps the most compute units busy, and of those the smallest.
-static int rows_slices_per_xcd(int64_t nQT, int sx_max) {
+// Opening and closing an item (operands, the ring, the lists) costs about what eight tiles of a slice do, so that short
+// slices are not worth a slightly fuller last round (60 items of 256 queries over 803 tiles: 2 rounds of 100 tiles are 94 %
+// full, 15 rounds of 13 tiles are 100 % full and took 1.8 times as long; 205 654 x 256, 50 000 queries 13.5 -> 7.6 ms from
+// scratch, 7.4 -> 5.4 from thresholds; 2 M x 128, 30 000 queries 23.3 -> 13.7).
+static int rows_slices_per_xcd(int64_t nQT, int64_t n_tiles, int sx_max) {
     int best = sx_max;
     double best_eff = -1.0;
     for (int sx = 1; sx <= sx_max; sx <<= 1) {
         const int qx = kCusPerXcd / sx;
         const int64_t rounds = (nQT + qx - 1) / qx;
-        const double eff = static_cast<double>(nQT) / static_cast<double>(rounds * qx);
+        const double per = static_cast<double>(n_tiles) / (kXcds * sx);
+        const double eff = static_cast<double>(nQT) / static_cast<double>(rounds * qx) * per / (per + 8.0);
         if (eff > best_eff + 1e-9) { best_eff = eff; best = sx; }
     }
     return best;
@@ -1346,7 +1351,7 @@ static int rows_slices_per_xcd(int64_t nQT, int sx_max) {
 
 // Work items of 512 queries (the row kernel with all eight waves along the queries) stage half the
 // bytes of W per flop, but there are half as many of them: they are taken where they keep the 32 compute
-// units of an XCD busy with one label slice, as well as items of 256 would.  Measured, 256 against 512:
+// units of an XCD busy with one label slice (nine in ten over all rounds), as well as items of 256 would.  Measured, 256 against 512:
 // 4 M x 256, k = 50: 512 queries 1.90 : 3.43 ms, 2048 4.25 : 4.53, 8192 14.9 : 14.9, 16 384 28.8 : 28.0;
 // 1.3 M x 128: 4096 queries 2.31 : 2.46 ms, 16 384 8.2 : 7.6.  XC_MINE_ROWS=narrow or wide in the
 // environment (read at every call) overrides the rule, for A/B timing and for tests.
@@ -1357,11 +1362,11 @@ static bool force_rows_layout() {
 static bool rows_wide_items(int64_t Zq) {
     if (force_rows_layout()) return getenv("XC_MINE_ROWS")[0] == 'w';
     const int64_t wide = (Zq + 2 * kBN - 1) / (2 * kBN), narrow = (Zq + kBN - 1) / kBN;
-    if (wide < kCusPerXcd) return false;
-    // compute units that a full set of rounds would have busy, against those that are: wide / its rounds >= narrow / its
-    // rounds, crosswise
+    // the share of an XCD's compute units that one slice's items keep busy, over all rounds
     const int64_t rw = (wide + kCusPerXcd - 1) / kCusPerXcd, rn = (narrow + kCusPerXcd - 1) / kCusPerXcd;
-    return 17 * wide * rn >= 16 * narrow * rw;
+    const double busy_w = static_cast<double>(wide) / static_cast<double>(rw * kCusPerXcd);
+    const double busy_n = static_cast<double>(narrow) / static_cast<double>(rn * kCusPerXcd);
+    return busy_w >= 0.9 && busy_w >= 0.94 * busy_n;
 }
 
 static int plan_mine(int64_t Zq, int64_t L, int d, int k_h, xc_dtype t, MinePlan* p) {
@@ -1500,7 +1505,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             // flight per XCD and their Z rows stay in that XCD's L2
             int Sx = 8;
             while (Sx > 1 && (nT < static_cast<int64_t>(kXcds) * Sx || kXcds * Sx > slices_cap(p.kcap))) Sx >>= 1;
-            if (rows_kernel) Sx = rows_slices_per_xcd(a.nQT, Sx);
+            if (rows_kernel) Sx = rows_slices_per_xcd(a.nQT, nT, Sx);
             a.S = kXcds * Sx;
             a.Qx = kCusPerXcd / Sx;
         } else {                                           // a few tiles: one slice per tile, plain order
