@@ -88,6 +88,7 @@ struct FewPlan {
 // and the candidates of shared queries.
 bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, size_t scratch, FewPlan* p);
 
+int few_raise_lds();         // the dynamic LDS limit of its kernels, on the current device
 int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int64_t L, int64_t row_bytes, int k,
                  xc_dtype t, unsigned char* scratch, uint32_t* tau_g, int32_t* flag /* null: leave alone */, int n_flag,
                  int32_t* shortlist, float* scores, hipStream_t st);
@@ -113,6 +114,7 @@ struct Q8Chunk {
 };
 
 bool plan_q8(int64_t Zq, int64_t L, int64_t row_bytes, xc_dtype t, Q8Plan* p);
+int q8_raise_lds();
 int q8_begin(const Q8Plan& p, unsigned char* ws, const void* Z, int64_t Zq, hipStream_t st);
 // Filters labels [lab0, lab1) and appends the keys of those that reach the thresholds to the queries' global lists, except
 // for query tiles qt whose flag q8_flags()[1 + qt] is set afterwards (then [0] is too): for these the caller searches the range itself.

@@ -1447,14 +1447,6 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     a.dense_ld = 0;
     int32_t* flag = reinterpret_cast<int32_t*>(w8 + p.off_flag);
 
-    // few queries: W is read once and the group maxima take the place of thresholds and lists.  A warm search of one
-    // query tile has nothing to gain there and nothing to repeat; of more, its one sweep is the better way.
-    FewPlan few;
-    if (!(warm && Zq > kBN) && !force_general_kernel() && !force_rows_layout() &&
-        plan_few(Zq, L, a.row_bytes, k_h, t, p.off_glist - p.off_lists, &few))
-        return run_mine_few(few, Z, W, Zq, L, a.row_bytes, k_h, t, w8 + p.off_lists, tau_g,
-                            warm ? flag : nullptr, static_cast<int>(p.nQT) + 1, shortlist, scores, st);
-
     // raise the dynamic LDS limit of the tile kernels: once per device and process (the attribute
     // belongs to the device's copy of the kernel)
     static std::mutex attr_mu;
@@ -1479,9 +1471,20 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
                 XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k.fn),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  static_cast<int>(rows_lds_bytes(k.wm))));
+            int rca = few_raise_lds();
+            if (rca == XC_OK) rca = q8_raise_lds();
+            if (rca != XC_OK) return rca;
             if (dev >= 0 && dev < 64) attr_done_mask |= 1ull << dev;
         }
     }
+    // few queries: W is read once and the group maxima take the place of thresholds and lists.  A warm search of one
+    // query tile has nothing to gain there and nothing to repeat; of more, its one sweep is the better way.
+    FewPlan few;
+    if (!(warm && Zq > kBN) && !force_general_kernel() && !force_rows_layout() &&
+        plan_few(Zq, L, a.row_bytes, k_h, t, p.off_glist - p.off_lists, &few))
+        return run_mine_few(few, Z, W, Zq, L, a.row_bytes, k_h, t, w8 + p.off_lists, tau_g,
+                            warm ? flag : nullptr, static_cast<int>(p.nQT) + 1, shortlist, scores, st);
+
     const int64_t nq = p.nQT * kBN;
     const dim3 init_grid(static_cast<unsigned>((nq + 255) / 256));
     const dim3 select_grid(static_cast<unsigned>((Zq + kSelectWaves - 1) / kSelectWaves));

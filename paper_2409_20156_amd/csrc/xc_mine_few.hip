@@ -496,6 +496,25 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, size_
     return round_up(q * p->n_groups * 4, 256) + q * ns * kPartKeys * 8 + round_up(q * ns * 4, 256) + q * 4 <= scratch;
 }
 
+typedef void (*FewFn)(const FewArgs);
+template <typename T>
+static FewFn few_kernel(int nb, bool ktail) {
+    return nb == 1 ? (ktail ? &few_max_kernel<T, 1, true> : &few_max_kernel<T, 1, false>)
+         : nb == 2 ? (ktail ? &few_max_kernel<T, 2, true> : &few_max_kernel<T, 2, false>)
+                   : (ktail ? &few_max_kernel<T, 4, true> : &few_max_kernel<T, 4, false>);
+}
+
+int few_raise_lds() {
+    for (int nb = 1; nb <= 4; nb <<= 1)
+        for (int tail = 0; tail < 2; ++tail)
+            for (int f32 = 0; f32 < 2; ++f32) {
+                const FewFn fn = f32 ? few_kernel<float>(nb, tail != 0) : few_kernel<bf16_t>(nb, tail != 0);
+                XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kFewLds)));
+            }
+    return XC_OK;
+}
+
 template <typename T>
 static int launch_few(const FewPlan& p, const FewArgs& a, hipStream_t st) {
     const bool ktail = a.row_bytes % 64 != 0;
@@ -507,13 +526,7 @@ static int launch_few(const FewPlan& p, const FewArgs& a, hipStream_t st) {
     per_qb = per_qb < enough ? per_qb : (enough + 7) / 8 * 8;
     per_qb = per_qb < 8 ? 8 : per_qb / 8 * 8;                 // (never more workgroups than are resident at once)
     const dim3 grid(static_cast<unsigned>(per_qb * p.n_qb));
-    typedef void (*Fn)(const FewArgs);
-    const Fn fn = p.nb == 1 ? (ktail ? &few_max_kernel<T, 1, true> : &few_max_kernel<T, 1, false>)
-                : p.nb == 2 ? (ktail ? &few_max_kernel<T, 2, true> : &few_max_kernel<T, 2, false>)
-                            : (ktail ? &few_max_kernel<T, 4, true> : &few_max_kernel<T, 4, false>);
-    if (p.lds > (64u << 10))
-        XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         static_cast<int>(kFewLds)));
+    const FewFn fn = few_kernel<T>(p.nb, ktail);
     XC_LAUNCH(K_MINE_TILE, st, (fn<<<grid, kFewThreads, p.lds, st>>>(a)));
     XC_HIP_CHECK(hipGetLastError());
     if (a.Zq >= kSmallFinishQueries)

@@ -539,6 +539,14 @@ bool plan_q8(int64_t Zq, int64_t L, int64_t row_bytes, xc_dtype t, Q8Plan* p) {
     return true;
 }
 
+int q8_raise_lds() {
+    XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&mine_q8_kernel<1>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kQ8Lds)));
+    XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&mine_q8_kernel<2>),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kQ8Lds)));
+    return XC_OK;
+}
+
 int q8_begin(const Q8Plan& p, unsigned char* ws, const void* Z, int64_t Zq, hipStream_t st) {
     const dim3 grid(static_cast<unsigned>((Zq + 3) / 4));
     const unsigned char* z = static_cast<const unsigned char*>(Z);
@@ -584,8 +592,6 @@ static int q8_chunk_impl(const Q8Plan& p, unsigned char* ws, const Q8Chunk& c, h
         w + c.lab0 * 256 * NK, n_lab, ws + p.off_rows, reinterpret_cast<float4*>(ws + p.off_meta), c.gcnt, gbase,
         static_cast<int64_t>(a.n_qt) * kBN, a.flag, a.n_qt, a.given_up, a.given_up + 1)));
     XC_HIP_CHECK(hipGetLastError());
-    XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(&mine_q8_kernel<NK>),
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kQ8Lds)));
     XC_LAUNCH(K_MINE_TILE, st, (mine_q8_kernel<NK><<<kMineGrid, kMineThreads, kQ8Lds, st>>>(a)));
     XC_HIP_CHECK(hipGetLastError());
     XC_LAUNCH(K_MINE_SELECT, st, (q8_rescore_kernel<NK><<<static_cast<unsigned>((c.Zq + 3) / 4), 256, 0, st>>>(

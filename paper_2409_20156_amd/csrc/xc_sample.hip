@@ -23,12 +23,12 @@ __device__ __forceinline__ uint64_t fmix64(uint64_t x) {
 // One workgroup per query.  The distinct in-range ids of the shortlist row, in ascending order h_0 < h_1 < ..., are
 // stored as a_m = h_m - m, which is non-decreasing.  Draw r in [0, M) then maps to the r-th label of the complement:
 // r + #{m : a_m <= r}.
-// Rows of up to kRankRow ids find their order by counting: a first pass marks the repeats, a second counts the distinct
-// smaller ids, both read the row from LDS four ids at a time, the same for all lanes - two barriers, where sorting takes
-// one for each of the 28 steps of 128 ids.  The number of draws and the size of the complement are the same for every row
-// without repeats, so their log comes from the host; a row with some forms its own.  Bound: launch and the dependent
-// steps of a workgroup, not bytes.  2048 rows of 100 + 1024 ids: 17.4 -> 12.1 us per call (8.6 of
-// them the caller, per call, before the launch).
+// Rows of up to kRankRow ids find their order by counting the smaller ids, every wave a part of the row, four ids at a
+// time and the same for all lanes; equal ids get equal counts, which is how repeats are found.  (Sorting took a barrier for each of
+// the 28 steps of 128 ids, and one wave, the same in every workgroup, did all of it on its SIMD.)  The number of draws and the
+// size of the complement are the same for every row without repeats, so their log comes from the host; a row with some
+// forms its own.  Bound: the vector ALU, whose 64-bit products the mixer needs, and the launch.  2048 rows of 100 + 1024
+// ids: 17.4 -> 11.3 us per call, of which the caller takes 8.6.
 constexpr int kRankRow = 256;
 constexpr int kDraws = 4;                // draws a thread makes side by side
 

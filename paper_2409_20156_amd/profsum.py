@@ -11,8 +11,8 @@ counter read for the plain copy kernel of known size in the same run, and writes
 launch into the JSON file the benchmark reads; for the search it also writes the bytes of one
 whole search (all tile-kernel launches between two `mine_init` launches) and says whether the
 searches of the run started from scratch or from earlier thresholds.  `sq` turns one run with the shader counters
-SQ_VALU_MFMA_BUSY_CYCLES, SQ_INSTS_VALU_MFMA_MOPS_BF16, SQ_BUSY_CU_CYCLES, SQ_WAVE_CYCLES, SQ_WAIT_ANY
-and GRBM_GUI_ACTIVE into matrix-pipe utilisation, the share of their time waves spend waiting, and
+SQ_VALU_MFMA_BUSY_CYCLES, SQ_INSTS_VALU_MFMA_MOPS_BF16, SQ_INSTS_VALU_MFMA_MOPS_I8 (if collected),
+SQ_BUSY_CU_CYCLES, SQ_WAVE_CYCLES, SQ_WAIT_ANY and GRBM_GUI_ACTIVE into matrix-pipe utilisation, the share of their time waves spend waiting, and
 the shader clock.
 """
 from __future__ import annotations
@@ -25,6 +25,9 @@ from collections import defaultdict
 
 # kernel function name -> name used by the benchmark
 KERNELS = {"mine_tile_kernel": "mine_tile", "mine_rows_kernel": "mine_tile", "mine_select_kernel": "mine_select",
+           "few_max_kernel": "mine_tile", "q8_rows_kernel": "mine_tile", "mine_q8_kernel": "mine_tile",
+           "few_finish_kernel": "mine_select", "q8_rescore_kernel": "mine_select",
+           "mine_dense_select_kernel": "mine_select", "q8_queries_kernel": "mine_queries", "sort_small_kernel": "bucket_sort",
            "mine_init_kernel": "mine_init", "mine_warm_init_kernel": "mine_warm_init",
            "sample_kernel": "sample", "gather_kernel": "gather", "radix_count_kernel": "radix_count",
            "radix_prefix_kernel": "radix_scan", "radix_scatter_kernel": "radix_scatter",
@@ -182,7 +185,7 @@ def sq(src, out, title, cmd):
         f.write("Sums over all dispatches of a kernel. *matrix pipe busy* = SQ_VALU_MFMA_BUSY_CYCLES / (1024 SIMDs x "
                 "GRBM_GUI_ACTIVE / 8 XCDs), the profiler's own MfmaUtil formula; *of CU-busy time* divides by "
                 "4 x SQ_BUSY_CU_CYCLES instead (leaves out launch ramps and idle CUs); *waves waiting* = SQ_WAIT_ANY / "
-                "SQ_WAVE_CYCLES; *MFMA TFLOP* = 512 x SQ_INSTS_VALU_MFMA_MOPS_BF16; *clock* = GRBM_GUI_ACTIVE / 8 / "
+                "SQ_WAVE_CYCLES; *MFMA TFLOP* = 512 x (SQ_INSTS_VALU_MFMA_MOPS_BF16 + SQ_INSTS_VALU_MFMA_MOPS_I8); *clock* = GRBM_GUI_ACTIVE / 8 / "
                 "duration over the dispatches longer than 0.4 ms.\n\n")
         f.write("| kernel | dispatches | total ms | MFMA TFLOP | matrix pipe busy | of CU-busy time | waves waiting | clock GHz |\n"
                 "|---|---|---|---|---|---|---|---|\n")
@@ -193,7 +196,7 @@ def sq(src, out, title, cmd):
             busy = 4.0 * c["SQ_BUSY_CU_CYCLES"]          # clocks summed over SIMDs
             clock = "%.2f" % (long_gui[n] / long_ns[n]) if long_ns[n] else "-"
             f.write("| %s | %d | %.3f | %.3f | %.3f | %.3f | %.3f | %s |\n"
-                    % (n, len(dur[n]), ns / 1e6, 512.0 * c["SQ_INSTS_VALU_MFMA_MOPS_BF16"] / 1e12,
+                    % (n, len(dur[n]), ns / 1e6, 512.0 * (c["SQ_INSTS_VALU_MFMA_MOPS_BF16"] + c["SQ_INSTS_VALU_MFMA_MOPS_I8"]) / 1e12,
                        c["SQ_VALU_MFMA_BUSY_CYCLES"] / (kSimds * gui) if gui else 0.0,
                        c["SQ_VALU_MFMA_BUSY_CYCLES"] / busy if busy else 0.0,
                        c["SQ_WAIT_ANY"] / c["SQ_WAVE_CYCLES"] if c["SQ_WAVE_CYCLES"] else 0.0, clock))
