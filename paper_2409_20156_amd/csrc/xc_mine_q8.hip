@@ -171,8 +171,8 @@ void q8_rows_kernel(const unsigned char* __restrict__ W /* first row of the chun
 // 16 384 queries x 12 M labels x 256 (search, ms): 44.0; without the looks at single scores and the pushes 38.2; also
 // without the maxima 38.1, the stage loads 35.5, the stage barriers 35.1, the operand reads 32.6, which leaves the products
 // (3.5 POP/s at the chip's power limit) and what goes before them.  A score is looked at on its own only in a group of eight
-// whose maximum passes (all 32 of a column in turn: 47.7).  16 384 x 120 M x 256, k = 50: 371 ms, of which 15 form the 8-bit
-// rows; 685 with the bf16 kernel.
+// whose maximum passes (all 32 of a column in turn: 47.7).  16 384 x 120 M x 256, k = 50: 371 to 389 ms on different
+// boxes, of which 15 form the 8-bit rows; 685 to 707 with the bf16 kernel.
 // ---------------------------------------------------------------------------
 struct Q8Args {
     const unsigned char* Z;          // 8-bit queries [Zq][128 NK]
