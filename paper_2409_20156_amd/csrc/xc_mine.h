@@ -28,7 +28,20 @@ constexpr int kSelectRegs = 16;     // keys per lane held in registers by the ph
 constexpr uint32_t kTauInit = 0x007fffffu;   // ordered image of -inf
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+
+// One order of sums.  A label's score has the same bits in every search kernel, so that equal rows tie wherever they are
+// scored and every route to a shortlist (from scratch, from thresholds, few queries, the filter) gives the same one.  The order
+// is that of the tile kernels: a row's 16-byte chunks in pairs, each pair one v_mfma_f32_32x32x16_bf16, from an accumulator
+// of zero.  v_mfma_f32_16x16x32_bf16, which takes two pairs, adds its products as two of those do: 21 million random sums
+// of 64 products, with exponents spread over 0 to 40 binary orders, agree bit for bit.
+__device__ __forceinline__ f32x4 row_mma_bf16(const uint4& a /* 16 rows */, const uint4& b /* 16 columns */, f32x4 c) {
+    bf16x8 av, bv;
+    __builtin_memcpy(&av, &a, 16);
+    __builtin_memcpy(&bv, &b, 16);
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
+}
 
 constexpr int kRing = 8;            // stages in LDS (8 or 16 KiB each)
 static_assert(kRing >= 4 && (kRing & (kRing - 1)) == 0, "stage slots are indexed modulo a power of two, and the two halves of the workgroup fill them in turn");

@@ -21,9 +21,6 @@
 
 namespace xc {
 
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 few_bf16x8 __attribute__((ext_vector_type(8)));
-
 constexpr int kFewThreads = 512;
 constexpr int kFewWaves = kFewThreads / kWave;
 constexpr int kFewRing = 8;              // 64-byte steps in flight per wave (two rows of 16 B per lane each: 16 KiB)
@@ -43,10 +40,7 @@ static_assert(kPartKeys >= XC_MAX_K_MINE, "a workgroup hands over at least its b
 template <typename T> struct FewMma;
 template <> struct FewMma<bf16_t> {
     static __device__ __forceinline__ f32x4 mma(const uint4& a, const uint4& b, f32x4 c) {
-        few_bf16x8 av, bv;
-        __builtin_memcpy(&av, &a, 16);
-        __builtin_memcpy(&bv, &b, 16);
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
+        return row_mma_bf16(a, b, c);
     }
 };
 template <> struct FewMma<float> {

@@ -5,7 +5,8 @@
 //   <z, w> = a b <p, q> + <a p, dw> + <dz, w>,  hence  <z, w> <= a b <p, q> + |a p| |dw| + |dz| |w|   (Cauchy-Schwarz),
 // with <p, q> exact in the integer accumulators.  A label whose right side stays below the threshold is out; the few
 // others (four to five times as many as a filter without error would let through, at 256 elements) get their score from
-// the bf16 rows, summed in fp32, and only these scores decide.  The result is that of the bf16 search.
+// the bf16 rows, summed in fp32 in the order of the bf16 kernels, and only these scores decide.  The result is that of
+// the bf16 search, bit for bit.
 //   q8_queries_kernel   p, 1 / a and the margins of a query, once per search
 //   per chunk of labels (up to kQ8ChunkBytes of 8-bit rows):
 //   q8_rows_kernel      q, 1 / b and the largest |dw|, |w| of every tile of 64 labels (HBM: 3 bytes per element)
@@ -22,7 +23,6 @@ namespace xc {
 
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 q8_bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kQ8Tile = 64;              // labels of a tile: one scale
 constexpr int kQ8Queries = 512;          // queries of a work item
@@ -448,7 +448,10 @@ void mine_q8_kernel(const Q8Args a) {
 
 // ---------------------------------------------------------------------------
 // scores of the labels that passed: entries [gbase, gcnt) of a query's list are labels and become keys.  One wave per
-// query; G lanes per row, eight rows of a lane in flight.  Bound: HBM, random rows.
+// query; 16 rows at a time as the A operand of the matrix product, the query in all 16 columns of B.  The products are summed
+// in the order of mine_rows_kernel, so a row's score has the same bits whichever kernel formed it: equal rows tie wherever
+// they lie, and a search from thresholds or without the filter gives the same shortlist.  Bound: HBM, random rows (up to 32
+// of a wave in flight).
 // ---------------------------------------------------------------------------
 template <int NK>
 __global__ __launch_bounds__(256)
@@ -456,7 +459,7 @@ void q8_rescore_kernel(const unsigned char* __restrict__ Z, const unsigned char*
                        uint64_t* __restrict__ glist, int glist_cap, int32_t* __restrict__ gcnt,
                        const int32_t* __restrict__ gbase, const uint32_t* __restrict__ tau_g,
                        const int32_t* __restrict__ flag) {
-    constexpr int G = 16 * NK, NG = kWave / G, U = 8, R = NG * U;        // R entries per round
+    constexpr int kSteps = 4 * NK, kBlocks = 2, kRow = NK * 256;         // steps of 64 bytes; blocks of 16 rows per round
     const int lane = lane_id();
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (q >= Zq) return;
@@ -469,39 +472,42 @@ void q8_rescore_kernel(const unsigned char* __restrict__ Z, const unsigned char*
     if (n == base) return;
     const float tau = ordered_to_float(tau_g[q]);
     uint64_t* list = glist + static_cast<size_t>(q) * glist_cap;
-    const int grp = lane / G, gl = lane % G;
-    const uint4 z = *reinterpret_cast<const uint4*>(Z + (q * G + gl) * 16);
+    const int r = lane & 15, g = lane >> 4;              // operands: 16 bytes of row r, chunk 4 s + g in step s
+    uint4 z[kSteps];
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) z[s] = *reinterpret_cast<const uint4*>(Z + q * kRow + s * 64 + g * 16);
     int out = base;
-    for (int e0 = base; e0 < n; e0 += R) {
-        const int e = e0 + lane;
-        const bool have = lane < R && e < n;
-        const int32_t id = have ? static_cast<int32_t>(list[e]) : 0;
-        uint4 w[U];
+    for (int e0 = base; e0 < n; e0 += 16 * kBlocks) {
+        int32_t id[kBlocks];
+        uint4 w[kBlocks][kSteps];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int32_t l = __shfl(id, u * NG + grp, kWave);
-            w[u] = *reinterpret_cast<const uint4*>(W + (static_cast<int64_t>(l) * G + gl) * 16);
+        for (int b = 0; b < kBlocks; ++b) {
+            const int e = e0 + 16 * b + r;
+            id[b] = e < n ? static_cast<int32_t>(list[e]) : 0;           // (past the end: a row that exists, dropped below)
+            if (e0 + 16 * b < n)                         // uniform
+#pragma unroll
+                for (int s = 0; s < kSteps; ++s)
+                    w[b][s] = *reinterpret_cast<const uint4*>(W + static_cast<int64_t>(id[b]) * kRow + s * 64 + g * 16);
         }
+        // accumulator i: row 4 g + i, in every column.  Lanes with r = 4 b + i, i < 4, take row 4 g + i of block b.
         float mine = 0.0f;
+        int32_t my_id = 0;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            float s = 0.0f;
-            const uint32_t a4[4] = {w[u].x, w[u].y, w[u].z, w[u].w}, b4[4] = {z.x, z.y, z.z, z.w};
+        for (int b = 0; b < kBlocks; ++b) {
+            if (e0 + 16 * b < n) {                       // uniform
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                q8_bf16x2 x, y;
-                __builtin_memcpy(&x, &a4[c], 4);
-                __builtin_memcpy(&y, &b4[c], 4);
-                s = __builtin_amdgcn_fdot2_f32_bf16(x, y, s, false);
+                for (int s = 0; s < kSteps; ++s) acc = row_mma_bf16(w[b][s], z[s], acc);
+                const float v = (r & 2) ? ((r & 1) ? acc[3] : acc[2]) : ((r & 1) ? acc[1] : acc[0]);
+                if ((r >> 2) == b) mine = v;
             }
-#pragma unroll
-            for (int off = G / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
-            const float t = __shfl(s, (lane % NG) * G, kWave);           // entry u NG + j: group j's row u
-            if (lane / NG == u) mine = t;
+            const int32_t from = __shfl(id[b], 4 * g + (r & 3), kWave);
+            if ((r >> 2) == b) my_id = from;
         }
+        const bool have = r < 4 * kBlocks && e0 + 16 * (r >> 2) + 4 * g + (r & 3) < n;
         const bool keep = have && mine >= tau;           // (false for NaN)
         const uint64_t bal = __ballot(keep);
-        if (keep) list[out + __popcll(bal & lanemask_lt())] = make_key(mine + 0.0f /* -0 -> +0 */, id);
+        if (keep) list[out + __popcll(bal & lanemask_lt())] = make_key(mine + 0.0f /* -0 -> +0 */, my_id);
         out += __popcll(bal);
     }
     if (lane == 0) gcnt[q] = out;
@@ -515,7 +521,7 @@ void q8_rescore_kernel(const unsigned char* __restrict__ Z, const unsigned char*
 // than the products saved), from 4096 queries on (forming the 8-bit rows costs as much as the products of about 900), and from
 // 2^20 labels on (the first 2^17 are searched in bf16).  Measured, bf16 : filter, 1.05 M labels: 256 elements, k = 50, 4096
 // queries 2.59 : 2.23 ms, 65 536 35.3 : 27.7; k = 100, 4096 2.94 : 2.67; 128 elements, 4096 1.89 : 1.53; 4 M labels, k = 100,
-// 4096 8.2 : 6.2.  Relative error of the scores against 64 bits: 5.0e-8 with the filter, 8.2e-8 without (256 elements).
+// 4096 8.2 : 6.2.
 bool plan_q8(int64_t Zq, int64_t L, int64_t row_bytes, xc_dtype t, Q8Plan* p) {
     p->nk = 0;
     if (t != XC_BF16 || (row_bytes != 256 && row_bytes != 512)) return false;

@@ -1,0 +1,58 @@
+"""A label's score has the same bits in every search kernel: whichever route a call takes - from scratch, from thresholds,
+through the 8-bit filter, the row kernel in either width or the general kernel - ids and scores are equal bit for bit, and
+identical rows of W, which tie, come in the order of their ids wherever they were scored."""
+import pytest
+import torch
+
+from paper_2409_20156_amd import synth
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _inputs(seed, Zq, L, d, dtype):
+    return (synth.make_matrix(seed, synth.TAG_Z, Zq, d, dtype, DEV), synth.make_matrix(seed, synth.TAG_W, L, d, dtype, DEV))
+
+
+def _cold(Z, W, k, ws=None):
+    import paper_2409_20156_amd as xc
+    return xc.mine_negatives(Z, W, k, want_scores=True, workspace=ws)
+
+
+def _all_routes(monkeypatch, Z, W, k, forced, margins=(0.0, 0.1)):
+    """The result of the default route, after comparing every other one with it."""
+    import paper_2409_20156_amd as xc
+    code = xc.XC_BF16 if Z.dtype == torch.bfloat16 else xc.XC_F32
+    ws = torch.empty(xc.mine_workspace(Z.shape[0], W.shape[0], Z.shape[1], k, code), dtype=torch.uint8, device=DEV)
+    ids, sc = (t.clone() for t in _cold(Z, W, k, ws))
+    for margin in margins:                                          # from the thresholds of a search of any route
+        w_ids, w_sc = xc.mine_negatives(Z, W, k, want_scores=True, workspace=ws, warm_margin=margin)
+        assert torch.equal(ids, w_ids) and torch.equal(sc, w_sc), margin
+        assert int(ws[:4].view(torch.int32).item()) == 0, margin    # the k-th score reaches itself: no repeat, also without a margin
+        _cold(Z, W, k, ws)
+    for name, value in forced:
+        monkeypatch.setenv(name, value)
+        f_ids, f_sc = _cold(Z, W, k)
+        monkeypatch.delenv(name)
+        assert torch.equal(ids, f_ids) and torch.equal(sc, f_sc), (name, value)
+    return ids, sc
+
+
+GENERAL, NARROW, WIDE = ("XC_MINE_GENERAL", "1"), ("XC_MINE_ROWS", "narrow"), ("XC_MINE_ROWS", "wide")
+
+
+@pytest.mark.parametrize("Zq,L,d,k", [(4100, 1050001, 128, 100), (4300, 1100000, 256, 50)])
+def test_filter_scores_as_the_other_kernels_do(monkeypatch, Zq, L, d, k):
+    """Rows before label 2^17 are scored by the row kernel, rows behind it after the filter."""
+    Z, W = _inputs(71, Zq, L, d, torch.bfloat16)
+    early = torch.arange(1000, device=DEV) * 131
+    late = L - 1 - 701 * torch.arange(1000, device=DEV)
+    W[late] = W[early]
+    q = torch.arange(1000, device=DEV) * 4
+    Z[q] += W[early]                                                # a query beside each pair of equal rows
+    ids, sc = _all_routes(monkeypatch, Z, W, k, [NARROW, WIDE, GENERAL])
+    at = ids[q].eq(early[:, None].to(torch.int32)).int().argmax(dim=1)
+    assert bool((ids[q, at] == early).all())
+    later = ids[q].eq(late[:, None].to(torch.int32)).int().argmax(dim=1)
+    assert bool((ids[q, later] == late).all()) and bool((later == at + 1).all())
+    assert torch.equal(sc[q, at], sc[q, later])
