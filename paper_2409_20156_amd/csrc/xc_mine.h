@@ -33,9 +33,29 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 // One order of sums.  A label's score has the same bits in every search kernel, so that equal rows tie wherever they are
 // scored and every route to a shortlist (from scratch, from thresholds, few queries, the filter) gives the same one.  The order
-// is that of the tile kernels: a row's 16-byte chunks in pairs, each pair one v_mfma_f32_32x32x16_bf16, from an accumulator
-// of zero.  v_mfma_f32_16x16x32_bf16, which takes two pairs, adds its products as two of those do: 21 million random sums
-// of 64 products, with exponents spread over 0 to 40 binary orders, agree bit for bit.
+// is that of RowMma: from an accumulator of zero, a row's 16-byte chunks in pairs (lanes 0..31 hold the first of a pair, lanes
+// 32..63 the second), each pair one v_mfma_f32_32x32x16_bf16 or four v_mfma_f32_32x32x2_f32.
+// The 16x16 instructions give the same bits: v_mfma_f32_16x16x32_bf16 takes two pairs and adds their products as two of the
+// former do (21 million random sums of 64 products, with exponents spread over 0 to 40 binary orders, agree bit for bit); both
+// fp32 instructions are chains of fused multiply-adds over their elements in lane order (fmaf on as many sums agrees), so
+// v_mfma_f32_16x16x4_f32 may take four elements of the order at a time.
+template <typename T> struct RowMma;
+template <> struct RowMma<bf16_t> {
+    static __device__ __forceinline__ void mma(const uint4& a, const uint4& b, f32x16& c) {
+        bf16x8 av, bv;
+        __builtin_memcpy(&av, &a, 16);
+        __builtin_memcpy(&bv, &b, 16);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, c, 0, 0, 0);
+    }
+};
+template <> struct RowMma<float> {
+    static __device__ __forceinline__ void mma(const uint4& a, const uint4& b, f32x16& c) {
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
+        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
+    }
+};
 __device__ __forceinline__ f32x4 row_mma_bf16(const uint4& a /* 16 rows */, const uint4& b /* 16 columns */, f32x4 c) {
     bf16x8 av, bv;
     __builtin_memcpy(&av, &a, 16);

@@ -121,27 +121,6 @@ __device__ __noinline__ float wave_select_k(uint64_t* __restrict__ buf, Load loa
     return key_score(kmax);
 }
 
-// ---------------------------------------------------------------------------
-// element-type specifics of the tile product
-// ---------------------------------------------------------------------------
-template <typename T> struct MineTraits;
-template <> struct MineTraits<bf16_t> {
-    static __device__ __forceinline__ void mma(const uint4& a, const uint4& b, f32x16& c) {
-        bf16x8 av, bv;
-        __builtin_memcpy(&av, &a, 16);
-        __builtin_memcpy(&bv, &b, 16);
-        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, c, 0, 0, 0);
-    }
-};
-template <> struct MineTraits<float> {
-    static __device__ __forceinline__ void mma(const uint4& a, const uint4& b, f32x16& c) {
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
-    }
-};
-
 struct MineArgs {
     const unsigned char* Z;
     const unsigned char* W;
@@ -339,7 +318,7 @@ void mine_tile_kernel(const MineArgs a) {
             for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt)
-                    MineTraits<T>::mma(fa[sel][mt], fb[sel][nt], acc[mt][nt]);
+                    RowMma<T>::mma(fa[sel][mt], fb[sel][nt], acc[mt][nt]);
         };
         // the first k-step of a tile: the accumulators start from a zero operand instead of being cleared
         // one register at a time after the filter (128 vector moves per tile and wave)
@@ -349,7 +328,7 @@ void mine_tile_kernel(const MineArgs a) {
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt) {
                     f32x16 c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                    MineTraits<T>::mma(fa[sel][mt], fb[sel][nt], c);
+                    RowMma<T>::mma(fa[sel][mt], fb[sel][nt], c);
                     acc[mt][nt] = c;
                 }
         };

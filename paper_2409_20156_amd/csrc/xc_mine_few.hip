@@ -9,11 +9,11 @@
 //       labels score tau or more, so every label of the answer does, and it lies in a group whose maximum is
 //       above tau or, for scores equal to tau, in one of the first groups (in label order) whose maximum is tau:
 //       of equal scores the smaller ids win, and each of these groups holds one.  So k groups in all hold the
-//       answer.  Their scores are formed again, with the same instructions in the same order (hence the same
+//       answer.  Their scores are formed again, with the sums in the same order (hence the same
 //       bits), what is below tau is dropped, the rest sorted.
 // Bound: HBM, one read of W.  131 072 x 768 bf16, 32 queries, k = 5: 70 us in all (first kernel 44 us, 4.5 TB/s of the 5.1
 // a plain copy reaches), where the general kernel took 378; 30 M x 256 bf16, 32 queries: 3.3 ms (4.7 TB/s) against 8.5.  In
-// fp32 with many queries the matrix pipe: 1000 queries x 50 021 x 300, 368 us against 782 (the products alone take 195).
+// fp32 with many queries the matrix pipe: 1000 queries x 50 021 x 300, 364 us against 782 (the products alone take 195).
 // No thresholds to find in phases, no lists that could overflow, two launches.  The general kernel pads the
 // pool to 256 queries and sweeps the labels in four or more serial phases, of which the first have fewer work
 // items than the chip has compute units.
@@ -37,19 +37,26 @@ constexpr int kMaxSplit = 8;             // workgroups per query of the second k
 constexpr int kPartKeys = Finish<1024>::kKeys / kMaxSplit;      // candidates one of them hands over at most
 static_assert(kPartKeys >= XC_MAX_K_MINE, "a workgroup hands over at least its best k");
 
+// Products in the order of the other search kernels (RowMma and the text above it).  `operand` turns a lane's 16 bytes
+// of a row (chunk g of a 64-byte step) into what the matrix instructions of the step take from that lane.
 template <typename T> struct FewMma;
 template <> struct FewMma<bf16_t> {
-    static __device__ __forceinline__ f32x4 mma(const uint4& a, const uint4& b, f32x4 c) {
-        return row_mma_bf16(a, b, c);
-    }
+    static __device__ __forceinline__ uint4 operand(const uint4& v) { return v; }
+    static constexpr int kSteps = 1;             // matrix instructions per step
+    static __device__ __forceinline__ f32x4 mma(int, const uint4& a, const uint4& b, f32x4 c) { return row_mma_bf16(a, b, c); }
 };
 template <> struct FewMma<float> {
-    static __device__ __forceinline__ f32x4 mma(const uint4& a, const uint4& b, f32x4 c) {
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), c, 0, 0, 0);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
-        return c;
+    // Lanes g = 0, 1, 2, 3 of a product stand for elements 2i of chunks 0 and 1, then 2i + 1 of them: elements 2i + 1 of
+    // the lower chunk pair change places with elements 2i of the upper one.  x, z: the lower pair; y, w: the upper one.
+    static __device__ __forceinline__ uint4 operand(const uint4& v) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(v.x, v.y, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(v.z, v.w, false, false);
+        return make_uint4(lo[0], lo[1], hi[0], hi[1]);
+    }
+    static constexpr int kSteps = 4;
+    static __device__ __forceinline__ f32x4 mma(int t, const uint4& a, const uint4& b, f32x4 c) {
+        const uint32_t av = t == 0 ? a.x : t == 1 ? a.z : t == 2 ? a.y : a.w, bv = t == 0 ? b.x : t == 1 ? b.z : t == 2 ? b.y : b.w;
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(av), __uint_as_float(bv), c, 0, 0, 0);
     }
 };
 
@@ -74,8 +81,8 @@ struct FewArgs {
 // ordered image of a score; 0 (below every number) for NaN.  -0 counts as +0, as in the result.
 __device__ __forceinline__ uint32_t score_image(float v) { return v == v ? float_to_ordered(v + 0.0f) : 0u; }
 
-// MFMA operands: lane (r, g) = (lane & 15, lane >> 4) holds 16 bytes of row r: chunk 4 s + g of the row in step s, for
-// labels and queries alike.  (Which k a chunk stands for does not matter as long as both sides agree.)
+// MFMA operands: lane (r, g) = (lane & 15, lane >> 4) loads 16 bytes of row r: chunk 4 s + g of the row in step s, for
+// labels and queries alike.
 template <typename T, int NB, bool KTAIL>
 __global__ __launch_bounds__(kFewThreads)
 void few_max_kernel(const FewArgs a) {
@@ -100,7 +107,7 @@ void few_max_kernel(const FewArgs a) {
         const int64_t off = static_cast<int64_t>(s) * 64 + (l >> 4) * 16;
         uint4 v = make_uint4(0, 0, 0, 0);
         if (q < a.Zq && off < a.row_bytes) v = *reinterpret_cast<const uint4*>(a.Z + q * a.row_bytes + off);
-        *reinterpret_cast<uint4*>(zlds + static_cast<size_t>(e) * 16) = v;
+        *reinterpret_cast<uint4*>(zlds + static_cast<size_t>(e) * 16) = FewMma<T>::operand(v);      // (a wave takes whole blocks)
     }
     if (id == 0)
         for (int64_t i = tid; i < a.Zq; i += kFewThreads) a.done[i] = 0;
@@ -160,13 +167,23 @@ void few_max_kernel(const FewArgs a) {
         for (int j = 0; j < kFewRing; ++j) {
             uint4 a0 = ra[j][0], a1 = ra[j][1];
             if (KTAIL && s == KS - 1 && tail_chunk) { a0 = make_uint4(0, 0, 0, 0); a1 = make_uint4(0, 0, 0, 0); }
+            a0 = FewMma<T>::operand(a0);
+            a1 = FewMma<T>::operand(a1);
             const unsigned char* zb = zlds + static_cast<size_t>(s) * NB * 1024 + lane * 16;
+            uint4 b[NB];
 #pragma unroll
-            for (int n = 0; n < NB; ++n) {
-                const uint4 b = *reinterpret_cast<const uint4*>(zb + n * 1024);
-                acc[0][n] = FewMma<T>::mma(a0, b, acc[0][n]);
-                acc[1][n] = FewMma<T>::mma(a1, b, acc[1][n]);
-            }
+            for (int n = 0; n < NB; ++n) b[n] = *reinterpret_cast<const uint4*>(zb + n * 1024);
+            // (an accumulator's own instructions lie 2 NB apart: one that follows the other waits for it)
+#pragma unroll
+            for (int m = 0; m < FewMma<T>::kSteps; ++m)
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    acc[0][n] = FewMma<T>::mma(m, a0, b[n], acc[0][n]);
+                    acc[1][n] = FewMma<T>::mma(m, a1, b[n], acc[1][n]);
+                }
+            // (fp32 exchanges operands in the ring's registers: a load scheduled before their last use would need others, which
+            // the compiler then moves at the end of the loop, awaiting the whole ring)
+            if (FewMma<T>::kSteps > 1) __builtin_amdgcn_sched_barrier(0);
             load_step(j);
             if (++s == KS) {                                    // uniform: a tile is complete
                 s = 0;
@@ -203,6 +220,146 @@ void few_max_kernel(const FewArgs a) {
                             run[n] = fmaxf(run[n], __shfl_xor(run[n], 16, kWave));
                             run[n] = fmaxf(run[n], __shfl_xor(run[n], 32, kWave));
                             if (g == 0 && q < a.Zq) a.gmax[q * a.n_groups + unit] = score_image(run[n]);
+                            run[n] = nan;
+                        }
+                    }
+                }
+                ++t;
+                if (unit_done) { t = 0; unit += u_step; if (unit >= n_units) return; }
+            }
+        }
+    }
+}
+
+// The same in fp32 for more than 16 queries, with the operands of the tile kernels: lane (r, h) = (lane & 31, lane >> 5) holds
+// chunks 4 s + h and 4 s + 2 + h of row r.  Nothing is exchanged.  fp32 matrix instructions run on the vector unit, which the
+// exchanges of few_max_kernel and every address come out of: 600 queries x 300 000 x 768 4.55 ms with them, 3.93 without;
+// 2048 x 130 000 x 64 522 and 445 us; 256 x 1 M x 128 729 and 639; 1000 x 50 021 x 300 380 and 365.  An instruction loads 32 bytes of a row
+// instead of 64, which costs where loads bind: 64 queries x 500 000 x 520 368 us and 376; one block of 16 queries, 1.3 M x 256,
+// 331 and 373, so that one stays there.
+template <int NB, bool KTAIL>
+__global__ __launch_bounds__(kFewThreads)
+void few_wide_kernel(const FewArgs a) {
+    constexpr int NC = NB / 2;                                  // blocks of 32 queries
+    extern __shared__ __align__(16) unsigned char zlds[];       // [ks][NC][2] operands of 1 KiB
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 31, h = lane >> 5;
+    const int KS = a.ks;
+    // workgroups of one XCD (id % 8) that differ in the query block only are neighbours: they read the same rows of W
+    // at about the same time, and all but the first find them in that XCD's L2
+    const int id = blockIdx.x;
+    const int qb = (id / 8) % a.n_qb;
+    const int wg = (id % 8) + 8 * (id / (8 * a.n_qb));
+    const int n_wg = gridDim.x / a.n_qb;                        // (a multiple of 8, see the launch)
+    const int64_t q0 = static_cast<int64_t>(qb) * NB * 16;
+
+    for (int e = tid; e < KS * NB * 64; e += kFewThreads) {
+        const int l = e & 63, blk = e >> 6;
+        const int m = blk & 1, n = (blk >> 1) % NC, s = (blk >> 1) / NC;
+        const int64_t q = q0 + n * 32 + (l & 31);
+        const int64_t off = static_cast<int64_t>(s) * 64 + m * 32 + (l >> 5) * 16;
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (q < a.Zq && off < a.row_bytes) v = *reinterpret_cast<const uint4*>(a.Z + q * a.row_bytes + off);
+        *reinterpret_cast<uint4*>(zlds + static_cast<size_t>(e) * 16) = v;
+    }
+    if (id == 0)
+        for (int64_t i = tid; i < a.Zq; i += kFewThreads) a.done[i] = 0;
+    __syncthreads();
+
+    // a unit is the tiles whose maxima one wave combines: a tile of two groups (gshift 0), or 2^(gshift-1) tiles of one
+    const int comb = a.gshift > 0 ? 1 << (a.gshift - 1) : 1;
+    const int64_t n_tiles = (a.L + kFewTile - 1) / kFewTile;
+    const int64_t n_units = (n_tiles + comb - 1) / comb;
+    const int64_t u_step = static_cast<int64_t>(n_wg) * kFewWaves;
+    int64_t unit = static_cast<int64_t>(wg) * kFewWaves + wave;
+    if (unit >= n_units) return;                                // (no barrier below)
+
+    // ---- the load stream: ring of kFewRing steps, running ahead across tiles and units
+    int64_t ld_unit = unit;
+    int ld_t = 0;
+    int ld_off = 0;                                             // bytes into the rows
+    const unsigned char* p;
+    auto set_rows = [&]() {
+        const int64_t l = (ld_unit * comb + ld_t) * kFewTile + r;
+        p = a.W + (l < a.L ? l : a.L - 1) * a.row_bytes;        // rows past the end: dropped later
+    };
+    set_rows();
+    uint4 ra[kFewRing][2];
+    auto load_step = [&](int j) {
+        int64_t o0 = ld_off + h * 16, o1 = o0 + 32;
+        if (KTAIL) { o0 = o0 < a.row_bytes ? o0 : 0; o1 = o1 < a.row_bytes ? o1 : 0; }      // (zeroed where it is used)
+        ra[j][0] = *reinterpret_cast<const uint4*>(p + o0);
+        ra[j][1] = *reinterpret_cast<const uint4*>(p + o1);
+        ld_off += 64;
+        if (ld_off == KS * 64) {                                // uniform
+            ld_off = 0;
+            ++ld_t;
+            if (ld_t == comb || ld_unit * comb + ld_t >= n_tiles) { ld_t = 0; ld_unit += u_step; }
+            if (ld_unit < n_units) set_rows();                  // else: the last tile again, never used
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < kFewRing; ++j) load_step(j);
+
+    // this lane's chunks of the last step that lie past the row's end
+    const bool tail0 = static_cast<int64_t>(KS - 1) * 64 + h * 16 >= a.row_bytes, tail1 = static_cast<int64_t>(KS - 1) * 64 + 32 + h * 16 >= a.row_bytes;
+    f32x16 acc[NC];
+    const float nan = __builtin_nanf("");
+    float run[NC];
+#pragma unroll
+    for (int n = 0; n < NC; ++n) {
+        run[n] = nan;
+        acc[n] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    }
+    int t = 0, s = 0;
+    for (;;) {
+#pragma unroll
+        for (int j = 0; j < kFewRing; ++j) {
+            uint4 a0 = ra[j][0], a1 = ra[j][1];
+            if (KTAIL && s == KS - 1) {                         // uniform
+                if (tail0) a0 = make_uint4(0, 0, 0, 0);
+                if (tail1) a1 = make_uint4(0, 0, 0, 0);
+            }
+            const unsigned char* zb = zlds + static_cast<size_t>(s) * NB * 1024 + lane * 16;
+#pragma unroll
+            for (int n = 0; n < NC; ++n) {
+                RowMma<float>::mma(a0, *reinterpret_cast<const uint4*>(zb + (2 * n) * 1024), acc[n]);
+                RowMma<float>::mma(a1, *reinterpret_cast<const uint4*>(zb + (2 * n + 1) * 1024), acc[n]);
+            }
+            load_step(j);
+            if (++s == KS) {                                    // uniform: a tile is complete
+                s = 0;
+                const int64_t tile = unit * comb + t;
+                const int64_t lab = tile * kFewTile + 4 * h;    // accumulator i: label lab + 8 (i / 4) + i % 4, query r
+                const bool full = (tile + 1) * kFewTile <= a.L;
+                const bool unit_done = t + 1 == comb || tile + 1 >= n_tiles;
+#pragma unroll
+                for (int n = 0; n < NC; ++n) {
+                    if (!full)
+#pragma unroll
+                        for (int i = 0; i < 16; ++i)
+                            if (lab + 8 * (i >> 2) + (i & 3) >= a.L) acc[n][i] = nan;
+                    float m[2];                                 // labels 0..15 and 16..31 of the tile
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        m[b] = acc[n][8 * b];
+#pragma unroll
+                        for (int i = 1; i < 8; ++i) m[b] = fmaxf(m[b], acc[n][8 * b + i]);
+                    }
+                    acc[n] = f32x16{0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    const int64_t q = q0 + n * 32 + r;
+                    if (a.gshift == 0) {
+                        // the lower lanes store the first group's maxima, the upper ones the second's
+                        const float v = fmaxf(h == 0 ? m[0] : m[1], __shfl_xor(h == 0 ? m[1] : m[0], 32, kWave));
+                        const int64_t grp = 2 * tile + h;
+                        if (q < a.Zq && grp < a.n_groups) a.gmax[q * a.n_groups + grp] = score_image(v);
+                    } else {
+                        run[n] = fmaxf(run[n], fmaxf(m[0], m[1]));
+                        if (unit_done) {
+                            run[n] = fmaxf(run[n], __shfl_xor(run[n], 32, kWave));
+                            if (h == 0 && q < a.Zq) a.gmax[q * a.n_groups + unit] = score_image(run[n]);
                             run[n] = nan;
                         }
                     }
@@ -371,7 +528,9 @@ void few_finish_kernel(const FewArgs a) {
             for (int s = 0; s < full; ++s) {
                 const uint4 w = *reinterpret_cast<const uint4*>(wrow + s * 64 + g * 16);
                 const uint4 z = *reinterpret_cast<const uint4*>(zrow + s * 64 + g * 16);
-                acc = FewMma<T>::mma(w, z, acc);
+                const uint4 wo = FewMma<T>::operand(w), zo = FewMma<T>::operand(z);
+#pragma unroll
+                for (int m = 0; m < FewMma<T>::kSteps; ++m) acc = FewMma<T>::mma(m, wo, zo, acc);
             }
             if (full < a.ks) {
                 uint4 w = make_uint4(0, 0, 0, 0), z = make_uint4(0, 0, 0, 0);
@@ -379,7 +538,9 @@ void few_finish_kernel(const FewArgs a) {
                     w = *reinterpret_cast<const uint4*>(wrow + full * 64 + g * 16);
                     z = *reinterpret_cast<const uint4*>(zrow + full * 64 + g * 16);
                 }
-                acc = FewMma<T>::mma(w, z, acc);
+                const uint4 wo = FewMma<T>::operand(w), zo = FewMma<T>::operand(z);
+#pragma unroll
+                for (int m = 0; m < FewMma<T>::kSteps; ++m) acc = FewMma<T>::mma(m, wo, zo, acc);
             }
             const float v = (r & 2) ? ((r & 1) ? acc[3] : acc[2]) : ((r & 1) ? acc[1] : acc[0]);
             const int64_t lab = l0 + 4 * g + r;
@@ -492,10 +653,16 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, size_
 
 typedef void (*FewFn)(const FewArgs);
 template <typename T>
-static FewFn few_kernel(int nb, bool ktail) {
-    return nb == 1 ? (ktail ? &few_max_kernel<T, 1, true> : &few_max_kernel<T, 1, false>)
-         : nb == 2 ? (ktail ? &few_max_kernel<T, 2, true> : &few_max_kernel<T, 2, false>)
-                   : (ktail ? &few_max_kernel<T, 4, true> : &few_max_kernel<T, 4, false>);
+static FewFn few_kernel(int nb, bool ktail);
+template <> FewFn few_kernel<bf16_t>(int nb, bool ktail) {
+    return nb == 1 ? (ktail ? &few_max_kernel<bf16_t, 1, true> : &few_max_kernel<bf16_t, 1, false>)
+         : nb == 2 ? (ktail ? &few_max_kernel<bf16_t, 2, true> : &few_max_kernel<bf16_t, 2, false>)
+                   : (ktail ? &few_max_kernel<bf16_t, 4, true> : &few_max_kernel<bf16_t, 4, false>);
+}
+template <> FewFn few_kernel<float>(int nb, bool ktail) {
+    return nb == 1 ? (ktail ? &few_max_kernel<float, 1, true> : &few_max_kernel<float, 1, false>)
+         : nb == 2 ? (ktail ? &few_wide_kernel<2, true> : &few_wide_kernel<2, false>)
+                   : (ktail ? &few_wide_kernel<4, true> : &few_wide_kernel<4, false>);
 }
 
 int few_raise_lds() {

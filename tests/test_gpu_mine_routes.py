@@ -56,3 +56,39 @@ def test_filter_scores_as_the_other_kernels_do(monkeypatch, Zq, L, d, k):
     later = ids[q].eq(late[:, None].to(torch.int32)).int().argmax(dim=1)
     assert bool((ids[q, later] == late).all()) and bool((later == at + 1).all())
     assert torch.equal(sc[q, at], sc[q, later])
+
+
+@pytest.mark.parametrize("Zq,L,d,k", [
+    (1000, 50021, 300, 32),                # rows of 1200 bytes: a step of three chunks at the end
+    (300, 20000, 68, 64),                  # 272 bytes: a step of one chunk
+    (520, 9000, 76, 128),                  # 304 bytes: three chunks; one workgroup of 256 threads per query at the end
+    (64, 30000, 768, 50),                  # two blocks of queries fit LDS
+    (16, 5000, 300, 40), (17, 5001, 300, 40), (33, 5017, 256, 40),     # one, two and four blocks of 16 queries; ragged labels
+    (9, 3000, 1216, 20),                   # the longest rows of which two blocks of queries fit LDS, and longer ones
+    (40, 3001, 1220, 20),
+    (3, 2100000, 8, 100), (20, 2100016, 8, 100),                       # groups of 32 labels
+])
+def test_few_queries_score_as_the_general_kernel_does_fp32(monkeypatch, Zq, L, d, k):
+    Z, W = _inputs(72, Zq, L, d, torch.float32)
+    n = min(Zq, 200)
+    late = L - 1 - 7 * torch.arange(n, device=DEV)
+    W[:n] *= 3.0                            # (the longest rows: among the best of their own query)
+    W[late] = W[:n].clone()
+    Z[:n] += W[:n]
+    ids, sc = _all_routes(monkeypatch, Z, W, k, [GENERAL])
+    at = ids[:n].eq(torch.arange(n, device=DEV, dtype=torch.int32)[:, None]).int().argmax(dim=1)
+    q = torch.arange(n, device=DEV)
+    assert bool((ids[q, at + 1] == late).all()) and torch.equal(sc[q, at], sc[q, at + 1])
+
+
+@pytest.mark.parametrize("Zq,L,d,k", [
+    (512, 60000, 768, 64),                 # rows that the general kernel takes
+    (1000, 50000, 256, 50),                # ... that the row kernel takes
+    (300, 20000, 40, 64),                  # 80 bytes: a step of one chunk at the end
+    (20, 3000, 1152, 20),
+    (5, 2100000, 64, 100),                 # groups of 32 labels
+])
+def test_few_queries_score_as_the_other_kernels_do_bf16(monkeypatch, Zq, L, d, k):
+    Z, W = _inputs(73, Zq, L, d, torch.bfloat16)
+    forced = [GENERAL, NARROW, WIDE] if d * 2 % 128 == 0 and d * 2 <= 512 else [GENERAL]
+    _all_routes(monkeypatch, Z, W, k, forced)
