@@ -29,6 +29,8 @@ constexpr int kQ8Queries = 512;          // queries of a work item
 constexpr int kQ8Cap = 512;              // entries of a lane's list (2 lists per query)
 constexpr int kQ8MaxTiles = 4096;        // tiles of a slice at most (their margins are kept in LDS)
 constexpr float kQ8Huge = 3.0e38f;
+// kinds of queries (last component of their parameters)
+constexpr float kQueryPlain = 0.0f, kQueryWide = 1.0f /* infinite, or out of the margins' range */, kQueryZero = 2.0f, kQueryNan = 3.0f;
 
 // ---------------------------------------------------------------------------
 // operands
@@ -81,6 +83,7 @@ void q8_queries_kernel(const unsigned char* __restrict__ Z, int64_t Zq, unsigned
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) { const uint32_t o = __shfl_xor(m, off, kWave); m = o > m ? o : m; }
     const bool bad = unusable(m) || m == 0;
+    const float kind = m == 0 ? kQueryZero : m > 0x7f800000u ? kQueryNan : bad ? kQueryWide : kQueryPlain;
     const float inv = bad ? 0.0f : 127.0f / __uint_as_float(m), step = __uint_as_float(m) / 127.0f;
     float e2 = 0.0f, s2 = 0.0f, a2 = 0.0f;
     const uint2 o = quantise8(v, inv, step, e2, s2, a2);
@@ -94,7 +97,7 @@ void q8_queries_kernel(const unsigned char* __restrict__ Z, int64_t Zq, unsigned
         // a ten-thousandth on top covers the rounding of the norms and of the threshold itself
         constexpr float kSum = 4.0f * (128 * NK) * 5.97e-8f;
         const float p = sqrtf(a2) * 1.0001f, w = fmaxf((sqrtf(e2) + kSum * sqrtf(s2)) * inv * 1.0001f, 1e-20f);
-        zpar[q] = bad ? make_float4(0.0f, 0.0f, 1e-20f, 1.0f) : make_float4(inv, p, w, 0.0f);
+        zpar[q] = bad ? make_float4(0.0f, 0.0f, 1e-20f, kind) : make_float4(inv, p, w, kind);
     }
 }
 
@@ -244,7 +247,11 @@ void mine_q8_kernel(const Q8Args a) {
             const int64_t qc = q < a.Zq ? q : a.Zq - 1;
             const float4 zp = a.zpar[qc];
             const float tau = ordered_to_float(a.tau_g[qc]);
-            tu[nt] = q >= a.Zq ? INFINITY : (zp.w != 0.0f ? -kQ8Huge : fminf(fmaxf(tau * zp.x, -kQ8Huge), kQ8Huge));
+            // Nothing in this chunk can change the result of a query that is not there, whose scores are all NaN, or whose k
+            // best so far already hold the largest score it can have (+inf; zero for a zero query: labels of this chunk have
+            // larger ids and lose the tie).  Other queries that 8 bits do not describe: everything passes.
+            const bool settled = q >= a.Zq || zp.w == kQueryNan || tau == INFINITY || (zp.w == kQueryZero && tau >= 0.0f);
+            tu[nt] = settled ? INFINITY : (zp.w != kQueryPlain ? -kQ8Huge : fminf(fmaxf(tau * zp.x, -kQ8Huge), kQ8Huge));
             tv[nt] = zp.y;
             tw[nt] = zp.z;
             const unsigned char* zr = a.Z + qc * row_bytes + half * 16;
@@ -362,7 +369,7 @@ void mine_q8_kernel(const Q8Args a) {
 #pragma unroll
                         for (int nt = 0; nt < 2; ++nt) {
                             const float t = fmaf(tu[nt], m.x, -fmaf(tv[nt], m.y, fmaf(tw[nt], m.z, 2.0f)));
-                            tc[nt] = static_cast<int>(fmaxf(fminf(t, 2.0e9f), -2.0e9f));     // (no query: NaN, out of reach as well)
+                            tc[nt] = static_cast<int>(fmaxf(fminf(t, 2.0e9f), -2.0e9f));     // (settled, or NaN where the tile is unusable: out of reach as well)
                         }
                     }
                     __builtin_amdgcn_sched_barrier(0);
