@@ -107,6 +107,30 @@ __device__ __noinline__ void issue_stage_ragged(const unsigned char* W, int64_t 
     }
 }
 
+// Slices per XCD for the kernel that keeps the query tile in registers.  The compute units of an XCD
+// that work on one slice read the same stream of W tiles, a few tiles apart, so all but the first find
+// them in that XCD's L2: the fewer slices per XCD, the fewer times W comes from memory (with 8 slices
+// per XCD the search of 16 384 queries over 120 M rows of 512 bytes ran at the rate the memory system
+// delivered W, with one slice 19 % faster).  The other side: 32 / slices query tiles are in flight per
+// XCD, and compute units without a query tile idle.  Among the counts the phase allows (<= sx_max) take
+// the one that keeps the most compute units busy, and of those the smallest.
+// Opening and closing an item (operands, the ring, the lists) costs about what eight tiles of a slice do, so that short
+// slices are not worth a slightly fuller last round (60 items of 256 queries over 803 tiles: 2 rounds of 100 tiles are 94 %
+// full, 15 rounds of 13 tiles are 100 % full and took 1.8 times as long; 205 654 x 256, 50 000 queries 13.5 -> 7.6 ms from
+// scratch, 7.4 -> 5.4 from thresholds; 2 M x 128, 30 000 queries 23.3 -> 13.7).
+__host__ __device__ inline int rows_slices_per_xcd(int64_t nQT, int64_t n_tiles, int sx_max) {
+    int best = sx_max;
+    double best_eff = -1.0;
+    for (int sx = 1; sx <= sx_max; sx <<= 1) {
+        const int qx = kCusPerXcd / sx;
+        const int64_t rounds = (nQT + qx - 1) / qx;
+        const double per = static_cast<double>(n_tiles) / (kXcds * sx);
+        const double eff = static_cast<double>(nQT) / static_cast<double>(rounds * qx) * per / (per + 8.0);
+        if (eff > best_eff + 1e-9) { best_eff = eff; best = sx; }
+    }
+    return best;
+}
+
 struct FewPlan {
     int ks;                  // 64-byte steps of a row
     int nb;                  // blocks of 16 queries per workgroup
@@ -135,7 +159,7 @@ constexpr int kQ8Growth = 3;                         // labels of a chunk / labe
 struct Q8Plan {
     int nk;                                          // row bytes / 256; 0 = not used
     int64_t chunk;                                   // labels at a time
-    size_t off_rows, off_meta, off_z, off_zpar, off_base, off_flag, bytes;      // within its part of the workspace
+    size_t off_rows, off_meta, off_z, off_zpar, off_base, off_items, off_flag, bytes;      // within its part of the workspace
 };
 struct Q8Chunk {
     const void *Z, *W;
@@ -144,6 +168,9 @@ struct Q8Chunk {
     uint64_t *lists, *glist;
     int32_t* gcnt;
     const uint32_t* tau_g;
+    int item_tiles;                                  // the caller's own search of the range: query tiles per work item,
+    int64_t sweep_tiles;                             // label tiles
+    int sx_max;                                      // and slices per XCD at most
 };
 
 bool plan_q8(int64_t Zq, int64_t L, int64_t row_bytes, xc_dtype t, Q8Plan* p);
@@ -153,5 +180,6 @@ int q8_begin(const Q8Plan& p, unsigned char* ws, const void* Z, int64_t Zq, hipS
 // for query tiles qt whose flag q8_flags()[1 + qt] is set afterwards (then [0] is too): for these the caller searches the range itself.
 int q8_chunk(const Q8Plan& p, unsigned char* ws, const Q8Chunk& c, hipStream_t st);
 const int32_t* q8_flags(const Q8Plan& p, const unsigned char* ws);
+const int32_t* q8_items(const Q8Plan& p, const unsigned char* ws);       // the work items of that search, see MineArgs::items
 
 }  // namespace xc

@@ -144,6 +144,7 @@ struct MineArgs {
     int dense_ld;
     const int32_t* cond;     // not null: repeat of a warm search; cond[0] != 0 if any query tile needs it,
                              // cond[1 + qt] != 0 if query tile qt does
+    const int32_t* items;    // not null (row kernel): only these work items, [0] their number, [1] slices per XCD, [2..] the items
 };
 
 // ---------------------------------------------------------------------------
@@ -648,12 +649,24 @@ void mine_rows_kernel(const MineArgs a) {
 
     int item, item_step, item_end;
     int slice_fixed = -1;
+    int64_t tiles_per_slice = a.tiles_per_slice;
+    int append_max = a.append_max;
     if (a.Qx > 0) {                   // slices bound to XCDs: workgroup w runs on XCD w % 8
         const int xcd = blockIdx.x % kXcds;
         const int cu = blockIdx.x / kXcds;
-        slice_fixed = xcd + kXcds * (cu / a.Qx);
-        item = cu % a.Qx; item_step = a.Qx; item_end = static_cast<int>(a.nQT);
-        if (slice_fixed >= a.S) item_end = 0;
+        int S = a.S, Qx = a.Qx;
+        item_end = static_cast<int>(a.nQT);
+        if (a.items != nullptr) {     // a plan of its own for the few items there are (see the 8-bit filter)
+            item_end = __builtin_amdgcn_readfirstlane(a.items[0]);
+            const int sx = __builtin_amdgcn_readfirstlane(a.items[1]);
+            S = kXcds * sx;
+            Qx = kCusPerXcd / sx;
+            tiles_per_slice = (a.tile_hi - a.tile_lo + S - 1) / S;
+            append_max = (a.glist_cap - a.kcap) / S;
+        }
+        slice_fixed = __builtin_amdgcn_readfirstlane(xcd + kXcds * (cu / Qx));
+        item = __builtin_amdgcn_readfirstlane(cu % Qx); item_step = Qx;
+        if (slice_fixed >= S) item_end = 0;
     } else {
         item = blockIdx.x; item_step = kMineGrid; item_end = static_cast<int>(a.nQT * a.S);
     }
@@ -676,7 +689,7 @@ void mine_rows_kernel(const MineArgs a) {
     const uint32_t dma_dst = lds_base + wq * kLd * 1024;
 
     for (; item < item_end; item += item_step) {
-        const int64_t qtile = a.Qx > 0 ? item : item / a.S;
+        const int64_t qtile = a.Qx > 0 ? (a.items != nullptr ? __builtin_amdgcn_readfirstlane(a.items[2 + item]) : item) : item / a.S;
         const int64_t q0 = qtile * kQN;
         if (a.cond != nullptr) {                             // uniform: every 256-query tile of the item came out complete
             bool any = false;
@@ -684,10 +697,10 @@ void mine_rows_kernel(const MineArgs a) {
             if (!any) continue;
         }
         const int slice = a.Qx > 0 ? slice_fixed : static_cast<int>(item % a.S);
-        const int64_t t_begin = a.tile_lo + static_cast<int64_t>(slice) * a.tiles_per_slice;
+        const int64_t t_begin = a.tile_lo + static_cast<int64_t>(slice) * tiles_per_slice;
         int64_t lab_begin, lab_end;
         {
-            int64_t t_end = t_begin + a.tiles_per_slice;
+            int64_t t_end = t_begin + tiles_per_slice;
             t_end = t_end < a.tile_hi ? t_end : a.tile_hi;
             if (t_end <= t_begin) continue;                  // uniform: an empty slice
             lab_begin = t_begin * kBM;
@@ -903,7 +916,7 @@ void mine_rows_kernel(const MineArgs a) {
 #pragma unroll
             for (int s = 0; s < kOwn; ++s) { c[s] = qok ? cnt4[ql * kOwn + s] : 0; n += c[s]; }
             uint64_t* qlist = my_lists + static_cast<size_t>(ql) * kQCap;
-            uint64_t todo = __ballot(lane < 32 && n > a.append_max);
+            uint64_t todo = __ballot(lane < 32 && n > append_max);
             while (todo) {                                   // more than a slice may append: the best k of them all
                 const int src = __ffsll(static_cast<long long>(todo)) - 1;
                 todo &= todo - 1;
@@ -1304,30 +1317,6 @@ static int64_t even_phase_tiles(int64_t lo, int64_t nLT, int64_t nQT, int k, int
     return n < nLT - lo ? n : nLT - lo;
 }
 
-// Slices per XCD for the kernel that keeps the query tile in registers.  The compute units of an XCD
-// that work on one slice read the same stream of W tiles, a few tiles apart, so all but the first find
-// them in that XCD's L2: the fewer slices per XCD, the fewer times W comes from memory (with 8 slices
-// per XCD the search of 16 384 queries over 120 M rows of 512 bytes ran at the rate the memory system
-// delivered W, with one slice 19 % faster).  The other side: 32 / slices query tiles are in flight per
-// XCD, and compute units without a query tile idle.  Among the counts the phase allows (<= sx_max) take
-// the one that keeps the most compute units busy, and of those the smallest.
-// Opening and closing an item (operands, the ring, the lists) costs about what eight tiles of a slice do, so that short
-// slices are not worth a slightly fuller last round (60 items of 256 queries over 803 tiles: 2 rounds of 100 tiles are 94 %
-// full, 15 rounds of 13 tiles are 100 % full and took 1.8 times as long; 205 654 x 256, 50 000 queries 13.5 -> 7.6 ms from
-// scratch, 7.4 -> 5.4 from thresholds; 2 M x 128, 30 000 queries 23.3 -> 13.7).
-static int rows_slices_per_xcd(int64_t nQT, int64_t n_tiles, int sx_max) {
-    int best = sx_max;
-    double best_eff = -1.0;
-    for (int sx = 1; sx <= sx_max; sx <<= 1) {
-        const int qx = kCusPerXcd / sx;
-        const int64_t rounds = (nQT + qx - 1) / qx;
-        const double per = static_cast<double>(n_tiles) / (kXcds * sx);
-        const double eff = static_cast<double>(nQT) / static_cast<double>(rounds * qx) * per / (per + 8.0);
-        if (eff > best_eff + 1e-9) { best_eff = eff; best = sx; }
-    }
-    return best;
-}
-
 // Work items of 512 queries (the row kernel with all eight waves along the queries) stage half the
 // bytes of W per flop, but there are half as many of them: they are taken where they keep the 32 compute
 // units of an XCD busy with one label slice (nine in ten over all rounds), as well as items of 256 would.  Measured, 256 against 512:
@@ -1395,6 +1384,13 @@ namespace xc {
 // The search proper.  warm: one sweep with the thresholds found in the workspace (lowered by
 // rel_margin * |tau|), then the full search if some query came out short; the kernels of the full
 // search are enqueued in any case and return at once when the flag says they are not needed.
+// Slices per XCD at most: every slice has a tile, and the global lists have room for what each of them appends.
+static int most_slices_per_xcd(int64_t nT, int kcap) {
+    int sx = 8;
+    while (sx > 1 && (nT < static_cast<int64_t>(kXcds) * sx || kXcds * sx > slices_cap(kcap))) sx >>= 1;
+    return sx;
+}
+
 static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, int k_h, xc_dtype t,
                     bool warm, float rel_margin, int32_t* shortlist, float* scores, void* ws,
                     size_t ws_bytes, void* stream) {
@@ -1424,6 +1420,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     a.cond = nullptr;
     a.dense = nullptr;
     a.dense_ld = 0;
+    a.items = nullptr;
     int32_t* flag = reinterpret_cast<int32_t*>(w8 + p.off_flag);
 
     // raise the dynamic LDS limit of the tile kernels: once per device and process (the attribute
@@ -1478,15 +1475,15 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     }
 
     // one phase: the tile kernel over label tiles [lo, hi), then the select
-    auto sweep = [&](int64_t lo, int64_t hi, const int32_t* cond) -> int {
+    auto sweep = [&](int64_t lo, int64_t hi, const int32_t* cond, const int32_t* items) -> int {
         const int64_t nT = hi - lo;
         const bool rows_kernel = rk != nullptr;
         a.nQT = rows_kernel ? (Zq + 2 * kBN / rk->wm - 1) / (2 * kBN / rk->wm) : p.nQT;
+        a.items = items;
         if (nT >= kXcds) {
             // slices per XCD: as many as the phase supports, so that few query tiles are in
             // flight per XCD and their Z rows stay in that XCD's L2
-            int Sx = 8;
-            while (Sx > 1 && (nT < static_cast<int64_t>(kXcds) * Sx || kXcds * Sx > slices_cap(p.kcap))) Sx >>= 1;
+            int Sx = most_slices_per_xcd(nT, p.kcap);
             if (rows_kernel) Sx = rows_slices_per_xcd(a.nQT, nT, Sx);
             a.S = kXcds * Sx;
             a.Qx = kCusPerXcd / Sx;
@@ -1522,7 +1519,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     };
 
     auto phase = [&](int64_t lo, int64_t hi, const int32_t* cond, int32_t* short_flag) -> int {
-        const int rcs = sweep(lo, hi, cond);
+        const int rcs = sweep(lo, hi, cond, nullptr);
         return rcs != XC_OK ? rcs : select(hi, cond, short_flag);
     };
 
@@ -1584,8 +1581,11 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             c.lab1 = hi * kBM < L ? hi * kBM : L;
             c.kcap = p.kcap; c.glist_cap = p.glist_cap; c.max_slices = slices_cap(p.kcap);
             c.lists = a.lists; c.glist = a.glist; c.gcnt = a.gcnt; c.tau_g = tau_g;
+            c.item_tiles = rk->wm == 1 ? 2 : 1;
+            c.sweep_tiles = hi - lo;
+            c.sx_max = most_slices_per_xcd(hi - lo, p.kcap);
             int rcp = q8_chunk(p.q8, q8_ws, c, st);
-            if (rcp == XC_OK) rcp = sweep(lo, hi, q8_flags(p.q8, q8_ws));
+            if (rcp == XC_OK) rcp = sweep(lo, hi, q8_flags(p.q8, q8_ws), hi - lo >= kXcds ? q8_items(p.q8, q8_ws) : nullptr);
             if (rcp == XC_OK) rcp = select(hi, nullptr, nullptr);
             if (rcp != XC_OK) return rcp;
             lo = hi;

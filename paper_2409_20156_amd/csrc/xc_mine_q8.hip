@@ -465,9 +465,24 @@ __global__ __launch_bounds__(256)
 void q8_rescore_kernel(const unsigned char* __restrict__ Z, const unsigned char* __restrict__ W, int64_t Zq,
                        uint64_t* __restrict__ glist, int glist_cap, int32_t* __restrict__ gcnt,
                        const int32_t* __restrict__ gbase, const uint32_t* __restrict__ tau_g,
-                       const int32_t* __restrict__ flag) {
+                       const int32_t* __restrict__ flag, int n_qt, int item_tiles, int64_t sweep_tiles, int sx_max,
+                       int32_t* __restrict__ items) {
     constexpr int kSteps = 4 * NK, kBlocks = 2, kRow = NK * 256;         // steps of 64 bytes; blocks of 16 rows per round
     const int lane = lane_id();
+    if (blockIdx.x == 0 && threadIdx.x < kWave && flag[0] != 0) {
+        // the work items that hold a tile given up, and how the search of them splits the labels: with the plan of the whole
+        // pool a single item would keep one compute unit per slice busy for as long as all of them take
+        int n = 0;
+        for (int i0 = 0; i0 * item_tiles < n_qt; i0 += kWave) {
+            const int i = i0 + lane;
+            bool any = false;
+            for (int t = i * item_tiles; t < (i + 1) * item_tiles && t < n_qt; ++t) any = any || flag[1 + t] != 0;
+            const uint64_t bal = __ballot(any);
+            if (any) items[2 + n + __popcll(bal & lanemask_lt())] = i;
+            n += __popcll(bal);
+        }
+        if (lane == 0) { items[0] = n; items[1] = rows_slices_per_xcd(n, sweep_tiles, sx_max); }
+    }
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (q >= Zq) return;
     const int base = gbase[q];
@@ -547,6 +562,7 @@ bool plan_q8(int64_t Zq, int64_t L, int64_t row_bytes, xc_dtype t, Q8Plan* p) {
     p->off_z = take(static_cast<size_t>(Zq) * 128 * p->nk);
     p->off_zpar = take(static_cast<size_t>(Zq) * sizeof(float4));
     p->off_base = take(static_cast<size_t>((Zq + kBN - 1) / kBN * kBN) * sizeof(int32_t));
+    p->off_items = take(static_cast<size_t>((Zq + kBN - 1) / kBN + 2) * sizeof(int32_t));
     p->off_flag = take(static_cast<size_t>((Zq + kBN - 1) / kBN + 3) * sizeof(int32_t));
     p->bytes = off;
     return true;
@@ -572,6 +588,8 @@ int q8_begin(const Q8Plan& p, unsigned char* ws, const void* Z, int64_t Zq, hipS
 }
 
 const int32_t* q8_flags(const Q8Plan& p, const unsigned char* ws) { return reinterpret_cast<const int32_t*>(ws + p.off_flag) + 2; }
+
+const int32_t* q8_items(const Q8Plan& p, const unsigned char* ws) { return reinterpret_cast<const int32_t*>(ws + p.off_items); }
 
 template <int NK>
 static int q8_chunk_impl(const Q8Plan& p, unsigned char* ws, const Q8Chunk& c, hipStream_t st) {
@@ -608,7 +626,8 @@ static int q8_chunk_impl(const Q8Plan& p, unsigned char* ws, const Q8Chunk& c, h
     XC_LAUNCH(K_MINE_TILE, st, (mine_q8_kernel<NK><<<kMineGrid, kMineThreads, kQ8Lds, st>>>(a)));
     XC_HIP_CHECK(hipGetLastError());
     XC_LAUNCH(K_MINE_SELECT, st, (q8_rescore_kernel<NK><<<static_cast<unsigned>((c.Zq + 3) / 4), 256, 0, st>>>(
-        static_cast<const unsigned char*>(c.Z), w, c.Zq, c.glist, c.glist_cap, c.gcnt, gbase, c.tau_g, a.flag)));
+        static_cast<const unsigned char*>(c.Z), w, c.Zq, c.glist, c.glist_cap, c.gcnt, gbase, c.tau_g, a.flag, a.n_qt,
+        c.item_tiles, c.sweep_tiles, c.sx_max, reinterpret_cast<int32_t*>(ws + p.off_items))));
     XC_HIP_CHECK(hipGetLastError());
     return XC_OK;
 }

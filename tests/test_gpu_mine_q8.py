@@ -146,6 +146,29 @@ def test_q8_scores_that_rise_along_the_labels(monkeypatch):
     _check_exact(Z, W, ids, sc, k)
 
 
+@pytest.mark.parametrize("Zq,given_up", [
+    (4300, [0]),                           # work items of one tile of 256 queries; the first
+    (4300, [16]),                          # the last, ragged one
+    (4300, [1, 4, 5, 11]),
+    (16200, [62]),                         # work items of two tiles
+    (16200, [0, 1, 7, 30, 63]),
+])
+def test_q8_few_tiles_given_up(monkeypatch, Zq, given_up):
+    """A query out of the filter's range makes its tile of 256 queries run over: those tiles alone are searched in bf16, in more
+    slices of the labels than a search of the whole pool has."""
+    L, d, k = 1100000, 128, 60
+    W = synth.make_matrix(47, synth.TAG_W, L, d, torch.bfloat16, DEV)
+    Z = synth.make_matrix(47, synth.TAG_Z, Zq, d, torch.bfloat16, DEV)
+    q = torch.tensor([256 * t + 3 for t in given_up], device=DEV)
+    Z[q] *= 2.0 ** 60
+    ws, state = _room(Zq, L, d, k)
+    ids, sc = _same_as_bf16(monkeypatch, Z, W, k, ws)
+    assert state[0].item() >= len(given_up) and state[1].item() == 0
+    Z[q] *= 2.0 ** -60
+    ids2, sc2 = _search(Z, W, k, ws)
+    assert torch.equal(ids, ids2) and torch.equal(sc[q], sc2[q] * 2.0 ** 60)
+
+
 def test_q8_needs_its_room_and_is_reproducible(monkeypatch):
     import paper_2409_20156_amd as xc
     Z, W = _base(45)
