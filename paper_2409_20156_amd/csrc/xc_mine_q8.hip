@@ -16,7 +16,8 @@
 //   mine_rows_kernel    on the 256-query tiles that the filter gave up (a list ran over: scores that rise along the label
 //                       range, rows too uneven for 8 bits, infinities); returns at once if there are none
 //   mine_select_kernel  the best k so far and the next threshold
-// If the filter gives up as many tiles as there are, it is not tried again in this search.
+// Once the tiles that a chunk gives up take more than half as long as a search without the filter, it is not tried again in
+// this search.
 #include "xc_mine.h"
 
 namespace xc {
@@ -71,11 +72,11 @@ __device__ __forceinline__ uint2 quantise8(const uint4& v, float inv, float step
 template <int NK>
 __global__ __launch_bounds__(256)
 void q8_queries_kernel(const unsigned char* __restrict__ Z, int64_t Zq, unsigned char* __restrict__ out,
-                       float4* __restrict__ zpar, int32_t* __restrict__ given_up) {
+                       float4* __restrict__ zpar, int32_t* __restrict__ state) {
     constexpr int G = 16 * NK;                           // lanes with a chunk
     const int lane = lane_id();
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (blockIdx.x == 0 && threadIdx.x == 0) given_up[0] = 0;
+    if (blockIdx.x == 0 && threadIdx.x < 2) state[threadIdx.x] = 0;
     if (q >= Zq) return;
     uint4 v = make_uint4(0, 0, 0, 0);
     if (lane < G) v = *reinterpret_cast<const uint4*>(Z + (q * G + lane) * 16);
@@ -106,18 +107,17 @@ __global__ __launch_bounds__(256)
 void q8_rows_kernel(const unsigned char* __restrict__ W /* first row of the chunk */, int64_t n_lab,
                     unsigned char* __restrict__ out, float4* __restrict__ tmeta, const int32_t* __restrict__ gcnt,
                     int32_t* __restrict__ gbase, int64_t nq, int32_t* __restrict__ flag /* [1 + n_qt] */, int n_qt,
-                    const int32_t* __restrict__ given_up, int32_t* __restrict__ skip) {
+                    const int32_t* __restrict__ state) {
     constexpr int G = 16 * NK;                           // lanes per row
     constexpr int kRows = 256 / G;                       // rows of one pass
     constexpr int kIter = kQ8Tile / kRows;
     __shared__ uint32_t shm[4];
     __shared__ float shf[4][2];
     const int tid = threadIdx.x, lane = lane_id(), wave = tid >> 6;
-    const bool off = given_up[0] >= n_qt;                // the filter is not tried again: every tile goes the other way
+    const bool off = state[1] != 0;                      // the filter is not tried again: every tile goes the other way
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + tid; i < nq; i += static_cast<int64_t>(gridDim.x) * 256)
         gbase[i] = gcnt[i];
     for (int i = blockIdx.x * 256 + tid; i <= n_qt; i += gridDim.x * 256) flag[i] = off ? 1 : 0;
-    if (blockIdx.x == 0 && tid == 0) skip[0] = off ? 1 : 0;
     if (off) return;                                     // uniform
     const int64_t row0 = static_cast<int64_t>(blockIdx.x) * kQ8Tile + tid / G;
     const int c = tid % G;
@@ -190,8 +190,7 @@ struct Q8Args {
     int32_t* gcnt;
     const uint32_t* tau_g;
     int32_t* flag;
-    int32_t* given_up;               // query tiles given up in this search so far
-    const int32_t* skip;
+    const int32_t* state;            // [0] tiles given up so far, once per chunk; [1] 1: the filter is switched off
 };
 constexpr size_t kQ8Lds = static_cast<size_t>(kRing) * kQ8Tile * kStageBytes + kQ8MaxTiles * sizeof(float4) +
                           kQ8Queries * 2 * sizeof(int);
@@ -205,7 +204,7 @@ void mine_q8_kernel(const Q8Args a) {
     extern __shared__ __align__(16) unsigned char smem[];
     float4* meta = reinterpret_cast<float4*>(smem + kRing * kStage);
     int* cnt2 = reinterpret_cast<int*>(meta + kQ8MaxTiles);               // [kQ8Queries][2] list fills at the end of a slice
-    if (a.skip[0] != 0) return;                          // uniform (a word of its own: given_up grows while this kernel runs)
+    if (a.state[1] != 0) return;                         // uniform (only the rescoring kernel writes it)
     const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
         (__attribute__((address_space(3))) unsigned char*)smem));
     const int tid = threadIdx.x;
@@ -441,7 +440,7 @@ void mine_q8_kernel(const Q8Args a) {
             const bool over = c0 > kQ8Cap || c1 > kQ8Cap || n > a.append_max;
             if (over && lane < 32) {
                 a.flag[0] = 1;
-                if (atomicExch(&a.flag[1 + q / kBN], 1) == 0) atomicAdd(a.given_up, 1);
+                a.flag[1 + q / kBN] = 1;
             }
             int base = 0;
             if (lane < 32 && n > 0 && !over) base = atomicAdd(&a.gcnt[q], n);
@@ -471,22 +470,36 @@ void q8_rescore_kernel(const unsigned char* __restrict__ Z, const unsigned char*
                        uint64_t* __restrict__ glist, int glist_cap, int32_t* __restrict__ gcnt,
                        const int32_t* __restrict__ gbase, const uint32_t* __restrict__ tau_g,
                        const int32_t* __restrict__ flag, int n_qt, int item_tiles, int64_t sweep_tiles, int sx_max,
-                       int32_t* __restrict__ items) {
+                       int32_t* __restrict__ items, int32_t* __restrict__ state) {
     constexpr int kSteps = 4 * NK, kBlocks = 2, kRow = NK * 256;         // steps of 64 bytes; blocks of 16 rows per round
     const int lane = lane_id();
     if (blockIdx.x == 0 && threadIdx.x < kWave && flag[0] != 0) {
         // the work items that hold a tile given up, and how the search of them splits the labels: with the plan of the whole
         // pool a single item would keep one compute unit per slice busy for as long as all of them take
-        int n = 0;
+        int n = 0, tiles = 0;
         for (int i0 = 0; i0 * item_tiles < n_qt; i0 += kWave) {
             const int i = i0 + lane;
-            bool any = false;
-            for (int t = i * item_tiles; t < (i + 1) * item_tiles && t < n_qt; ++t) any = any || flag[1 + t] != 0;
-            const uint64_t bal = __ballot(any);
-            if (any) items[2 + n + __popcll(bal & lanemask_lt())] = i;
+            int have = 0;
+            for (int t = i * item_tiles; t < (i + 1) * item_tiles && t < n_qt; ++t) have += flag[1 + t] != 0 ? 1 : 0;
+            const uint64_t bal = __ballot(have > 0);
+            if (have > 0) items[2 + n + __popcll(bal & lanemask_lt())] = i;
             n += __popcll(bal);
+            for (int u = 1; u <= item_tiles; ++u) tiles += __popcll(__ballot(have >= u));
         }
-        if (lane == 0) { items[0] = n; items[1] = rows_slices_per_xcd(n, sweep_tiles, sx_max); }
+        if (lane == 0) {
+            const int sx = rows_slices_per_xcd(n, sweep_tiles, sx_max);
+            items[0] = n;
+            items[1] = sx;
+            // The filter costs about six tenths of the bf16 search.  It is not tried again in this search once the tiles that
+            // one chunk gives up take more than half of the time that all of them would take without it: n items in
+            // ceil(n / (32 / sx)) rounds over slices of 1 / (8 sx) of the labels.
+            if (state[1] == 0) {
+                const int n_all = (n_qt + item_tiles - 1) / item_tiles, sx_all = rows_slices_per_xcd(n_all, sweep_tiles, sx_max);
+                const int qx = kCusPerXcd / sx, qx_all = kCusPerXcd / sx_all;
+                state[0] += tiles;
+                if (2 * ((n + qx - 1) / qx) * sx_all > ((n_all + qx_all - 1) / qx_all) * sx) state[1] = 1;
+            }
+        }
     }
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     if (q >= Zq) return;
@@ -585,9 +598,9 @@ int q8_begin(const Q8Plan& p, unsigned char* ws, const void* Z, int64_t Zq, hipS
     const dim3 grid(static_cast<unsigned>((Zq + 3) / 4));
     const unsigned char* z = static_cast<const unsigned char*>(Z);
     float4* zpar = reinterpret_cast<float4*>(ws + p.off_zpar);
-    int32_t* given_up = reinterpret_cast<int32_t*>(ws + p.off_flag);
-    if (p.nk == 1) q8_queries_kernel<1><<<grid, 256, 0, st>>>(z, Zq, ws + p.off_z, zpar, given_up);
-    else q8_queries_kernel<2><<<grid, 256, 0, st>>>(z, Zq, ws + p.off_z, zpar, given_up);
+    int32_t* state = reinterpret_cast<int32_t*>(ws + p.off_flag);
+    if (p.nk == 1) q8_queries_kernel<1><<<grid, 256, 0, st>>>(z, Zq, ws + p.off_z, zpar, state);
+    else q8_queries_kernel<2><<<grid, 256, 0, st>>>(z, Zq, ws + p.off_z, zpar, state);
     XC_HIP_CHECK(hipGetLastError());
     return XC_OK;
 }
@@ -619,20 +632,20 @@ static int q8_chunk_impl(const Q8Plan& p, unsigned char* ws, const Q8Chunk& c, h
     a.glist_cap = c.glist_cap;
     a.lists = reinterpret_cast<uint32_t*>(c.lists);
     a.glist = c.glist; a.gcnt = c.gcnt; a.tau_g = c.tau_g;
-    a.given_up = reinterpret_cast<int32_t*>(ws + p.off_flag);
-    a.skip = a.given_up + 1;
-    a.flag = a.given_up + 2;
+    int32_t* state = reinterpret_cast<int32_t*>(ws + p.off_flag);
+    a.state = state;
+    a.flag = state + 2;
     int32_t* gbase = reinterpret_cast<int32_t*>(ws + p.off_base);
     const unsigned char* w = static_cast<const unsigned char*>(c.W);
     XC_LAUNCH(K_MINE_TILE, st, (q8_rows_kernel<NK><<<static_cast<unsigned>(a.n_tiles), 256, 0, st>>>(
         w + c.lab0 * 256 * NK, n_lab, ws + p.off_rows, reinterpret_cast<float4*>(ws + p.off_meta), c.gcnt, gbase,
-        static_cast<int64_t>(a.n_qt) * kBN, a.flag, a.n_qt, a.given_up, a.given_up + 1)));
+        static_cast<int64_t>(a.n_qt) * kBN, a.flag, a.n_qt, state)));
     XC_HIP_CHECK(hipGetLastError());
     XC_LAUNCH(K_MINE_TILE, st, (mine_q8_kernel<NK><<<kMineGrid, kMineThreads, kQ8Lds, st>>>(a)));
     XC_HIP_CHECK(hipGetLastError());
     XC_LAUNCH(K_MINE_SELECT, st, (q8_rescore_kernel<NK><<<static_cast<unsigned>((c.Zq + 3) / 4), 256, 0, st>>>(
         static_cast<const unsigned char*>(c.Z), w, c.Zq, c.glist, c.glist_cap, c.gcnt, gbase, c.tau_g, a.flag, a.n_qt,
-        c.item_tiles, c.sweep_tiles, c.sx_max, reinterpret_cast<int32_t*>(ws + p.off_items))));
+        c.item_tiles, c.sweep_tiles, c.sx_max, reinterpret_cast<int32_t*>(ws + p.off_items), state)));
     XC_HIP_CHECK(hipGetLastError());
     return XC_OK;
 }

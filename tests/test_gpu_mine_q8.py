@@ -169,6 +169,19 @@ def test_q8_few_tiles_given_up(monkeypatch, Zq, given_up):
     assert torch.equal(ids, ids2) and torch.equal(sc[q], sc2[q] * 2.0 ** 60)
 
 
+@pytest.mark.parametrize("n_tiles,off", [(8, 0), (17, 1)])
+def test_q8_is_switched_off_by_what_one_chunk_gives_up(monkeypatch, n_tiles, off):
+    """Four chunks of labels.  Eight tiles of seventeen given up in each are worth it (they do not add up from chunk to chunk),
+    all of them are not."""
+    Zq, L, d, k = 4300, 4500000, 256, 50
+    W = synth.make_matrix(48, synth.TAG_W, L, d, torch.bfloat16, DEV)
+    Z = synth.make_matrix(48, synth.TAG_Z, Zq, d, torch.bfloat16, DEV)
+    Z[3:256 * n_tiles:256] *= 2.0 ** 60
+    ws, state = _room(Zq, L, d, k)
+    _same_as_bf16(monkeypatch, Z, W, k, ws)
+    assert state.cpu().tolist() == [17 if off else 4 * n_tiles, off]
+
+
 def test_q8_needs_its_room_and_is_reproducible(monkeypatch):
     import paper_2409_20156_amd as xc
     Z, W = _base(45)
