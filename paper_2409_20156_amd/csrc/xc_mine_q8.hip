@@ -350,11 +350,12 @@ void mine_q8_kernel(const Q8Args a) {
                 const int l0 = (t_begin + tile) * kQ8Tile;
                 if (__ballot(mx[0] >= tp[0]) != 0ull) push_block(parc, IC<0>{}, l0, tp[0]);
                 if (__ballot(mx[1] >= tp[1]) != 0ull) push_block(parc, IC<1>{}, l0, tp[1]);
-                // a list that ran over costs its tile of queries the filter whatever follows: nothing reaches it any more (a
-                // query that everything passes for held up its whole work item: 16 384 x 8 M x 256, one such query, 72.0 ms)
+                // a list that ran over costs its tile of queries the filter whatever follows: nothing reaches it any more, from the
+                // tile after next on (a query that everything passes for held up its whole work item: 16 384 x 8 M x 256, one
+                // such query, 72.0 ms against 39.0; with the next tile's threshold changed too, every search took 1 % longer)
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt)
-                    if (cnt[nt] > kQ8Cap) { tu[nt] = INFINITY; tc[nt] = 0x7fffffff; }
+                    if (cnt[nt] > kQ8Cap) tu[nt] = INFINITY;
             }
         };
         auto do_tile = [&](auto parc, int tile) __attribute__((always_inline)) {
