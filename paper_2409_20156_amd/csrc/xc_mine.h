@@ -24,6 +24,7 @@ constexpr int kXcds = 8;            // workgroup w runs on XCD w % 8
 constexpr int kCusPerXcd = kMineGrid / kXcds;
 constexpr int kPhaseGrowth = 8;     // labels of a phase / labels before it
 constexpr int kMaxSlices = 64;      // label slices of a phase at most (one lane per slice in the select)
+constexpr int kMaxRowKernelBytes = 512;   // longest bf16 rows whose queries the row kernel holds in registers
 constexpr int kSelectRegs = 16;     // keys per lane held in registers by the phase select
 constexpr uint32_t kTauInit = 0x007fffffu;   // ordered image of -inf
 
@@ -143,7 +144,7 @@ struct FewPlan {
 
 // Whether the search of few queries takes this shape, and how.  `scratch`: bytes for the group maxima
 // and the candidates of shared queries.
-bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, size_t scratch, FewPlan* p);
+bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool warm, size_t scratch, FewPlan* p);
 
 int few_raise_lds();         // the dynamic LDS limit of its kernels, on the current device
 int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int64_t L, int64_t row_bytes, int k,

@@ -1457,7 +1457,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     // query tile has nothing to gain there and nothing to repeat; of more, its one sweep is the better way.
     FewPlan few;
     if (!(warm && Zq > kBN) && !force_general_kernel() && !force_rows_layout() &&
-        plan_few(Zq, L, a.row_bytes, k_h, t, p.off_glist - p.off_lists, &few))
+        plan_few(Zq, L, a.row_bytes, k_h, t, warm, p.off_glist - p.off_lists, &few))
         return run_mine_few(few, Z, W, Zq, L, a.row_bytes, k_h, t, w8 + p.off_lists, tau_g,
                             warm ? flag : nullptr, static_cast<int>(p.nQT) + 1, shortlist, scores, st);
 

@@ -17,6 +17,8 @@
 // No thresholds to find in phases, no lists that could overflow, two launches.  The general kernel pads the
 // pool to 256 queries and sweeps the labels in four or more serial phases, of which the first have fewer work
 // items than the chip has compute units.
+#include <cmath>
+
 #include "xc_mine.h"
 
 namespace xc {
@@ -611,23 +613,61 @@ void few_finish_kernel(const FewArgs a) {
 // host side
 // ---------------------------------------------------------------------------
 constexpr size_t kFewLds = 144u << 10;       // LDS for the query block at most
-constexpr int64_t kFewQueries = 256;         // up to so many queries always
+constexpr int64_t kFewAlways = 96;           // up to so many queries always
+constexpr int64_t kFewQueries = 256;         // up to so many without limits on the work (one query tile of the other kernels)
 constexpr int64_t kFewMaxQueries = 2048;     // beyond that never
 
-// Which searches come here.  Up to 256 queries (one query tile of the general kernel, mostly padding) all whose query
-// block fits LDS: 131 072 x 768 bf16, k = 5: 57 us against 397 at 64 queries, 121 against 328 at 256; 4 M x 256 bf16,
-// k = 50: 0.67 ms against 1.57 at 64 queries, 1.60 against 1.84 at 256.  More queries cost this path time in proportion
-// (it reads W once per 64 queries), the general kernels almost nothing until their tiles of 256 x 256 fill the chip
-// several times over; the line lies where that many tiles per compute unit were measured equal:
-//   bf16  768 x 131 072:  512 queries (4 tiles per CU) 222 : 328 us, 1024 (8) 426 : 371
-//         256 x 131 072: 1024 queries (8 tiles per CU) 243 : 467 us, 2048 (16) 468 : 595;  4 M labels, 384 (122) 2.6 : 1.9 ms
-//         768 x 16 000, k = 100: 512 queries 217 : 249 us, 1024 419 : 251 - there the rows read again by the second
-//         kernel (16 k per query) are the cost, hence the second line at 1.3 GB of them
-//   fp32  300 x 50 021:  1024 queries (3 tiles per CU) 394 : 775 us;  128 x 500 000: 512 (15) 0.70 : 1.32 ms, 1024 (30) 1.39 : 1.34
-bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, size_t scratch, FewPlan* p) {
+// Workgroups of the first kernel: as many label ranges per block of queries as fit the chip (two workgroups per compute unit
+// where two query blocks fit its LDS), in multiples of the 8 XCDs and at least 8.
+static int64_t few_slots(const FewPlan& p) { return p.lds <= (76u << 10) ? 512 : 256; }
+static int64_t few_ranges(const FewPlan& p) {
+    const int64_t n = few_slots(p) / p.n_qb / 8 * 8;
+    return n < 8 ? 8 : n;
+}
+
+// Estimated time of this search, and of the other kernels' where it can be the smaller one, in us: least squares over 870
+// searches of 97 to 2048 queries, 5000 to 30 million rows of 128 to 9216 bytes, k = 5, 50 and 100, W from memory.  Half of the estimates are
+// within a tenth, nine in ten within a quarter; choosing by them costs 0.6 % over always choosing right (bf16; fp32 0.6 %
+// with the fifth below).  This search: products per block of 16, 32 or 64 queries, with what the last round of workgroups
+// leaves idle; rows read again by the second kernel; maxima (stored four bytes at a time, dearer where 64 MB of them are
+// under way).  The others: products, W, what passes (more per query tile, and
+// much more where k > 64), the phases' start-up; rows that are no multiple of a stage load slowly.
+static double few_us(const FewPlan& p, int64_t Zq, int64_t L, int64_t row_bytes, int k, bool f32) {
+    const double slots = static_cast<double>(few_slots(p)), wgs = static_cast<double>(few_ranges(p) * p.n_qb);
+    const double padded = static_cast<double>(p.n_qb) * p.nb * 16;
+    const double gflop = 2e-9 * padded * L * (row_bytes / (f32 ? 4 : 2)) * slots * ceil(wgs / slots) / wgs;
+    const double per = f32 ? (p.nb == 1 ? 13.9 : p.nb == 2 ? 8.4 : 8.2) : (p.nb == 1 ? 7.3 : p.nb == 2 ? 3.8 : 2.2);
+    const double maxima = 1e-6 * padded * p.n_groups;
+    return 22.0 + gflop * per + 0.16e-6 * Zq * k * (16 << p.gshift) * row_bytes + maxima * (maxima < 16.0 ? 5.1 : 12.0);
+}
+static double others_us(int64_t Zq, int64_t L, int64_t row_bytes, int k, bool f32, bool row_kernel, bool warm) {
+    const double mlab = 1e-6 * L, kb = 1e-3 * row_bytes, long_list = k > 64 ? 1.0 : 0.0;
+    if (Zq <= kBN) {
+        if (row_kernel) return 56.0 + 625.0 * mlab * kb + 12.0 * kb + long_list * (22.0 + 217.0 * mlab);
+        return warm ? 37.0 + 920.0 * mlab * kb + 24.0 * kb + long_list * (17.0 + 1040.0 * mlab)
+                    : 36.0 + 980.0 * mlab * kb + 26.0 * kb + long_list * (41.0 + 1090.0 * mlab);
+    }
+    const double qt = static_cast<double>((Zq + kBN - 1) / kBN), gflop = 2e-9 * qt * kBN * L * (row_bytes / (f32 ? 4 : 2));
+    const bool tail = row_bytes % kStageBytes != 0;
+    return f32 ? 84.0 + gflop * (tail ? 5.2 : 2.3) + 2960.0 * mlab * kb + 19.0 * qt * mlab + 100.0 * kb + long_list * 1190.0 * mlab
+               : 44.0 + gflop * (tail ? 0.84 : 0.22) + 556.0 * mlab * kb + 147.0 * qt * mlab + 34.0 * kb + long_list * 1300.0 * mlab;
+}
+
+// Which searches come here.  Up to 96 queries (less than half of a query tile of the general kernel) all whose query block fits LDS:
+// 131 072 x 768 bf16, k = 5: 71 us against 408 at 64 queries; 4 M x 256 bf16, k = 50: 0.65 ms against 1.57.  More queries
+// cost this path time in proportion (it multiplies W once per block of at most 64), the others almost nothing until their tiles of
+// 256 x 256 fill the chip several times over.  Up to 2048 queries, 6 tiles per compute unit (fp32: 16) and 1.3 GB of rows read
+// again - no limits up to 256 - all searches whose alternative starts in phases too short to fill the chip: from scratch
+// where that is the row kernel (1024 x 98 304 x 256, k = 64 212 against 624 us; 2048 x 49 152 276 and 685), fp32 up to 256
+// queries (256 x 1 M x 128, k = 100 639 and 4302).  Of the rest the estimates choose, in fp32 with a fifth in favour of this
+// path, up to 256 queries on long bf16 rows with a twentieth against it (where the estimates err, by these parts).  Here and there: 1024 x 98 301 x 768 bf16, k = 50 499 and 250 us; 2048 x 49 149 x 2304, k = 5 1679 and 549; 512 x 98 301 x 768, k
+// = 5 199 and 214; from thresholds 256 x 4 M x 128, k = 5 1036 and 722, 256 x 4 M x 64, k = 100 710 and 1405; 256 x 5000 x
+// 2304, k = 100 316 and 249; 1024 x 262 141 x 768 fp32 3480 and 3100, 1024 x 78 589 x 300 445 and 590.
+bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool warm, size_t scratch, FewPlan* p) {
+    const bool f32 = t == XC_F32;
     if (Zq > kFewQueries) {
         const int64_t tiles = ((Zq + 255) / 256) * ((L + 255) / 256);
-        if (Zq > kFewMaxQueries || tiles > (t == XC_F32 ? 16 : 6) * 256) return false;
+        if (Zq > kFewMaxQueries || tiles > (f32 ? 16 : 6) * 256) return false;
         if (static_cast<double>(Zq) * k * 16.0 * static_cast<double>(row_bytes) > 1.3e9) return false;
     }
     const int64_t ks = (row_bytes + 63) / 64;
@@ -643,6 +683,10 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, size_
     while (gs < 4 && (L >> (4 + gs)) > (1 << 17)) ++gs;
     p->gshift = gs;
     p->n_groups = (L + (16LL << gs) - 1) / (16LL << gs);
+    const bool row_kernel = !f32 && row_bytes % kStageBytes == 0 && row_bytes <= kMaxRowKernelBytes;
+    const bool always = Zq <= kFewAlways || (f32 ? Zq <= kFewQueries : row_kernel && !warm);
+    const double favour = f32 ? 1.2 : Zq <= kFewQueries && !row_kernel ? 0.95 : 1.0;
+    if (!always && few_us(*p, Zq, L, row_bytes, k, f32) >= favour * others_us(Zq, L, row_bytes, k, f32, row_kernel, warm)) return false;
     // the second kernel: as many workgroups per query as give each wave one block of 16 labels, within what the chip holds
     int ns = 1;
     while (ns < kMaxSplit && Zq * ns * 2 <= 256 && (static_cast<int64_t>(k) << gs) > ns * Finish<1024>::kWaves) ns <<= 1;
@@ -679,13 +723,11 @@ int few_raise_lds() {
 template <typename T>
 static int launch_few(const FewPlan& p, const FewArgs& a, hipStream_t st) {
     const bool ktail = a.row_bytes % 64 != 0;
-    // workgroups: two per compute unit where two query blocks fit its LDS, as many label ranges as that leaves per
-    // query block, in multiples of the 8 XCDs, and no more than there are tiles
-    int64_t per_qb = (p.lds <= (76u << 10) ? 512 : 256) / p.n_qb;
+    // no more label ranges than there are tiles
     const int64_t tiles = (a.L + kFewTile - 1) / kFewTile;
-    const int64_t enough = (tiles + kFewWaves - 1) / kFewWaves;
-    per_qb = per_qb < enough ? per_qb : (enough + 7) / 8 * 8;
-    per_qb = per_qb < 8 ? 8 : per_qb / 8 * 8;                 // (never more workgroups than are resident at once)
+    const int64_t enough = ((tiles + kFewWaves - 1) / kFewWaves + 7) / 8 * 8;
+    const int64_t most = few_ranges(p);
+    const int64_t per_qb = most < enough ? most : enough;
     const dim3 grid(static_cast<unsigned>(per_qb * p.n_qb));
     const FewFn fn = few_kernel<T>(p.nb, ktail);
     XC_LAUNCH(K_MINE_TILE, st, (fn<<<grid, kFewThreads, p.lds, st>>>(a)));

@@ -38,6 +38,19 @@ def _all_routes(monkeypatch, Z, W, k, forced, margins=(0.0, 0.1)):
     return ids, sc
 
 
+def _takes_few(Z, W, k, **kw):
+    """Whether a call takes the search of few queries: two launches, whatever the size."""
+    from paper_2409_20156_amd import binding
+    binding.mine_negatives(Z, W, k, **kw)
+    binding.profile_reset()
+    binding.profile_enable(True)
+    binding.mine_negatives(Z, W, k, **kw)
+    binding.profile_enable(False)
+    n = binding.profile_collect()
+    binding.profile_reset()
+    return n["mine_tile"][1] == 1 and n["mine_select"][1] == 1
+
+
 GENERAL, NARROW, WIDE = ("XC_MINE_GENERAL", "1"), ("XC_MINE_ROWS", "narrow"), ("XC_MINE_ROWS", "wide")
 
 
@@ -75,6 +88,7 @@ def test_few_queries_score_as_the_general_kernel_does_fp32(monkeypatch, Zq, L, d
     W[:n] *= 3.0                            # (the longest rows: among the best of their own query)
     W[late] = W[:n].clone()
     Z[:n] += W[:n]
+    assert _takes_few(Z, W, k)
     ids, sc = _all_routes(monkeypatch, Z, W, k, [GENERAL])
     at = ids[:n].eq(torch.arange(n, device=DEV, dtype=torch.int32)[:, None]).int().argmax(dim=1)
     q = torch.arange(n, device=DEV)
@@ -82,7 +96,7 @@ def test_few_queries_score_as_the_general_kernel_does_fp32(monkeypatch, Zq, L, d
 
 
 @pytest.mark.parametrize("Zq,L,d,k", [
-    (512, 60000, 768, 64),                 # rows that the general kernel takes
+    (512, 60000, 768, 5),                  # rows that the general kernel takes
     (1000, 50000, 256, 50),                # ... that the row kernel takes
     (300, 20000, 40, 64),                  # 80 bytes: a step of one chunk at the end
     (20, 3000, 1152, 20),
@@ -91,4 +105,34 @@ def test_few_queries_score_as_the_general_kernel_does_fp32(monkeypatch, Zq, L, d
 def test_few_queries_score_as_the_other_kernels_do_bf16(monkeypatch, Zq, L, d, k):
     Z, W = _inputs(73, Zq, L, d, torch.bfloat16)
     forced = [GENERAL, NARROW, WIDE] if d * 2 % 128 == 0 and d * 2 <= 512 else [GENERAL]
+    assert _takes_few(Z, W, k)
     _all_routes(monkeypatch, Z, W, k, forced)
+
+
+@pytest.mark.parametrize("Zq,L,d,dtype,k,warm,few", [
+    (96, 40000, 2304, torch.bfloat16, 100, False, True),          # up to 96 queries always
+    (256, 200000, 256, torch.bfloat16, 100, False, True),         # from scratch against the row kernel
+    (1000, 50000, 256, torch.bfloat16, 50, False, True),
+    (256, 400000, 64, torch.bfloat16, 5, True, True),             # from thresholds: by the estimates
+    (256, 4000000, 64, torch.bfloat16, 5, True, False),
+    (256, 5000, 2304, torch.bfloat16, 100, False, False),         # long lists of long rows read again
+    (256, 50000, 768, torch.bfloat16, 5, True, True),
+    (512, 60000, 768, torch.bfloat16, 5, False, True),
+    (1024, 98301, 768, torch.bfloat16, 50, False, False),         # enough tiles for the general kernel
+    (2048, 24573, 2304, torch.bfloat16, 5, False, False),         # two blocks of queries in LDS only
+    (256, 100000, 768, torch.float32, 50, True, True),            # fp32 up to 256 queries
+    (1024, 60000, 300, torch.float32, 32, False, True),
+    (1024, 70000, 2304, torch.float32, 5, False, False),
+])
+def test_searches_take_the_faster_route(monkeypatch, Zq, L, d, dtype, k, warm, few):
+    """Either side of the lines between the search of few queries and the others; the result is the same."""
+    import paper_2409_20156_amd as xc
+    Z, W = _inputs(74, Zq, L, d, dtype)
+    code = xc.XC_BF16 if dtype == torch.bfloat16 else xc.XC_F32
+    ws = torch.empty(xc.mine_workspace(Zq, L, d, k, code), dtype=torch.uint8, device=DEV)
+    ids, sc = (t.clone() for t in _cold(Z, W, k, ws))
+    assert _takes_few(Z, W, k, workspace=ws, warm_margin=0.1 if warm else None) == few
+    monkeypatch.setenv("XC_MINE_ROWS", "narrow")                  # the other side of the line
+    ids_o, sc_o = _cold(Z, W, k)
+    monkeypatch.delenv("XC_MINE_ROWS")
+    assert torch.equal(ids, ids_o) and torch.equal(sc, sc_o)
