@@ -1,4 +1,6 @@
-"""GPU parity of xc_mine_negatives against the oracle's exact top-k."""
+"""GPU parity of xc_mine_negatives against the oracle's exact top-k.  At these sizes nearly every call takes the search of
+few queries by default, so each case is run on the other kernels as well - the row kernel in both widths (bf16 rows of 128,
+256, 384 or 512 bytes) and the general kernel - and has to give the same bits there."""
 import numpy as np
 import pytest
 import torch
@@ -10,18 +12,29 @@ from tests.parity import check_topk, f64
 pytestmark = pytest.mark.gpu
 
 
-def _run(Z, W, k):
+def _run(Z, W, k, monkeypatch=None):
+    """The default route's result; with `monkeypatch` every other route is run too and compared with it."""
     import paper_2409_20156_amd as xc
     ids, sc = xc.mine_negatives(Z, W, k, want_scores=True)
     torch.cuda.synchronize()
+    if monkeypatch is not None:
+        row = Z.shape[1] * Z.element_size()
+        short = Z.dtype == torch.bfloat16 and row % 128 == 0 and row <= 512
+        for name, value in [("XC_MINE_ROWS", "narrow")] + [("XC_MINE_ROWS", "wide")] * short + [("XC_MINE_GENERAL", "1")]:
+            print("route", name, value, flush=True)
+            monkeypatch.setenv(name, value)
+            ids_r, sc_r = xc.mine_negatives(Z, W, k, want_scores=True)
+            torch.cuda.synchronize()
+            monkeypatch.delenv(name)
+            assert torch.equal(ids, ids_r) and torch.equal(sc, sc_r), (name, value)
     return ids.cpu().numpy(), sc.cpu().numpy()
 
 
-def _case(seed, Zq, L, d, dtype, k):
+def _case(seed, Zq, L, d, dtype, k, monkeypatch=None):
     dev = "cuda:0"
     W = synth.make_matrix(seed, synth.TAG_W, L, d, dtype, dev)
     Z = synth.make_matrix(seed, synth.TAG_Z, Zq, d, dtype, dev)
-    ids, sc = _run(Z, W, k)
+    ids, sc = _run(Z, W, k, monkeypatch)
     Z64, W64 = f64(Z), f64(W)
     ids_o, sc_o = orc.mine_negatives(Z64, W64, k)
     n_tied = check_topk(ids, sc, ids_o, sc_o, Z64, W64)
@@ -39,34 +52,34 @@ def _case(seed, Zq, L, d, dtype, k):
     (3, 64, 64, torch.bfloat16, 64),           # k = L, single partial tile
     (257, 3000, 768, torch.bfloat16, 128),     # maximum k, d of the large configurations
     (5, 129, 8, torch.bfloat16, 7),            # minimum row (16 bytes)
-    # 128-byte rows are one pipeline stage per tile, and query tiles with few real queries leave half
+    # general kernel: 128-byte rows are one pipeline stage per tile, and query tiles with few real queries leave half
     # of the waves with nothing to filter: they run a tile ahead of the others
     (78, 30000, 64, torch.bfloat16, 63),
     (200, 30000, 64, torch.bfloat16, 63),
     (600, 30000, 64, torch.bfloat16, 63),
     (78, 30000, 32, torch.float32, 63),
     (78, 16384, 64, torch.bfloat16, 8),
-    # bf16 rows of 128, 256, 384 and 512 bytes take the kernel that keeps the query tile in registers
+    # row kernel, which keeps the query tile in registers
     (300, 70000, 256, torch.bfloat16, 50),     # the row shape of the largest configuration
     (513, 9000, 192, torch.bfloat16, 100),     # three query tiles, the last with one query; ragged last label tile
     (64, 200, 256, torch.bfloat16, 128),       # maximum k, fewer labels than two tiles
     (257, 40000, 128, torch.bfloat16, 64),
     (31, 127, 64, torch.bfloat16, 127),        # a single ragged label tile, k = L
 ])
-def test_mine_matches_oracle(Zq, L, d, dtype, k):
+def test_mine_matches_oracle(monkeypatch, Zq, L, d, dtype, k):
     print("case", Zq, L, d, dtype, k, flush=True)
-    _case(11, Zq, L, d, dtype, k)
+    _case(11, Zq, L, d, dtype, k, monkeypatch)
 
 
-def test_mine_long_slices_exercise_list_reduction():
-    # 512 queries x 131072 labels: 4096 labels per slice, so candidate lists fill and are reduced
+def test_mine_long_slices_exercise_list_reduction(monkeypatch):
+    # 512 queries x 131072 labels: 4096 labels per slice of the row and general kernels, so candidate lists fill and are reduced
     print("case long slices", flush=True)
-    _case(5, 512, 131072, 64, torch.bfloat16, 64)
+    _case(5, 512, 131072, 64, torch.bfloat16, 64, monkeypatch)
 
 
 @pytest.mark.parametrize("L,Zq,k,d", [(40000, 140, 33, 16), (300000, 260, 128, 16), (40000, 140, 33, 64),
                                       (300000, 260, 128, 256), (150000, 700, 100, 128)])
-def test_mine_increasing_scores_worst_case_for_the_threshold(L, Zq, k, d):
+def test_mine_increasing_scores_worst_case_for_the_threshold(monkeypatch, L, Zq, k, d):
     # score(i, l) grows with l: every label beats the running threshold, in every phase, so every
     # accumulator is parked and the candidate lists are cut all the time (32-byte rows: the general kernel,
     # its pools and shared lists; 128..512-byte rows: the lists of the kernel with register-resident queries)
@@ -75,7 +88,7 @@ def test_mine_increasing_scores_worst_case_for_the_threshold(L, Zq, k, d):
     W = (torch.arange(L, dtype=torch.float32)[:, None] / 65536.0 * base[None, :]).to(torch.bfloat16).to(dev)
     Z = torch.ones((Zq, d), dtype=torch.bfloat16, device=dev)
     Z[1::2] *= -1.0                                  # odd queries prefer small ids
-    ids, sc = _run(Z, W, k)
+    ids, sc = _run(Z, W, k, monkeypatch)
     Z64, W64 = f64(Z), f64(W)
     ids_o, sc_o = orc.mine_negatives(Z64, W64, k)
     check_topk(ids, sc, ids_o, sc_o, Z64, W64)
@@ -130,32 +143,32 @@ def test_row_kernel_layouts_warm_repeat_of_some_tiles(monkeypatch, mode):
         check_topk(ids.cpu().numpy(), sc.cpu().numpy(), ids_o, sc_o, f64(Zp), f64(W))
 
 
-def test_mine_all_scores_equal_orders_by_id():
+def test_mine_all_scores_equal_orders_by_id(monkeypatch):
     dev = "cuda:0"
     W = torch.zeros((3000, 64), dtype=torch.bfloat16, device=dev)
     Z = synth.make_matrix(1, synth.TAG_Z, 70, 64, torch.bfloat16, dev)
-    ids, sc = _run(Z, W, 20)
+    ids, sc = _run(Z, W, 20, monkeypatch)
     assert (ids == np.arange(20)[None, :]).all()
     assert (sc == 0).all()
 
 
-def test_mine_planted_rows_come_first():
+def test_mine_planted_rows_come_first(monkeypatch):
     dev = "cuda:0"
     L, d, Zq, k = 20000, 128, 64, 10
     W = synth.make_matrix(2, synth.TAG_W, L, d, torch.bfloat16, dev)
     Z = synth.make_matrix(2, synth.TAG_Z, Zq, d, torch.bfloat16, dev)
     plant = (torch.arange(Zq) * 311 + 7) % L
     W[plant.to(dev)] = (Z.float() * 8.0).to(torch.bfloat16)       # <z, 8 z> dwarfs every random score
-    ids, _ = _run(Z, W, k)
+    ids, _ = _run(Z, W, k, monkeypatch)
     assert (ids[:, 0] == plant.numpy()).all()
 
 
-def test_mine_is_reproducible_run_to_run():
+def test_mine_is_reproducible_run_to_run(monkeypatch):
     dev = "cuda:0"
     W = synth.make_matrix(3, synth.TAG_W, 30000, 64, torch.bfloat16, dev)
     Z = synth.make_matrix(3, synth.TAG_Z, 300, 64, torch.bfloat16, dev)
-    a = _run(Z, W, 64)
-    b = _run(Z, W, 64)
+    a = _run(Z, W, 64, monkeypatch)
+    b = _run(Z, W, 64, monkeypatch)
     assert (a[0] == b[0]).all() and (a[1] == b[1]).all()
 
 

@@ -1,5 +1,5 @@
 """The general search kernel's dense first phase (all scores of its tiles written, the best k taken by one wave per query)
-against the oracle, forced through XC_MINE_GENERAL: both widths of the selection, row lengths with and without a tail, equal
+against the oracle, forced through XC_MINE_GENERAL: the three widths of the selection (4, 8 and 16 tiles), row lengths with and without a tail, equal
 scores (more pass the bound than the list holds), scores that are no numbers, fewer scores than k."""
 import numpy as np
 import pytest
@@ -26,7 +26,9 @@ def _run(Z, W, k):
 
 
 @pytest.mark.parametrize("Zq,L,d,dtype,k", [
-    (300, 16 * 256, 64, torch.bfloat16, 5),       # 16 tiles: eight of them dense
+    (300, 16 * 256, 64, torch.bfloat16, 5),       # 16 tiles: four of them dense
+    (300, 13 * 256 + 9, 64, torch.bfloat16, 100), # 13 tiles: six of them dense, what half of the range allows
+    (520, 9000, 128, torch.bfloat16, 40),         # eight dense tiles
     (257, 9000, 768, torch.bfloat16, 128),        # maximum k: every half of a lane's scores has its maximum taken
     (700, 12001, 100, torch.float32, 100),        # fp32 with a tail, ragged last tile
     (40, 20000, 40, torch.bfloat16, 1),           # 80-byte rows, mostly empty query tile
@@ -41,28 +43,33 @@ def test_dense_phase_matches_oracle(Zq, L, d, dtype, k):
     check_topk(ids, sc, ids_o, sc_o, f64(Z), f64(W))
 
 
-def test_dense_phase_equal_scores_order_by_id():
-    L, k = 9000, 100
+# labels, k, dense tiles
+_WIDTHS = [(9000, 100, 16), (9000, 40, 8), (3337, 100, 6), (4096, 5, 4)]
+
+
+@pytest.mark.parametrize("L,k,tiles", _WIDTHS)
+def test_dense_phase_equal_scores_order_by_id(L, k, tiles):
     W = torch.zeros((L, 64), dtype=torch.bfloat16, device=DEV)
     Z = synth.make_matrix(1, synth.TAG_Z, 300, 64, torch.bfloat16, DEV)
     ids, _ = _run(Z, W, k)
     assert (ids == np.arange(k)[None, :]).all()
     W = torch.ones((L, 64), dtype=torch.bfloat16, device=DEV)      # some above the ties, on either side of the dense tiles
     Z = torch.ones((300, 64), dtype=torch.bfloat16, device=DEV)
-    W[70:1500:100] = 2.0
-    W[8000:8005] = 2.0
+    better = np.concatenate([np.arange(70, 1500, 100), np.arange(L - 5, L)])
+    W[torch.as_tensor(better, device=DEV)] = 2.0
     ids, _ = _run(Z, W, k)
-    better = np.concatenate([np.arange(70, 1500, 100), np.arange(8000, 8005)])
-    rest = np.setdiff1d(np.arange(L), better)[:k - len(better)]
-    assert (ids == np.concatenate([better, rest])[None, :]).all()
+    rest = np.setdiff1d(np.arange(L), better)
+    assert (ids == np.concatenate([better, rest])[None, :k]).all()
 
 
-def test_dense_phase_scores_that_are_no_numbers():
-    L, d, k = 9000, 64, 100
+@pytest.mark.parametrize("L,k,tiles", _WIDTHS)
+def test_dense_phase_scores_that_are_no_numbers(L, k, tiles):
+    d = 64
     W = synth.make_matrix(3, synth.TAG_W, L, d, torch.bfloat16, DEV)
     Z = synth.make_matrix(3, synth.TAG_Z, 300, d, torch.bfloat16, DEV)
-    W[:4000] = float("nan")                                        # most of the dense tiles
-    W[10:60] = synth.make_matrix(4, synth.TAG_W, 50, d, torch.bfloat16, DEV)       # fewer numbers there than k
+    W[:256 * tiles + 10] = float("nan")                            # all of the dense tiles, but for
+    few = k // 2
+    W[10:10 + few] = synth.make_matrix(4, synth.TAG_W, few, d, torch.bfloat16, DEV)        # fewer numbers there than k
     Z[7] = float("nan")
     ids, sc = _run(Z, W, k)
     assert (ids[7] == -1).all() and np.isneginf(sc[7]).all()

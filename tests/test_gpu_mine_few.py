@@ -28,7 +28,8 @@ def _run(Z, W, k, **kw):
     (33, 70000, 104, torch.bfloat16, 64),       # four query blocks, three in use
     (64, 16 * 1024, 256, torch.bfloat16, 1),
     (65, 4100, 768, torch.bfloat16, 20),        # a second group of query blocks
-    (256, 9000, 768, torch.bfloat16, 128),
+    (256, 9000, 768, torch.bfloat16, 20),
+    (256, 9000, 256, torch.bfloat16, 128),
     (5, 3000, 2048, torch.bfloat16, 9),         # 4096-byte rows: fewer query blocks fit LDS
     (40, 3000, 1152, torch.bfloat16, 9),        # 2304-byte rows: two query blocks, two groups of them
     (1, 1000, 4608, torch.bfloat16, 3),         # the longest row it takes (9216 bytes)
@@ -48,12 +49,14 @@ def test_few_queries_match_oracle(Zq, L, d, dtype, k):
     assert all(len(set(row)) == k for row in ids.tolist()) and (np.diff(sc, axis=1) <= 0).all()
 
 
-@pytest.mark.parametrize("L", [1000, 2200000, 4300001])          # 4300001: more tied candidates than the key list holds
-def test_few_queries_equal_scores_order_by_id(L):
-    W = torch.ones((L, 8), dtype=torch.bfloat16, device=DEV)
-    Z = torch.ones((3, 8), dtype=torch.bfloat16, device=DEV)
+# 4300001: more tied candidates than the key list holds; from 512 queries on a query has 256 threads and a list of 1024 keys,
+# which 128 groups of 16 tied labels overflow, from more than 512 groups with the same maximum
+@pytest.mark.parametrize("Zq,L,d", [(3, 1000, 8), (3, 2200000, 8), (3, 4300001, 8), (512, 1900, 64), (700, 40000, 64)])
+def test_few_queries_equal_scores_order_by_id(Zq, L, d):
+    W = torch.ones((L, d), dtype=torch.bfloat16, device=DEV)
+    Z = torch.ones((Zq, d), dtype=torch.bfloat16, device=DEV)
     ids, sc = _run(Z, W, 128)
-    assert (ids == np.arange(128)[None, :]).all() and (sc == 8.0).all()
+    assert (ids == np.arange(128)[None, :]).all() and (sc == d).all()
     W[L // 2:L // 2 + 40] = 2.0                                   # some better, the rest still tied
     ids, sc = _run(Z, W, 128)
     want = np.concatenate([np.arange(L // 2, L // 2 + 40), np.arange(88)])
@@ -79,10 +82,7 @@ def test_few_queries_scores_that_are_no_numbers(monkeypatch, dtype):
         monkeypatch.setenv("XC_MINE_GENERAL", "1")
         ids_g, sc_g = _run(Z, M, k)
         monkeypatch.delenv("XC_MINE_GENERAL")
-        assert (ids == ids_g).mean() > 0.999                      # (a pair may change places where sums round differently)
-        fin = np.isfinite(sc_g)
-        assert (fin == np.isfinite(sc)).all() and (sc[~fin] == sc_g[~fin]).all()
-        assert np.abs(sc[fin] - sc_g[fin]).max() <= 1e-5 * max(1.0, np.abs(sc_g[fin]).max())
+        assert (ids == ids_g).all() and (sc == sc_g).all()        # bit for bit
         assert (ids[5] == -1).all()
 
 

@@ -55,12 +55,13 @@ def test_schedule_matches_oracle(kind, lag, warm):
     check_rows_close(f64(W), W64, tol, "W after the schedule")
 
 
-@pytest.mark.parametrize("lag,warm,cut", [(0, None, 3), (2, None, 4), (0, 0.1, 4), (2, 0.0, 2)])
-def test_schedule_resumes_from_a_saved_state_bit_for_bit(lag, warm, cut):
+# (pool 320: the search from scratch after the resume takes another kernel than the one from thresholds it stands in for)
+@pytest.mark.parametrize("lag,warm,cut,pool", [(0, None, 3, 64), (2, None, 4, 64), (0, 0.1, 4, 64), (2, 0.0, 2, 64), (0, 0.1, 4, 320)])
+def test_schedule_resumes_from_a_saved_state_bit_for_bit(lag, warm, cut, pool):
     """Stop after `cut` steps (with lag 2 and refreshes at 1, 3, 5 a search is then waiting to take over), save,
     build a new schedule on other tensors, load, go on: losses and the final W equal the uninterrupted run's bits."""
     from paper_2409_20156_amd.schedule import Schedule
-    L, d, B, pool, k_p, k_h, k_r = 4096, 64, 32, 64, 2, 8, 16
+    L, d, B, k_p, k_h, k_r = 4096, 64, 32, 2, 8, 16
     steps, tau_s, tau_r, lr = 8, 1, 2, 0.3
     W0 = synth.make_matrix(12, synth.TAG_W, L, d, torch.float32, DEV)
     Z = synth.make_matrix(12, synth.TAG_Z, pool, d, torch.float32, DEV)
