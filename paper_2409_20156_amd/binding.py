@@ -120,7 +120,8 @@ def mine_negatives(Z: torch.Tensor, W: torch.Tensor, k_h: int, *, want_scores: b
     """shortlist int32 [Zq, k_h] (and fp32 scores if asked): exact top-k_h of Z W^T per row.
 
     warm_margin (relative, >= 0): start from the thresholds the previous search left in `workspace`
-    (same result, usually less time); `workspace[:4]` viewed as int32 is 1 afterwards if the full
+    (same result; less time, except for 4096 queries and more on 2^20 and more bf16 rows of 256 or 512 bytes, where
+    only a search from scratch takes the 8-bit filter); `workspace[:4]` viewed as int32 is 1 afterwards if the full
     search had to be repeated."""
     lib = load_library()
     code = _dtype_code(Z)
