@@ -870,14 +870,13 @@ void heads_write_kernel(const uint2* __restrict__ pairs, int64_t P, int64_t chun
 }
 
 // ---------------------------------------------------------------------------
-// The whole pair sort, the segment heads and the lists of a small step in one workgroup: up to kSmallPairs pairs.
-// Bound: launches.  The five kernels above take 5 us each whatever the size; 800 pairs (32 queries of 25 candidates):
-// fp32 rows of 64: step 35.6 -> 26.0 us.
+// The whole pair sort, the segment heads and the lists of a small step in one workgroup (sort_in_one).
+// Bound: launches.  The five kernels above take 5 us each whatever the size; 800 pairs (32 queries of 25 candidates),
+// fp32 rows of 64: step 35.6 -> 23.8 us.
 // A pair is one integer, key << ib | pair index (all different, so any sorting network is stable), held E to a thread in a
 // bitonic network: neighbours within a thread, within a wave by lane exchange, further away through LDS.
 // ---------------------------------------------------------------------------
 constexpr int kSmallThreads = 1024;
-constexpr int kSmallPairs = 4 * kSmallThreads;
 
 template <typename K> __device__ __forceinline__ K lane_xor(K v, int off);
 template <> __device__ __forceinline__ uint32_t lane_xor<uint32_t>(uint32_t v, int off) { return __shfl_xor(v, off, kWave); }
@@ -1383,6 +1382,14 @@ static int plan_step(int64_t B, int64_t L, int d, int k_p, int n_neg, xc_dtype t
     return XC_OK;
 }
 
+// Up to 2 pairs per thread always, up to 4 where the keys are so wide that the alternative sorts in rounds instead of one
+// round and buckets.  Step with the one workgroup and with the other kernels, us, bf16 rows of 64, BCE: 1000 pairs over 1 M labels
+// 23.2 : 37.4, 2040 28.5 : 38.3, 2100 42.3 : 37.0, 4080 47.3 : 39.7; over 4096 labels 2040 29.5 : 37.4, 2100 35.9 : 32.7; over 10 M
+// labels 2100 42.3 : 52.3, 4080 47.0 : 53.3.
+static bool sort_in_one(const StepPlan& pl) {
+    return pl.P <= 2 * kSmallThreads || (pl.P <= 4 * kSmallThreads && pl.n_buckets == 0);
+}
+
 template <typename T, int KIND>
 static void launch_gather(const StepPlan& pl, hipStream_t st, const void* Z, void* W, int64_t B,
                           int64_t L, int d, const int32_t* pos, int k_p, const int32_t* neg,
@@ -1535,7 +1542,7 @@ static int step_impl(const void* Z, void* W, int64_t B, int64_t L, int d, const 
     // S5, first half: the pairs sorted by label and the segment heads.  They depend on the ids alone, so they come
     // first, and the gather that follows knows which rows it may update itself.
     uint2 *kin = pairs0, *kout = pairs1;
-    if (pl.P <= kSmallPairs) {
+    if (sort_in_one(pl)) {
         // one workgroup does it all; 32-bit elements where key and pair index fit them
         int ib = 0;
         while ((static_cast<int64_t>(1) << ib) < pl.P) ++ib;
@@ -1546,7 +1553,7 @@ static int step_impl(const void* Z, void* W, int64_t B, int64_t L, int d, const 
         const bool narrow = pl.key_bits + ib < 32;           // (below 32: the padding element stays larger than every pair)
         if (n <= kSmallThreads) { if (narrow) XC_SORT_SMALL(uint32_t, 1); else XC_SORT_SMALL(uint64_t, 1); }
         else if (n <= 2 * kSmallThreads) { if (narrow) XC_SORT_SMALL(uint32_t, 2); else XC_SORT_SMALL(uint64_t, 2); }
-        else { if (narrow) XC_SORT_SMALL(uint32_t, 4); else XC_SORT_SMALL(uint64_t, 4); }
+        else XC_SORT_SMALL(uint64_t, 4);                     // (wide keys only)
 #undef XC_SORT_SMALL
         XC_HIP_CHECK(hipGetLastError());
     } else if (pl.n_buckets > 0) {

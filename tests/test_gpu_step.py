@@ -279,11 +279,13 @@ def test_step_wide_keys_in_a_narrow_label_range():
 @pytest.mark.parametrize("B,n_neg,L", [
     (1, 1, 300), (31, 32, 50), (32, 31, 4096), (41, 24, 4096),                  # 2, 1023, 1024, 1025 pairs
     (32, 63, 4096), (683, 2, 4096), (64, 63, 700), (64, 63, 3000000),           # 2048, 2049, 4096 pairs; 64-bit elements
-    (241, 16, 3000000), (30, 30, 3000000), (1, 4095, 40),                       # 4097 pairs: the general sort; few labels
+    (241, 16, 3000000), (30, 30, 3000000), (1, 4095, 40),                       # 4097 pairs; few labels
+    (683, 2, 4200000), (64, 63, 4200000), (241, 16, 4200000),                   # 2049, 4096, 4097 pairs with wide keys
 ])
 def test_step_small_pair_sort(B, n_neg, L):
-    """Steps of up to 4096 pairs sort them in one workgroup: both element widths, one to four elements per thread, a
-    last one partly filled, masked pairs among them; labels with one and with many pairs."""
+    """Steps of up to 2048 pairs, with keys of more than 22 bits up to 4096, sort them in one workgroup: both element
+    widths, one to four elements per thread, a last one partly filled, masked pairs among them; labels with one and with
+    many pairs; and the sizes just behind these lines."""
     print("case", B, n_neg, L, flush=True)
     Z, W, pos, neg, logq, Z64, W64 = _inputs(31, B, L, 8, torch.float32, 1, 0, n_neg)
     neg[0, n_neg // 2] = -1
