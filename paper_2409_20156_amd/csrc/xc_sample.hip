@@ -4,6 +4,7 @@
 // of Alg. 1 when no shortlist is given).  Integer arithmetic only, so the ids
 // are a function of (seed, query, draw, shortlist row) and of no launch shape.
 #include <cmath>
+#include <type_traits>
 
 #include "xc_common.h"
 
@@ -28,7 +29,8 @@ __device__ __forceinline__ uint64_t fmix64(uint64_t x) {
 // the 28 steps of 128 ids, and one wave, the same in every workgroup, did all of it on its SIMD.)  The number of draws and the
 // size of the complement are the same for every row without repeats, so their log comes from the host; a row with some
 // forms its own.  Bound: the vector ALU, whose 64-bit products the mixer needs, and the launch.  2048 rows of 100 + 1024
-// ids: 17.4 -> 11.3 us per call, of which the caller takes 8.6.
+// ids: 17.4 -> 11.5 us per call, of which the caller takes 8.6.  Rows with repeats number the distinct ids by the bits of their
+// counts (counted a second time, id by id: 32 768 rows of 216 with repeats + 1 draw 302 us, now 174).
 constexpr int kRankRow = 256;
 constexpr int kDraws = 4;                // draws a thread makes side by side
 
@@ -40,11 +42,14 @@ void sample_kernel(const int32_t* __restrict__ shortlist, int k_h, int k_r, int6
     __shared__ int32_t adj[XC_MAX_K_SAMPLE];
     __shared__ int n_unique;
     __shared__ int wave_cnt[kSampleThreads / kWave];
+    __shared__ uint32_t head_bits[kRankRow / 32];
     const int64_t i = blockIdx.x;
     const int n = k_h + k_r;
     int32_t* out = neg + i * n;
     float* lq = logq + i * n;
     int u = 0, n_draw = n, first = 0;
+    // (here, so that it is formed while the row is on its way)
+    uint64_t state = fmix64(seed ^ (kQueryMul * static_cast<uint64_t>(i + 1))) + kDrawMul * static_cast<uint64_t>(threadIdx.x + 1);
 
     if (shortlist != nullptr) {
         const int32_t* row = shortlist + i * k_h;
@@ -57,7 +62,7 @@ void sample_kernel(const int32_t* __restrict__ shortlist, int k_h, int k_r, int6
                 if (id >= 0 && id < L) v = id;
             }
             hs[m] = v;
-            adj[m] = 0;
+            if (n2 <= kRankRow) adj[m] = 0;
         }
         if (threadIdx.x == 0) n_unique = 0;
         __syncthreads();
@@ -91,10 +96,15 @@ void sample_kernel(const int32_t* __restrict__ shortlist, int k_h, int k_r, int6
 #pragma unroll
             for (int w = 0; w < kSampleThreads / kWave; ++w) u += wave_cnt[w];
             if (u < k_h) {                                   // uniform: repeats or padding, count the distinct ones only
-                if (threadIdx.x < n2 && !head) hs[m] = 0x7fffffff;
+                if (threadIdx.x < kRankRow / 32) head_bits[threadIdx.x] = 0;
                 __syncthreads();
-                rank = 0;
-                for (int e = 0; e < n2; ++e) rank += hs[e] < v ? 1 : 0;
+                if (head) atomicOr(&head_bits[rank >> 5], 1u << (rank & 31));
+                __syncthreads();
+                if (head) {                                  // (waves without one pass by)
+                    int below = __popc(head_bits[rank >> 5] & ((1u << (rank & 31)) - 1u));
+                    for (int w = 0; w < (rank >> 5); ++w) below += __popc(head_bits[w]);
+                    rank = below;
+                }
             }
             if (head) adj[rank] = v - rank;
         } else {
@@ -140,25 +150,26 @@ void sample_kernel(const int32_t* __restrict__ shortlist, int k_h, int k_r, int6
         first = k_h;
     }
 
-    const uint64_t M = static_cast<uint64_t>(L) - static_cast<uint64_t>(u);
-    const uint64_t qstate = fmix64(seed ^ (kQueryMul * static_cast<uint64_t>(i + 1)));
-    // log of the expected number of copies of a label among the draws
-    const float lq_rand = u == (shortlist != nullptr ? k_h : 0)
-                              ? lq_distinct
-                              : static_cast<float>(log(static_cast<double>(n_draw) / static_cast<double>(M)));
     // the list ends in entries no draw reaches, so the search below needs no bounds
     if (shortlist != nullptr) {
         for (int m = u + static_cast<int>(threadIdx.x); m < n2; m += kSampleThreads) adj[m] = 0x7fffffff;
         __syncthreads();
     }
+    if (static_cast<int>(threadIdx.x & ~(kWave - 1u)) >= n_draw) return;     // a wave without draws (no barrier below)
+    const uint64_t M = static_cast<uint64_t>(L) - static_cast<uint64_t>(u);
+    // log of the expected number of copies of a label among the draws
+    const float lq_rand = u == (shortlist != nullptr ? k_h : 0)
+                              ? lq_distinct
+                              : static_cast<float>(log(static_cast<double>(n_draw) / static_cast<double>(M)));
     const uint32_t M32 = static_cast<uint32_t>(M);           // (L < 2^31)
-    uint64_t state = qstate + kDrawMul * static_cast<uint64_t>(threadIdx.x + 1);
     constexpr uint64_t kStride = kDrawMul * kSampleThreads;
-    for (int j0 = threadIdx.x; j0 < n_draw; j0 += kDraws * kSampleThreads) {
-        uint32_t r[kDraws];
-        int pos[kDraws];
+    // N draws of a thread, j0 the first; the last ones of the row possibly past its end
+    auto draw = [&](auto nc, int j0) {
+        constexpr int N = decltype(nc)::value;
+        uint32_t r[N];
+        int pos[N];
 #pragma unroll
-        for (int d = 0; d < kDraws; ++d) {
+        for (int d = 0; d < N; ++d) {
             const uint64_t w = fmix64(state);
             state += kStride;
             // floor(w M / 2^64) by halves of w
@@ -170,18 +181,23 @@ void sample_kernel(const int32_t* __restrict__ shortlist, int k_h, int k_r, int6
         if (u > 0) {
             for (int s = n2 >> 1; s > 0; s >>= 1)
 #pragma unroll
-                for (int d = 0; d < kDraws; ++d) pos[d] += static_cast<uint32_t>(adj[pos[d] + s - 1]) <= r[d] ? s : 0;
+                for (int d = 0; d < N; ++d) pos[d] += static_cast<uint32_t>(adj[pos[d] + s - 1]) <= r[d] ? s : 0;
 #pragma unroll
-            for (int d = 0; d < kDraws; ++d) pos[d] += static_cast<uint32_t>(adj[pos[d]]) <= r[d] ? 1 : 0;
+            for (int d = 0; d < N; ++d) pos[d] += static_cast<uint32_t>(adj[pos[d]]) <= r[d] ? 1 : 0;
         }
 #pragma unroll
-        for (int d = 0; d < kDraws; ++d) {
+        for (int d = 0; d < N; ++d) {
             const int j = j0 + d * kSampleThreads;
             if (j < n_draw) {
                 out[first + j] = static_cast<int32_t>(r[d] + static_cast<uint32_t>(pos[d]));
                 lq[first + j] = lq_rand;
             }
         }
+    };
+    if (n_draw > (kDraws - 1) * kSampleThreads) {
+        for (int j0 = threadIdx.x; j0 < n_draw; j0 += kDraws * kSampleThreads) draw(std::integral_constant<int, kDraws>{}, j0);
+    } else {                                                 // (fewer: three of four would be made for nothing)
+        for (int j0 = threadIdx.x; (j0 & ~(kWave - 1)) < n_draw; j0 += kSampleThreads) draw(std::integral_constant<int, 1>{}, j0);
     }
 }
 

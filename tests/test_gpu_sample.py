@@ -242,3 +242,23 @@ def test_sample_orders_short_rows_by_counting(k_h):
     neg_o, logq_o = orc.sample_negatives(sl, 6, k_h, k_r, L, seed=seed)
     assert (neg.cpu().numpy() == neg_o).all()
     assert np.allclose(logq.cpu().numpy(), logq_o, rtol=2e-7, atol=1e-7)
+
+
+@pytest.mark.parametrize("k_h", [0, 40, 256, 300])
+@pytest.mark.parametrize("k_r", [1, 64, 65, 256, 768, 769, 1025])
+def test_sample_few_draws_and_many(k_h, k_r):
+    """Waves without a draw leave early, up to 768 draws are made one by one, more of them four at a time; rows of
+    distinct ids, repeats and padding next to each other."""
+    import paper_2409_20156_amd as xc
+    L, seed = 5000, 13
+    rng = np.random.default_rng(1000 * k_h + k_r)
+    sl = np.stack([rng.permutation(L)[:k_h] for _ in range(4)]).astype(np.int32) if k_h else np.zeros((4, 0), np.int32)
+    if k_h:
+        sl[1, 1::2] = sl[1, 0::2]                     # every id twice
+        sl[2, 5:] = -1                                # padding
+        sl[3] = sl[3, rng.integers(0, k_h, k_h)]      # drawn with repeats
+    neg, logq = xc.sample_negatives(torch.tensor(sl, device="cuda:0"), k_h, k_r, L, seed)
+    torch.cuda.synchronize()
+    neg_o, logq_o = orc.sample_negatives(sl, 4, k_h, k_r, L, seed=seed)
+    assert (neg.cpu().numpy() == neg_o).all()
+    assert np.allclose(logq.cpu().numpy(), logq_o, rtol=2e-7, atol=1e-7)
