@@ -140,6 +140,10 @@ struct FewPlan {
     int64_t n_groups;
     int n_split;             // workgroups per query in the second kernel
     size_t lds;              // bytes of the query block in LDS
+    // fp32 with group maxima from 16-bit products (hnb 0: not used)
+    int hnb, hn_qb, hks, hgshift;
+    int64_t hn_groups;
+    size_t hlds;
 };
 
 // Whether the search of few queries takes this shape, and how.  `scratch`: bytes for the group maxima

@@ -11,9 +11,11 @@
 //       of equal scores the smaller ids win, and each of these groups holds one.  So k groups in all hold the
 //       answer.  Their scores are formed again, with the sums in the same order (hence the same
 //       bits), what is below tau is dropped, the rest sorted.
-// Bound: HBM, one read of W.  131 072 x 768 bf16, 32 queries, k = 5: 70 us in all (first kernel 44 us, 4.5 TB/s of the 5.1
+// Bound: HBM, one read of W.  131 072 x 768 bf16, 32 queries, k = 5: 65 us in all (first kernel 51 us, 3.9 TB/s of the 5.1
 // a plain copy reaches), where the general kernel took 378; 30 M x 256 bf16, 32 queries: 3.3 ms (4.7 TB/s) against 8.5.  In
-// fp32 with many queries the matrix pipe: 1000 queries x 50 021 x 300, 364 us against 782 (the products alone take 195).
+// fp32 with more than 16 queries the matrix pipe, which is why the maxima then come from 16-bit products (few_half_kernel): 1000
+// queries x 50 021 x 300, 158 us (76 and 83 the two kernels) against 364 with fp32 products (318 and 105; these alone need 195) and 782
+// by the general kernel.
 // No thresholds to find in phases, no lists that could overflow, two launches.  The general kernel pads the
 // pool to 256 queries and sweeps the labels in four or more serial phases, of which the first have fewer work
 // items than the chip has compute units.
@@ -24,6 +26,7 @@
 namespace xc {
 
 constexpr int kFewThreads = 512;
+constexpr size_t kFewLds = 144u << 10;   // LDS for the query block at most
 constexpr int kFewWaves = kFewThreads / kWave;
 constexpr int kFewRing = 8;              // 64-byte steps in flight per wave (two rows of 16 B per lane each: 16 KiB)
 constexpr int kFewTile = 32;             // labels a wave multiplies at a time
@@ -78,10 +81,21 @@ struct FewArgs {
     uint64_t* part;              // [Zq][n_split][kPartKeys] their candidates
     int32_t* part_n;             // [Zq][n_split]
     int32_t* done;               // [Zq] how many of them are through (cleared by the first kernel)
+    float* gnorm;                // 16-bit maxima: [n_groups] largest |w| of the group
+    int32_t* redo;               // 16-bit maxima: [0] 1 if any query has to be searched again in fp32, [1 + q] 1 if q has (cleared by the first kernel)
+    int again;                   // 1: this is that search: only queries with redo[1 + q]
 };
 
 // ordered image of a score; 0 (below every number) for NaN.  -0 counts as +0, as in the result.
 __device__ __forceinline__ uint32_t score_image(float v) { return v == v ? float_to_ordered(v + 0.0f) : 0u; }
+
+// Whether one of the queries [q0, q0 + n) has to be searched again; workgroup 0 of such a launch goes on in any case (it clears the counters).
+__device__ __forceinline__ bool few_again(const FewArgs& a, int64_t q0, int n) {
+    if (a.redo[0] == 0) return false;
+    bool any = blockIdx.x == 0;
+    for (int i = 0; i < n && q0 + i < a.Zq; ++i) any = any || a.redo[1 + q0 + i] != 0;
+    return any;
+}
 
 // MFMA operands: lane (r, g) = (lane & 15, lane >> 4) loads 16 bytes of row r: chunk 4 s + g of the row in step s, for
 // labels and queries alike.
@@ -101,6 +115,7 @@ void few_max_kernel(const FewArgs a) {
     const int wg = (id % 8) + 8 * (id / (8 * a.n_qb));
     const int n_wg = gridDim.x / a.n_qb;                        // (a multiple of 8, see the launch)
     const int64_t q0 = static_cast<int64_t>(qb) * NB * 16;
+    if (a.again && !few_again(a, q0, NB * 16)) return;          // uniform
 
     for (int e = tid; e < KS * NB * 64; e += kFewThreads) {
         const int l = e & 63, blk = e >> 6;
@@ -256,6 +271,7 @@ void few_wide_kernel(const FewArgs a) {
     const int wg = (id % 8) + 8 * (id / (8 * a.n_qb));
     const int n_wg = gridDim.x / a.n_qb;                        // (a multiple of 8, see the launch)
     const int64_t q0 = static_cast<int64_t>(qb) * NB * 16;
+    if (a.again && !few_again(a, q0, NB * 16)) return;          // uniform
 
     for (int e = tid; e < KS * NB * 64; e += kFewThreads) {
         const int l = e & 63, blk = e >> 6;
@@ -373,6 +389,270 @@ void few_wide_kernel(const FewArgs a) {
     }
 }
 
+// ---- fp32 rows, group maxima from 16-bit products.  fp32 matrix instructions do a sixteenth of what the 16-bit ones do, and
+// which groups can hold an answer is known well enough from fp16 copies formed on the way to the matrix pipe: with z and
+// w rounded to 11 bits each a score is off by at most half_error() |z| |w|, a thousandth, about a thirtieth of the scores'
+// spread at 1024 elements.  The second kernel forms the scores of the k best groups in fp32 as ever, and then of every other group whose
+// maximum plus its error reaches the k-th of them: the answer is that of the fp32 search, bit for bit.
+// Powers of two keep fp16's range out of it: a query is scaled by its largest element, W by kHalfScale.  Elements of W beyond
+// 1023 become infinite, and so does their group's norm: such a group is always looked at.  Where too many groups are
+// (equal rows by the thousand, odd numbers), the query is searched again by the fp32 kernels, whose launches return at once otherwise.
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+constexpr int kHalfRing = 4;             // steps of 32 elements in flight per wave (two rows of 32 B per lane each: 16 KiB)
+constexpr float kHalfScale = 64.0f;
+constexpr int kMoreGroups = 512;         // groups beside the k best that the second kernel looks at
+constexpr float kHalfLeast = 1e-15f, kHalfMost = 1e15f;      // largest elements of a query that scaling and norm cover (or all zero)
+
+// |score - 16-bit score| <= this |z| |w| + 2^-20 sqrt(d) |z|: two roundings of 2^-11, what fp32 sums of d products lose on both sides, a
+// hundredth of that to spare; the second term is what elements of W below fp16's normal range can lose.
+__device__ __forceinline__ float half_error(int d) { return (2.0f / 2048.0f) * 1.01f + 6.0f * static_cast<float>(d) * 5.97e-8f; }
+__device__ __forceinline__ float half_error_small(int d) { return 1.0e-6f * sqrtf(static_cast<float>(d)); }
+
+__device__ __forceinline__ f16x8 to_half8(const uint4& a, const uint4& b, float scale) {
+    const float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
+                        __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
+    f16x8 h;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) h[i] = static_cast<_Float16>(f[i] * scale);
+    return h;
+}
+
+// The structure of few_max_kernel: a step is 32 elements, lane (r, g) holds elements 4 g .. 4 g + 3 and 16 + 4 g .. of row r (labels
+// and queries alike; the order of the sums does not matter here).  gshift -1: groups of 8 labels, so that the second kernel has
+// half the rows to read.
+template <int NB, bool KTAIL>
+__global__ __launch_bounds__(kFewThreads)
+void few_half_kernel(const FewArgs a) {
+    extern __shared__ __align__(16) unsigned char zlds[];       // [ks][NB] operands of 1 KiB, then a factor per query
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int KS = a.ks;
+    float* back = reinterpret_cast<float*>(zlds + static_cast<size_t>(KS) * NB * 1024);      // [NB * 16] from 16-bit scores to scores
+    const int id = blockIdx.x;
+    const int qb = (id / 8) % a.n_qb;
+    const int wg = (id % 8) + 8 * (id / (8 * a.n_qb));
+    const int n_wg = gridDim.x / a.n_qb;                        // (a multiple of 8, see the launch)
+    const int64_t q0 = static_cast<int64_t>(qb) * NB * 16;
+
+    // a unit is the tiles whose maxima one wave combines: a tile of its groups (gshift <= 0), or 2^(gshift-1) tiles of one
+    const int comb = a.gshift > 0 ? 1 << (a.gshift - 1) : 1;
+    const int64_t n_tiles = (a.L + kFewTile - 1) / kFewTile;
+    const int64_t n_units = (n_tiles + comb - 1) / comb;
+    const int64_t u_step = static_cast<int64_t>(n_wg) * kFewWaves;
+    int64_t unit = static_cast<int64_t>(wg) * kFewWaves + wave;
+
+    // ---- the load stream, begun before the queries are laid out
+    int64_t ld_unit = unit < n_units ? unit : n_units - 1;
+    int ld_t = 0;
+    int ld_off = 0;                                             // bytes into the rows
+    const unsigned char *p0, *p1;
+    auto set_rows = [&]() {
+        const int64_t l = (ld_unit * comb + ld_t) * kFewTile + r;
+        const int64_t l0 = l < a.L ? l : a.L - 1, l1 = l + 16 < a.L ? l + 16 : a.L - 1;      // rows past the end: dropped later
+        p0 = a.W + l0 * a.row_bytes;
+        p1 = a.W + l1 * a.row_bytes;
+    };
+    set_rows();
+    uint4 ra[kHalfRing][4];
+    auto load_step = [&](int j) {
+        int64_t o0 = ld_off + g * 16, o1 = o0 + 64;             // (64 bytes of a row together per instruction)
+        if (KTAIL) { o0 = o0 < a.row_bytes ? o0 : 0; o1 = o1 < a.row_bytes ? o1 : 0; }      // (zeroed where it is used)
+        ra[j][0] = *reinterpret_cast<const uint4*>(p0 + o0);
+        ra[j][1] = *reinterpret_cast<const uint4*>(p0 + o1);
+        ra[j][2] = *reinterpret_cast<const uint4*>(p1 + o0);
+        ra[j][3] = *reinterpret_cast<const uint4*>(p1 + o1);
+        ld_off += 128;
+        if (ld_off == KS * 128) {                               // uniform
+            ld_off = 0;
+            ++ld_t;
+            if (ld_t == comb || ld_unit * comb + ld_t >= n_tiles) { ld_t = 0; ld_unit += u_step; }
+            if (ld_unit < n_units) set_rows();                  // else: the last tile again, never used
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < kHalfRing; ++j) load_step(j);
+
+    // ---- the queries, 512 / (16 NB) neighbouring lanes for each: the largest element, then the scaled row
+    {
+        constexpr int TQ = kFewThreads / (NB * 16);
+        const int i = tid / TQ, sub = tid % TQ;
+        const int64_t q = q0 + i;
+        const int chunks = static_cast<int>(a.row_bytes / 16);
+        const unsigned char* zr = a.Z + (q < a.Zq ? q : a.Zq - 1) * a.row_bytes;
+        uint32_t m = 0;
+#pragma unroll 8
+        for (int c = sub; c < chunks; c += TQ) {
+            const uint4 v = *reinterpret_cast<const uint4*>(zr + c * 16);
+            const uint32_t x = v.x & 0x7fffffffu, y = v.y & 0x7fffffffu, z = v.z & 0x7fffffffu, w = v.w & 0x7fffffffu;
+            const uint32_t xy = x > y ? x : y, zw = z > w ? z : w, all = xy > zw ? xy : zw;
+            m = all > m ? all : m;
+        }
+#pragma unroll
+        for (int off = TQ / 2; off > 0; off >>= 1) { const uint32_t o = __shfl_xor(m, off, kWave); m = o > m ? o : m; }
+        const float mf = __uint_as_float(m);
+        const bool ok = m == 0 || (mf >= kHalfLeast && mf <= kHalfMost);        // (else the second kernel has it searched again)
+        const int e = m == 0 || !ok ? 0 : 14 - (static_cast<int>(m >> 23) - 127);            // largest element to [2^14, 2^15)
+        const float up = ldexpf(1.0f, e);
+        if (sub == 0) back[i] = ldexpf(1.0f / kHalfScale, -e);
+#pragma unroll 8
+        for (int c = sub; c < KS * 8; c += TQ) {                // chunk c: elements 4 c .. 4 c + 3
+            uint4 v = make_uint4(0, 0, 0, 0);
+            if (c < chunks && ok && q < a.Zq) v = *reinterpret_cast<const uint4*>(zr + c * 16);
+            typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+            f16x4 h;
+            h[0] = static_cast<_Float16>(__uint_as_float(v.x) * up); h[1] = static_cast<_Float16>(__uint_as_float(v.y) * up);
+            h[2] = static_cast<_Float16>(__uint_as_float(v.z) * up); h[3] = static_cast<_Float16>(__uint_as_float(v.w) * up);
+            *reinterpret_cast<f16x4*>(zlds + (static_cast<size_t>(c >> 3) * NB + (i >> 4)) * 1024 + ((c & 3) * 16 + (i & 15)) * 16 + ((c >> 2) & 1) * 8) = h;
+        }
+    }
+    if (id == 0) {
+        for (int64_t i = tid; i < a.Zq; i += kFewThreads) a.done[i] = 0;
+        for (int64_t i = tid; i <= a.Zq; i += kFewThreads) a.redo[i] = 0;
+    }
+    __syncthreads();
+    if (unit >= n_units) return;                                // (no barrier below)
+    float bk[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) bk[n] = back[n * 16 + r];
+
+    // this lane's chunks of the last step that lie past the row's end
+    const bool tail0 = static_cast<int64_t>(KS - 1) * 128 + g * 16 >= a.row_bytes, tail1 = static_cast<int64_t>(KS - 1) * 128 + g * 16 + 64 >= a.row_bytes;
+    f32x4 acc[2][NB];
+    const float nan = __builtin_nanf("");
+    float run[NB], sq[2] = {0.0f, 0.0f}, run_sq = 0.0f;
+    uint32_t any = 0;                                           // an element that is not zero
+    // the norms of a unit's rows are taken by one of the query blocks
+    bool norms = static_cast<int>(unit % a.n_qb) == qb;
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        run[n] = nan;
+        acc[0][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        acc[1][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    int t = 0, s = 0;
+    for (;;) {
+#pragma unroll
+        for (int j = 0; j < kHalfRing; ++j) {
+            // the queries' operands, all on their way before the rows are converted (one at a time, as the compiler orders them by
+            // itself, every pair of products waited for its own: 81 us, with this 76, at 1000 queries x 50 021 x 300)
+            const unsigned char* zb = zlds + static_cast<size_t>(s) * NB * 1024 + lane * 16;
+            f16x8 b[NB];
+#pragma unroll
+            for (int n = 0; n < NB; ++n) b[n] = *reinterpret_cast<const f16x8*>(zb + n * 1024);
+            __builtin_amdgcn_sched_barrier(0);
+            if (KTAIL && s == KS - 1) {                         // uniform
+                if (tail0) { ra[j][0] = make_uint4(0, 0, 0, 0); ra[j][2] = make_uint4(0, 0, 0, 0); }
+                if (tail1) { ra[j][1] = make_uint4(0, 0, 0, 0); ra[j][3] = make_uint4(0, 0, 0, 0); }
+            }
+            const f16x8 a0 = to_half8(ra[j][0], ra[j][1], kHalfScale), a1 = to_half8(ra[j][2], ra[j][3], kHalfScale);
+            if (norms) {                                        // uniform
+#pragma unroll
+                for (int u = 0; u < 4; ++u) any |= (ra[j][u].x | ra[j][u].y | ra[j][u].z | ra[j][u].w) << 1;
+#pragma unroll
+                for (int i = 0; i < 8; i += 2) {
+                    sq[0] = __builtin_amdgcn_fdot2(f16x2{a0[i], a0[i + 1]}, f16x2{a0[i], a0[i + 1]}, sq[0], false);
+                    sq[1] = __builtin_amdgcn_fdot2(f16x2{a1[i], a1[i + 1]}, f16x2{a1[i], a1[i + 1]}, sq[1], false);
+                }
+            }
+            load_step(j);
+#pragma unroll
+            for (int n = 0; n < NB; ++n) {
+                acc[0][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, b[n], acc[0][n], 0, 0, 0);
+                acc[1][n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, b[n], acc[1][n], 0, 0, 0);
+            }
+            if (++s == KS) {                                    // uniform: a tile is complete
+                s = 0;
+                const int64_t tile = unit * comb + t;
+                const int64_t lab = tile * kFewTile + 4 * g;    // accumulator i of block b: label lab + 16 b + i, query r
+                const bool full = (tile + 1) * kFewTile <= a.L;
+                const bool unit_done = t + 1 == comb || tile + 1 >= n_tiles;
+                if (norms) {
+                    // the largest |w|^2 of the rows of a group (rows past the end repeat the last one): zero only if every element
+                    // of the tile is, infinite where something is no number
+                    const float least = __ballot(any != 0u) != 0ull ? 1e-30f : 0.0f;
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        float v = sq[b];
+                        v += __shfl_xor(v, 16, kWave);
+                        v += __shfl_xor(v, 32, kWave);
+                        v = v == v ? fmaxf(v, least) : INFINITY;
+                        v = fmaxf(v, __shfl_xor(v, 1, kWave));
+                        v = fmaxf(v, __shfl_xor(v, 2, kWave));
+                        v = fmaxf(v, __shfl_xor(v, 4, kWave));
+                        if (a.gshift >= 0) v = fmaxf(v, __shfl_xor(v, 8, kWave));
+                        sq[b] = v;
+                    }
+                    constexpr float kBack = 1.001f / kHalfScale;        // (rounded elements are up to 2^-11 smaller)
+                    if (a.gshift <= 0) {
+                        const int per = a.gshift < 0 ? 4 : 2;   // groups of a tile: lanes 0, 8, 16, 24 of it, or 0, 16
+                        const int grp = a.gshift < 0 ? (lane >> 3) : (lane >> 4);
+                        const float v = (a.gshift < 0 ? grp >> 1 : grp) == 0 ? sq[0] : sq[1];
+                        // (of block 1 the lanes 16.. hold the values of their r as well: rows 0..7 in lanes r < 8, 8..15 in r >= 8)
+                        if (grp < per && (lane & (a.gshift < 0 ? 7 : 15)) == 0 && tile * per + grp < a.n_groups)
+                            a.gnorm[tile * per + grp] = sqrtf(v) * kBack;
+                    } else {
+                        run_sq = fmaxf(run_sq, fmaxf(sq[0], sq[1]));
+                        if (unit_done) {
+                            if (lane == 0) a.gnorm[unit] = sqrtf(run_sq) * kBack;
+                            run_sq = 0.0f;
+                        }
+                    }
+                    sq[0] = 0.0f;
+                    sq[1] = 0.0f;
+                    any = 0;
+                }
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    float m[2];
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        if (!full)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                if (lab + 16 * b + i >= a.L) acc[b][n][i] = nan;
+                        m[b] = fmaxf(fmaxf(acc[b][n][0], acc[b][n][1]), fmaxf(acc[b][n][2], acc[b][n][3])) * bk[n];
+                    }
+                    acc[0][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    acc[1][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    const int64_t q = q0 + n * 16 + r;
+                    if (a.gshift <= 0) {
+                        m[0] = fmaxf(m[0], __shfl_xor(m[0], 16, kWave));         // lanes g = 0, 1: labels 0..7 of a block, 2, 3: 8..15
+                        m[1] = fmaxf(m[1], __shfl_xor(m[1], 16, kWave));
+                        if (a.gshift < 0) {
+                            // lane g stores group g & 1 of ... : g = 0: block 0 first half, 2: second half, 1 and 3 those of block 1
+                            const int64_t grp = 4 * tile + (g >> 1) + 2 * (g & 1);
+                            if (q < a.Zq && grp < a.n_groups) a.gmax[q * a.n_groups + grp] = score_image((g & 1) == 0 ? m[0] : m[1]);
+                        } else {
+                            m[0] = fmaxf(m[0], __shfl_xor(m[0], 32, kWave));
+                            m[1] = fmaxf(m[1], __shfl_xor(m[1], 32, kWave));
+                            const int64_t grp = 2 * tile + g;
+                            if (g < 2 && q < a.Zq && grp < a.n_groups) a.gmax[q * a.n_groups + grp] = score_image(g == 0 ? m[0] : m[1]);
+                        }
+                    } else {
+                        run[n] = fmaxf(run[n], fmaxf(m[0], m[1]));
+                        if (unit_done) {
+                            run[n] = fmaxf(run[n], __shfl_xor(run[n], 16, kWave));
+                            run[n] = fmaxf(run[n], __shfl_xor(run[n], 32, kWave));
+                            if (g == 0 && q < a.Zq) a.gmax[q * a.n_groups + unit] = score_image(run[n]);
+                            run[n] = nan;
+                        }
+                    }
+                }
+                ++t;
+                if (unit_done) {
+                    t = 0;
+                    unit += u_step;
+                    if (unit >= n_units) return;
+                    norms = static_cast<int>(unit % a.n_qb) == qb;
+                }
+            }
+        }
+    }
+}
+
 // Bitonic sort of keys[0..n), n <= Finish<NT>::kKeys, by the whole workgroup (ascending; padded with sentinels).
 template <int NT>
 __device__ void block_sort(uint64_t* keys, int n) {
@@ -408,13 +688,17 @@ __device__ __forceinline__ int block_excl_scan(int v, int* sh, int* total) {
     return before + incl - v;
 }
 
-template <typename T, int NT>
+// HALF: the maxima are those of few_half_kernel, off by up to their error.
+template <typename T, int NT, bool HALF>
 __global__ __launch_bounds__(NT)
 void few_finish_kernel(const FewArgs a) {
+    static_assert(!HALF || std::is_same<T, float>::value, "");
     __shared__ uint64_t keys[Finish<NT>::kKeys];
-    __shared__ int hist[2048];
+    __shared__ __align__(16) int hist[2048];
     __shared__ int sh[Finish<NT>::kWaves];
-    __shared__ int32_t groups[XC_MAX_K_MINE];
+    __shared__ int32_t groups[HALF ? kMoreGroups : XC_MAX_K_MINE];
+    __shared__ uint64_t best[HALF ? XC_MAX_K_MINE : 1];
+    __shared__ uint4 zop[kFewLds / 256];                       // the query's chunks as operands (ks * 4 of them)
     __shared__ int n_sel, n_key, sel_bin, sel_need, sel_have;
     __shared__ uint32_t tau_sh;
     const int tid = threadIdx.x;
@@ -423,14 +707,24 @@ void few_finish_kernel(const FewArgs a) {
     const int64_t q = blockIdx.x / a.n_split;
     const int split = blockIdx.x % a.n_split;
     const uint32_t* gm = a.gmax + q * a.n_groups;
+    if (!HALF && a.again && a.redo[1 + q] == 0) return;        // uniform
     if (a.flag != nullptr && blockIdx.x == 0)
         for (int i = tid; i < a.n_flag; i += NT) a.flag[i] = 0;
 
-    // ---- the k groups: digits of 11, 11, 10 bits of the maxima, from the top, until the groups at or above the digit of the
-    // k-th are few enough to be ordered by counting (after the first digit where k is small).  The maxima are read once
-    // where the threads can hold them.
-    constexpr int kHold = 8;
+    // ---- the k groups.  Of 256 parts of the groups the k-th largest maximum is no more than the k-th largest of all, and usually
+    // close below it: the groups at or above it are ordered by counting.  Where they are too many for that (large maxima close
+    // together in the label range, equal ones), digits of 11, 11, 10 bits from the top, until those at or above the digit of
+    // the k-th are few enough.  (Digits alone: every maximum adds to one of a few counters, whose additions wait for each
+    // other.)  The maxima are read once where the threads can hold them.
+    constexpr int kHold = HALF && NT == 256 ? 32 : 8;
     const bool held = a.n_groups <= NT * kHold;                // uniform
+    for (int c0 = wave * 4; c0 * 16 < a.row_bytes; c0 += Finish<NT>::kWaves * 4) {         // a step per wave
+        const int c = c0 + (lane >> 4);
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (c * 16 < a.row_bytes) v = *reinterpret_cast<const uint4*>(a.Z + q * a.row_bytes + c * 16);
+        v = FewMma<T>::operand(v);
+        if ((lane & 15) == 0) zop[c] = v;
+    }
     uint32_t hv[kHold];
     if (held) {
 #pragma unroll
@@ -446,11 +740,71 @@ void few_finish_kernel(const FewArgs a) {
         }
     };
     if (tid == 0) { n_sel = 0; n_key = 0; tau_sh = 0xffffffffu; }
+    // the query's norm, and what a group's norm is multiplied with to give the error of its maximum
+    float zn = 0.0f;
+    auto redo = [&]() {                                        // (every thread that gets here writes the same)
+        a.redo[0] = 1;
+        a.redo[1 + q] = 1;
+    };
+    if constexpr (HALF) {
+        float s2 = 0.0f, zmax = 0.0f;
+        for (int64_t i = lane; i * 4 < a.row_bytes; i += kWave) {
+            const float v = *reinterpret_cast<const float*>(a.Z + q * a.row_bytes + i * 4);
+            s2 = fmaf(v, v, s2);
+            zmax = fabsf(v) <= kHalfMost ? fmaxf(zmax, fabsf(v)) : INFINITY;       // (also where it is no number; stays, see below)
+            if (!(fabsf(v) <= kHalfMost)) s2 = INFINITY;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) { s2 += __shfl_xor(s2, off, kWave); zmax = fmaxf(zmax, __shfl_xor(zmax, off, kWave)); }
+        if (!(s2 < INFINITY) || (zmax != 0.0f && zmax < kHalfLeast)) { redo(); return; }      // uniform over the workgroup: every wave sees the whole row
+        zn = sqrtf(s2) * 1.001f;
+    }
+    const float he = HALF ? half_error(static_cast<int>(a.row_bytes / 4)) : 0.0f, hs = HALF ? half_error_small(static_cast<int>(a.row_bytes / 4)) : 0.0f;
+    auto group_error = [&](int64_t i) {
+        const float w = a.gnorm[i];
+        return w == 0.0f ? 0.0f : zn * (w * he + hs);
+    };
     uint32_t prefix = 0;           // the digits found so far
     int bits = 32;                 // bits below them
     int need = a.k;                // groups still to take among those that share the prefix
     uint32_t bound = 0;            // the groups at or above it are ordered by counting; 0: too many with the same maximum
-    for (int pass = 0; pass < 3; ++pass) {
+    {
+        constexpr int kShare = NT / 256;                        // threads of a part
+        uint32_t* part_max = reinterpret_cast<uint32_t*>(hist);             // [256]
+        uint32_t mine = 0;
+        for_groups([&](uint32_t o, int32_t) { mine = o > mine ? o : mine; });
+#pragma unroll
+        for (int off = kShare / 2; off > 0; off >>= 1) { const uint32_t o = __shfl_xor(mine, off, kWave); mine = o > mine ? o : mine; }
+        if (tid % kShare == 0) part_max[tid / kShare] = mine;
+        __syncthreads();
+        if (wave == 0) {
+            const uint4 v = *reinterpret_cast<const uint4*>(part_max + lane * 4);
+            uint32_t t0 = 0;                                    // the k-th largest of them, bit by bit
+            for (int b = 31; b >= 0; --b) {
+                const uint32_t c = t0 | (1u << b);
+                const int have = __popcll(__ballot(v.x >= c)) + __popcll(__ballot(v.y >= c)) + __popcll(__ballot(v.z >= c)) + __popcll(__ballot(v.w >= c));
+                if (have >= a.k) t0 = c;
+            }
+            if (lane == 0) sel_bin = static_cast<int>(t0);      // (0: fewer parts with a score than k)
+        }
+        __syncthreads();
+        const uint32_t t0 = static_cast<uint32_t>(sel_bin);
+        if (t0 != 0) {
+            for_groups([&](uint32_t o, int32_t i) {
+                if (o >= t0) {
+                    const int at = atomicAdd(&n_key, 1);
+                    if (at < kRankSort) keys[at] = (static_cast<uint64_t>(~o) << 32) | static_cast<uint32_t>(i);
+                }
+            });
+            __syncthreads();
+            if (n_key <= kRankSort) bound = t0;
+            __syncthreads();
+            if (bound == 0 && tid == 0) n_key = 0;
+        }
+        __syncthreads();
+    }
+    const bool listed = bound != 0;
+    for (int pass = 0; pass < 3 && bound == 0; ++pass) {
         const int width = pass < 2 ? 11 : 10;
         for (int d = tid; d < 2048; d += NT) hist[d] = 0;
         __syncthreads();
@@ -480,7 +834,7 @@ void few_finish_kernel(const FewArgs a) {
     // (bound 0: the prefix is a whole score.  Taken are the groups above it and the first `need` in label order of those
     // that share it; adding 1 cannot wrap: the largest image is that of a NaN)
     const uint32_t least = bound != 0 ? bound : prefix + 1u;
-    for_groups([&](uint32_t o, int32_t i) {
+    if (!listed) for_groups([&](uint32_t o, int32_t i) {
         if (o >= least) keys[atomicAdd(&n_key, 1)] = (static_cast<uint64_t>(~o) << 32) | static_cast<uint32_t>(i);
     });
     __syncthreads();
@@ -488,6 +842,7 @@ void few_finish_kernel(const FewArgs a) {
     for (int m = tid; m < n_cand; m += NT) {                   // larger maxima first, of equal ones the smaller labels
         const uint64_t mine = keys[m];
         int rank = 0;
+#pragma unroll 8
         for (int e = 0; e < n_cand; ++e) rank += keys[e] < mine ? 1 : 0;
         if (rank < a.k) groups[rank] = static_cast<int32_t>(mine & 0xffffffffu);
         if (rank == a.k - 1) tau_sh = ~static_cast<uint32_t>(mine >> 32);
@@ -511,47 +866,96 @@ void few_finish_kernel(const FewArgs a) {
     __syncthreads();
     if (tid == 0) n_key = 0;
     __syncthreads();
-    const int n_blocks = n_sel << a.gshift;                    // blocks of 16 labels
+    const int gsh = 4 + a.gshift;                              // labels of a group: 1 << gsh
+    int n_rows = n_sel << gsh;
+    int n_blocks = (n_rows + 15) >> 4;                         // blocks of 16 labels
+    // the first one that is not among the k best groups, as the key of its maximum and place; and the least score that can matter
+    uint64_t group_key = 0xffffffffull << 32;                  // (fewer groups with a score: all that have one are)
+    if constexpr (HALF) {
+        if (n_sel == a.k) group_key = ((static_cast<uint64_t>(~tau) << 32) | static_cast<uint32_t>(groups[a.k - 1])) + 1;
+        __syncthreads();
+        if (tid == 0) tau_sh = n_sel == a.k ? 0xffffffffu : kTauInit;
+        __syncthreads();
+        for (int m = tid; m < n_sel; m += NT) {
+            const float lo = ordered_to_float(gm[groups[m]]) - group_error(groups[m]);
+            atomicMin(&tau_sh, lo == lo ? float_to_ordered(lo) : kTauInit);
+        }
+        __syncthreads();
+    }
+    const uint32_t least_score = HALF ? tau_sh : tau;
 
     // ---- the scores of these groups again: one query in all 16 columns of the product
     const int r = lane & 15, g = lane >> 4;
+    auto row_label = [&](int j) { return (static_cast<int64_t>(groups[j >> gsh]) << gsh) + (j & ((1 << gsh) - 1)); };
+    // block b: rows 16 b .. 16 b + 15 of the groups; a lane with r < 4 gets the score and label of row 4 g + r.  A wave takes kSide
+    // blocks side by side, kAhead steps of each under way: it waits for memory, not for the products.
+    constexpr int kSide = NT == 256 ? 2 : 1, kAhead = NT == 256 ? 4 : 16;
+    const int row_bytes = static_cast<int>(a.row_bytes), steps_whole = row_bytes / 64;
+    auto score_blocks = [&](int b, int b_step, int64_t (&lab)[kSide], float (&score)[kSide]) {
+        const unsigned char* wrow[kSide];
+        f32x4 acc[kSide];
+#pragma unroll
+        for (int u = 0; u < kSide; ++u) {
+            const int j0 = 16 * (b + u * b_step) + r, j = j0 < n_rows ? j0 : n_rows - 1;
+            const int64_t l = row_label(j);
+            wrow[u] = a.W + (l < a.L ? l : a.L - 1) * row_bytes;
+            acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        auto product = [&](int u, int s, const uint4& w) {
+            const uint4 wo = FewMma<T>::operand(w), zo = zop[4 * s + g];
+#pragma unroll
+            for (int m = 0; m < FewMma<T>::kSteps; ++m) acc[u] = FewMma<T>::mma(m, wo, zo, acc[u]);
+        };
+        int s = 0;
+        for (; s + kAhead <= steps_whole; s += kAhead) {
+            uint4 w[kAhead][kSide];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+                for (int u = 0; u < kSide; ++u) w[i][u] = *reinterpret_cast<const uint4*>(wrow[u] + (s + i) * 64 + g * 16);
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+                for (int u = 0; u < kSide; ++u) product(u, s + i, w[i][u]);
+        }
+        if (s * 64 < row_bytes) {                               // the last steps, of which one may be a part
+            uint4 w[kAhead][kSide];
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+                for (int u = 0; u < kSide; ++u) {
+                    w[i][u] = make_uint4(0, 0, 0, 0);
+                    if ((s + i) * 64 + g * 16 < row_bytes) w[i][u] = *reinterpret_cast<const uint4*>(wrow[u] + (s + i) * 64 + g * 16);
+                }
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i)
+                if ((s + i) * 64 < row_bytes)                   // uniform
+#pragma unroll
+                    for (int u = 0; u < kSide; ++u) product(u, s + i, w[i][u]);
+        }
+#pragma unroll
+        for (int u = 0; u < kSide; ++u) {
+            const int jr = 16 * (b + u * b_step) + 4 * g + r;
+            lab[u] = r < 4 && jr < n_rows ? row_label(jr) : a.L;
+            score[u] = (r & 2) ? ((r & 1) ? acc[u][3] : acc[u][2]) : ((r & 1) ? acc[u][1] : acc[u][0]);
+        }
+    };
     const bool may_overflow = (n_blocks / a.n_split + 1) * 16 > Finish<NT>::kKeys;
-    const unsigned char* zrow = a.Z + q * a.row_bytes;
     const int n_mine = (n_blocks - split + a.n_split - 1) / a.n_split;          // blocks split, split + n_split, ...
-    for (int b0 = 0; b0 < n_mine; b0 += Finish<NT>::kWaves) {
+    for (int b0 = 0; b0 < n_mine; b0 += Finish<NT>::kWaves * kSide) {
         const int b = split + (b0 + wave) * a.n_split;
         if (b < n_blocks) {
-            const int64_t l0 = ((static_cast<int64_t>(groups[b >> a.gshift]) << a.gshift) + (b & ((1 << a.gshift) - 1))) * 16;
-            const int64_t lr = l0 + r < a.L ? l0 + r : a.L - 1;
-            const unsigned char* wrow = a.W + lr * a.row_bytes;
-            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-            const int full = static_cast<int>(a.row_bytes / 64);
-#pragma unroll 8
-            for (int s = 0; s < full; ++s) {
-                const uint4 w = *reinterpret_cast<const uint4*>(wrow + s * 64 + g * 16);
-                const uint4 z = *reinterpret_cast<const uint4*>(zrow + s * 64 + g * 16);
-                const uint4 wo = FewMma<T>::operand(w), zo = FewMma<T>::operand(z);
+            int64_t lab[kSide];
+            float v[kSide];
+            score_blocks(b, Finish<NT>::kWaves * a.n_split, lab, v);
 #pragma unroll
-                for (int m = 0; m < FewMma<T>::kSteps; ++m) acc = FewMma<T>::mma(m, wo, zo, acc);
-            }
-            if (full < a.ks) {
-                uint4 w = make_uint4(0, 0, 0, 0), z = make_uint4(0, 0, 0, 0);
-                if (full * 64 + g * 16 < a.row_bytes) {
-                    w = *reinterpret_cast<const uint4*>(wrow + full * 64 + g * 16);
-                    z = *reinterpret_cast<const uint4*>(zrow + full * 64 + g * 16);
-                }
-                const uint4 wo = FewMma<T>::operand(w), zo = FewMma<T>::operand(z);
-#pragma unroll
-                for (int m = 0; m < FewMma<T>::kSteps; ++m) acc = FewMma<T>::mma(m, wo, zo, acc);
-            }
-            const float v = (r & 2) ? ((r & 1) ? acc[3] : acc[2]) : ((r & 1) ? acc[1] : acc[0]);
-            const int64_t lab = l0 + 4 * g + r;
-            if (r < 4 && lab < a.L && score_image(v) >= tau)
-                keys[atomicAdd(&n_key, 1)] = make_key(v + 0.0f, static_cast<int32_t>(lab));
+            for (int u = 0; u < kSide; ++u)
+                if (lab[u] < a.L && score_image(v[u]) >= least_score)
+                    keys[atomicAdd(&n_key, 1)] = make_key(v[u] + 0.0f, static_cast<int32_t>(lab[u]));
         }
         if (may_overflow) {                                    // uniform
             __syncthreads();
-            if (n_key > Finish<NT>::kKeys - Finish<NT>::kWaves * 16) {     // the next round might not fit: keep the best k
+            if (n_key > Finish<NT>::kKeys - Finish<NT>::kWaves * kSide * 16) {     // the next round might not fit: keep the best k
                 const int n = n_key;
                 block_sort<NT>(keys, n);
                 if (tid == 0) n_key = n < a.k ? n : a.k;
@@ -585,6 +989,61 @@ void few_finish_kernel(const FewArgs a) {
         }
         __syncthreads();
     }
+    if constexpr (HALF) {
+        // ---- the other groups whose maximum, with its error, reaches the k-th best so far (of equal scores the smaller label)
+        if (n < a.k) { redo(); return; }                       // uniform (scores that are no numbers)
+        if (n <= kRankSort) {
+            for (int m = tid; m < n; m += NT) {
+                const uint64_t mine = keys[m];
+                int rank = 0;
+#pragma unroll 8
+                for (int e = 0; e < n; ++e) rank += keys[e] < mine ? 1 : 0;
+                if (rank < a.k) best[rank] = mine;
+            }
+        } else {
+            block_sort<NT>(keys, n);
+            if (tid < a.k) best[tid] = keys[tid];
+        }
+        if (tid == 0) { n_sel = 0; n_key = 0; }
+        __syncthreads();
+        const uint64_t kth = best[a.k - 1];
+        const float kth_score = key_score(kth);
+        // (a maximum that is no number: some score may be one)
+        for_groups([&](uint32_t o, int32_t i) {
+            if (i >= a.n_groups) return;
+            float most = ordered_to_float(o) + group_error(i);
+            if (o != 0 && most < kth_score) return;             // nearly all of them
+            if (((static_cast<uint64_t>(~o) << 32) | static_cast<uint32_t>(i)) < group_key) return;
+            most = o == 0 ? INFINITY : most;
+            if (most == most && make_key(most + 0.0f, static_cast<int32_t>(static_cast<int64_t>(i) << gsh)) >= kth) return;
+            const int at = atomicAdd(&n_sel, 1);
+            if (at < kMoreGroups) groups[at] = i;
+        });
+        __syncthreads();
+        if (n_sel > kMoreGroups) { redo(); return; }           // uniform
+        n_rows = n_sel << gsh;
+        n_blocks = (n_rows + 15) >> 4;
+        for (int b = wave; b < n_blocks; b += Finish<NT>::kWaves * kSide) {
+            int64_t lab[kSide];
+            float v[kSide];
+            score_blocks(b, Finish<NT>::kWaves, lab, v);
+#pragma unroll
+            for (int u = 0; u < kSide; ++u) {
+                const uint64_t key = make_key(v[u] + 0.0f, static_cast<int32_t>(lab[u]));
+                if (lab[u] < a.L && v[u] == v[u] && key < kth) {
+                    const int at = atomicAdd(&n_key, 1);
+                    if (at < Finish<NT>::kKeys - XC_MAX_K_MINE) keys[at] = key;
+                }
+            }
+        }
+        __syncthreads();
+        n = n_key;
+        if (n > Finish<NT>::kKeys - XC_MAX_K_MINE) { redo(); return; }        // uniform
+        __syncthreads();
+        if (tid < a.k) keys[n + tid] = best[tid];
+        n += a.k;
+        __syncthreads();
+    }
     int32_t* ids = a.shortlist + q * a.k;
     float* sc = a.scores != nullptr ? a.scores + q * a.k : nullptr;
     auto put = [&](int rank, uint64_t key) {
@@ -596,6 +1055,7 @@ void few_finish_kernel(const FewArgs a) {
         for (int m = tid; m < n; m += NT) {
             const uint64_t mine = keys[m];
             int rank = 0;
+#pragma unroll 8
             for (int e = 0; e < n; ++e) rank += keys[e] < mine ? 1 : 0;
             if (rank < a.k) put(rank, mine);
         }
@@ -612,16 +1072,16 @@ void few_finish_kernel(const FewArgs a) {
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-constexpr size_t kFewLds = 144u << 10;       // LDS for the query block at most
+constexpr int64_t kHalfFrom = 16;            // fp32: more queries than this take 16-bit maxima
 constexpr int64_t kFewAlways = 96;           // up to so many queries always
 constexpr int64_t kFewQueries = 256;         // up to so many without limits on the work (one query tile of the other kernels)
 constexpr int64_t kFewMaxQueries = 2048;     // beyond that never
 
 // Workgroups of the first kernel: as many label ranges per block of queries as fit the chip (two workgroups per compute unit
 // where two query blocks fit its LDS), in multiples of the 8 XCDs and at least 8.
-static int64_t few_slots(const FewPlan& p) { return p.lds <= (76u << 10) ? 512 : 256; }
-static int64_t few_ranges(const FewPlan& p) {
-    const int64_t n = few_slots(p) / p.n_qb / 8 * 8;
+static int64_t few_slots(size_t lds) { return lds <= (76u << 10) ? 512 : 256; }
+static int64_t few_ranges(size_t lds, int n_qb) {
+    const int64_t n = few_slots(lds) / n_qb / 8 * 8;
     return n < 8 ? 8 : n;
 }
 
@@ -633,7 +1093,7 @@ static int64_t few_ranges(const FewPlan& p) {
 // under way).  The others: products, W, what passes (more per query tile, and
 // much more where k > 64), the phases' start-up; rows that are no multiple of a stage load slowly.
 static double few_us(const FewPlan& p, int64_t Zq, int64_t L, int64_t row_bytes, int k, bool f32) {
-    const double slots = static_cast<double>(few_slots(p)), wgs = static_cast<double>(few_ranges(p) * p.n_qb);
+    const double slots = static_cast<double>(few_slots(p.lds)), wgs = static_cast<double>(few_ranges(p.lds, p.n_qb) * p.n_qb);
     const double padded = static_cast<double>(p.n_qb) * p.nb * 16;
     const double gflop = 2e-9 * padded * L * (row_bytes / (f32 ? 4 : 2)) * slots * ceil(wgs / slots) / wgs;
     const double per = f32 ? (p.nb == 1 ? 13.9 : p.nb == 2 ? 8.4 : 8.2) : (p.nb == 1 ? 7.3 : p.nb == 2 ? 3.8 : 2.2);
@@ -692,7 +1152,20 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
     while (ns < kMaxSplit && Zq * ns * 2 <= 256 && (static_cast<int64_t>(k) << gs) > ns * Finish<1024>::kWaves) ns <<= 1;
     p->n_split = ns;
     const size_t q = static_cast<size_t>(Zq);
-    return round_up(q * p->n_groups * 4, 256) + q * ns * kPartKeys * 8 + round_up(q * ns * 4, 256) + q * 4 <= scratch;
+    auto bytes = [&](int64_t groups) { return round_up(q * groups * 4, 256) + q * ns * kPartKeys * 8 + 2 * round_up(q * ns * 4, 256) + round_up(groups * 4, 256) + q * 8 + 4; };
+    if (bytes(p->n_groups) > scratch) return false;
+    p->hnb = 0;
+    if (f32 && Zq > kHalfFrom) {
+        p->hks = static_cast<int>((row_bytes + 127) / 128);
+        int hnb = 2;
+        while (hnb < 8 && hnb * 16 < Zq && static_cast<size_t>(2 * hnb * p->hks) * 1024 + 2 * hnb * 64 <= kFewLds) hnb <<= 1;
+        p->hlds = static_cast<size_t>(hnb) * p->hks * 1024 + hnb * 64;
+        p->hn_qb = static_cast<int>((Zq + hnb * 16 - 1) / (hnb * 16));
+        p->hgshift = gs == 0 ? -1 : gs;
+        p->hn_groups = gs == 0 ? (L + 7) / 8 : p->n_groups;
+        if (p->hlds <= kFewLds && bytes(p->hn_groups) <= scratch) p->hnb = hnb;
+    }
+    return true;
 }
 
 typedef void (*FewFn)(const FewArgs);
@@ -709,7 +1182,17 @@ template <> FewFn few_kernel<float>(int nb, bool ktail) {
                    : (ktail ? &few_wide_kernel<4, true> : &few_wide_kernel<4, false>);
 }
 
+static FewFn half_kernel(int nb, bool ktail) {
+    return nb == 2 ? (ktail ? &few_half_kernel<2, true> : &few_half_kernel<2, false>)
+         : nb == 4 ? (ktail ? &few_half_kernel<4, true> : &few_half_kernel<4, false>)
+                   : (ktail ? &few_half_kernel<8, true> : &few_half_kernel<8, false>);
+}
+
 int few_raise_lds() {
+    for (int nb = 2; nb <= 8; nb <<= 1)
+        for (int tail = 0; tail < 2; ++tail)
+            XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(half_kernel(nb, tail != 0)),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(kFewLds)));
     for (int nb = 1; nb <= 4; nb <<= 1)
         for (int tail = 0; tail < 2; ++tail)
             for (int f32 = 0; f32 < 2; ++f32) {
@@ -720,22 +1203,49 @@ int few_raise_lds() {
     return XC_OK;
 }
 
+// Workgroups of a first kernel: no more label ranges than there are tiles.
+static dim3 few_grid(size_t lds, int n_qb, int64_t L) {
+    const int64_t tiles = (L + kFewTile - 1) / kFewTile;
+    const int64_t enough = ((tiles + kFewWaves - 1) / kFewWaves + 7) / 8 * 8;
+    const int64_t most = few_ranges(lds, n_qb);
+    return dim3(static_cast<unsigned>((most < enough ? most : enough) * n_qb));
+}
+
+template <typename T, bool HALF>
+static void launch_finish(const FewArgs& a, hipStream_t st) {
+    const unsigned n = static_cast<unsigned>(a.Zq * a.n_split);
+    if (a.Zq >= kSmallFinishQueries) few_finish_kernel<T, 256, HALF><<<n, 256, 0, st>>>(a);
+    else few_finish_kernel<T, 1024, HALF><<<n, 1024, 0, st>>>(a);
+}
+
 template <typename T>
 static int launch_few(const FewPlan& p, const FewArgs& a, hipStream_t st) {
-    const bool ktail = a.row_bytes % 64 != 0;
-    // no more label ranges than there are tiles
-    const int64_t tiles = (a.L + kFewTile - 1) / kFewTile;
-    const int64_t enough = ((tiles + kFewWaves - 1) / kFewWaves + 7) / 8 * 8;
-    const int64_t most = few_ranges(p);
-    const int64_t per_qb = most < enough ? most : enough;
-    const dim3 grid(static_cast<unsigned>(per_qb * p.n_qb));
-    const FewFn fn = few_kernel<T>(p.nb, ktail);
+    const FewFn fn = few_kernel<T>(p.nb, a.row_bytes % 64 != 0);
+    const dim3 grid = few_grid(p.lds, p.n_qb, a.L);
     XC_LAUNCH(K_MINE_TILE, st, (fn<<<grid, kFewThreads, p.lds, st>>>(a)));
     XC_HIP_CHECK(hipGetLastError());
-    if (a.Zq >= kSmallFinishQueries)
-        XC_LAUNCH(K_MINE_SELECT, st, (few_finish_kernel<T, 256><<<static_cast<unsigned>(a.Zq * a.n_split), 256, 0, st>>>(a)));
-    else
-        XC_LAUNCH(K_MINE_SELECT, st, (few_finish_kernel<T, 1024><<<static_cast<unsigned>(a.Zq * a.n_split), 1024, 0, st>>>(a)));
+    XC_LAUNCH(K_MINE_SELECT, st, (launch_finish<T, false>(a, st)));
+    XC_HIP_CHECK(hipGetLastError());
+    return XC_OK;
+}
+
+// 16-bit maxima; then the fp32 kernels for the queries that these did not settle (without any, they return at once).
+static int launch_half(const FewPlan& p, const FewArgs& exact, hipStream_t st) {
+    FewArgs a = exact;
+    a.ks = p.hks; a.n_qb = p.hn_qb; a.gshift = p.hgshift; a.n_groups = p.hn_groups;
+    const FewFn fn = half_kernel(p.hnb, a.row_bytes % 128 != 0);
+    const dim3 grid = few_grid(p.hlds, p.hn_qb, a.L);
+    XC_LAUNCH(K_MINE_TILE, st, (fn<<<grid, kFewThreads, p.hlds, st>>>(a)));
+    XC_HIP_CHECK(hipGetLastError());
+    XC_LAUNCH(K_MINE_SELECT, st, (launch_finish<float, true>(a, st)));
+    XC_HIP_CHECK(hipGetLastError());
+    a = exact;
+    a.again = 1;
+    a.flag = nullptr;
+    const FewFn again = few_kernel<float>(p.nb, a.row_bytes % 64 != 0);
+    again<<<few_grid(p.lds, p.n_qb, a.L), kFewThreads, p.lds, st>>>(a);
+    XC_HIP_CHECK(hipGetLastError());
+    launch_finish<float, false>(a, st);
     XC_HIP_CHECK(hipGetLastError());
     return XC_OK;
 }
@@ -752,12 +1262,17 @@ int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int
     a.tau_g = tau_g; a.flag = flag; a.n_flag = n_flag;
     a.shortlist = shortlist; a.scores = scores;
     a.n_split = p.n_split;
+    a.again = 0;
+    const int64_t most_groups = p.hnb > 0 && p.hn_groups > p.n_groups ? p.hn_groups : p.n_groups;
     unsigned char* s = scratch;
-    a.gmax = reinterpret_cast<uint32_t*>(s); s += round_up(static_cast<size_t>(Zq) * p.n_groups * 4, 256);
+    a.gmax = reinterpret_cast<uint32_t*>(s); s += round_up(static_cast<size_t>(Zq) * most_groups * 4, 256);
     a.part = reinterpret_cast<uint64_t*>(s); s += static_cast<size_t>(Zq) * p.n_split * kPartKeys * 8;
     a.part_n = reinterpret_cast<int32_t*>(s); s += round_up(static_cast<size_t>(Zq) * p.n_split * 4, 256);
-    a.done = reinterpret_cast<int32_t*>(s);
-    return t == XC_BF16 ? launch_few<bf16_t>(p, a, st) : launch_few<float>(p, a, st);
+    a.gnorm = reinterpret_cast<float*>(s); s += round_up(static_cast<size_t>(most_groups) * 4, 256);
+    a.done = reinterpret_cast<int32_t*>(s); s += static_cast<size_t>(Zq) * 4;
+    a.redo = reinterpret_cast<int32_t*>(s);
+    if (t == XC_BF16) return launch_few<bf16_t>(p, a, st);
+    return p.hnb > 0 ? launch_half(p, a, st) : launch_few<float>(p, a, st);
 }
 
 }  // namespace xc
