@@ -11,7 +11,7 @@
 //       of equal scores the smaller ids win, and each of these groups holds one.  So k groups in all hold the
 //       answer.  Their scores are formed again, with the sums in the same order (hence the same
 //       bits), what is below tau is dropped, the rest sorted.
-// Bound: HBM, one read of W.  131 072 x 768 bf16, 32 queries, k = 5: 65 us in all (first kernel 51 us, 3.9 TB/s of the 5.1
+// Bound: HBM, one read of W.  131 072 x 768 bf16, 32 queries, k = 5: 63 us in all (first kernel 50 us, 4.0 TB/s of the 5.1
 // a plain copy reaches), where the general kernel took 378; 30 M x 256 bf16, 32 queries: 3.3 ms (4.7 TB/s) against 8.5.  In
 // fp32 with more than 16 queries the matrix pipe, which is why the maxima then come from 16-bit products (few_half_kernel): 1000
 // queries x 50 021 x 300, 158 us (76 and 83 the two kernels) against 364 with fp32 products (318 and 105; these alone need 195) and 782
@@ -117,29 +117,16 @@ void few_max_kernel(const FewArgs a) {
     const int64_t q0 = static_cast<int64_t>(qb) * NB * 16;
     if (a.again && !few_again(a, q0, NB * 16)) return;          // uniform
 
-    for (int e = tid; e < KS * NB * 64; e += kFewThreads) {
-        const int l = e & 63, blk = e >> 6;
-        const int s = blk / NB, n = blk % NB;
-        const int64_t q = q0 + n * 16 + (l & 15);
-        const int64_t off = static_cast<int64_t>(s) * 64 + (l >> 4) * 16;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (q < a.Zq && off < a.row_bytes) v = *reinterpret_cast<const uint4*>(a.Z + q * a.row_bytes + off);
-        *reinterpret_cast<uint4*>(zlds + static_cast<size_t>(e) * 16) = FewMma<T>::operand(v);      // (a wave takes whole blocks)
-    }
-    if (id == 0)
-        for (int64_t i = tid; i < a.Zq; i += kFewThreads) a.done[i] = 0;
-    __syncthreads();
-
     // a unit is the tiles whose maxima one wave combines: a tile of two groups (gshift 0), or 2^(gshift-1) tiles of one
     const int comb = a.gshift > 0 ? 1 << (a.gshift - 1) : 1;
     const int64_t n_tiles = (a.L + kFewTile - 1) / kFewTile;
     const int64_t n_units = (n_tiles + comb - 1) / comb;
     const int64_t u_step = static_cast<int64_t>(n_wg) * kFewWaves;
     int64_t unit = static_cast<int64_t>(wg) * kFewWaves + wave;
-    if (unit >= n_units) return;                                // (no barrier below)
 
-    // ---- the load stream: ring of kFewRing steps, running ahead across tiles and units
-    int64_t ld_unit = unit;
+    // ---- the load stream: ring of kFewRing steps, running ahead across tiles and units; begun before the queries are laid out (a
+    // call with few labels has one tile per wave, and would wait for memory twice: 32 x 131 072 x 768 65.2 -> 62.5 us in all)
+    int64_t ld_unit = unit < n_units ? unit : n_units - 1;
     int ld_t = 0;
     int ld_off = 0;                                             // bytes into the rows
     const unsigned char *p0, *p1;
@@ -166,6 +153,29 @@ void few_max_kernel(const FewArgs a) {
     };
 #pragma unroll
     for (int j = 0; j < kFewRing; ++j) load_step(j);
+
+    // ---- the queries, four chunks of a thread at a time
+    for (int e0 = tid; e0 < KS * NB * 64; e0 += 4 * kFewThreads) {
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * kFewThreads, l = e & 63, blk = e >> 6;
+            const int64_t q = q0 + (blk % NB) * 16 + (l & 15);
+            const int64_t off = static_cast<int64_t>(blk / NB) * 64 + (l >> 4) * 16;
+            v[u] = make_uint4(0, 0, 0, 0);
+            if (q < a.Zq && off < a.row_bytes) v[u] = *reinterpret_cast<const uint4*>(a.Z + q * a.row_bytes + off);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * kFewThreads;
+            const uint4 o = FewMma<T>::operand(v[u]);           // (a wave takes whole blocks)
+            if (e < KS * NB * 64) *reinterpret_cast<uint4*>(zlds + static_cast<size_t>(e) * 16) = o;
+        }
+    }
+    if (id == 0)
+        for (int64_t i = tid; i < a.Zq; i += kFewThreads) a.done[i] = 0;
+    __syncthreads();
+    if (unit >= n_units) return;                                // (no barrier below)
 
     const bool tail_chunk = static_cast<int64_t>(KS - 1) * 64 + g * 16 >= a.row_bytes;       // this lane's chunk of the last step
     f32x4 acc[2][NB];
