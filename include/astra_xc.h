@@ -72,11 +72,13 @@ int xc_version(void);
  * (for A/B timing and tests): XC_MINE_GENERAL=1
  * sends every shape through the general tile kernel; XC_MINE_ROWS=narrow or
  * wide fixes the work-item width of the kernel for bf16 rows of 128..512 bytes
- * (with either set, the kernels for few queries and the 8-bit filter stay out).
+ * (with either set, the kernels for few queries, the 8-bit filter and the fp16 copies of fp32 rows stay out).
  * xc_mine_workspace includes room for the 8-bit filter where a search takes it
  * (bf16 rows of 256 or 512 bytes, at least 4096 queries and 2^20 labels: up to
- * 545 MB); a workspace without that room is accepted as before, and the search
- * then runs in bf16 throughout.
+ * 545 MB), and for fp16 copies where a search of fp32 rows sweeps the labels on these
+ * first (more than 256 queries, rows of up to 8 KB: up to 512 MiB and the queries);
+ * a workspace without that room is accepted as before, and the search
+ * then runs on the rows themselves throughout.
  * ------------------------------------------------------------------------- */
 int xc_mine_workspace(int64_t Zq, int64_t L, int d, int k_h, xc_dtype t, size_t* bytes);
 int xc_mine_negatives(const void* Z, const void* W, int64_t Zq, int64_t L, int d, int k_h,

@@ -57,12 +57,96 @@ template <> struct RowMma<float> {
         c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), c, 0, 0, 0);
     }
 };
+// fp16 copies of fp32 rows (the filter of xc_mine_half.h, which forms the scores that decide from the fp32 rows)
+struct half_t { uint16_t bits; };
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+template <> struct RowMma<half_t> {
+    static __device__ __forceinline__ void mma(const uint4& a, const uint4& b, f32x16& c) {
+        f16x8 av, bv;
+        __builtin_memcpy(&av, &a, 16);
+        __builtin_memcpy(&bv, &b, 16);
+        c = __builtin_amdgcn_mfma_f32_32x32x16_f16(av, bv, c, 0, 0, 0);
+    }
+};
 __device__ __forceinline__ f32x4 row_mma_bf16(const uint4& a /* 16 rows */, const uint4& b /* 16 columns */, f32x4 c) {
     bf16x8 av, bv;
     __builtin_memcpy(&av, &a, 16);
     __builtin_memcpy(&bv, &b, 16);
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, c, 0, 0, 0);
 }
+
+// Products in the order of the other search kernels (RowMma and the text above it).  `operand` turns a lane's 16 bytes
+// of a row (chunk g of a 64-byte step) into what the matrix instructions of the step take from that lane.
+template <typename T> struct FewMma;
+template <> struct FewMma<bf16_t> {
+    static __device__ __forceinline__ uint4 operand(const uint4& v) { return v; }
+    static constexpr int kSteps = 1;             // matrix instructions per step
+    static __device__ __forceinline__ f32x4 mma(int, const uint4& a, const uint4& b, f32x4 c) { return row_mma_bf16(a, b, c); }
+};
+template <> struct FewMma<float> {
+    // Lanes g = 0, 1, 2, 3 of a product stand for elements 2i of chunks 0 and 1, then 2i + 1 of them: elements 2i + 1 of
+    // the lower chunk pair change places with elements 2i of the upper one.  x, z: the lower pair; y, w: the upper one.
+    static __device__ __forceinline__ uint4 operand(const uint4& v) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(v.x, v.y, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(v.z, v.w, false, false);
+        return make_uint4(lo[0], lo[1], hi[0], hi[1]);
+    }
+    static constexpr int kSteps = 4;
+    static __device__ __forceinline__ f32x4 mma(int t, const uint4& a, const uint4& b, f32x4 c) {
+        const uint32_t av = t == 0 ? a.x : t == 1 ? a.z : t == 2 ? a.y : a.w, bv = t == 0 ? b.x : t == 1 ? b.z : t == 2 ? b.y : b.w;
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(av), __uint_as_float(bv), c, 0, 0, 0);
+    }
+};
+
+// kSide blocks of 16 rows (a lane's row of each: wrow) by one query, whose chunks lie in LDS as operands (zop, whole steps of 64 bytes);
+// kAhead steps of each are under way at a time.  Accumulator i of a lane: row 4 g + i, in every column r.
+template <typename T, int kSide, int kAhead>
+__device__ __forceinline__ void score_rows(const unsigned char* const (&wrow)[kSide], const uint4* zop, int row_bytes, int g, f32x4 (&acc)[kSide]) {
+    auto product = [&](int u, int s, const uint4& w) {
+        const uint4 wo = FewMma<T>::operand(w), zo = zop[4 * s + g];
+#pragma unroll
+        for (int m = 0; m < FewMma<T>::kSteps; ++m) acc[u] = FewMma<T>::mma(m, wo, zo, acc[u]);
+    };
+#pragma unroll
+    for (int u = 0; u < kSide; ++u) acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
+    int s = 0;
+    for (; s + kAhead <= row_bytes / 64; s += kAhead) {
+        uint4 w[kAhead][kSide];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+            for (int u = 0; u < kSide; ++u) w[i][u] = *reinterpret_cast<const uint4*>(wrow[u] + (s + i) * 64 + g * 16);
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+            for (int u = 0; u < kSide; ++u) product(u, s + i, w[i][u]);
+    }
+    if (s * 64 < row_bytes) {                               // the last steps, of which one may be a part
+        uint4 w[kAhead][kSide];
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+#pragma unroll
+            for (int u = 0; u < kSide; ++u) {
+                w[i][u] = make_uint4(0, 0, 0, 0);
+                if ((s + i) * 64 + g * 16 < row_bytes) w[i][u] = *reinterpret_cast<const uint4*>(wrow[u] + (s + i) * 64 + g * 16);
+            }
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i)
+            if ((s + i) * 64 < row_bytes)                   // uniform
+#pragma unroll
+                for (int u = 0; u < kSide; ++u) product(u, s + i, w[i][u]);
+    }
+}
+
+// ---- scores of fp32 rows from fp16 copies (few_half_kernel, xc_mine_half.h)
+// Powers of two keep fp16's range out of it: a query is scaled by its largest element, W by kHalfScale.
+constexpr float kHalfScale = 64.0f;
+constexpr float kHalfLeast = 1e-15f, kHalfMost = 1e15f;      // largest elements of a query that scaling and norm cover (or all zero)
+
+// |score - 16-bit score| <= this |z| |w| + 2^-20 sqrt(d) |z|: two roundings of 2^-11, what fp32 sums of d products lose on both sides, a
+// hundredth of that to spare; the second term is what elements of W below fp16's normal range can lose.
+__device__ __forceinline__ float half_error(int d) { return (2.0f / 2048.0f) * 1.01f + 6.0f * static_cast<float>(d) * 5.97e-8f; }
+__device__ __forceinline__ float half_error_small(int d) { return 1.0e-6f * sqrtf(static_cast<float>(d)); }
 
 constexpr int kRing = 8;            // stages in LDS (8 or 16 KiB each)
 static_assert(kRing >= 4 && (kRing & (kRing - 1)) == 0, "stage slots are indexed modulo a power of two, and the two halves of the workgroup fill them in turn");
@@ -148,7 +232,8 @@ struct FewPlan {
 
 // Whether the search of few queries takes this shape, and how.  `scratch`: bytes for the group maxima
 // and the candidates of shared queries.
-bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool warm, size_t scratch, FewPlan* p);
+// `half`: the search of many queries on fp16 copies (xc_mine_half.h) is the alternative.
+bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool warm, bool half, size_t scratch, FewPlan* p);
 
 int few_raise_lds();         // the dynamic LDS limit of its kernels, on the current device
 int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int64_t L, int64_t row_bytes, int k,

@@ -125,6 +125,7 @@ struct MineArgs {
     const unsigned char* Z;
     const unsigned char* W;
     int64_t Zq, L, row_bytes;
+    int64_t z_rows, w_rows;  // rows that can be read (copies made for a search are padded to whole tiles)
     int k, kcap;
     int nkb;                 // K stages per tile
     int64_t nQT;             // query tiles
@@ -144,6 +145,7 @@ struct MineArgs {
     int dense_ld;
     const int32_t* cond;     // not null: repeat of a warm search; cond[0] != 0 if any query tile needs it,
                              // cond[1 + qt] != 0 if query tile qt does
+    int32_t* over;           // fp16 copies: [0] and [1 + qt] are set when query tile qt is given up (a list ran over)
     const int32_t* items;    // not null (row kernel): only these work items, [0] their number, [1] slices per XCD, [2..] the items
 };
 
@@ -247,7 +249,7 @@ void mine_tile_kernel(const MineArgs a) {
         // tiles [0, full_tiles) of the slice have all kBM rows
         int full_tiles;
         {
-            const int64_t f = a.L / kBM - t_begin;
+            const int64_t f = a.w_rows / kBM - t_begin;
             full_tiles = f < 0 ? 0 : (f < n_tiles ? static_cast<int>(f) : n_tiles);
         }
         const int64_t q0 = qtile * kBN;
@@ -257,7 +259,7 @@ void mine_tile_kernel(const MineArgs a) {
         // ---- the load stream runs one stage ahead of the compute stream and stops at the last stage
         const unsigned char* zbase = a.Z + q0 * a.row_bytes;
         const unsigned char* wld = a.W + t_begin * kBM * a.row_bytes;       // W rows of the tile being loaded
-        const bool z_full = a.Zq - q0 >= kBN;
+        const bool z_full = a.z_rows - q0 >= kBN;
         int ld_tile = 0;
         int ld_kb = 0, ld_slot = 0;
         int to_issue = n_tiles * a.nkb;
@@ -289,7 +291,7 @@ void mine_tile_kernel(const MineArgs a) {
                     pair(std::integral_constant<int, 8>{});  pair(std::integral_constant<int, 10>{});
                     pair(std::integral_constant<int, 12>{}); pair(std::integral_constant<int, 14>{});
                 } else {
-                    const int64_t last_row = dma_z ? a.Zq - 1 - q0 : a.L - 1 - (t_begin + ld_tile) * kBM;
+                    const int64_t last_row = dma_z ? a.z_rows - 1 - q0 : a.w_rows - 1 - (t_begin + ld_tile) * kBM;
                     issue_stage_slow<KTAIL>(base, last_row, a.row_bytes, kb, drow, dcol[0], dcol[1], dst, a.zeros);
                 }
             }
@@ -511,6 +513,12 @@ void mine_tile_kernel(const MineArgs a) {
                 const bool want = lane < 32 && qok &&
                                   (last ? n > a.append_max : n > kCandCap - 2 * kBM - 2 * kPoolKeep);
                 uint64_t todo = __ballot(want);
+                if (std::is_same<T, half_t>::value && todo != 0ull) {
+                    // scores that are not exact choose nothing: the query tile is left to the fp32 kernels
+                    if (want) { tau[qloc] = INFINITY; cnt[qloc] = 0; n = 0; }
+                    if (lane == 0) { a.over[0] = 1; a.over[1 + qtile] = 1; }
+                    todo = 0ull;
+                }
                 if (todo != 0ull || last) {
                     float t_new = -INFINITY;
                     while (todo) {
@@ -523,7 +531,7 @@ void mine_tile_kernel(const MineArgs a) {
                             lsel, [lsel](int idx) { return lsel[idx]; }, nsel, a.k, hist + wave * 256);
                         if (lane == src) { t_new = t; n = a.k; }
                     }
-                    if (want) { tau[qloc] = fmaxf(tau[qloc], t_new); cnt[qloc] = n; }
+                    if (!std::is_same<T, half_t>::value && want) { tau[qloc] = fmaxf(tau[qloc], t_new); cnt[qloc] = n; }
                     if (last) {
                         // ---- close the slice: append the survivors to the global list of each query
                         int base = 0;
@@ -619,7 +627,7 @@ static bool force_general_kernel() {
     return e != nullptr && e[0] == '1';
 }
 
-template <int NK, int WM>
+template <typename T, int NK, int WM>
 __global__ __launch_bounds__(kMineThreads, 1)
 void mine_rows_kernel(const MineArgs a) {
     static_assert(WM == 1 || WM == 2, "wave layouts");
@@ -732,7 +740,7 @@ void mine_rows_kernel(const MineArgs a) {
         int ld_stage = 0, ld_kb = 0, ld_tile = 0;
         uint32_t ld_dst = dma_dst;
         const unsigned char* ld_w = a.W + (lab_begin + wq * 8 * kLd) * row_bytes;   // this wave's rows of the tile being loaded
-        const int full_tiles = static_cast<int>((a.L - lab_begin) / kRowTile < n_tiles ? (a.L - lab_begin) / kRowTile : n_tiles);
+        const int full_tiles = static_cast<int>((a.w_rows - lab_begin) / kRowTile < n_tiles ? (a.w_rows - lab_begin) / kRowTile : n_tiles);
         auto issue_stage = [&]() {
             if ((ld_stage & 1) != my_parity) {
                 // the other half's turn
@@ -753,7 +761,7 @@ void mine_rows_kernel(const MineArgs a) {
                 }
             } else {
                 // the last tile of the label range: rows past the end repeat the last row (dropped by the filter)
-                issue_stage_ragged(a.W, a.L, lab_begin + static_cast<int64_t>(ld_tile) * kRowTile + wq * 8 * kLd + drow,
+                issue_stage_ragged(a.W, a.w_rows, lab_begin + static_cast<int64_t>(ld_tile) * kRowTile + wq * 8 * kLd + drow,
                                    row_bytes, ld_kb * kStageBytes, dcol[0], dcol[1], ld_dst, kLd);
             }
             ++ld_stage;
@@ -830,7 +838,17 @@ void mine_rows_kernel(const MineArgs a) {
         };
         // ---- a list that the next tile could overflow: cut to its best k, by this wave alone
         auto cut_lists = [&]() {
-            if (__builtin_expect(__ballot(cnt[0] > kSubFull || cnt[1] > kSubFull) != 0ull, 0)) {
+            if (std::is_same<T, half_t>::value) {            // (not exact: the query's tile is left to the fp32 kernels)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+                    if (cnt[nt] > kSubFull) {
+                        const int64_t q = q0 + wn * 64 + nt * 32 + (lane_now() & 31u);
+                        a.over[0] = 1;
+                        a.over[1 + q / kBN] = 1;
+                        cnt[nt] = 0;
+                        tau[nt] = INFINITY;
+                    }
+            } else if (__builtin_expect(__ballot(cnt[0] > kSubFull || cnt[1] > kSubFull) != 0ull, 0)) {
                 __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");       // this wave's list stores are complete ...
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");       // ... and are what the loads below see
 #pragma unroll
@@ -876,14 +894,12 @@ void mine_rows_kernel(const MineArgs a) {
                     for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
                         for (int nt = 0; nt < 2; ++nt) {
-                            bf16x8 av, bv;
-                            __builtin_memcpy(&av, &fa[sel][mt], 16);
-                            __builtin_memcpy(&bv, &zf[kb * 4 + kk][nt], 16);
                             if (kb == 0 && kk == 0) {
-                                const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                                acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, zero, 0, 0, 0);
+                                f32x16 c = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                                RowMma<T>::mma(fa[sel][mt], zf[kb * 4 + kk][nt], c);
+                                acc[mt][nt] = c;
                             } else {
-                                acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[mt][nt], 0, 0, 0);
+                                RowMma<T>::mma(fa[sel][mt], zf[kb * 4 + kk][nt], acc[mt][nt]);
                             }
                         }
                     __builtin_amdgcn_sched_barrier(0);
@@ -961,16 +977,20 @@ void mine_rows_kernel(const MineArgs a) {
 // SIMD and 512 registers each, the queries of rows up to 1 KiB fit as well; measured at 1 KiB rows that
 // ran 15 % slower than the general kernel - no second wave covers a wave's barrier and filter time.)
 typedef void (*RowsKernelFn)(const MineArgs);
-struct RowsKernel { RowsKernelFn fn; int nk, wm; };
+struct RowsKernel { RowsKernelFn fn; int nk, wm; bool half; };
 static const RowsKernel kRowsKernels[] = {
-    {&mine_rows_kernel<1, 2>, 1, 2}, {&mine_rows_kernel<2, 2>, 2, 2},
-    {&mine_rows_kernel<3, 2>, 3, 2}, {&mine_rows_kernel<4, 2>, 4, 2},
-    {&mine_rows_kernel<1, 1>, 1, 1}, {&mine_rows_kernel<2, 1>, 2, 1},
-    {&mine_rows_kernel<3, 1>, 3, 1}, {&mine_rows_kernel<4, 1>, 4, 1},
+    {&mine_rows_kernel<bf16_t, 1, 2>, 1, 2, false}, {&mine_rows_kernel<bf16_t, 2, 2>, 2, 2, false},
+    {&mine_rows_kernel<bf16_t, 3, 2>, 3, 2, false}, {&mine_rows_kernel<bf16_t, 4, 2>, 4, 2, false},
+    {&mine_rows_kernel<bf16_t, 1, 1>, 1, 1, false}, {&mine_rows_kernel<bf16_t, 2, 1>, 2, 1, false},
+    {&mine_rows_kernel<bf16_t, 3, 1>, 3, 1, false}, {&mine_rows_kernel<bf16_t, 4, 1>, 4, 1, false},
+    {&mine_rows_kernel<half_t, 1, 2>, 1, 2, true}, {&mine_rows_kernel<half_t, 2, 2>, 2, 2, true},
+    {&mine_rows_kernel<half_t, 3, 2>, 3, 2, true}, {&mine_rows_kernel<half_t, 4, 2>, 4, 2, true},
+    {&mine_rows_kernel<half_t, 1, 1>, 1, 1, true}, {&mine_rows_kernel<half_t, 2, 1>, 2, 1, true},
+    {&mine_rows_kernel<half_t, 3, 1>, 3, 1, true}, {&mine_rows_kernel<half_t, 4, 1>, 4, 1, true},
 };
-static const RowsKernel* find_rows_kernel(int nk, int wm) {
+static const RowsKernel* find_rows_kernel(int nk, int wm, bool half) {
     for (const RowsKernel& k : kRowsKernels)
-        if (k.nk == nk && k.wm == wm) return &k;
+        if (k.nk == nk && k.wm == wm && k.half == half) return &k;
     return nullptr;
 }
 
@@ -1001,7 +1021,8 @@ __global__ void mine_warm_init_kernel(uint32_t* tau_g, int32_t* gcnt, int64_t n,
 // Radix select for lists too long for registers (n > 64*kSelectRegs): the keys
 // are streamed from memory in every pass.  Same result as wave_select_k.
 // ---------------------------------------------------------------------------
-__device__ __noinline__ float wave_select_stream(uint64_t* __restrict__ buf, int n, int k, int* hist) {
+// Bound such that exactly k of the n > k keys are at or below it.
+__device__ __noinline__ uint64_t wave_bound_stream(const uint64_t* __restrict__ buf, int n, int k, int* hist) {
     const int lane = lane_id();
     uint64_t prefix = 0, pmask = 0;
     int need = k;
@@ -1044,7 +1065,12 @@ __device__ __noinline__ float wave_select_stream(uint64_t* __restrict__ buf, int
         need = needn;
         if (have == need) break;
     }
-    const uint64_t bound = prefix | ~pmask;
+    return prefix | ~pmask;
+}
+
+__device__ __noinline__ float wave_select_stream(uint64_t* __restrict__ buf, int n, int k, int* hist) {
+    const int lane = lane_id();
+    const uint64_t bound = wave_bound_stream(buf, n, k, hist);
     // compaction in place: a chunk is read into registers before anything of it is
     // overwritten, and the write position never passes the read position
     uint64_t kmax = 0;
@@ -1070,6 +1096,30 @@ __device__ __noinline__ float wave_select_stream(uint64_t* __restrict__ buf, int
 // k and publishes the k-th score as the threshold of the next phase.  After the
 // last phase the winners are sorted and written out.
 // ---------------------------------------------------------------------------
+// bitonic sort of the (at most 128) winners inside the wave, and the result
+__device__ __forceinline__ void wave_write_winners(const uint64_t* list, int n, int k, uint64_t* srt, int32_t* ids, float* scores) {
+    const int lane = lane_id();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // the select's stores to `list` are visible
+    for (int e = lane; e < XC_MAX_K_MINE; e += kWave) srt[e] = e < n ? list[e] : kKeySentinel;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+    for (int size = 2; size <= XC_MAX_K_MINE; size <<= 1) {
+        for (int stride = size >> 1; stride > 0; stride >>= 1) {
+            const int t = lane;                       // 64 compare-exchanges cover 128 keys
+            const int lo = 2 * t - (t & (stride - 1));
+            const int hi = lo + stride;
+            const bool up = (lo & size) == 0;
+            const uint64_t x = srt[lo], y = srt[hi];
+            if ((x > y) == up) { srt[lo] = y; srt[hi] = x; }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+        }
+    }
+    for (int r = lane; r < k; r += kWave) {
+        const uint64_t v = srt[r];
+        ids[r] = key_id(v);
+        if (scores) scores[r] = (v == kKeySentinel) ? -INFINITY : key_score(v);
+    }
+}
+
 constexpr int kSelectWaves = 4;
 
 __global__ __launch_bounds__(kSelectWaves * kWave)
@@ -1099,27 +1149,7 @@ void mine_select_kernel(uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt
         if (lane == 0) { gcnt[q] = k; tau_g[q] = float_to_ordered(t); }
     }
     if (!final_phase) return;
-    // bitonic sort of the (at most 128) winners inside the wave
-    uint64_t* srt = sorted[wave];
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // the select's stores to `list` are visible
-    for (int e = lane; e < XC_MAX_K_MINE; e += kWave) srt[e] = e < n ? list[e] : kKeySentinel;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-    for (int size = 2; size <= XC_MAX_K_MINE; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            const int t = lane;                       // 64 compare-exchanges cover 128 keys
-            const int lo = 2 * t - (t & (stride - 1));
-            const int hi = lo + stride;
-            const bool up = (lo & size) == 0;
-            const uint64_t x = srt[lo], y = srt[hi];
-            if ((x > y) == up) { srt[lo] = y; srt[hi] = x; }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
-        }
-    }
-    for (int r = lane; r < k; r += kWave) {
-        const uint64_t v = srt[r];
-        shortlist[q * k + r] = key_id(v);
-        if (scores) scores[q * k + r] = (v == kKeySentinel) ? -INFINITY : key_score(v);
-    }
+    wave_write_winners(list, n, k, sorted[wave], shortlist + q * k, scores != nullptr ? scores + q * k : nullptr);
 }
 
 // ---------------------------------------------------------------------------
@@ -1234,6 +1264,12 @@ void mine_dense_select_kernel(const float* __restrict__ dense, int dense_ld, uin
     if (lane == 0) { gcnt[q] = out; tau_g[q] = t; }
 }
 
+}  // namespace xc
+
+#include "xc_mine_half.h"
+
+namespace xc {
+
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
@@ -1243,6 +1279,7 @@ struct MinePlan {
     size_t off_flag, off_lists, off_glist, off_gcnt, off_tau, off_zero;
     size_t ws_min, ws_bytes;         // with ws_min the 8-bit filter, which needs the rest, stays out
     Q8Plan q8;
+    HalfPlan half;
     size_t lds_tile;
 };
 
@@ -1278,8 +1315,8 @@ static int64_t phase_tiles(int64_t lo, int64_t nQT) {
 // Measured, without : with, 131 072 x 768 bf16: k = 64, 1024 queries 435 : 279 us, 4096 1043 : 894, 10 240 2308 : 2180;
 // k = 5, 4096 873 : 783, 20 000 3782 : 3781; 300 000 x 768, k = 128, 40 000 19.8 : 19.4 ms; 60 000 x 128 fp32, k = 100,
 // 30 000 5.44 : 4.71.  Many queries with a short list have nothing to gain (131 072 x 392, k = 20, 20 000 3.47 : 3.55 ms).
-static int dense_tiles(int64_t nQT, int64_t full_tiles, int k, size_t room) {
-    if (k < 32 && nQT > 64) return 0;
+static int dense_tiles(int64_t nQT, int64_t full_tiles, int k, size_t room, bool half) {
+    if (!half && k < 32 && nQT > 64) return 0;
     int64_t most = (48 * k + kBM - 1) / kBM;
     most = most < kDenseMin ? kDenseMin : (most > kDenseTiles ? kDenseTiles : most);
     const int64_t fits = static_cast<int64_t>(room / (static_cast<size_t>(nQT) * kBN * kBM * sizeof(float)));
@@ -1317,6 +1354,22 @@ static int64_t even_phase_tiles(int64_t lo, int64_t nLT, int64_t nQT, int k, int
     return n < nLT - lo ? n : nLT - lo;
 }
 
+// End of a phase on fp16 copies that starts at tile `lo` with thresholds from `seen` tiles (the dense ones are swept again): even growth
+// as above, a quarter less because more passes than by exact scores.
+static int64_t half_phase_end(int64_t lo, int64_t seen, int64_t nLT, int64_t nQT, int k, int slices) {
+    const double ratio = static_cast<double>(nLT) / static_cast<double>(seen);
+    double most = 720.0 / k;
+    most = most > 8.5 ? 8.5 : most;
+    if (seen * nQT >= 512 * kMineGrid && most > 3.0) most = 3.0;
+    const int m = static_cast<int>(ceil(log(ratio) / log(most + 1.0) - 0.01));
+    if (m <= 1) return nLT;
+    const int64_t end = static_cast<int64_t>(static_cast<double>(seen) * pow(ratio, 1.0 / m));
+    while (slices > kXcds && end - lo < 2 * slices) slices /= 2;
+    int64_t n = (end - lo + slices / 2) / slices * slices;
+    if (n < slices) n = slices;
+    return lo + n;
+}
+
 // Work items of 512 queries (the row kernel with all eight waves along the queries) stage half the
 // bytes of W per flop, but there are half as many of them: they are taken where they keep the 32 compute
 // units of an XCD busy with one label slice (nine in ten over all rounds), as well as items of 256 would.  Measured, 256 against 512:
@@ -1335,6 +1388,39 @@ static bool rows_wide_items(int64_t Zq) {
     const double busy_w = static_cast<double>(wide) / static_cast<double>(rw * kCusPerXcd);
     const double busy_n = static_cast<double>(narrow) / static_cast<double>(rn * kCusPerXcd);
     return busy_w >= 0.9 && busy_w >= 0.94 * busy_n;
+}
+
+// Which fp32 searches run on fp16 copies, of those that the search of few queries does not take: by estimates of both times in us,
+// least squares over 150 searches of 416 to 65 536 queries, 1100 to 300 000 rows of 16 to 972 elements, k = 5 to 128 (within a
+// seventh for half of them).  What the copies save is fp32 products; what they cost is per query: thresholds, lists, scores formed
+// again.  With a sixth in favour of the fp32 kernels no search is slower than with them (of the 150), and 4 % are lost over always choosing right.
+// fp32 : copies in ms, 10 240 queries x 131 072 x 768, k = 64 15.1 : 3.0, from thresholds 14.4 : 2.6; 4096 x 1.3 M x 256, k = 100
+// 19.6 : 3.8; 20 000 x 300 000 x 300, k = 32 33.7 : 5.0; 2500 x 4 M x 64, k = 50 12.1 : 3.2; 60 000 x 9000 x 300, k = 8 4.0 : 2.3; the
+// other way 60 000 x 4096 x 64, k = 100 0.88 : 1.84; 20 000 x 4096 x 300, k = 100 0.95 : 0.74.  Below 2048 labels there is no dense phase to find
+// thresholds with (47 767 x 1292 x 972, k = 89: 1.8 : 3.1).
+static void plan_half(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, HalfPlan* p) {
+    p->pitch = 0;
+    p->bytes = 0;
+    if (t != XC_F32 || row_bytes > kHalfMaxRowBytes || Zq <= kBN || L < 8 * kBM) return;
+    {
+        const double z = 1e-3 * Zq, cells = static_cast<double>((Zq + kBN - 1) / kBN * kBN) * static_cast<double>((L + kBM - 1) / kBM * kBM);
+        const double copies = 79.0 + z * (12.9 + 0.193 * k) + 0.50e-6 * cells + 0.85e-9 * 2.0 * cells * ((row_bytes + 255) / 256 * 64) +
+                              1.21e-6 * L * row_bytes + 8.8e-6 * z * k * row_bytes;
+        const double fp32 = 63.0 + z * (4.9 + 0.0325 * k) + 0.43e-6 * cells + 10.5e-9 * 2.0 * cells * ((row_bytes + 127) / 128 * 32) + 0.041 * row_bytes;
+        if (copies > 0.85 * fp32) return;
+    }
+    const int64_t nLT = (L + kBM - 1) / kBM, nq = (Zq + kBN - 1) / kBN * kBN;
+    p->pitch = (row_bytes / 2 + kStageBytes - 1) / kStageBytes * kStageBytes;
+    const int64_t fit = kHalfChunkBytes / (p->pitch * kBM);
+    p->chunk = fit < nLT ? fit : nLT;
+    size_t off = 0;
+    auto take = [&off](size_t bytes) { const size_t o = off; off += round_up(bytes, 256); return o; };
+    p->off_rows = take(static_cast<size_t>(p->chunk) * kBM * p->pitch);
+    p->off_z = take(static_cast<size_t>(nq) * p->pitch);
+    p->off_zpar = take(static_cast<size_t>(nq) * sizeof(float4));
+    p->off_stats = take(256);
+    p->off_over = take(static_cast<size_t>(nq / kBN + 1) * sizeof(int32_t));
+    p->bytes = off;
 }
 
 static int plan_mine(int64_t Zq, int64_t L, int d, int k_h, xc_dtype t, MinePlan* p) {
@@ -1363,6 +1449,8 @@ static int plan_mine(int64_t Zq, int64_t L, int d, int k_h, xc_dtype t, MinePlan
     p->off_zero = take(256);
     p->ws_min = off;
     if (plan_q8(Zq, L, row_bytes, t, &p->q8)) off += p->q8.bytes;
+    plan_half(Zq, L, row_bytes, k_h, t, &p->half);
+    off += p->half.bytes;
     p->ws_bytes = off;
     p->lds_tile = 2 * static_cast<size_t>(kBM + kBN) * kStageBytes + kBN * 8 + kMineWaves * 256 * 4 +
                   static_cast<size_t>(kMineWaves) * kPool * 8 + 16;
@@ -1421,6 +1509,9 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     a.dense = nullptr;
     a.dense_ld = 0;
     a.items = nullptr;
+    a.over = nullptr;
+    a.z_rows = Zq;
+    a.w_rows = L;
     int32_t* flag = reinterpret_cast<int32_t*>(w8 + p.off_flag);
 
     // raise the dynamic LDS limit of the tile kernels: once per device and process (the attribute
@@ -1432,7 +1523,9 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         XC_HIP_CHECK(hipGetDevice(&dev));
         std::lock_guard<std::mutex> lock(attr_mu);
         if (dev < 0 || dev >= 64 || !(attr_done_mask & (1ull << dev))) {
-            const void* fns[8] = {reinterpret_cast<const void*>(&mine_tile_kernel<bf16_t, false, true>),
+            const void* fns[10] = {reinterpret_cast<const void*>(&mine_tile_kernel<half_t, false, true>),
+                                  reinterpret_cast<const void*>(&mine_tile_kernel<half_t, false, false>),
+                                  reinterpret_cast<const void*>(&mine_tile_kernel<bf16_t, false, true>),
                                   reinterpret_cast<const void*>(&mine_tile_kernel<bf16_t, true, true>),
                                   reinterpret_cast<const void*>(&mine_tile_kernel<float, false, true>),
                                   reinterpret_cast<const void*>(&mine_tile_kernel<float, true, true>),
@@ -1456,8 +1549,9 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     // few queries: W is read once and the group maxima take the place of thresholds and lists.  A warm search of one
     // query tile has nothing to gain there and nothing to repeat; of more, its one sweep is the better way.
     FewPlan few;
+    const bool half = p.half.pitch > 0 && ws_bytes >= p.ws_bytes && !force_general_kernel() && !force_rows_layout();
     if (!(warm && Zq > kBN) && !force_general_kernel() && !force_rows_layout() &&
-        plan_few(Zq, L, a.row_bytes, k_h, t, warm, p.off_glist - p.off_lists, &few))
+        plan_few(Zq, L, a.row_bytes, k_h, t, warm, half, p.off_glist - p.off_lists, &few))
         return run_mine_few(few, Z, W, Zq, L, a.row_bytes, k_h, t, w8 + p.off_lists, tau_g,
                             warm ? flag : nullptr, static_cast<int>(p.nQT) + 1, shortlist, scores, st);
 
@@ -1471,15 +1565,14 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     const RowsKernel* rk = nullptr;
     if (t == XC_BF16 && a.row_bytes % kStageBytes == 0 && !force_general_kernel()) {
         const int nk = static_cast<int>(a.row_bytes / kStageBytes);
-        rk = find_rows_kernel(nk, rows_wide_items(Zq) ? 1 : 2);
+        rk = find_rows_kernel(nk, rows_wide_items(Zq) ? 1 : 2, false);
     }
 
-    // one phase: the tile kernel over label tiles [lo, hi), then the select
-    auto sweep = [&](int64_t lo, int64_t hi, const int32_t* cond, const int32_t* items) -> int {
+    // the split of label tiles [lo, hi) over the compute units
+    auto split = [&](int64_t lo, int64_t hi, const RowsKernel* rk) {
         const int64_t nT = hi - lo;
         const bool rows_kernel = rk != nullptr;
         a.nQT = rows_kernel ? (Zq + 2 * kBN / rk->wm - 1) / (2 * kBN / rk->wm) : p.nQT;
-        a.items = items;
         if (nT >= kXcds) {
             // slices per XCD: as many as the phase supports, so that few query tiles are in
             // flight per XCD and their Z rows stay in that XCD's L2
@@ -1495,6 +1588,12 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         a.tiles_per_slice = (nT + a.S - 1) / a.S;
         a.append_max = (p.glist_cap - p.kcap) / a.S;
         if (a.append_max > kCandCap) a.append_max = kCandCap;
+    };
+    // one phase: the tile kernel over label tiles [lo, hi), then the select
+    auto sweep = [&](int64_t lo, int64_t hi, const int32_t* cond, const int32_t* items) -> int {
+        const bool rows_kernel = rk != nullptr;
+        split(lo, hi, rk);
+        a.items = items;
         a.cond = cond;
         const bool ktail = (a.row_bytes % kStageBytes) != 0;
         if (rows_kernel) {
@@ -1518,10 +1617,114 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         return XC_OK;
     };
 
+    auto dense_select = [&](int n0) {
+        if (n0 <= kDenseMin)
+            XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<kDenseMin><<<select_grid, kSelectWaves * kWave, 0, st>>>(
+                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
+        else if (n0 <= 8)
+            XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<8><<<select_grid, kSelectWaves * kWave, 0, st>>>(
+                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
+        else
+            XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<kDenseTiles><<<select_grid, kSelectWaves * kWave, 0, st>>>(
+                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
+    };
+
     auto phase = [&](int64_t lo, int64_t hi, const int32_t* cond, int32_t* short_flag) -> int {
         const int rcs = sweep(lo, hi, cond, nullptr);
         return rcs != XC_OK ? rcs : select(hi, cond, short_flag);
     };
+
+    // fp32 on fp16 copies; then what these did not settle, in two phases of the fp32 kernels
+    if (half) {
+        const HalfPlan& hp = p.half;
+        unsigned char* hw = w8 + p.ws_min;
+        unsigned char* rows = hw + hp.off_rows;
+        float4* zpar = reinterpret_cast<float4*>(hw + hp.off_zpar);
+        uint32_t* stats = reinterpret_cast<uint32_t*>(hw + hp.off_stats);
+        int32_t* over = warm ? flag : reinterpret_cast<int32_t*>(hw + hp.off_over);
+        const int row_bytes = static_cast<int>(a.row_bytes), pitch = static_cast<int>(hp.pitch);
+        int LG = 8;
+        while (LG < kWave && LG * 16 < pitch) LG <<= 1;
+        const MineArgs exact = a;
+        a.Z = hw + hp.off_z;
+        a.row_bytes = pitch;
+        a.nkb = pitch / kStageBytes;
+        a.z_rows = nq;
+        a.over = over;
+        const RowsKernel* hk = pitch <= kMaxRowKernelBytes ? find_rows_kernel(pitch / kStageBytes, rows_wide_items(Zq) ? 1 : 2, true) : nullptr;
+        int64_t chunk_end = 0;
+        auto convert = [&]() -> int {                        // the next chunk's copies
+            const int64_t lo = chunk_end;
+            chunk_end = lo + hp.chunk < p.nLT ? lo + hp.chunk : p.nLT;
+            const int64_t n_rows = (chunk_end - lo) * kBM, n_lab = (L < chunk_end * kBM ? L : chunk_end * kBM) - lo * kBM;
+            const int64_t blocks = (n_rows + 4 * (kWave / LG) - 1) / (4 * (kWave / LG));
+            half_rows_kernel<<<static_cast<unsigned>(blocks < 2048 ? blocks : 2048), 256, 0, st>>>(
+                exact.W + lo * kBM * row_bytes, n_lab, n_rows, row_bytes, pitch, LG, rows, stats);
+            XC_HIP_CHECK(hipGetLastError());
+            a.W = reinterpret_cast<const unsigned char*>(reinterpret_cast<uintptr_t>(rows) - static_cast<uintptr_t>(lo * kBM * pitch));    // (row numbers count from 0)
+            a.w_rows = chunk_end * kBM;
+            return XC_OK;
+        };
+        half_queries_kernel<<<static_cast<unsigned>(nq / 4), 256, 0, st>>>(exact.Z, Zq, nq, row_bytes, pitch, hw + hp.off_z, zpar, stats);
+        XC_HIP_CHECK(hipGetLastError());
+        int rch = convert();
+        if (rch != XC_OK) return rch;
+        const int n0 = warm ? 0 : dense_tiles(p.nQT, L / kBM < chunk_end ? L / kBM : chunk_end, k_h, p.off_glist - p.off_lists, true);
+        if (n0 > 0) {                                        // only for its thresholds: its labels are swept with the others
+            a.nQT = p.nQT;
+            a.tile_lo = 0; a.tile_hi = n0; a.tiles_per_slice = 1;
+            a.S = n0; a.Qx = 0;
+            a.dense = reinterpret_cast<float*>(w8 + p.off_lists);
+            a.dense_ld = n0 * kBM;
+            XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<half_t, false, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            XC_HIP_CHECK(hipGetLastError());
+            dense_select(n0);
+            XC_HIP_CHECK(hipGetLastError());
+        }
+        half_start_kernel<<<static_cast<unsigned>((nq + 256) / 256), 256, 0, st>>>(warm ? 2 : n0 > 0 ? 1 : 0, rel_margin, tau_g, a.gcnt, zpar, stats, over, nq, Zq, d);
+        XC_HIP_CHECK(hipGetLastError());
+        const int slices = slices_cap(p.kcap);
+        int64_t seen = n0;                                   // labels behind the thresholds
+        for (int64_t lo = 0; lo < p.nLT;) {
+            int64_t hi = p.nLT;
+            if (!warm) {
+                if (n0 == 0) hi = lo + phase_tiles(lo, p.nQT);
+                else hi = half_phase_end(lo, seen, p.nLT, p.nQT, k_h, slices);
+                if (hi > p.nLT || (p.nLT - hi) < hi / 4) hi = p.nLT;
+            }
+            if (hi > chunk_end) hi = chunk_end;
+            split(lo, hi, hk);
+            a.append_max = kCandCap;                         // (a list is never cut; one that runs over gives its query tile up)
+            if (hk != nullptr) XC_LAUNCH(K_MINE_TILE, st, (hk->fn<<<kMineGrid, kMineThreads, rows_lds_bytes(hk->wm), st>>>(a)));
+            else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<half_t, false, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            XC_HIP_CHECK(hipGetLastError());
+            if (hi == chunk_end && hi < p.nLT) {             // before the select: the thresholds hold for the rows to come
+                rch = convert();
+                if (rch != XC_OK) return rch;
+            }
+            if (hi < p.nLT) {
+                XC_LAUNCH(K_MINE_SELECT, st, (half_select_kernel<<<select_grid, 256, 0, st>>>(a.glist, a.gcnt, tau_g, zpar, stats, over, Zq, p.glist_cap, k_h, d)));
+                XC_HIP_CHECK(hipGetLastError());
+            }
+            lo = hi;
+            seen = seen > hi ? seen : hi;
+        }
+        const size_t zop = static_cast<size_t>((row_bytes + 63) / 64 * 64);
+        if (Zq >= kHalfWaveQueries)
+            XC_LAUNCH(K_MINE_SELECT, st, (half_finish_kernel<1><<<select_grid, 256, 4 * zop, st>>>(
+                exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, stats, over, p.glist_cap, k_h, Zq, shortlist, scores)));
+        else
+            XC_LAUNCH(K_MINE_SELECT, st, (half_finish_kernel<4><<<static_cast<unsigned>(Zq), 256, zop, st>>>(
+                exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, stats, over, p.glist_cap, k_h, Zq, shortlist, scores)));
+        XC_HIP_CHECK(hipGetLastError());
+        a = exact;
+        mine_init_kernel<<<init_grid, 256, 0, st>>>(tau_g, a.gcnt, nq, zeros32, over);
+        XC_HIP_CHECK(hipGetLastError());
+        const int64_t first = p.nLT > 2 * kXcds ? kXcds : p.nLT;
+        rch = phase(0, first, over, nullptr);
+        if (rch == XC_OK && first < p.nLT) rch = phase(first, p.nLT, over, nullptr);
+        return rch;
+    }
 
     const int32_t* cond = nullptr;
     if (warm) {
@@ -1538,7 +1741,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     unsigned char* q8_ws = w8 + p.ws_min;
     if (cond == nullptr && rk == nullptr) {
         // the first phase dense, by the general kernel: as many tiles as one or a few full rounds of the compute units take
-        const int n0 = dense_tiles(p.nQT, L / kBM, k_h, p.off_glist - p.off_lists);
+        const int n0 = dense_tiles(p.nQT, L / kBM, k_h, p.off_glist - p.off_lists, false);
         if (n0 > 0) {
             a.nQT = p.nQT;
             a.tile_lo = 0; a.tile_hi = n0; a.tiles_per_slice = 1;
@@ -1555,15 +1758,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
                 else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, false, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
             }
             XC_HIP_CHECK(hipGetLastError());
-            if (n0 <= kDenseMin)
-                XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<kDenseMin><<<select_grid, kSelectWaves * kWave, 0, st>>>(
-                    a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
-            else if (n0 <= 8)
-                XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<8><<<select_grid, kSelectWaves * kWave, 0, st>>>(
-                    a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
-            else
-                XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<kDenseTiles><<<select_grid, kSelectWaves * kWave, 0, st>>>(
-                    a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
+            dense_select(n0);
             XC_HIP_CHECK(hipGetLastError());
             lo = n0;
         }

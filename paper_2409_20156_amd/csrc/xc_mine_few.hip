@@ -42,29 +42,6 @@ constexpr int kMaxSplit = 8;             // workgroups per query of the second k
 constexpr int kPartKeys = Finish<1024>::kKeys / kMaxSplit;      // candidates one of them hands over at most
 static_assert(kPartKeys >= XC_MAX_K_MINE, "a workgroup hands over at least its best k");
 
-// Products in the order of the other search kernels (RowMma and the text above it).  `operand` turns a lane's 16 bytes
-// of a row (chunk g of a 64-byte step) into what the matrix instructions of the step take from that lane.
-template <typename T> struct FewMma;
-template <> struct FewMma<bf16_t> {
-    static __device__ __forceinline__ uint4 operand(const uint4& v) { return v; }
-    static constexpr int kSteps = 1;             // matrix instructions per step
-    static __device__ __forceinline__ f32x4 mma(int, const uint4& a, const uint4& b, f32x4 c) { return row_mma_bf16(a, b, c); }
-};
-template <> struct FewMma<float> {
-    // Lanes g = 0, 1, 2, 3 of a product stand for elements 2i of chunks 0 and 1, then 2i + 1 of them: elements 2i + 1 of
-    // the lower chunk pair change places with elements 2i of the upper one.  x, z: the lower pair; y, w: the upper one.
-    static __device__ __forceinline__ uint4 operand(const uint4& v) {
-        const auto lo = __builtin_amdgcn_permlane32_swap(v.x, v.y, false, false);
-        const auto hi = __builtin_amdgcn_permlane32_swap(v.z, v.w, false, false);
-        return make_uint4(lo[0], lo[1], hi[0], hi[1]);
-    }
-    static constexpr int kSteps = 4;
-    static __device__ __forceinline__ f32x4 mma(int t, const uint4& a, const uint4& b, f32x4 c) {
-        const uint32_t av = t == 0 ? a.x : t == 1 ? a.z : t == 2 ? a.y : a.w, bv = t == 0 ? b.x : t == 1 ? b.z : t == 2 ? b.y : b.w;
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(av), __uint_as_float(bv), c, 0, 0, 0);
-    }
-};
-
 struct FewArgs {
     const unsigned char* Z;
     const unsigned char* W;
@@ -407,18 +384,9 @@ void few_wide_kernel(const FewArgs a) {
 // Powers of two keep fp16's range out of it: a query is scaled by its largest element, W by kHalfScale.  Elements of W beyond
 // 1023 become infinite, and so does their group's norm: such a group is always looked at.  Where too many groups are
 // (equal rows by the thousand, odd numbers), the query is searched again by the fp32 kernels, whose launches return at once otherwise.
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 constexpr int kHalfRing = 4;             // steps of 32 elements in flight per wave (two rows of 32 B per lane each: 16 KiB)
-constexpr float kHalfScale = 64.0f;
 constexpr int kMoreGroups = 512;         // groups beside the k best that the second kernel looks at
-constexpr float kHalfLeast = 1e-15f, kHalfMost = 1e15f;      // largest elements of a query that scaling and norm cover (or all zero)
-
-// |score - 16-bit score| <= this |z| |w| + 2^-20 sqrt(d) |z|: two roundings of 2^-11, what fp32 sums of d products lose on both sides, a
-// hundredth of that to spare; the second term is what elements of W below fp16's normal range can lose.
-__device__ __forceinline__ float half_error(int d) { return (2.0f / 2048.0f) * 1.01f + 6.0f * static_cast<float>(d) * 5.97e-8f; }
-__device__ __forceinline__ float half_error_small(int d) { return 1.0e-6f * sqrtf(static_cast<float>(d)); }
-
 __device__ __forceinline__ f16x8 to_half8(const uint4& a, const uint4& b, float scale) {
     const float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
                         __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
@@ -900,7 +868,7 @@ void few_finish_kernel(const FewArgs a) {
     // block b: rows 16 b .. 16 b + 15 of the groups; a lane with r < 4 gets the score and label of row 4 g + r.  A wave takes kSide
     // blocks side by side, kAhead steps of each under way: it waits for memory, not for the products.
     constexpr int kSide = NT == 256 ? 2 : 1, kAhead = NT == 256 ? 4 : 16;
-    const int row_bytes = static_cast<int>(a.row_bytes), steps_whole = row_bytes / 64;
+    const int row_bytes = static_cast<int>(a.row_bytes);
     auto score_blocks = [&](int b, int b_step, int64_t (&lab)[kSide], float (&score)[kSide]) {
         const unsigned char* wrow[kSide];
         f32x4 acc[kSide];
@@ -909,40 +877,8 @@ void few_finish_kernel(const FewArgs a) {
             const int j0 = 16 * (b + u * b_step) + r, j = j0 < n_rows ? j0 : n_rows - 1;
             const int64_t l = row_label(j);
             wrow[u] = a.W + (l < a.L ? l : a.L - 1) * row_bytes;
-            acc[u] = f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        auto product = [&](int u, int s, const uint4& w) {
-            const uint4 wo = FewMma<T>::operand(w), zo = zop[4 * s + g];
-#pragma unroll
-            for (int m = 0; m < FewMma<T>::kSteps; ++m) acc[u] = FewMma<T>::mma(m, wo, zo, acc[u]);
-        };
-        int s = 0;
-        for (; s + kAhead <= steps_whole; s += kAhead) {
-            uint4 w[kAhead][kSide];
-#pragma unroll
-            for (int i = 0; i < kAhead; ++i)
-#pragma unroll
-                for (int u = 0; u < kSide; ++u) w[i][u] = *reinterpret_cast<const uint4*>(wrow[u] + (s + i) * 64 + g * 16);
-#pragma unroll
-            for (int i = 0; i < kAhead; ++i)
-#pragma unroll
-                for (int u = 0; u < kSide; ++u) product(u, s + i, w[i][u]);
-        }
-        if (s * 64 < row_bytes) {                               // the last steps, of which one may be a part
-            uint4 w[kAhead][kSide];
-#pragma unroll
-            for (int i = 0; i < kAhead; ++i)
-#pragma unroll
-                for (int u = 0; u < kSide; ++u) {
-                    w[i][u] = make_uint4(0, 0, 0, 0);
-                    if ((s + i) * 64 + g * 16 < row_bytes) w[i][u] = *reinterpret_cast<const uint4*>(wrow[u] + (s + i) * 64 + g * 16);
-                }
-#pragma unroll
-            for (int i = 0; i < kAhead; ++i)
-                if ((s + i) * 64 < row_bytes)                   // uniform
-#pragma unroll
-                    for (int u = 0; u < kSide; ++u) product(u, s + i, w[i][u]);
-        }
+        score_rows<T, kSide, kAhead>(wrow, zop, row_bytes, g, acc);
 #pragma unroll
         for (int u = 0; u < kSide; ++u) {
             const int jr = 16 * (b + u * b_step) + 4 * g + r;
@@ -1123,6 +1059,20 @@ static double others_us(int64_t Zq, int64_t L, int64_t row_bytes, int k, bool f3
                : 44.0 + gflop * (tail ? 0.84 : 0.22) + 556.0 * mlab * kb + 147.0 * qt * mlab + 34.0 * kb + long_list * 1300.0 * mlab;
 }
 
+// The same where both have fp16 copies (fp32 rows, more than 256 queries): least squares over 70 searches of 128 to 2048 queries, 5000 to
+// 4 million rows of 64 to 768 elements, k = 5 to 100, within a tenth for half of them; choosing by these costs 1.2 % over always choosing
+// right, 38 % at worst.
+static double few_half_us(const FewPlan& p, int64_t Zq, int64_t L, int64_t row_bytes, int k) {
+    const double slots = static_cast<double>(few_slots(p.hlds)), wgs = static_cast<double>(few_ranges(p.hlds, p.hn_qb) * p.hn_qb);
+    const double gflop = 2e-9 * p.hn_qb * p.hnb * 16 * L * (row_bytes / 4) * slots * ceil(wgs / slots) / wgs;
+    const double rows = static_cast<double>(Zq) * k * (1 << (4 + p.hgshift)) * row_bytes;
+    return 30.0 + gflop * (p.hnb == 8 ? 1.73 : 3.04) + 0.157e-6 * rows + 9.5e-6 * Zq * p.hn_groups + 0.143e-6 * L * row_bytes;
+}
+static double others_half_us(int64_t Zq, int64_t L, int64_t row_bytes, int k) {
+    const double nq = static_cast<double>((Zq + kBN - 1) / kBN * kBN), zk = static_cast<double>(Zq) * k;
+    return 142.0 + 0.075e-9 * 2.0 * nq * L * (row_bytes / 4) + 0.70e-6 * L * row_bytes + 1.07e-3 * zk + 0.386e-6 * nq * L + 0.235e-6 * zk * row_bytes;
+}
+
 // Which searches come here.  Up to 96 queries (less than half of a query tile of the general kernel) all whose query block fits LDS:
 // 131 072 x 768 bf16, k = 5: 71 us against 408 at 64 queries; 4 M x 256 bf16, k = 50: 0.65 ms against 1.57.  More queries
 // cost this path time in proportion (it multiplies W once per block of at most 64), the others almost nothing until their tiles of
@@ -1133,7 +1083,7 @@ static double others_us(int64_t Zq, int64_t L, int64_t row_bytes, int k, bool f3
 // path, up to 256 queries on long bf16 rows with a twentieth against it (where the estimates err, by these parts).  Here and there: 1024 x 98 301 x 768 bf16, k = 50 499 and 250 us; 2048 x 49 149 x 2304, k = 5 1679 and 549; 512 x 98 301 x 768, k
 // = 5 199 and 214; from thresholds 256 x 4 M x 128, k = 5 1036 and 722, 256 x 4 M x 64, k = 100 710 and 1405; 256 x 5000 x
 // 2304, k = 100 316 and 249; 1024 x 262 141 x 768 fp32 3480 and 3100, 1024 x 78 589 x 300 445 and 590.
-bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool warm, size_t scratch, FewPlan* p) {
+bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool warm, bool half, size_t scratch, FewPlan* p) {
     const bool f32 = t == XC_F32;
     if (Zq > kFewQueries) {
         const int64_t tiles = ((Zq + 255) / 256) * ((L + 255) / 256);
@@ -1156,7 +1106,8 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
     const bool row_kernel = !f32 && row_bytes % kStageBytes == 0 && row_bytes <= kMaxRowKernelBytes;
     const bool always = Zq <= kFewAlways || (f32 ? Zq <= kFewQueries : row_kernel && !warm);
     const double favour = f32 ? 1.2 : Zq <= kFewQueries && !row_kernel ? 0.95 : 1.0;
-    if (!always && few_us(*p, Zq, L, row_bytes, k, f32) >= favour * others_us(Zq, L, row_bytes, k, f32, row_kernel, warm)) return false;
+    // (the choice among the fp16 forms of both is made below)
+    if (!always && !(f32 && half) && few_us(*p, Zq, L, row_bytes, k, f32) >= favour * others_us(Zq, L, row_bytes, k, f32, row_kernel, warm)) return false;
     // the second kernel: as many workgroups per query as give each wave one block of 16 labels, within what the chip holds
     int ns = 1;
     while (ns < kMaxSplit && Zq * ns * 2 <= 256 && (static_cast<int64_t>(k) << gs) > ns * Finish<1024>::kWaves) ns <<= 1;
@@ -1175,6 +1126,7 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
         p->hn_groups = gs == 0 ? (L + 7) / 8 : p->n_groups;
         if (p->hlds <= kFewLds && bytes(p->hn_groups) <= scratch) p->hnb = hnb;
     }
+    if (!always && f32 && half && (p->hnb == 0 || few_half_us(*p, Zq, L, row_bytes, k) >= others_half_us(Zq, L, row_bytes, k))) return false;
     return true;
 }
 

@@ -75,3 +75,81 @@ def test_odd_rows(monkeypatch, Zq, rows):
         Z[5] *= -1e30
         Z[6, 1:] = 0.0
     _check(monkeypatch, Z, W, k)
+
+
+# ---- many queries: the sweep runs on fp16 copies, what it leaves is scored in fp32
+def _thresholds(monkeypatch, Z, W, k, margin):
+    """A search from scratch, then from its thresholds on the same rows; the ids and scores of the second are those of the fp32 kernels."""
+    import paper_2409_20156_amd as xc
+    ws = torch.empty(xc.mine_workspace(Z.shape[0], W.shape[0], Z.shape[1], k, xc.XC_F32), dtype=torch.uint8, device=DEV)
+    xc.mine_negatives(Z, W, k, workspace=ws)
+    W[::3] *= 0.9                                    # fewer labels than k reach some of the thresholds
+    ids, sc = xc.mine_negatives(Z, W, k, want_scores=True, workspace=ws, warm_margin=margin)
+    repeats = int(ws[:4].view(torch.int32).item())
+    monkeypatch.setenv("XC_MINE_GENERAL", "1")
+    want, want_sc = xc.mine_negatives(Z, W, k, want_scores=True)
+    monkeypatch.delenv("XC_MINE_GENERAL")
+    assert torch.equal(ids, want)
+    assert torch.equal(sc.view(torch.int32), want_sc.view(torch.int32))
+    return repeats
+
+
+@pytest.mark.parametrize("Zq,L,d,k", [
+    (2049, 60001, 100, 50),                         # 256-byte copies: the row kernel, items of 256 queries
+    (8300, 40010, 128, 10), (4100, 30010, 252, 128),  # items of 512; 512-byte copies
+    (4097, 20010, 260, 100), (3000, 20003, 772, 64),   # the general kernel; a stage that is mostly padding
+    (2100, 9000, 2048, 20),                         # the longest rows
+    (300, 1300000, 512, 30),                        # fewer queries: a workgroup each at the end
+    (2300, 4300000, 60, 16),                        # copies of more than one chunk
+    (16500, 8192, 512, 5),                          # few labels
+])
+def test_many_queries(monkeypatch, Zq, L, d, k):
+    Z, W = _inputs(Zq, L, d)
+    _check(monkeypatch, Z, W, k)
+    _thresholds(monkeypatch, Z, W, k, 0.1)
+
+
+@pytest.mark.parametrize("rows", ["zero", "mostly zero", "equal", "pairs", "large", "tiny", "wide", "inf", "nan", "rising", "queries"])
+def test_many_queries_odd_rows(monkeypatch, rows):
+    Zq, L, d, k = 2560, 40011, 320, 32
+    Z, W = _inputs(Zq, L, d)
+    if rows == "zero":
+        W.zero_()
+    elif rows == "mostly zero":
+        Z.abs_()
+        W.abs_().neg_()
+        W[torch.arange(L, device=DEV) % 10 != 3] = 0.0
+    elif rows == "equal":
+        W[:] = W[5].clone()
+    elif rows == "pairs":
+        W[1::2] = W[0:L - 1:2]
+        W[1::2, 7] = torch.nextafter(W[1::2, 7], W[1::2, 7] + 1)
+    elif rows == "large":
+        W[::50] *= 1e5
+    elif rows == "tiny":
+        W *= 1e-9
+    elif rows == "wide":
+        W *= torch.logspace(-20, 2, L, device=DEV)[:, None]
+    elif rows == "inf":
+        W[77, 3] = float("inf")
+        W[9000, 50] = -float("inf")
+    elif rows == "nan":
+        W[123] = float("nan")
+        W[40010, 99] = float("nan")
+    elif rows == "rising":                           # the scores of two query tiles rise along the label range: lists run over
+        W[:, 0] = torch.linspace(0, 20, L, device=DEV)
+        Z[256:512, 0] = 3.0
+        Z[1000, 0] = 3.0
+    else:
+        Z[0] = 0.0
+        Z[1] *= 1e20
+        Z[300] *= 1e-20
+        Z[800, 5] = float("inf")
+        Z[1400, 6] = float("nan")
+        Z[2500, 1:] = 0.0
+    _check(monkeypatch, Z, W, k)
+
+
+def test_thresholds_too_high_are_repeated(monkeypatch):
+    Z, W = _inputs(3000, 30000, 320)
+    assert _thresholds(monkeypatch, Z, W, 50, 0.0) == 1
