@@ -1,7 +1,7 @@
 // The search for few queries: the same exact top-k as xc_mine.hip (score of Sec. 2.1) where the work is
 // reading W once, not the products.  Inference over a handful of queries, small pools.
 //
-//   few_max_kernel     streams W once.  A wave multiplies 32 labels with all queries of the workgroup, whose
+//   few_line_kernel    streams W once (few_max_kernel rows of under 128 bytes and very long ones).  A wave multiplies 32 labels with all queries of the workgroup, whose
 //       rows lie in LDS as MFMA operands, and keeps of every group of 16 << gshift labels the largest score per
 //       query: the only thing written, 1 / (16 << gshift) of the score matrix.
 //   few_finish_kernel  one workgroup per query: the k-th largest group maximum tau (one radix digit or more, then by
@@ -11,8 +11,8 @@
 //       of equal scores the smaller ids win, and each of these groups holds one.  So k groups in all hold the
 //       answer.  Their scores are formed again, with the sums in the same order (hence the same
 //       bits), what is below tau is dropped, the rest sorted.
-// Bound: HBM, one read of W.  131 072 x 768 bf16, 32 queries, k = 5: 63 us in all (first kernel 50 us, 4.0 TB/s of the 5.1
-// a plain copy reaches), where the general kernel took 378; 30 M x 256 bf16, 32 queries: 3.3 ms (4.7 TB/s) against 8.5.  In
+// Bound: HBM, one read of W.  131 072 x 768 bf16, 32 queries, k = 5: 54 us in all (first kernel 41 us, 4.9 TB/s; a plain
+// copy reaches 5.1), where the general kernel took 378; 4 M x 256 bf16, 32 queries: 0.47 ms against 0.55 by half lines.  In
 // fp32 with more than 16 queries the matrix pipe, which is why the maxima then come from 16-bit products (few_half_kernel): 1000
 // queries x 50 021 x 300, 158 us (76 and 83 the two kernels) against 364 with fp32 products (318 and 105; these alone need 195) and 782
 // by the general kernel.
@@ -27,6 +27,7 @@ namespace xc {
 
 constexpr int kFewThreads = 512;
 constexpr size_t kFewLds = 144u << 10;   // LDS for the query block at most
+constexpr size_t kLineLds = 160u << 10;  // the same with a stage per wave beside it
 constexpr int kFewWaves = kFewThreads / kWave;
 constexpr int kFewRing = 8;              // 64-byte steps in flight per wave (two rows of 16 B per lane each: 16 KiB)
 constexpr int kFewTile = 32;             // labels a wave multiplies at a time
@@ -190,6 +191,191 @@ void few_max_kernel(const FewArgs a) {
             if (FewMma<T>::kSteps > 1) __builtin_amdgcn_sched_barrier(0);
             load_step(j);
             if (++s == KS) {                                    // uniform: a tile is complete
+                s = 0;
+                const int64_t tile = unit * comb + t;
+                const int64_t lab = tile * kFewTile + 4 * g;    // accumulator i of block b: label lab + 16 b + i, query r
+                const bool full = (tile + 1) * kFewTile <= a.L;
+                const bool unit_done = t + 1 == comb || tile + 1 >= n_tiles;
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    float m[2];
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        if (!full)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i)
+                                if (lab + 16 * b + i >= a.L) acc[b][n][i] = nan;
+                        m[b] = fmaxf(fmaxf(acc[b][n][0], acc[b][n][1]), fmaxf(acc[b][n][2], acc[b][n][3]));
+                    }
+                    acc[0][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    acc[1][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    const int64_t q = q0 + n * 16 + r;
+                    if (a.gshift == 0) {
+#pragma unroll
+                        for (int b = 0; b < 2; ++b) {
+                            m[b] = fmaxf(m[b], __shfl_xor(m[b], 16, kWave));
+                            m[b] = fmaxf(m[b], __shfl_xor(m[b], 32, kWave));
+                        }
+                        // lanes 0..15 store the first group's maxima, lanes 16..31 the second's
+                        const int64_t grp = 2 * tile + g;
+                        if (g < 2 && q < a.Zq && grp < a.n_groups) a.gmax[q * a.n_groups + grp] = score_image(g == 0 ? m[0] : m[1]);
+                    } else {
+                        run[n] = fmaxf(run[n], fmaxf(m[0], m[1]));
+                        if (unit_done) {
+                            run[n] = fmaxf(run[n], __shfl_xor(run[n], 16, kWave));
+                            run[n] = fmaxf(run[n], __shfl_xor(run[n], 32, kWave));
+                            if (g == 0 && q < a.Zq) a.gmax[q * a.n_groups + unit] = score_image(run[n]);
+                            run[n] = nan;
+                        }
+                    }
+                }
+                ++t;
+                if (unit_done) { t = 0; unit += u_step; if (unit >= n_units) return; }
+            }
+        }
+    }
+}
+
+// The same for rows of 128 bytes and more, with W read a line at a time.  What few_max_kernel loads with one instruction, 64 bytes of
+// each of 16 rows, is half a line each, and memory delivered 4.2 TB/s that way whatever was under way; here an instruction brings
+// 128 bytes of 8 rows, and the wave exchanges them for operands through 4 KiB of LDS of its own (chunk c of row r at position
+// c ^ (r >> 1) & 7, so that 16 lanes reading one chunk of 16 rows meet no bank twice).  Half lines and whole ones, us in all: 32 queries x
+// 4 M x 200 bf16 515 and 484, 30 x 300 000 x 504 99 and 87, 500 x 60 000 x 768 126 and 94, 1000 x 50 000 x 256 130 and 105; read past the caches (see
+// line_way) 32 x 1.3 M x 768 484 and 400 (5.0 TB/s), 8 x 1.3 M x 768 442 and 360 (5.5), 16 x 1 M x 256 fp32 260 and 217.
+constexpr int kFewStage = kFewTile * 128;   // bytes of a wave's stage
+
+template <typename T, int NB, bool KTAIL, bool STREAM>
+__global__ __launch_bounds__(kFewThreads, 4)
+void few_line_kernel(const FewArgs a) {
+    extern __shared__ __align__(16) unsigned char zlds[];       // [ks][NB] operands of 1 KiB, then a stage per wave
+    constexpr int kStages = NB == 1 ? 4 : NB == 2 ? 3 : 2;      // in a wave's registers, 4 KiB each (so that four waves fit a SIMD)
+    const int tid = threadIdx.x;
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int KS = (a.ks + 1) & ~1;                             // steps of 64 bytes, in pairs
+    // workgroups of one XCD (id % 8) that differ in the query block only are neighbours: they read the same rows of W
+    // at about the same time, and all but the first find them in that XCD's L2
+    const int id = blockIdx.x;
+    const int qb = (id / 8) % a.n_qb;
+    const int wg = (id % 8) + 8 * (id / (8 * a.n_qb));
+    const int n_wg = gridDim.x / a.n_qb;                        // (a multiple of 8, see the launch)
+    const int64_t q0 = static_cast<int64_t>(qb) * NB * 16;
+    if (a.again && !few_again(a, q0, NB * 16)) return;          // uniform
+
+    // a unit is the tiles whose maxima one wave combines: a tile of two groups (gshift 0), or 2^(gshift-1) tiles of one
+    const int comb = a.gshift > 0 ? 1 << (a.gshift - 1) : 1;
+    const int64_t n_tiles = (a.L + kFewTile - 1) / kFewTile;
+    const int64_t n_units = (n_tiles + comb - 1) / comb;
+    const int64_t u_step = static_cast<int64_t>(n_wg) * kFewWaves;
+    int64_t unit = static_cast<int64_t>(wg) * kFewWaves + wave;
+
+    // ---- the load stream: ring of stages of 128 bytes of 32 rows, running ahead across tiles and units; begun before the queries are
+    // laid out (a call with few labels has one tile per wave, and would wait for memory twice)
+    const int srow = lane >> 3, schunk = lane & 7;              // of the 8 rows of a load instruction
+    int64_t ld_unit = unit < n_units ? unit : n_units - 1;
+    int ld_t = 0;
+    int ld_off = schunk * 16;                                   // bytes into the rows
+    const int row_bytes = static_cast<int>(a.row_bytes);
+    const unsigned char* p[4];
+    auto set_rows = [&]() {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int64_t l = (ld_unit * comb + ld_t) * kFewTile + 8 * t + srow;
+            p[t] = a.W + (l < a.L ? l : a.L - 1) * a.row_bytes; // rows past the end: dropped later
+        }
+    };
+    set_rows();
+    uint4 ra[kStages][4];
+    auto load_stage = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            ra[j][t] = load16<STREAM>(p[t] + (KTAIL && ld_off >= row_bytes ? 0 : ld_off));           // (zeroed where it is used)
+        }
+        ld_off += 128;
+        if (ld_off - schunk * 16 == KS * 64) {                  // uniform
+            ld_off = schunk * 16;
+            ++ld_t;
+            if (ld_t == comb || ld_unit * comb + ld_t >= n_tiles) { ld_t = 0; ld_unit += u_step; }
+            if (ld_unit < n_units) set_rows();                  // else: the last tile again, never used
+        }
+    };
+#pragma unroll
+    for (int j = 0; j < kStages; ++j) load_stage(j);
+
+    // ---- the queries, four chunks of a thread at a time
+    for (int e0 = tid; e0 < KS * NB * 64; e0 += 4 * kFewThreads) {
+        uint4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * kFewThreads, l = e & 63, blk = e >> 6;
+            const int64_t q = q0 + (blk % NB) * 16 + (l & 15);
+            const int64_t off = static_cast<int64_t>(blk / NB) * 64 + (l >> 4) * 16;
+            v[u] = make_uint4(0, 0, 0, 0);
+            if (q < a.Zq && off < a.row_bytes) v[u] = *reinterpret_cast<const uint4*>(a.Z + q * a.row_bytes + off);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = e0 + u * kFewThreads;
+            const uint4 o = FewMma<T>::operand(v[u]);           // (a wave takes whole blocks)
+            if (e < KS * NB * 64) *reinterpret_cast<uint4*>(zlds + static_cast<size_t>(e) * 16) = o;
+        }
+    }
+    if (id == 0)
+        for (int64_t i = tid; i < a.Zq; i += kFewThreads) a.done[i] = 0;
+    __syncthreads();
+    if (unit >= n_units) return;                                // (no barrier below)
+
+    f32x4 acc[2][NB];
+    // maxima are taken as floats: fmaxf passes over NaN, so a group is NaN only if all its scores are
+    const float nan = __builtin_nanf("");
+    float run[NB];
+#pragma unroll
+    for (int n = 0; n < NB; ++n) {
+        run[n] = nan;
+        acc[0][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+        acc[1][n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    unsigned char* stage = zlds + static_cast<size_t>(KS) * NB * 1024 + wave * kFewStage;
+    const bool tail = KS * 64 - 128 + schunk * 16 >= row_bytes;
+    // (the swizzle term of the 8 rows of load t is 4 (t & 1) + (lane >> 4), that of an operand's rows (lane >> 1) & 7)
+    const uint32_t put[2] = {static_cast<uint32_t>(srow * 128 + ((schunk ^ (lane >> 4)) * 16)),
+                             static_cast<uint32_t>(srow * 128 + ((schunk ^ ((lane >> 4) + 4)) * 16))};
+    const uint32_t get = static_cast<uint32_t>(r * 128 + ((g ^ ((lane >> 1) & 7)) * 16));
+    int t = 0, s = 0;
+    for (;;) {
+#pragma unroll
+        for (int j = 0; j < kStages; ++j) {
+            if (KTAIL && s + 2 == KS && tail)                   // this lane's chunks lie past the rows' end
+#pragma unroll
+                for (int u = 0; u < 4; ++u) ra[j][u] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) *reinterpret_cast<uint4*>(stage + put[u & 1] + u * 1024) = ra[j][u];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");      // (a wave's LDS operations are done in order)
+            load_stage(j);
+            uint4 w[2][2], b[2][NB];                            // [half of the stage][block of 16 rows]
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                for (int m = 0; m < 2; ++m) w[h][m] = *reinterpret_cast<const uint4*>(stage + (get ^ (h * 64)) + m * 2048);
+#pragma unroll
+                for (int n = 0; n < NB; ++n) b[h][n] = *reinterpret_cast<const uint4*>(zlds + (static_cast<size_t>(s + h) * NB + n) * 1024 + lane * 16);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint4 a0 = FewMma<T>::operand(w[h][0]), a1 = FewMma<T>::operand(w[h][1]);
+                // (an accumulator's own instructions lie 2 NB apart: one that follows the other waits for it)
+#pragma unroll
+                for (int m = 0; m < FewMma<T>::kSteps; ++m)
+#pragma unroll
+                    for (int n = 0; n < NB; ++n) {
+                        acc[0][n] = FewMma<T>::mma(m, a0, b[h][n], acc[0][n]);
+                        acc[1][n] = FewMma<T>::mma(m, a1, b[h][n], acc[1][n]);
+                    }
+            }
+            s += 2;
+            if (s == KS) {                                      // uniform: a tile is complete
                 s = 0;
                 const int64_t tile = unit * comb + t;
                 const int64_t lab = tile * kFewTile + 4 * g;    // accumulator i of block b: label lab + 16 b + i, query r
@@ -1025,7 +1211,7 @@ constexpr int64_t kFewMaxQueries = 2048;     // beyond that never
 
 // Workgroups of the first kernel: as many label ranges per block of queries as fit the chip (two workgroups per compute unit
 // where two query blocks fit its LDS), in multiples of the 8 XCDs and at least 8.
-static int64_t few_slots(size_t lds) { return lds <= (76u << 10) ? 512 : 256; }
+static int64_t few_slots(size_t lds) { return lds <= (80u << 10) ? 512 : 256; }
 static int64_t few_ranges(size_t lds, int n_qb) {
     const int64_t n = few_slots(lds) / n_qb / 8 * 8;
     return n < 8 ? 8 : n;
@@ -1133,6 +1319,19 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
 typedef void (*FewFn)(const FewArgs);
 template <typename T>
 static FewFn few_kernel(int nb, bool ktail);
+// way: 0 whole lines, 1 rows that end within one, 2 whole lines read past the caches
+template <typename T> static FewFn line_kernel(int nb, int way);
+template <> FewFn line_kernel<bf16_t>(int nb, int way) {
+    static const FewFn fns[3][3] = {
+        {&few_line_kernel<bf16_t, 1, false, false>, &few_line_kernel<bf16_t, 1, true, false>, &few_line_kernel<bf16_t, 1, false, true>},
+        {&few_line_kernel<bf16_t, 2, false, false>, &few_line_kernel<bf16_t, 2, true, false>, &few_line_kernel<bf16_t, 2, false, true>},
+        {&few_line_kernel<bf16_t, 4, false, false>, &few_line_kernel<bf16_t, 4, true, false>, &few_line_kernel<bf16_t, 4, false, true>}};
+    return fns[nb >> 1][way];
+}
+template <> FewFn line_kernel<float>(int nb, int way) {
+    static const FewFn fns[3] = {&few_line_kernel<float, 1, false, false>, &few_line_kernel<float, 1, true, false>, &few_line_kernel<float, 1, false, true>};
+    return nb == 1 ? fns[way] : nullptr;
+}
 template <> FewFn few_kernel<bf16_t>(int nb, bool ktail) {
     return nb == 1 ? (ktail ? &few_max_kernel<bf16_t, 1, true> : &few_max_kernel<bf16_t, 1, false>)
          : nb == 2 ? (ktail ? &few_max_kernel<bf16_t, 2, true> : &few_max_kernel<bf16_t, 2, false>)
@@ -1151,6 +1350,12 @@ static FewFn half_kernel(int nb, bool ktail) {
 }
 
 int few_raise_lds() {
+    for (int nb = 1; nb <= 4; nb <<= 1)
+        for (int way = 0; way < 3; ++way)
+            for (const FewFn fn : {line_kernel<bf16_t>(nb, way), line_kernel<float>(nb, way)})
+                if (fn != nullptr)
+                    XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                     static_cast<int>(kLineLds)));
     for (int nb = 2; nb <= 8; nb <<= 1)
         for (int tail = 0; tail < 2; ++tail)
             XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(half_kernel(nb, tail != 0)),
@@ -1180,11 +1385,23 @@ static void launch_finish(const FewArgs& a, hipStream_t st) {
     else few_finish_kernel<T, 1024, HALF><<<n, 1024, 0, st>>>(a);
 }
 
+// Rows of whole lines that one block of queries reads once, from a W that the last-level cache does not hold, leave the caches at once.
+// us without and with that: 32 queries x 1.3 M x 768 452 and 400, 64 x 3 M x 256 432 and 393, 2 x 500 000 x 384 94 and 91, 32 x 131 072 x 768 (201 MB) 52
+// and 52; but rows of 400 bytes, whose lines two loads share, 483 and 640, and several blocks of queries (1000 x 50 000 x 256) 105 and 117.
+static int line_way(const FewArgs& a, int n_qb) {
+    if (a.row_bytes % 128 != 0) return 1;
+    return n_qb == 1 && reinterpret_cast<uintptr_t>(a.W) % 128 == 0 && a.L * a.row_bytes > (256ll << 20) ? 2 : 0;
+}
+
 template <typename T>
 static int launch_few(const FewPlan& p, const FewArgs& a, hipStream_t st) {
-    const FewFn fn = few_kernel<T>(p.nb, a.row_bytes % 64 != 0);
-    const dim3 grid = few_grid(p.lds, p.n_qb, a.L);
-    XC_LAUNCH(K_MINE_TILE, st, (fn<<<grid, kFewThreads, p.lds, st>>>(a)));
+    // lines of W where the rows have them, and the stages fit LDS beside the queries
+    const size_t line_lds = static_cast<size_t>(p.nb) * ((p.ks + 1) & ~1) * 1024 + kFewWaves * kFewStage;
+    const bool lines = line_kernel<T>(p.nb, 0) != nullptr && a.row_bytes >= 128 && line_lds <= kLineLds;
+    const FewFn fn = lines ? line_kernel<T>(p.nb, line_way(a, p.n_qb)) : few_kernel<T>(p.nb, a.row_bytes % 64 != 0);
+    const size_t lds = lines ? line_lds : p.lds;
+    const dim3 grid = few_grid(lds, p.n_qb, a.L);
+    XC_LAUNCH(K_MINE_TILE, st, (fn<<<grid, kFewThreads, lds, st>>>(a)));
     XC_HIP_CHECK(hipGetLastError());
     XC_LAUNCH(K_MINE_SELECT, st, (launch_finish<T, false>(a, st)));
     XC_HIP_CHECK(hipGetLastError());

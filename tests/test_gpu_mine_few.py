@@ -97,3 +97,25 @@ def test_few_queries_warm_call_needs_no_repeat():
     assert ws[:8].view(torch.int32).cpu().tolist() == [0, 0]
     b = _run(Z, W, k)
     assert (a[0] == b[0]).all() and (a[1] == b[1]).all()
+
+
+@pytest.mark.parametrize("Zq,L,d,k,dtype", [
+    (1, 4097, 64, 5, torch.bfloat16), (16, 5001, 72, 30, torch.bfloat16), (17, 5021, 120, 30, torch.bfloat16),     # one stage; two, of which the
+    (33, 5033, 136, 30, torch.bfloat16), (65, 33, 1032, 30, torch.bfloat16),                       # second has one chunk, ...; fewer tiles than waves
+    (64, 30011, 768, 20, torch.bfloat16), (8, 5003, 2304, 20, torch.bfloat16),                     # no room for the stages; one block of queries
+    (20, 2200003, 64, 100, torch.bfloat16), (3, 400011, 384, 9, torch.bfloat16),                   # read past the caches, groups of 32 labels
+    (1, 4099, 32, 5, torch.float32), (16, 5003, 100, 60, torch.float32), (9, 150001, 512, 20, torch.float32),
+])
+@pytest.mark.parametrize("shift", [0, 8])
+def test_rows_read_by_lines(monkeypatch, Zq, L, d, k, dtype, shift):
+    """The ids and scores of the general kernel, also where the rows of W begin within a line (W 16 or 32 bytes off)."""
+    import paper_2409_20156_amd as xc
+    Z = synth.make_matrix(91, synth.TAG_Z, Zq, d, dtype, DEV)
+    W = torch.empty(L * d + shift, dtype=dtype, device=DEV)[shift:].view(L, d)
+    W.copy_(synth.make_matrix(91, synth.TAG_W, L, d, dtype, DEV))
+    ids, sc = (t.clone() for t in xc.mine_negatives(Z, W, k, want_scores=True))
+    monkeypatch.setenv("XC_MINE_GENERAL", "1")
+    want, want_sc = xc.mine_negatives(Z, W, k, want_scores=True)
+    monkeypatch.delenv("XC_MINE_GENERAL")
+    assert torch.equal(ids, want)
+    assert torch.equal(sc, want_sc)
