@@ -872,18 +872,69 @@ void heads_write_kernel(const uint2* __restrict__ pairs, int64_t P, int64_t chun
 // ---------------------------------------------------------------------------
 // The whole pair sort, the segment heads and the lists of a small step in one workgroup (sort_in_one).
 // Bound: launches.  The five kernels above take 5 us each whatever the size; 800 pairs (32 queries of 25 candidates),
-// fp32 rows of 64: step 35.6 -> 23.8 us.
+// fp32 rows of 64: step 35.6 -> 20.5 us.
 // A pair is one integer, key << ib | pair index (all different, so any sorting network is stable), held E to a thread in a
 // bitonic network: neighbours within a thread, within a wave by lane exchange, further away through LDS.
 // ---------------------------------------------------------------------------
 constexpr int kSmallThreads = 1024;
 
-template <typename K> __device__ __forceinline__ K lane_xor(K v, int off);
-template <> __device__ __forceinline__ uint32_t lane_xor<uint32_t>(uint32_t v, int off) { return __shfl_xor(v, off, kWave); }
-template <> __device__ __forceinline__ uint64_t lane_xor<uint64_t>(uint64_t v, int off) {
-    const uint32_t lo = __shfl_xor(static_cast<uint32_t>(v), off, kWave);
-    const uint32_t hi = __shfl_xor(static_cast<uint32_t>(v >> 32), off, kWave);
+// v of lane ^ OFF.  Within 16 lanes by the vector unit's own lane patterns: an exchange through the LDS crossbar takes ten times as long, and
+// a network of 1024 has 45 of them in a row (with this and all sizes fixed at compile time sort_small_kernel takes 6.7 us for 800 pairs, 10.9 before).
+template <int OFF>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+    const int x = static_cast<int>(v);
+    int o;
+    if constexpr (OFF == 1) o = __builtin_amdgcn_mov_dpp(x, 0xB1 /* quad_perm 1 0 3 2 */, 0xf, 0xf, true);
+    else if constexpr (OFF == 2) o = __builtin_amdgcn_mov_dpp(x, 0x4E /* quad_perm 2 3 0 1 */, 0xf, 0xf, true);
+    else if constexpr (OFF == 4) o = __builtin_amdgcn_mov_dpp(__builtin_amdgcn_mov_dpp(x, 0x1B /* quad_perm 3 2 1 0 */, 0xf, 0xf, true), 0x141 /* row_half_mirror */, 0xf, 0xf, true);
+    else if constexpr (OFF == 8) o = __builtin_amdgcn_mov_dpp(x, 0x128 /* row_ror 8 */, 0xf, 0xf, true);
+    else if constexpr (OFF == 16) o = __builtin_amdgcn_ds_swizzle(x, 0x401F /* xor 16 */);
+    else o = __shfl_xor(x, OFF, kWave);
+    return static_cast<uint32_t>(o);
+}
+template <int OFF>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t v) {
+    const uint32_t lo = lane_xor<OFF>(static_cast<uint32_t>(v)), hi = lane_xor<OFF>(static_cast<uint32_t>(v >> 32));
     return (static_cast<uint64_t>(hi) << 32) | lo;
+}
+
+// The bitonic network from runs of SIZE at distance STRIDE on: element e = tid E + j takes part in a run of SIZE, ascending where bit
+// SIZE of e is 0.
+template <typename K, int E, int SIZE, int STRIDE>
+__device__ __forceinline__ void bitonic_from(K (&v)[E], K* arr, int tid) {
+    if constexpr (STRIDE >= kWave * E) {                             // other waves
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < E; ++j) arr[j * kSmallThreads + tid] = v[j];
+        __syncthreads();
+        const int other = tid ^ (STRIDE / E);
+        const bool low = (tid & (STRIDE / E)) == 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const bool up = ((tid * E + j) & SIZE) == 0;
+            const K o = arr[j * kSmallThreads + other];
+            v[j] = (low == up) == (o < v[j]) ? o : v[j];
+        }
+    } else if constexpr (STRIDE >= E) {                              // other lanes
+        const bool low = (tid & (STRIDE / E)) == 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const bool up = ((tid * E + j) & SIZE) == 0;
+            const K o = lane_xor<STRIDE / E>(v[j]);
+            v[j] = (low == up) == (o < v[j]) ? o : v[j];
+        }
+    } else {                                                         // this thread
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            if ((j & STRIDE) == 0) {
+                const bool up = ((tid * E + j) & SIZE) == 0;
+                const K a = v[j], b = v[j | STRIDE];
+                if ((a > b) == up) { v[j] = b; v[j | STRIDE] = a; }
+            }
+        }
+    }
+    if constexpr (STRIDE > 1) bitonic_from<K, E, SIZE, STRIDE / 2>(v, arr, tid);
+    else if constexpr (SIZE < kSmallThreads * E) bitonic_from<K, E, SIZE * 2, SIZE>(v, arr, tid);
 }
 
 template <typename K, int E>
@@ -903,48 +954,7 @@ void sort_small_kernel(const KeySource ks, int P, int ib, uint2* __restrict__ pa
         const int p = tid * E + j;
         v[j] = p < P ? (static_cast<K>(pair_key(ks, static_cast<uint32_t>(p))) << ib) | static_cast<K>(p) : ~static_cast<K>(0);
     }
-    // element e = tid E + j takes part in a run of `size`, ascending where bit `size` of e is 0
-    for (int size = 2; size <= N; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            if (stride >= kWave * E) {                               // other waves
-                __syncthreads();
-#pragma unroll
-                for (int j = 0; j < E; ++j) arr[j * kSmallThreads + tid] = v[j];
-                __syncthreads();
-                const int other = tid ^ (stride / E);
-                const bool low = (tid & (stride / E)) == 0;
-#pragma unroll
-                for (int j = 0; j < E; ++j) {
-                    const bool up = ((tid * E + j) & size) == 0;
-                    const K o = arr[j * kSmallThreads + other];
-                    v[j] = (low == up) == (o < v[j]) ? o : v[j];
-                }
-            } else if (stride >= E) {                                // other lanes
-                const int off = stride / E;
-                const bool low = (tid & off) == 0;
-#pragma unroll
-                for (int j = 0; j < E; ++j) {
-                    const bool up = ((tid * E + j) & size) == 0;
-                    const K o = lane_xor<K>(v[j], off);
-                    v[j] = (low == up) == (o < v[j]) ? o : v[j];
-                }
-            } else {                                                 // this thread
-#pragma unroll
-                for (int s = E / 2; s > 0; s >>= 1) {
-                    if (s == stride) {
-#pragma unroll
-                        for (int j = 0; j < E; ++j) {
-                            if ((j & s) == 0) {
-                                const bool up = ((tid * E + j) & size) == 0;
-                                const K a = v[j], b = v[j | s];
-                                if ((a > b) == up) { v[j] = b; v[j | s] = a; }
-                            }
-                        }
-                    }
-                }
-            }
-        }
-    }
+    bitonic_from<K, E, 2, 1>(v, arr, tid);
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < E; ++j) arr[tid * E + j] = v[j];
