@@ -1392,13 +1392,10 @@ static int plan_step(int64_t B, int64_t L, int d, int k_p, int n_neg, xc_dtype t
     return XC_OK;
 }
 
-// Up to 2 pairs per thread always, up to 4 where the keys are so wide that the alternative sorts in rounds instead of one
-// round and buckets.  Step with the one workgroup and with the other kernels, us, bf16 rows of 64, BCE: 1000 pairs over 1 M labels
-// 23.2 : 37.4, 2040 28.5 : 38.3, 2100 42.3 : 37.0, 4080 47.3 : 39.7; over 4096 labels 2040 29.5 : 37.4, 2100 35.9 : 32.7; over 10 M
-// labels 2100 42.3 : 52.3, 4080 47.0 : 53.3.
-static bool sort_in_one(const StepPlan& pl) {
-    return pl.P <= 2 * kSmallThreads || (pl.P <= 4 * kSmallThreads && pl.n_buckets == 0);
-}
+// Up to 4 pairs per thread.  Step with the one workgroup and with the other kernels, us, bf16 rows of 64, BCE: 2100 pairs over 4096 labels
+// 28.7 : 32.5, over 1 M 33.6 : 39.0, over 10 M 33.0 : 52; 4080 pairs 32.1 : 36.3, 37.3 : 40.6, 37.1 : 53; rows of 768, 131 072 labels, 4080 pairs
+// 38.7 : 39.3.
+static bool sort_in_one(const StepPlan& pl) { return pl.P <= 4 * kSmallThreads; }
 
 template <typename T, int KIND>
 static void launch_gather(const StepPlan& pl, hipStream_t st, const void* Z, void* W, int64_t B,
@@ -1563,7 +1560,7 @@ static int step_impl(const void* Z, void* W, int64_t B, int64_t L, int d, const 
         const bool narrow = pl.key_bits + ib < 32;           // (below 32: the padding element stays larger than every pair)
         if (n <= kSmallThreads) { if (narrow) XC_SORT_SMALL(uint32_t, 1); else XC_SORT_SMALL(uint64_t, 1); }
         else if (n <= 2 * kSmallThreads) { if (narrow) XC_SORT_SMALL(uint32_t, 2); else XC_SORT_SMALL(uint64_t, 2); }
-        else XC_SORT_SMALL(uint64_t, 4);                     // (wide keys only)
+        else { if (narrow) XC_SORT_SMALL(uint32_t, 4); else XC_SORT_SMALL(uint64_t, 4); }
 #undef XC_SORT_SMALL
         XC_HIP_CHECK(hipGetLastError());
     } else if (pl.n_buckets > 0) {
