@@ -1,11 +1,12 @@
 // The search for few queries: the same exact top-k as xc_mine.hip (score of Sec. 2.1) where the work is
 // reading W once, not the products.  Inference over a handful of queries, small pools.
 //
-//   few_line_kernel    streams W once (few_max_kernel rows of under 128 bytes and very long ones).  A wave multiplies 32 labels with all queries of the workgroup, whose
-//       rows lie in LDS as MFMA operands, and keeps of every group of 16 << gshift labels the largest score per
+//   few_line_kernel    streams W once (few_max_kernel rows of under 128 bytes and very long ones; few_half_kernel
+//       more than 16 fp32 queries).  A wave multiplies 32 labels with all queries of the workgroup, whose rows
+//       lie in LDS as MFMA operands, and keeps of every group of 16 << gshift labels the largest score per
 //       query: the only thing written, 1 / (16 << gshift) of the score matrix.
-//   few_finish_kernel  one workgroup per query: the k-th largest group maximum tau (one radix digit or more, then by
-//       counting).  At least k
+//   few_finish_kernel  one workgroup per query: the k-th largest group maximum tau (a bound from 256 part maxima, then
+//       by counting).  At least k
 //       labels score tau or more, so every label of the answer does, and it lies in a group whose maximum is
 //       above tau or, for scores equal to tau, in one of the first groups (in label order) whose maximum is tau:
 //       of equal scores the smaller ids win, and each of these groups holds one.  So k groups in all hold the
@@ -421,7 +422,7 @@ void few_line_kernel(const FewArgs a) {
     }
 }
 
-// The same in fp32 for more than 16 queries, with the operands of the tile kernels: lane (r, h) = (lane & 31, lane >> 5) holds
+// The same in fp32 for more than 16 queries, where the 16-bit maxima below did not settle them, with the operands of the tile kernels: lane (r, h) = (lane & 31, lane >> 5) holds
 // chunks 4 s + h and 4 s + 2 + h of row r.  Nothing is exchanged.  fp32 matrix instructions run on the vector unit, which the
 // exchanges of few_max_kernel and every address come out of: 600 queries x 300 000 x 768 4.55 ms with them, 3.93 without;
 // 2048 x 130 000 x 64 522 and 445 us; 256 x 1 M x 128 729 and 639; 1000 x 50 021 x 300 380 and 365.  An instruction loads 32 bytes of a row
