@@ -1206,6 +1206,7 @@ void few_finish_kernel(const FewArgs a) {
 // host side
 // ---------------------------------------------------------------------------
 constexpr int64_t kHalfFrom = 16;            // fp32: more queries than this take 16-bit maxima
+constexpr double kHalfGflop = 2.5;           // and more products
 constexpr int64_t kFewAlways = 96;           // up to so many queries always
 constexpr int64_t kFewQueries = 256;         // up to so many without limits on the work (one query tile of the other kernels)
 constexpr int64_t kFewMaxQueries = 2048;     // beyond that never
@@ -1303,7 +1304,7 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
     auto bytes = [&](int64_t groups) { return round_up(q * groups * 4, 256) + q * ns * kPartKeys * 8 + 2 * round_up(q * ns * 4, 256) + round_up(groups * 4, 256) + q * 8 + 4; };
     if (bytes(p->n_groups) > scratch) return false;
     p->hnb = 0;
-    if (f32 && Zq > kHalfFrom) {
+    if (f32 && Zq > kHalfFrom && 2e-9 * p->n_qb * p->nb * 16 * L * (row_bytes / 4) > kHalfGflop) {
         p->hks = static_cast<int>((row_bytes + 127) / 128);
         int hnb = 2;
         while (hnb < 8 && hnb * 16 < Zq && static_cast<size_t>(2 * hnb * p->hks) * 1024 + 2 * hnb * 64 <= kFewLds) hnb <<= 1;
