@@ -1206,7 +1206,9 @@ void few_finish_kernel(const FewArgs a) {
 // host side
 // ---------------------------------------------------------------------------
 constexpr int64_t kHalfFrom = 16;            // fp32: more queries than this take 16-bit maxima
-constexpr double kHalfGflop = 2.5;           // and more products
+// ... and more Gflop (blocks of 16 queries padded): below, the two launches that return at once cost more than fp32 products.  us, fp32 and 16-bit
+// maxima: 20 queries x 4096 x 64 19 and 27, 250 x 10 000 x 128 33 and 38, 100 x 20 000 x 256 43 and 47, 128 x 40 000 x 256 65 and 51, 250 x 20 000 x 256 70 and 48
+constexpr double kHalfGflop = 2.5;
 constexpr int64_t kFewAlways = 96;           // up to so many queries always
 constexpr int64_t kFewQueries = 256;         // up to so many without limits on the work (one query tile of the other kernels)
 constexpr int64_t kFewMaxQueries = 2048;     // beyond that never

@@ -25,9 +25,10 @@ def _inputs(Zq, L, d):
 
 
 @pytest.mark.parametrize("Zq,L,d,k", [
-    (17, 4096, 4, 1), (32, 5001, 28, 100),          # one block of 32 queries; a step of seven chunks, of one
-    (33, 5003, 32, 128), (64, 9001, 36, 7),         # four blocks of 16
-    (65, 8191, 300, 32), (128, 5021, 768, 20),      # eight; a query block that fits LDS with four
+    (17, 10000003, 4, 5), (32, 1400001, 28, 100),   # one block of 32 queries; a step of seven chunks, of one
+    (33, 700003, 32, 128), (64, 600001, 36, 7),     # four blocks of 16
+    (65, 50021, 300, 32), (128, 15021, 768, 20),    # eight; a query block that fits LDS with four
+    (17, 4096, 4, 5), (100, 20000, 256, 20),        # too few products: the fp32 kernels
     (129, 2100001, 8, 100),                         # groups of 32 labels
     (200, 130, 64, 128),                            # fewer groups than k
     (513, 30011, 100, 50), (1025, 20001, 300, 32),  # 256 threads per query at the end
@@ -39,7 +40,7 @@ def test_sizes(monkeypatch, Zq, L, d, k):
 @pytest.mark.parametrize("Zq", [40, 600])
 @pytest.mark.parametrize("rows", ["zero", "mostly zero", "equal", "pairs", "large", "tiny", "wide", "inf", "nan", "far", "queries"])
 def test_odd_rows(monkeypatch, Zq, rows):
-    L, d, k = 20011, 100, 32
+    L, d, k = 20011 if Zq > 100 else 200011, 100, 32
     Z, W = _inputs(Zq, L, d)
     if rows == "zero":
         W.zero_()
