@@ -159,7 +159,7 @@ void half_select_kernel(uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt
     const float4 zp = zpar[q];
     if (zp.w != kHalfPlain) return;
     const int n = gcnt[q];
-    if (n > glist_cap || over[1 + q / kBN] != 0) {       // given up: nothing reaches it any more
+    if (n > glist_cap || __builtin_amdgcn_readfirstlane(over[1 + q / kBN]) != 0) {       // given up: nothing reaches it any more
         if (lane == 0) {
             over[0] = 1; over[1 + q / kBN] = 1;
             gcnt[q] = 0;
@@ -202,7 +202,7 @@ void half_finish_kernel(const unsigned char* __restrict__ Z, const unsigned char
     };
     const float4 zp = zpar[q];
     int n = gcnt[q];
-    if (stats[1] != 0u || zp.w == kHalfBad || (zp.w == kHalfPlain && (n > glist_cap || over[1 + q / kBN] != 0))) {     // uniform
+    if (stats[1] != 0u || zp.w == kHalfBad || (zp.w == kHalfPlain && n > glist_cap)) {       // uniform (nothing writes these here)
         if (tid == 0) { over[0] = 1; over[1 + q / kBN] = 1; }
         return;
     }
@@ -224,8 +224,11 @@ void half_finish_kernel(const unsigned char* __restrict__ Z, const unsigned char
     }
     float base = zp.y;
     if (wave == 0) {
+        // The other queries' workgroups set the tile's word meanwhile: what one wave reads holds for all of them (two waves that read
+        // for themselves could part here, one gone and one at the barrier with an n that nobody wrote).
         float thr;
-        n = half_prune(list, n, k, half_query_error(zp, stats, row_bytes / 4), &base, &thr, hist, srt);
+        n = __builtin_amdgcn_readfirstlane(over[1 + q / kBN]) != 0
+                ? 0 : half_prune(list, n, k, half_query_error(zp, stats, row_bytes / 4), &base, &thr, hist, srt);
         if (WQ > 1 && lane == 0) { n_sh = n; base_sh = base; }
     }
     meet();

@@ -154,3 +154,27 @@ def test_many_queries_odd_rows(monkeypatch, rows):
 def test_thresholds_too_high_are_repeated(monkeypatch):
     Z, W = _inputs(3000, 30000, 320)
     assert _thresholds(monkeypatch, Z, W, 50, 0.0) == 1
+
+
+@pytest.mark.parametrize("Zq", [300, 700, 2000])
+def test_unsettled_queries_beside_settled_ones(monkeypatch, Zq):
+    """Fewer than 2048 queries: the four waves of a query agree on whether its tile is given up, whatever the other queries of the tile
+    find out meanwhile.  From thresholds that are too high for some queries of every tile, with a query that is no number and one
+    out of fp16's range."""
+    import paper_2409_20156_amd as xc
+    L, d, k = 60001, 320, 32
+    Z, W = _inputs(Zq, L, d)
+    ws = torch.empty(xc.mine_workspace(Zq, L, d, k, xc.XC_F32), dtype=torch.uint8, device=DEV)
+    for margin in (0.0, 0.02, 0.1):
+        xc.mine_negatives(Z, W, k, workspace=ws)                # (the thresholds; from scratch these may come from another kernel)
+        Y = Z.clone()
+        Y[::37] *= 0.9                                          # these queries' scores sink below their thresholds
+        Y[11, 5] = float("nan")
+        Y[Zq - 5] *= 1e25
+        ids, sc = (t.clone() for t in xc.mine_negatives(Y, W, k, want_scores=True, workspace=ws, warm_margin=margin))
+        assert int(ws[:4].view(torch.int32).item()) == 1
+        monkeypatch.setenv("XC_MINE_GENERAL", "1")
+        want, want_sc = xc.mine_negatives(Y, W, k, want_scores=True)
+        monkeypatch.delenv("XC_MINE_GENERAL")
+        assert torch.equal(ids, want)
+        assert torch.equal(sc.view(torch.int32), want_sc.view(torch.int32))
