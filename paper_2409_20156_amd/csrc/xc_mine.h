@@ -235,10 +235,11 @@ struct FewPlan {
 // `half`: the search of many queries on fp16 copies (xc_mine_half.h) is the alternative.
 bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool warm, bool half, size_t scratch, FewPlan* p);
 
+constexpr int kRedoWord = 32;        // redo_any among the words of the search's flags (the tiles of so few queries take nine)
 int few_raise_lds();         // the dynamic LDS limit of its kernels, on the current device
 int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int64_t L, int64_t row_bytes, int k,
                  xc_dtype t, unsigned char* scratch, uint32_t* tau_g, int32_t* flag /* null: leave alone */, int n_flag,
-                 int32_t* shortlist, float* scores, hipStream_t st);
+                 int32_t* redo_any /* 1 afterwards if 16-bit maxima left a query to the fp32 kernels, 0 if none */, int32_t* shortlist, float* scores, hipStream_t st);
 
 // ---- the 8-bit filter (xc_mine_q8.hip)
 constexpr int64_t kQ8MinQueries = 4096, kQ8MinLabels = 1 << 20;

@@ -1440,7 +1440,8 @@ static int plan_mine(int64_t Zq, int64_t L, int d, int k_h, xc_dtype t, MinePlan
     size_t off = 0;
     auto take = [&off](size_t bytes) { size_t o = off; off += round_up(bytes, 256); return o; };
     const size_t nq = static_cast<size_t>(p->nQT) * kBN;
-    // first word: 1 if the last warm search had to repeat the full search for some query tile; then one word per tile
+    // first word: 1 if the last warm search had to repeat the full search for some query tile; then one word per tile (rounded up to 64
+    // words: few queries have kRedoWord behind them)
     p->off_flag = take(4 * (static_cast<size_t>(p->nQT) + 1));
     p->off_lists = take(static_cast<size_t>(kMineGrid) * kBN * kCandCap * sizeof(uint64_t));
     p->off_glist = take(nq * p->glist_cap * sizeof(uint64_t));
@@ -1553,7 +1554,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     if (!(warm && Zq > kBN) && !force_general_kernel() && !force_rows_layout() &&
         plan_few(Zq, L, a.row_bytes, k_h, t, warm, half, p.off_glist - p.off_lists, &few))
         return run_mine_few(few, Z, W, Zq, L, a.row_bytes, k_h, t, w8 + p.off_lists, tau_g,
-                            warm ? flag : nullptr, static_cast<int>(p.nQT) + 1, shortlist, scores, st);
+                            warm ? flag : nullptr, static_cast<int>(p.nQT) + 1, flag + kRedoWord, shortlist, scores, st);
 
     const int64_t nq = p.nQT * kBN;
     const dim3 init_grid(static_cast<unsigned>((nq + 255) / 256));

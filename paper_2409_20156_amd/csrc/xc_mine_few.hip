@@ -61,8 +61,9 @@ struct FewArgs {
     int32_t* part_n;             // [Zq][n_split]
     int32_t* done;               // [Zq] how many of them are through (cleared by the first kernel)
     float* gnorm;                // 16-bit maxima: [n_groups] largest |w| of the group
-    int32_t* redo;               // 16-bit maxima: [0] 1 if any query has to be searched again in fp32, [1 + q] 1 if q has (cleared by the first kernel)
-    int again;                   // 1: this is that search: only queries with redo[1 + q]
+    int32_t* redo_any;           // 16-bit maxima: 1 if any query has to be searched again in fp32 (cleared by the first kernel),
+    int32_t* redo;               // [Zq] 1 if q has
+    int again;                   // 1: this is that search: only queries with redo[q]
 };
 
 // ordered image of a score; 0 (below every number) for NaN.  -0 counts as +0, as in the result.
@@ -70,9 +71,9 @@ __device__ __forceinline__ uint32_t score_image(float v) { return v == v ? float
 
 // Whether one of the queries [q0, q0 + n) has to be searched again; workgroup 0 of such a launch goes on in any case (it clears the counters).
 __device__ __forceinline__ bool few_again(const FewArgs& a, int64_t q0, int n) {
-    if (a.redo[0] == 0) return false;
+    if (a.redo_any[0] == 0) return false;
     bool any = blockIdx.x == 0;
-    for (int i = 0; i < n && q0 + i < a.Zq; ++i) any = any || a.redo[1 + q0 + i] != 0;
+    for (int i = 0; i < n && q0 + i < a.Zq; ++i) any = any || a.redo[q0 + i] != 0;
     return any;
 }
 
@@ -674,8 +675,8 @@ void few_half_kernel(const FewArgs a) {
         }
     }
     if (id == 0) {
-        for (int64_t i = tid; i < a.Zq; i += kFewThreads) a.done[i] = 0;
-        for (int64_t i = tid; i <= a.Zq; i += kFewThreads) a.redo[i] = 0;
+        for (int64_t i = tid; i < a.Zq; i += kFewThreads) { a.done[i] = 0; a.redo[i] = 0; }
+        if (tid == 0) a.redo_any[0] = 0;
     }
     __syncthreads();
     if (unit >= n_units) return;                                // (no barrier below)
@@ -872,7 +873,7 @@ void few_finish_kernel(const FewArgs a) {
     const int64_t q = blockIdx.x / a.n_split;
     const int split = blockIdx.x % a.n_split;
     const uint32_t* gm = a.gmax + q * a.n_groups;
-    if (!HALF && a.again && a.redo[1 + q] == 0) return;        // uniform
+    if (!HALF && a.again && a.redo[q] == 0) return;        // uniform
     if (a.flag != nullptr && blockIdx.x == 0)
         for (int i = tid; i < a.n_flag; i += NT) a.flag[i] = 0;
 
@@ -908,8 +909,8 @@ void few_finish_kernel(const FewArgs a) {
     // the query's norm, and what a group's norm is multiplied with to give the error of its maximum
     float zn = 0.0f;
     auto redo = [&]() {                                        // (every thread that gets here writes the same)
-        a.redo[0] = 1;
-        a.redo[1 + q] = 1;
+        a.redo_any[0] = 1;
+        a.redo[q] = 1;
     };
     if constexpr (HALF) {
         float s2 = 0.0f, zmax = 0.0f;
@@ -1125,6 +1126,7 @@ void few_finish_kernel(const FewArgs a) {
     if constexpr (HALF) {
         // ---- the other groups whose maximum, with its error, reaches the k-th best so far (of equal scores the smaller label)
         if (n < a.k) { redo(); return; }                       // uniform (scores that are no numbers)
+        __syncthreads();                                       // every wave has read n_key, which starts again below
         if (n <= kRankSort) {
             for (int m = tid; m < n; m += NT) {
                 const uint64_t mine = keys[m];
@@ -1434,8 +1436,8 @@ static int launch_half(const FewPlan& p, const FewArgs& exact, hipStream_t st) {
 }
 
 int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int64_t L, int64_t row_bytes, int k,
-                 xc_dtype t, unsigned char* scratch, uint32_t* tau_g, int32_t* flag, int n_flag, int32_t* shortlist,
-                 float* scores, hipStream_t st) {
+                 xc_dtype t, unsigned char* scratch, uint32_t* tau_g, int32_t* flag, int n_flag, int32_t* redo_any,
+                 int32_t* shortlist, float* scores, hipStream_t st) {
     FewArgs a;
     a.Z = static_cast<const unsigned char*>(Z);
     a.W = static_cast<const unsigned char*>(W);
@@ -1446,6 +1448,7 @@ int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int
     a.shortlist = shortlist; a.scores = scores;
     a.n_split = p.n_split;
     a.again = 0;
+    a.redo_any = redo_any;
     const int64_t most_groups = p.hnb > 0 && p.hn_groups > p.n_groups ? p.hn_groups : p.n_groups;
     unsigned char* s = scratch;
     a.gmax = reinterpret_cast<uint32_t*>(s); s += round_up(static_cast<size_t>(Zq) * most_groups * 4, 256);
