@@ -1265,6 +1265,10 @@ static double others_half_us(int64_t Zq, int64_t L, int64_t row_bytes, int k) {
     return 142.0 + 0.075e-9 * 2.0 * nq * L * (row_bytes / 4) + 0.70e-6 * L * row_bytes + 1.07e-3 * zk + 0.386e-6 * nq * L + 0.235e-6 * zk * row_bytes;
 }
 
+// Scratch: maxima, candidates of shared queries and the counts that go with these; with 16-bit maxima the groups' norms and a word per query.
+static size_t few_bytes(size_t q, int64_t groups, int ns) { return round_up(q * groups * 4, 256) + q * ns * kPartKeys * 8 + round_up(q * ns * 4, 256) + q * 4; }
+static size_t few_half_bytes(size_t q, int64_t groups) { return 256 + round_up(static_cast<size_t>(groups) * 4, 256) + q * 4; }
+
 // Which searches come here.  Up to 96 queries (less than half of a query tile of the general kernel) all whose query block fits LDS:
 // 131 072 x 768 bf16, k = 5: 71 us against 408 at 64 queries; 4 M x 256 bf16, k = 50: 0.65 ms against 1.57.  More queries
 // cost this path time in proportion (it multiplies W once per block of at most 64), the others almost nothing until their tiles of
@@ -1305,8 +1309,7 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
     while (ns < kMaxSplit && Zq * ns * 2 <= 256 && (static_cast<int64_t>(k) << gs) > ns * Finish<1024>::kWaves) ns <<= 1;
     p->n_split = ns;
     const size_t q = static_cast<size_t>(Zq);
-    auto bytes = [&](int64_t groups) { return round_up(q * groups * 4, 256) + q * ns * kPartKeys * 8 + 2 * round_up(q * ns * 4, 256) + round_up(groups * 4, 256) + q * 8 + 4; };
-    if (bytes(p->n_groups) > scratch) return false;
+    if (few_bytes(q, p->n_groups, ns) > scratch) return false;
     p->hnb = 0;
     if (f32 && Zq > kHalfFrom && 2e-9 * p->n_qb * p->nb * 16 * L * (row_bytes / 4) > kHalfGflop) {
         p->hks = static_cast<int>((row_bytes + 127) / 128);
@@ -1316,7 +1319,7 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
         p->hn_qb = static_cast<int>((Zq + hnb * 16 - 1) / (hnb * 16));
         p->hgshift = gs == 0 ? -1 : gs;
         p->hn_groups = gs == 0 ? (L + 7) / 8 : p->n_groups;
-        if (p->hlds <= kFewLds && bytes(p->hn_groups) <= scratch) p->hnb = hnb;
+        if (p->hlds <= kFewLds && few_bytes(q, p->hn_groups, ns) + few_half_bytes(q, p->hn_groups) <= scratch) p->hnb = hnb;
     }
     if (!always && f32 && half && (p->hnb == 0 || few_half_us(*p, Zq, L, row_bytes, k) >= others_half_us(Zq, L, row_bytes, k))) return false;
     return true;
@@ -1454,8 +1457,8 @@ int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int
     a.gmax = reinterpret_cast<uint32_t*>(s); s += round_up(static_cast<size_t>(Zq) * most_groups * 4, 256);
     a.part = reinterpret_cast<uint64_t*>(s); s += static_cast<size_t>(Zq) * p.n_split * kPartKeys * 8;
     a.part_n = reinterpret_cast<int32_t*>(s); s += round_up(static_cast<size_t>(Zq) * p.n_split * 4, 256);
-    a.gnorm = reinterpret_cast<float*>(s); s += round_up(static_cast<size_t>(most_groups) * 4, 256);
-    a.done = reinterpret_cast<int32_t*>(s); s += static_cast<size_t>(Zq) * 4;
+    a.done = reinterpret_cast<int32_t*>(s); s += round_up(static_cast<size_t>(Zq) * 4, 256);
+    a.gnorm = reinterpret_cast<float*>(s); s += round_up(static_cast<size_t>(most_groups) * 4, 256);     // (these two only with 16-bit maxima)
     a.redo = reinterpret_cast<int32_t*>(s);
     if (t == XC_BF16) return launch_few<bf16_t>(p, a, st);
     return p.hnb > 0 ? launch_half(p, a, st) : launch_few<float>(p, a, st);

@@ -119,3 +119,25 @@ def test_rows_read_by_lines(monkeypatch, Zq, L, d, k, dtype, shift):
     monkeypatch.delenv("XC_MINE_GENERAL")
     assert torch.equal(ids, want)
     assert torch.equal(sc, want_sc)
+
+
+def test_few_queries_up_to_the_scratch_limit():
+    """The group maxima fill the lists' 512 MiB but for 3 MB: what 16-bit maxima of fp32 rows need beside them does not
+    count for bf16 rows (one launch that reads W, not phases)."""
+    import paper_2409_20156_amd as xc
+    from paper_2409_20156_amd import binding
+    Zq, L, d, k = 96, 1390000 * 256, 8, 5
+    W = torch.empty((L, d), dtype=torch.bfloat16, device=DEV).normal_(0.0, d ** -0.5)
+    Z = synth.make_matrix(7, synth.TAG_Z, Zq, d, torch.bfloat16, DEV)
+    W[-7:] = 4.0 * W[-7:]
+    binding.profile_reset()
+    binding.profile_enable(True)
+    ids, sc = xc.mine_negatives(Z, W, k, want_scores=True)
+    binding.profile_enable(False)
+    torch.cuda.synchronize()
+    prof = binding.profile_collect()
+    assert prof["mine_tile"][1] == 1 and prof["mine_select"][1] == 1
+    best = torch.zeros((Zq, 0), device=DEV)
+    for r in range(0, L, 1 << 22):
+        best = torch.cat([best, torch.topk(Z.float() @ W[r:r + (1 << 22)].float().T, k, dim=1)[0]], dim=1).topk(k, dim=1)[0]
+    assert torch.allclose(sc, best, rtol=1e-5, atol=1e-6)
