@@ -148,6 +148,26 @@ constexpr float kHalfLeast = 1e-15f, kHalfMost = 1e15f;      // largest elements
 __device__ __forceinline__ float half_error(int d) { return (2.0f / 2048.0f) * 1.01f + 6.0f * static_cast<float>(d) * 5.97e-8f; }
 __device__ __forceinline__ float half_error_small(int d) { return 1.0e-6f * sqrtf(static_cast<float>(d)); }
 
+// The errors of the tiles' scores from fp16 copies: range holds the bits of the largest and of the smallest that is not zero (of any wave's share
+// of a tile).  Within four of each other the largest stands for all: returned.  Else -1: each tile has its own.
+__device__ __forceinline__ float half_error_of_all(const uint32_t* range) {
+    const float most = __uint_as_float(range[0]), least = __uint_as_float(range[1]);
+    return most <= 4.0f * least ? most : -1.0f;
+}
+
+// p[i], the same for the whole wave and written before this launch, by a scalar load that is awaited here (a vector load's wait would be one
+// for every stage load under way).
+__device__ __forceinline__ float uniform_load(const float* p, int64_t i) {
+    typedef const __attribute__((address_space(4))) uint32_t* const_ptr;
+    const uint64_t at = reinterpret_cast<uint64_t>(p + i);
+    const uint64_t u = (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(at >> 32)))) << 32) |
+                       static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(at))));
+    uint32_t v = *reinterpret_cast<const_ptr>(u);
+    v = __builtin_amdgcn_readfirstlane(v);
+    asm volatile("" : "+s"(v));
+    return __uint_as_float(v);
+}
+
 constexpr int kRing = 8;            // stages in LDS (8 or 16 KiB each)
 static_assert(kRing >= 4 && (kRing & (kRing - 1)) == 0, "stage slots are indexed modulo a power of two, and the two halves of the workgroup fill them in turn");
 

@@ -145,7 +145,10 @@ struct MineArgs {
     int dense_ld;
     const int32_t* cond;     // not null: repeat of a warm search; cond[0] != 0 if any query tile needs it,
                              // cond[1 + qt] != 0 if query tile qt does
-    int32_t* over;           // fp16 copies: [0] and [1 + qt] are set when query tile qt is given up (a list ran over)
+    // fp16 copies: tau_g holds scores that k labels are known to reach; a label passes if its 16-bit score is below by no more than its error
+    const float* tile_err;   // [label tile] the error, for every query
+    const uint32_t* err_range;   // the errors' range, see half_error_of_all
+    int32_t* over;           // [0] and [1 + qt] are set when query tile qt is given up (a list ran over)
     const int32_t* items;    // not null (row kernel): only these work items, [0] their number, [1] slices per XCD, [2..] the items
 };
 
@@ -187,6 +190,7 @@ void mine_tile_kernel(const MineArgs a) {
     float* tau = reinterpret_cast<float*>(smem + 2 * kStageBuf);
     int* cnt = reinterpret_cast<int*>(tau + kBN);
     int* hist = cnt + kBN;                                   // [kMineWaves][256]
+    constexpr bool kHalf = std::is_same<T, half_t>::value;
     uint2* pools = reinterpret_cast<uint2*>(hist + kMineWaves * 256);       // [kMineWaves][kPool]
     int* dirty = reinterpret_cast<int*>(pools + kMineWaves * kPool);        // [2], by tile parity
     const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
@@ -357,6 +361,7 @@ void mine_tile_kernel(const MineArgs a) {
         uint2* pool = pools + wave * kPool;
         int fill = 0;
         int pool_tile = 0;                                   // labels in the pool count from this tile
+        const float err_all = kHalf && !DENSE ? half_error_of_all(a.err_range) : 0.0f;
         auto flush = [&]() {
             const int64_t l0 = (t_begin + pool_tile) * kBM;
 #pragma unroll 1
@@ -428,6 +433,10 @@ void mine_tile_kernel(const MineArgs a) {
 
             // ---- threshold filter: lane owns query column (lane & 31) of each N tile
             const bool last = tile + 1 == n_tiles;
+            float err = err_all;
+            if (kHalf && err_all < 0.0f) {                   // uniform
+                err = uniform_load(a.tile_err, t_begin + tile);
+            }
             // The flag this tile may set shares its slot with the flag of two tiles back, which the waves
             // read after the previous tile's filter: a barrier has to lie between that read and this
             // tile's filter.  Every tile has one in its main loop except a one-stage last tile.
@@ -436,7 +445,8 @@ void mine_tile_kernel(const MineArgs a) {
             auto filter = [&](auto ntc) {
                 constexpr int nt = decltype(ntc)::value;
                 const int qloc = wn * 64 + nt * 32 + (lane & 31);
-                const float t = (q0 + qloc) < a.Zq ? tau[qloc] : INFINITY;
+                float t = (q0 + qloc) < a.Zq ? tau[qloc] : INFINITY;
+                if (kHalf) t -= err;
                 // the largest score of each 32-label block, then of all: a block is looked through only if its own passes
                 // (late phases let through about one score per four blocks: 10 M x 120 bf16, 18 834 queries 69.4 -> 65.9 ms
                 // together with the smaller growth of these phases)
@@ -513,7 +523,7 @@ void mine_tile_kernel(const MineArgs a) {
                 const bool want = lane < 32 && qok &&
                                   (last ? n > a.append_max : n > kCandCap - 2 * kBM - 2 * kPoolKeep);
                 uint64_t todo = __ballot(want);
-                if (std::is_same<T, half_t>::value && todo != 0ull) {
+                if (kHalf && todo != 0ull) {
                     // scores that are not exact choose nothing: the query tile is left to the fp32 kernels
                     if (want) { tau[qloc] = INFINITY; cnt[qloc] = 0; n = 0; }
                     if (lane == 0) { a.over[0] = 1; a.over[1 + qtile] = 1; }
@@ -531,7 +541,7 @@ void mine_tile_kernel(const MineArgs a) {
                             lsel, [lsel](int idx) { return lsel[idx]; }, nsel, a.k, hist + wave * 256);
                         if (lane == src) { t_new = t; n = a.k; }
                     }
-                    if (!std::is_same<T, half_t>::value && want) { tau[qloc] = fmaxf(tau[qloc], t_new); cnt[qloc] = n; }
+                    if (!kHalf && want) { tau[qloc] = fmaxf(tau[qloc], t_new); cnt[qloc] = n; }
                     if (last) {
                         // ---- close the slice: append the survivors to the global list of each query
                         int base = 0;
@@ -627,10 +637,13 @@ static bool force_general_kernel() {
     return e != nullptr && e[0] == '1';
 }
 
-template <typename T, int NK, int WM>
+// fp16 copies: VARIED where each label tile has its own error, else one error for all.  Both forms are launched, and one returns at once (the
+// question asked where scores pass, or two ways in one kernel, cost rows of 128 to 512 bytes 3 to 9 %).
+template <typename T, int NK, int WM, bool VARIED>
 __global__ __launch_bounds__(kMineThreads, 1)
 void mine_rows_kernel(const MineArgs a) {
     static_assert(WM == 1 || WM == 2, "wave layouts");
+    constexpr bool kHalf = std::is_same<T, half_t>::value;
     constexpr int kRowTile = 64 * WM;                   // labels per tile
     constexpr int kRowStage = kRowTile * kStageBytes;   // bytes of a stage
     constexpr int kQN = (kMineWaves / WM) * 64;         // queries per work item
@@ -639,6 +652,7 @@ void mine_rows_kernel(const MineArgs a) {
     constexpr int kLd = 2 * WM;                         // load instructions of a wave per stage it brings in
     extern __shared__ __align__(16) unsigned char smem[];
     if (a.cond != nullptr && a.cond[0] == 0) return;          // uniform: a repeat that is not needed
+    if (kHalf && VARIED != (half_error_of_all(a.err_range) < 0.0f)) return;         // uniform
     int* cnt4 = reinterpret_cast<int*>(smem + kRing * kRowStage);            // [kQN][kOwn] list fills at the end of a slice
     int* hist = cnt4 + kBN * 4;                                             // [kMineWaves][256]
     const uint32_t lds_base = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(
@@ -727,6 +741,7 @@ void mine_rows_kernel(const MineArgs a) {
             const int64_t q = q0 + wn * 64 + nt * 32 + (lane & 31);
             const int64_t qc = q < a.Zq ? q : a.Zq - 1;
             tau[nt] = live(q) ? ordered_to_float(a.tau_g[q]) : INFINITY;
+            if (kHalf && !VARIED) tau[nt] -= half_error_of_all(a.err_range);
             const unsigned char* zr = a.Z + qc * row_bytes + half * 16;
 #pragma unroll
             for (int ks = 0; ks < NK * 4; ++ks) zf[ks][nt] = *reinterpret_cast<const uint4*>(zr + ks * 32);
@@ -810,9 +825,8 @@ void mine_rows_kernel(const MineArgs a) {
                 for (int i = 0; i < 16; ++i) mx = fmaxf(mx, acc[mt][nt][i]);
             return mx;
         };
-        auto push_block = [&](auto ntc, int64_t l0, float mx) {
+        auto push_block = [&](auto ntc, int64_t l0, float mx, float t) __attribute__((always_inline)) {
             constexpr int nt = decltype(ntc)::value;
-            const float t = tau[nt];
             if (__ballot(mx >= t) != 0ull) {
                 // Everything a push needs is formed here from the lane number, read afresh, and from wave-uniform
                 // values: a per-lane pointer or row number kept in a register over the main loop would be
@@ -838,7 +852,7 @@ void mine_rows_kernel(const MineArgs a) {
         };
         // ---- a list that the next tile could overflow: cut to its best k, by this wave alone
         auto cut_lists = [&]() {
-            if (std::is_same<T, half_t>::value) {            // (not exact: the query's tile is left to the fp32 kernels)
+            if (kHalf) {                                     // (not exact: the query's tile is left to the fp32 kernels)
 #pragma unroll
                 for (int nt = 0; nt < 2; ++nt)
                     if (cnt[nt] > kSubFull) {
@@ -908,10 +922,16 @@ void mine_rows_kernel(const MineArgs a) {
             }
             // one test per tile on the usual way: does any lane see a score at its threshold, or a list to cut?
             const float mx0 = block_max(IC<0>{}), mx1 = block_max(IC<1>{});
-            const bool look = mx0 >= tau[0] || mx1 >= tau[1] || cnt[0] > kSubFull || cnt[1] > kSubFull;
+            float t0 = tau[0], t1 = tau[1];
+            if (VARIED) {
+                const float err = uniform_load(a.tile_err, l0 / kBM);
+                t0 -= err;
+                t1 -= err;
+            }
+            const bool look = mx0 >= t0 || mx1 >= t1 || cnt[0] > kSubFull || cnt[1] > kSubFull;
             if (__builtin_expect(__ballot(look) != 0ull, 0)) {
-                push_block(IC<0>{}, l0, mx0);
-                push_block(IC<1>{}, l0, mx1);
+                push_block(IC<0>{}, l0, mx0, t0);
+                push_block(IC<1>{}, l0, mx1, t1);
                 cut_lists();
             }
         }
@@ -977,17 +997,16 @@ void mine_rows_kernel(const MineArgs a) {
 // SIMD and 512 registers each, the queries of rows up to 1 KiB fit as well; measured at 1 KiB rows that
 // ran 15 % slower than the general kernel - no second wave covers a wave's barrier and filter time.)
 typedef void (*RowsKernelFn)(const MineArgs);
-struct RowsKernel { RowsKernelFn fn; int nk, wm; bool half; };
+struct RowsKernel { RowsKernelFn fn; int nk, wm; bool half; RowsKernelFn varied; };
+#define XC_ROWS(NK, WM) {&mine_rows_kernel<bf16_t, NK, WM, false>, NK, WM, false, nullptr}
+#define XC_ROWS_HALF(NK, WM) {&mine_rows_kernel<half_t, NK, WM, false>, NK, WM, true, &mine_rows_kernel<half_t, NK, WM, true>}
 static const RowsKernel kRowsKernels[] = {
-    {&mine_rows_kernel<bf16_t, 1, 2>, 1, 2, false}, {&mine_rows_kernel<bf16_t, 2, 2>, 2, 2, false},
-    {&mine_rows_kernel<bf16_t, 3, 2>, 3, 2, false}, {&mine_rows_kernel<bf16_t, 4, 2>, 4, 2, false},
-    {&mine_rows_kernel<bf16_t, 1, 1>, 1, 1, false}, {&mine_rows_kernel<bf16_t, 2, 1>, 2, 1, false},
-    {&mine_rows_kernel<bf16_t, 3, 1>, 3, 1, false}, {&mine_rows_kernel<bf16_t, 4, 1>, 4, 1, false},
-    {&mine_rows_kernel<half_t, 1, 2>, 1, 2, true}, {&mine_rows_kernel<half_t, 2, 2>, 2, 2, true},
-    {&mine_rows_kernel<half_t, 3, 2>, 3, 2, true}, {&mine_rows_kernel<half_t, 4, 2>, 4, 2, true},
-    {&mine_rows_kernel<half_t, 1, 1>, 1, 1, true}, {&mine_rows_kernel<half_t, 2, 1>, 2, 1, true},
-    {&mine_rows_kernel<half_t, 3, 1>, 3, 1, true}, {&mine_rows_kernel<half_t, 4, 1>, 4, 1, true},
+    XC_ROWS(1, 2), XC_ROWS(2, 2), XC_ROWS(3, 2), XC_ROWS(4, 2), XC_ROWS(1, 1), XC_ROWS(2, 1), XC_ROWS(3, 1), XC_ROWS(4, 1),
+    XC_ROWS_HALF(1, 2), XC_ROWS_HALF(2, 2), XC_ROWS_HALF(3, 2), XC_ROWS_HALF(4, 2),
+    XC_ROWS_HALF(1, 1), XC_ROWS_HALF(2, 1), XC_ROWS_HALF(3, 1), XC_ROWS_HALF(4, 1),
 };
+#undef XC_ROWS
+#undef XC_ROWS_HALF
 static const RowsKernel* find_rows_kernel(int nk, int wm, bool half) {
     for (const RowsKernel& k : kRowsKernels)
         if (k.nk == nk && k.wm == wm && k.half == half) return &k;
@@ -1021,8 +1040,9 @@ __global__ void mine_warm_init_kernel(uint32_t* tau_g, int32_t* gcnt, int64_t n,
 // Radix select for lists too long for registers (n > 64*kSelectRegs): the keys
 // are streamed from memory in every pass.  Same result as wave_select_k.
 // ---------------------------------------------------------------------------
-// Bound such that exactly k of the n > k keys are at or below it.
-__device__ __noinline__ uint64_t wave_bound_stream(const uint64_t* __restrict__ buf, int n, int k, int* hist) {
+// Bound such that exactly k of the n > k keys load(0..n-1) are at or below it.
+template <typename Load>
+__device__ __noinline__ uint64_t wave_bound_stream(Load load, int n, int k, int* hist) {
     const int lane = lane_id();
     uint64_t prefix = 0, pmask = 0;
     int need = k;
@@ -1032,7 +1052,7 @@ __device__ __noinline__ uint64_t wave_bound_stream(const uint64_t* __restrict__ 
         for (int j = 0; j < 4; ++j) hist[lane * 4 + j] = 0;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
         for (int idx = lane; idx < n; idx += kWave) {
-            const uint64_t key = buf[idx];
+            const uint64_t key = load(idx);
             if ((key & pmask) == prefix) atomicAdd(&hist[static_cast<int>((key >> shift) & 255u)], 1);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
@@ -1070,7 +1090,7 @@ __device__ __noinline__ uint64_t wave_bound_stream(const uint64_t* __restrict__ 
 
 __device__ __noinline__ float wave_select_stream(uint64_t* __restrict__ buf, int n, int k, int* hist) {
     const int lane = lane_id();
-    const uint64_t bound = wave_bound_stream(buf, n, k, hist);
+    const uint64_t bound = wave_bound_stream([buf](int idx) { return buf[idx]; }, n, k, hist);
     // compaction in place: a chunk is read into registers before anything of it is
     // overwritten, and the write position never passes the read position
     uint64_t kmax = 0;
@@ -1167,7 +1187,8 @@ __device__ __forceinline__ uint32_t dense_image(float v) { return v == v ? float
 template <int R>
 __global__ __launch_bounds__(kSelectWaves * kWave)
 void mine_dense_select_kernel(const float* __restrict__ dense, int dense_ld, uint64_t* __restrict__ glist,
-                              int32_t* __restrict__ gcnt, uint32_t* __restrict__ tau_g, int64_t Zq, int glist_cap, int k) {
+                              int32_t* __restrict__ gcnt, uint32_t* __restrict__ tau_g, int64_t Zq, int glist_cap, int k,
+                              const float* __restrict__ tile_err /* not null: 16-bit scores, to be lowered by their errors */) {
     static_assert(R % 2 == 0 && R <= kDenseTiles, "");
     __shared__ int hist[kSelectWaves][256];
     __shared__ uint64_t picked[kSelectWaves][kDenseList];
@@ -1178,11 +1199,23 @@ void mine_dense_select_kernel(const float* __restrict__ dense, int dense_ld, uin
     uint64_t* list = glist + static_cast<size_t>(q) * glist_cap;
     // label of v[r][j]: 256 r + 4 lane + j; rows past dense_ld do not exist (image 0, as a score that is no number)
     uint32_t v[R][4];
+    float4 f[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        float4 f = make_float4(NAN, NAN, NAN, NAN);
-        if (r * 256 < dense_ld) f = *reinterpret_cast<const float4*>(dense + q * dense_ld + r * 256 + lane * 4);
-        v[r][0] = dense_image(f.x); v[r][1] = dense_image(f.y); v[r][2] = dense_image(f.z); v[r][3] = dense_image(f.w);
+        f[r] = make_float4(NAN, NAN, NAN, NAN);
+        if (r * 256 < dense_ld) f[r] = *reinterpret_cast<const float4*>(dense + q * dense_ld + r * 256 + lane * 4);
+    }
+    if (tile_err != nullptr) {                         // uniform
+        const float errs = lane * 256 < dense_ld ? tile_err[lane] : 0.0f;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const float e = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(errs), r));
+            f[r].x -= e; f[r].y -= e; f[r].z -= e; f[r].w -= e;
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        v[r][0] = dense_image(f[r].x); v[r][1] = dense_image(f[r].y); v[r][2] = dense_image(f[r].z); v[r][3] = dense_image(f[r].w);
     }
     uint32_t m[2] = {0, 0};
 #pragma unroll
@@ -1417,9 +1450,9 @@ static void plan_half(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype 
     auto take = [&off](size_t bytes) { const size_t o = off; off += round_up(bytes, 256); return o; };
     p->off_rows = take(static_cast<size_t>(p->chunk) * kBM * p->pitch);
     p->off_z = take(static_cast<size_t>(nq) * p->pitch);
-    p->off_zpar = take(static_cast<size_t>(nq) * sizeof(float4));
-    p->off_stats = take(256);
-    p->off_over = take(static_cast<size_t>(nq / kBN + 1) * sizeof(int32_t));
+    p->off_zpar = take(static_cast<size_t>(nq) * sizeof(float2));
+    p->off_err = take(static_cast<size_t>(nLT) * sizeof(float));
+    p->off_range = take(256);
     p->bytes = off;
 }
 
@@ -1440,8 +1473,8 @@ static int plan_mine(int64_t Zq, int64_t L, int d, int k_h, xc_dtype t, MinePlan
     size_t off = 0;
     auto take = [&off](size_t bytes) { size_t o = off; off += round_up(bytes, 256); return o; };
     const size_t nq = static_cast<size_t>(p->nQT) * kBN;
-    // first word: 1 if the last warm search had to repeat the full search for some query tile; then one word per tile (rounded up to 64
-    // words: few queries have kRedoWord behind them)
+    // first word: 1 if the last warm search, or the last on fp16 copies, had to repeat the full search for some query tile; then one word per
+    // tile (rounded up to 64 words: few queries have kRedoWord behind them)
     p->off_flag = take(4 * (static_cast<size_t>(p->nQT) + 1));
     p->off_lists = take(static_cast<size_t>(kMineGrid) * kBN * kCandCap * sizeof(uint64_t));
     p->off_glist = take(nq * p->glist_cap * sizeof(uint64_t));
@@ -1511,6 +1544,8 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     a.dense_ld = 0;
     a.items = nullptr;
     a.over = nullptr;
+    a.tile_err = nullptr;
+    a.err_range = nullptr;
     a.z_rows = Zq;
     a.w_rows = L;
     int32_t* flag = reinterpret_cast<int32_t*>(w8 + p.off_flag);
@@ -1538,9 +1573,11 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
                 XC_HIP_CHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                  static_cast<int>(p.lds_tile)));
             for (const RowsKernel& k : kRowsKernels)
-                XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(k.fn),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 static_cast<int>(rows_lds_bytes(k.wm))));
+                for (const RowsKernelFn fn : {k.fn, k.varied})
+                    if (fn != nullptr)
+                        XC_HIP_CHECK(hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                         static_cast<int>(rows_lds_bytes(k.wm))));
             int rca = few_raise_lds();
             if (rca == XC_OK) rca = q8_raise_lds();
             if (rca != XC_OK) return rca;
@@ -1621,13 +1658,13 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     auto dense_select = [&](int n0) {
         if (n0 <= kDenseMin)
             XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<kDenseMin><<<select_grid, kSelectWaves * kWave, 0, st>>>(
-                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
+                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h, a.tile_err)));
         else if (n0 <= 8)
             XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<8><<<select_grid, kSelectWaves * kWave, 0, st>>>(
-                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
+                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h, a.tile_err)));
         else
             XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<kDenseTiles><<<select_grid, kSelectWaves * kWave, 0, st>>>(
-                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h)));
+                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h, a.tile_err)));
     };
 
     auto phase = [&](int64_t lo, int64_t hi, const int32_t* cond, int32_t* short_flag) -> int {
@@ -1640,9 +1677,10 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         const HalfPlan& hp = p.half;
         unsigned char* hw = w8 + p.ws_min;
         unsigned char* rows = hw + hp.off_rows;
-        float4* zpar = reinterpret_cast<float4*>(hw + hp.off_zpar);
-        uint32_t* stats = reinterpret_cast<uint32_t*>(hw + hp.off_stats);
-        int32_t* over = warm ? flag : reinterpret_cast<int32_t*>(hw + hp.off_over);
+        float2* zpar = reinterpret_cast<float2*>(hw + hp.off_zpar);
+        float* tile_err = reinterpret_cast<float*>(hw + hp.off_err);
+        uint32_t* range = reinterpret_cast<uint32_t*>(hw + hp.off_range);
+        int32_t* over = flag;
         const int row_bytes = static_cast<int>(a.row_bytes), pitch = static_cast<int>(hp.pitch);
         int LG = 8;
         while (LG < kWave && LG * 16 < pitch) LG <<= 1;
@@ -1652,21 +1690,25 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         a.nkb = pitch / kStageBytes;
         a.z_rows = nq;
         a.over = over;
+        a.tile_err = tile_err;
+        a.err_range = range;
         const RowsKernel* hk = pitch <= kMaxRowKernelBytes ? find_rows_kernel(pitch / kStageBytes, rows_wide_items(Zq) ? 1 : 2, true) : nullptr;
         int64_t chunk_end = 0;
         auto convert = [&]() -> int {                        // the next chunk's copies
             const int64_t lo = chunk_end;
             chunk_end = lo + hp.chunk < p.nLT ? lo + hp.chunk : p.nLT;
             const int64_t n_rows = (chunk_end - lo) * kBM, n_lab = (L < chunk_end * kBM ? L : chunk_end * kBM) - lo * kBM;
-            const int64_t blocks = (n_rows + 4 * (kWave / LG) - 1) / (4 * (kWave / LG));
+            // rows a workgroup converts at a time: 131 072 x 768 64 rows 111 us, 128 103, 256 154; 131 072 x 256 43, 37 and 45
+            const int unit = n_rows >= (1 << 16) ? 128 : 64;
+            const int64_t blocks = n_rows / unit;
             half_rows_kernel<<<static_cast<unsigned>(blocks < 2048 ? blocks : 2048), 256, 0, st>>>(
-                exact.W + lo * kBM * row_bytes, n_lab, n_rows, row_bytes, pitch, LG, rows, stats);
+                exact.W + lo * kBM * row_bytes, n_lab, n_rows, row_bytes, pitch, LG, unit, rows, tile_err + lo);
             XC_HIP_CHECK(hipGetLastError());
             a.W = reinterpret_cast<const unsigned char*>(reinterpret_cast<uintptr_t>(rows) - static_cast<uintptr_t>(lo * kBM * pitch));    // (row numbers count from 0)
             a.w_rows = chunk_end * kBM;
             return XC_OK;
         };
-        half_queries_kernel<<<static_cast<unsigned>(nq / 4), 256, 0, st>>>(exact.Z, Zq, nq, row_bytes, pitch, hw + hp.off_z, zpar, stats);
+        half_queries_kernel<<<static_cast<unsigned>(nq / 4), 256, 0, st>>>(exact.Z, Zq, nq, row_bytes, pitch, hw + hp.off_z, zpar, tile_err, p.nLT);
         XC_HIP_CHECK(hipGetLastError());
         int rch = convert();
         if (rch != XC_OK) return rch;
@@ -1682,7 +1724,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             dense_select(n0);
             XC_HIP_CHECK(hipGetLastError());
         }
-        half_start_kernel<<<static_cast<unsigned>((nq + 256) / 256), 256, 0, st>>>(warm ? 2 : n0 > 0 ? 1 : 0, rel_margin, tau_g, a.gcnt, zpar, stats, over, nq, Zq, d);
+        half_start_kernel<<<static_cast<unsigned>((nq + 256) / 256 + 1), 256, 0, st>>>(warm ? 2 : n0 > 0 ? 1 : 0, rel_margin, tau_g, a.gcnt, zpar, over, nq, Zq, tile_err, chunk_end, range);
         XC_HIP_CHECK(hipGetLastError());
         const int slices = slices_cap(p.kcap);
         int64_t seen = n0;                                   // labels behind the thresholds
@@ -1696,15 +1738,20 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             if (hi > chunk_end) hi = chunk_end;
             split(lo, hi, hk);
             a.append_max = kCandCap;                         // (a list is never cut; one that runs over gives its query tile up)
-            if (hk != nullptr) XC_LAUNCH(K_MINE_TILE, st, (hk->fn<<<kMineGrid, kMineThreads, rows_lds_bytes(hk->wm), st>>>(a)));
-            else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<half_t, false, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            if (hk != nullptr) {
+                XC_LAUNCH(K_MINE_TILE, st, (hk->fn<<<kMineGrid, kMineThreads, rows_lds_bytes(hk->wm), st>>>(a)));
+                XC_HIP_CHECK(hipGetLastError());
+                XC_LAUNCH(K_MINE_TILE, st, (hk->varied<<<kMineGrid, kMineThreads, rows_lds_bytes(hk->wm), st>>>(a)));
+            } else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<half_t, false, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
             XC_HIP_CHECK(hipGetLastError());
-            if (hi == chunk_end && hi < p.nLT) {             // before the select: the thresholds hold for the rows to come
+            if (hi < p.nLT) {
+                XC_LAUNCH(K_MINE_SELECT, st, (half_select_kernel<<<select_grid, 256, 0, st>>>(a.glist, a.gcnt, tau_g, zpar, tile_err, range, over, Zq, p.glist_cap, k_h)));
+                XC_HIP_CHECK(hipGetLastError());
+            }
+            if (hi == chunk_end && hi < p.nLT) {
                 rch = convert();
                 if (rch != XC_OK) return rch;
-            }
-            if (hi < p.nLT) {
-                XC_LAUNCH(K_MINE_SELECT, st, (half_select_kernel<<<select_grid, 256, 0, st>>>(a.glist, a.gcnt, tau_g, zpar, stats, over, Zq, p.glist_cap, k_h, d)));
+                half_range_kernel<<<1, 256, 0, st>>>(tile_err, chunk_end, range);
                 XC_HIP_CHECK(hipGetLastError());
             }
             lo = hi;
@@ -1713,10 +1760,10 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         const size_t zop = static_cast<size_t>((row_bytes + 63) / 64 * 64);
         if (Zq >= kHalfWaveQueries)
             XC_LAUNCH(K_MINE_SELECT, st, (half_finish_kernel<1><<<select_grid, 256, 4 * zop, st>>>(
-                exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, stats, over, p.glist_cap, k_h, Zq, shortlist, scores)));
+                exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, tile_err, range, over, p.glist_cap, k_h, Zq, shortlist, scores)));
         else
             XC_LAUNCH(K_MINE_SELECT, st, (half_finish_kernel<4><<<static_cast<unsigned>(Zq), 256, zop, st>>>(
-                exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, stats, over, p.glist_cap, k_h, Zq, shortlist, scores)));
+                exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, tile_err, range, over, p.glist_cap, k_h, Zq, shortlist, scores)));
         XC_HIP_CHECK(hipGetLastError());
         a = exact;
         mine_init_kernel<<<init_grid, 256, 0, st>>>(tau_g, a.gcnt, nq, zeros32, over);

@@ -2,13 +2,16 @@
 // Bound of the fp32 kernels: the matrix pipe, whose fp32 products run at a sixteenth of the 16-bit rate.  z and w rounded to 11
 // bits give a score that is off by at most half_error() |z| |w| (a thousandth of it), so the sweep over all labels runs on fp16
 // copies with thresholds lowered by that, and the few labels left get their score from the fp32 rows, in the order of sums of the
-// other kernels.  With e(q) a query's error for the largest row so far:
-//   half_queries_kernel, half_rows_kernel   the copies, padded to whole tiles and stages, and the largest |w|
-//   mine_tile_kernel / mine_rows_kernel     on them, as for bf16 rows.  A label passes if its 16-bit score reaches T = B - e(q),
-//                                           where B is a score that k labels are known to reach: no label of the answer is lost
-//   half_select_kernel                      B = (k-th best 16-bit score) - e(q), and the list cut to what can still matter
+// other kernels.  Queries are brought to one norm, so that the error e(l) is
+// that of the largest row in the label's tile of 256, whatever the query:
+//   half_queries_kernel, half_rows_kernel   the copies, padded to whole tiles and stages, and the largest |w| of each tile
+//   mine_tile_kernel / mine_rows_kernel     on them, as for bf16 rows.  A label passes if its 16-bit score reaches B(q) - e(l), where
+//                                           B is a score that k labels are known to reach: no label of the answer is lost
+//   half_select_kernel                      B = the k-th best of (16-bit score - e), and the list cut to what can still matter
 //   half_finish_kernel                      the fp32 scores of the list, the best k of them
-// What this does not settle - a list that ran over, scores or rows out of fp16's range, a warm search whose thresholds were too
+// A tile with a row that fp16 cannot hold has an infinite error: its labels always pass.  (One error for all labels let one row of
+// norm 10 among a million of norm 1 double the time of a search, and one element of 2000 ran every list over.)
+// What this does not settle - a list that ran over, queries out of fp16's range, a warm search whose thresholds were too
 // high - is flagged by query tile, and the fp32 kernels take these tiles (they return at once where there are none).
 #pragma once
 
@@ -25,20 +28,19 @@ constexpr int64_t kHalfWaveQueries = 2048;           // from so many queries on,
 struct HalfPlan {
     int64_t pitch;                                   // bytes of an fp16 row: whole stages; 0 = not used
     int64_t chunk;                                   // label tiles at a time
-    size_t off_rows, off_z, off_zpar, off_stats, off_over, bytes;      // within its part of the workspace
+    size_t off_rows, off_z, off_zpar, off_err, off_range, bytes;      // within its part of the workspace
 };
 
-// e(q) in units of the scaled scores.  zpar: (|z| scaled, B scaled, scale, kind)
-__device__ __forceinline__ float half_query_error(const float4& zpar, const uint32_t* stats, int d) {
-    return zpar.x * (sqrtf(__uint_as_float(stats[0])) * 1.001f * half_error(d) + half_error_small(d));
-}
-
+// The copies: queries to a norm of kHalfNorm, W by kHalfScale.  A score's error then depends on the label alone: tile_err[l / kBM] at most.
+constexpr float kHalfNorm = 16384.0f;
+// zpar: (scale of a query's scores, kind)
 __global__ __launch_bounds__(256)
 void half_queries_kernel(const unsigned char* __restrict__ Z, int64_t Zq, int64_t nq, int row_bytes, int pitch,
-                         unsigned char* __restrict__ out, float4* __restrict__ zpar, uint32_t* __restrict__ stats) {
+                         unsigned char* __restrict__ out, float2* __restrict__ zpar,
+                         float* __restrict__ tile_err, int64_t nLT) {
     const int lane = lane_id();
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (blockIdx.x == 0 && threadIdx.x < 2) stats[threadIdx.x] = 0u;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < nLT; i += static_cast<int64_t>(gridDim.x) * 256) tile_err[i] = 0.0f;
     if (q >= nq) return;
     const float* zr = reinterpret_cast<const float*>(Z + (q < Zq ? q : 0) * row_bytes);
     const int d = q < Zq ? row_bytes / 4 : 0;
@@ -51,96 +53,130 @@ void half_queries_kernel(const unsigned char* __restrict__ Z, int64_t Zq, int64_
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) { m = fmaxf(m, __shfl_xor(m, off, kWave)); s2 += __shfl_xor(s2, off, kWave); }
     const bool bad = m > kHalfMost || (m != 0.0f && m < kHalfLeast);
-    const int e = m == 0.0f || bad ? 0 : 14 - (static_cast<int>(__float_as_uint(m) >> 23) - 127);         // largest element to [2^14, 2^15)
-    const float up = ldexpf(1.0f, e);
+    const float up = m == 0.0f || bad ? 0.0f : kHalfNorm / sqrtf(s2);
     for (int i = lane; i < pitch / 2; i += kWave)
         reinterpret_cast<_Float16*>(out + q * pitch)[i] = static_cast<_Float16>(i < d && !bad ? zr[i] * up : 0.0f);
-    if (lane == 0) {
-        const float scale = up * kHalfScale;
-        zpar[q] = make_float4(bad ? 0.0f : sqrtf(s2) * 1.001f * scale, -INFINITY, scale, q >= Zq || m == 0.0f ? kHalfZero : bad ? kHalfBad : kHalfPlain);
-    }
+    if (lane == 0) zpar[q] = make_float2(up * kHalfScale, q >= Zq || m == 0.0f ? kHalfZero : bad ? kHalfBad : kHalfPlain);
 }
 
 // Rows [0, n_lab) of the chunk, LG lanes (a power of two) to a row; rows up to n_rows are zeros.  Bound: HBM (6 bytes per element).
 __global__ __launch_bounds__(256)
-void half_rows_kernel(const unsigned char* __restrict__ W, int64_t n_lab, int64_t n_rows, int row_bytes, int pitch, int LG,
-                      unsigned char* __restrict__ out, uint32_t* __restrict__ stats) {
-    __shared__ float sh[4][2];
+void half_rows_kernel(const unsigned char* __restrict__ W, int64_t n_lab, int64_t n_rows, int row_bytes, int pitch, int LG, int unit,
+                      unsigned char* __restrict__ out, float* __restrict__ tile_err /* of the chunk's first tile */) {
+    const int wave_rows = unit / 4;                      // one after the other, of one tile
+    const uint32_t far = __float_as_uint(65504.0f / kHalfScale);
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int per = kWave / LG, l = lane & (LG - 1);
-    const int64_t step = static_cast<int64_t>(gridDim.x) * 4 * per;
-    float most = 0.0f, top = 0.0f;
-    for (int64_t r0 = (static_cast<int64_t>(blockIdx.x) * 4 + wave) * per; r0 < n_rows; r0 += step) {
-        const int64_t r = r0 + lane / LG;
-        float s2 = 0.0f;
-        for (int c = l; c * 16 < pitch; c += LG) {       // 8 elements: two chunks in, one out
-            uint4 a = make_uint4(0, 0, 0, 0), b = make_uint4(0, 0, 0, 0);
-            if (r < n_lab && c * 32 < row_bytes) a = load16<true>(W + r * row_bytes + c * 32);
-            if (r < n_lab && c * 32 + 16 < row_bytes) b = load16<true>(W + r * row_bytes + c * 32 + 16);
-            const float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
-                                __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
-            f16x8 h;
+    constexpr float kUp = kHalfNorm * kHalfScale * 1.002f;           // (both norms are rounded)
+    const float he = half_error(row_bytes / 4) * kUp, hs = half_error_small(row_bytes / 4) * kUp;
+    for (int64_t u0 = static_cast<int64_t>(blockIdx.x) * unit; u0 < n_rows; u0 += static_cast<int64_t>(gridDim.x) * unit) {
+        const int64_t w0 = u0 + wave * wave_rows;
+        float most = 0.0f;                               // the largest |w|^2
+        uint32_t top_bits = 0;                           // of the largest element
+        for (int i0 = 0; i0 < wave_rows; i0 += per) {
+            const int64_t r = w0 + i0 + lane / LG;
+            float s2 = 0.0f;
+            for (int c = l; c * 16 < pitch; c += LG) {   // 8 elements: two chunks in, one out
+                uint4 a = make_uint4(0, 0, 0, 0), b = make_uint4(0, 0, 0, 0);
+                if (r < n_lab && c * 32 < row_bytes) a = load16<true>(W + r * row_bytes + c * 32);
+                if (r < n_lab && c * 32 + 16 < row_bytes) b = load16<true>(W + r * row_bytes + c * 32 + 16);
+                const uint32_t u[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+                uint32_t m = 0;
+                f16x8 h;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                s2 = fmaf(f[i], f[i], s2);
-                top = fmaxf(top, fabsf(f[i]) <= 1e15f ? fabsf(f[i]) : INFINITY);
-                h[i] = static_cast<_Float16>(f[i] * kHalfScale);
+                for (int i = 0; i < 8; ++i) {
+                    const float f = __uint_as_float(u[i]);
+                    s2 = fmaf(f, f, s2);
+                    const uint32_t bits = u[i] & 0x7fffffffu;
+                    m = bits > m ? bits : m;
+                    h[i] = static_cast<_Float16>(f * kHalfScale);
+                }
+                if (m >= far) {                          // beyond fp16, or no number: such a row's score is never looked at
+#pragma unroll
+                    for (int i = 0; i < 8; ++i)
+                        if ((u[i] & 0x7fffffffu) >= far) h[i] = static_cast<_Float16>(0.0f);
+                }
+                top_bits = m > top_bits ? m : top_bits;
+                *reinterpret_cast<f16x8*>(out + r * pitch + c * 16) = h;
             }
-            if (r < n_rows) *reinterpret_cast<f16x8*>(out + r * pitch + c * 16) = h;
+            for (int off = LG >> 1; off > 0; off >>= 1) s2 += __shfl_xor(s2, off, kWave);
+            most = fmaxf(most, s2);                      // (of a row that is no number: see far)
         }
-        for (int off = LG >> 1; off > 0; off >>= 1) s2 += __shfl_xor(s2, off, kWave);
-        most = fmaxf(most, s2);                          // (of a row that is no number: see top)
-    }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) { most = fmaxf(most, __shfl_xor(most, off, kWave)); top = fmaxf(top, __shfl_xor(top, off, kWave)); }
-    if (lane == 0) { sh[wave][0] = most; sh[wave][1] = top; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int w = 1; w < 4; ++w) { most = fmaxf(most, sh[w][0]); top = fmaxf(top, sh[w][1]); }
-        atomicMax(&stats[0], __float_as_uint(most));
-        if (top >= 65504.0f / kHalfScale) stats[1] = 1u;         // beyond fp16: everything goes to the fp32 kernels
+        for (int off = 32; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off, kWave));
+        const bool all_zero = __ballot(top_bits != 0u) == 0ull, wide = __ballot(top_bits >= far) != 0ull;
+        if (lane == 0) {
+            const float e = wide ? INFINITY : all_zero ? 0.0f : sqrtf(most) * he + hs;
+            if (e > 0.0f) atomicMax(reinterpret_cast<uint32_t*>(tile_err) + w0 / kBM, __float_as_uint(e));
+        }
     }
 }
 
-// Thresholds of the first sweep.  from: 0 none yet, 1 the k-th best 16-bit scores of the dense phase, 2 those of the search before,
-// lowered by rel |tau| (fp32 scores).
-__global__ void half_start_kernel(int from, float rel, uint32_t* __restrict__ tau_g, int32_t* __restrict__ gcnt, float4* __restrict__ zpar,
-                                  const uint32_t* __restrict__ stats, int32_t* __restrict__ over /* [1 + n / kBN] */, int64_t n, int64_t Zq, int d) {
+// The range of the first n tiles' errors that are not zero, see half_error_of_all.  By one workgroup of 256.  (Additions of every workgroup of
+// half_rows_kernel to two words took longer than its rows: 200 000 x 128 62 us with them, 35 without.)
+__device__ void half_range(const float* __restrict__ tile_err, int64_t n, uint32_t* __restrict__ range) {
+    __shared__ float sh[4][2];
+    float top = 0.0f, low = INFINITY;
+#pragma unroll 8
+    for (int64_t i = threadIdx.x; i < n; i += 256) {
+        const float e = tile_err[i];
+        top = fmaxf(top, e);
+        low = e > 0.0f ? fminf(low, e) : low;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) { top = fmaxf(top, __shfl_xor(top, off, kWave)); low = fminf(low, __shfl_xor(low, off, kWave)); }
+    if (lane_id() == 0) { sh[threadIdx.x >> 6][0] = top; sh[threadIdx.x >> 6][1] = low; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        range[0] = __float_as_uint(fmaxf(fmaxf(sh[0][0], sh[1][0]), fmaxf(sh[2][0], sh[3][0])));
+        range[1] = __float_as_uint(fminf(fminf(sh[0][1], sh[1][1]), fminf(sh[2][1], sh[3][1])));
+    }
+}
+__global__ __launch_bounds__(256)
+void half_range_kernel(const float* __restrict__ tile_err, int64_t n, uint32_t* __restrict__ range) { half_range(tile_err, n, range); }
+
+// Thresholds of the first sweep.  from: 0 none yet, 1 the k-th best 16-bit scores of the dense phase, less their error, 2 those of the search
+// before, lowered by rel |tau| (fp32 scores).  The last workgroup has the errors' range to find.
+__global__ __launch_bounds__(256)
+void half_start_kernel(int from, float rel, uint32_t* __restrict__ tau_g, int32_t* __restrict__ gcnt, const float2* __restrict__ zpar,
+                       int32_t* __restrict__ over /* [1 + n / kBN] */, int64_t n, int64_t Zq,
+                       const float* __restrict__ tile_err, int64_t n_tiles, uint32_t* __restrict__ range) {
+    if (blockIdx.x == gridDim.x - 1) { half_range(tile_err, n_tiles, range); return; }
     const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (q <= n / kBN) over[q] = 0;
     if (q >= n) return;
     gcnt[q] = 0;
-    const float4 zp = zpar[q];
-    const float e = half_query_error(zp, stats, d);
-    float base = -INFINITY;
-    if (from == 1) base = ordered_to_float(tau_g[q]) - e;
-    if (from == 2) { const float t = ordered_to_float(tau_g[q]); base = (t - rel * fabsf(t)) * zp.z; }
-    zpar[q].y = base;
-    tau_g[q] = float_to_ordered(q >= Zq || zp.w != kHalfPlain ? INFINITY : base - e);
+    const float2 zp = zpar[q];
+    if (q >= Zq || zp.y != kHalfPlain) tau_g[q] = float_to_ordered(INFINITY);
+    else if (from == 0) tau_g[q] = kTauInit;
+    else if (from == 2) { const float t = ordered_to_float(tau_g[q]); tau_g[q] = float_to_ordered((t - rel * fabsf(t)) * zp.x); }
 }
 
-// A query's list cut to the labels that can still be among the best k; the threshold of the next sweep.  By one wave.
-__device__ int half_prune(uint64_t* list, int n, int k, float e, float* base, float* thr, int* hist, uint64_t* scratch) {
+// A query's list cut to the labels that can still be among the best k, `base` raised to what k of them are known to reach.  By one wave.
+__device__ int half_prune(uint64_t* list, int n, int k, const float* __restrict__ tile_err, float all, float* base, int* hist, uint64_t* scratch) {
     const int lane = lane_id();
     if (n >= k) {
         float t;
-        if (n == k || n > kSelectRegs * kWave) {
-            const uint64_t bound = n == k ? kKeySentinel : wave_bound_stream(list, n, k, hist);
-            uint64_t worst = 0;
-            for (int i = lane; i < n; i += kWave) { const uint64_t key = list[i]; if (key <= bound && key > worst) worst = key; }
-            t = key_score(wave_max_u64(worst));
-        } else {
-            auto at = [list](int idx) { return list[idx]; };
-            t = n <= kSelectRegs / 2 * kWave ? wave_select_k<kSelectRegs / 2>(scratch, at, n, k, hist) : wave_select_k<kSelectRegs>(scratch, at, n, k, hist);
-        }
-        *base = fmaxf(*base, t - e);
+        auto pick = [=](auto least) {                        // the k-th best
+            if (n == k || n > kSelectRegs * kWave) {
+                const uint64_t bound = n == k ? kKeySentinel : wave_bound_stream(least, n, k, hist);
+                uint64_t worst = 0;
+                for (int i = lane; i < n; i += kWave) { const uint64_t key = least(i); if (key <= bound && key > worst) worst = key; }
+                return key_score(wave_max_u64(worst));
+            }
+            return n <= kSelectRegs / 2 * kWave ? wave_select_k<kSelectRegs / 2>(scratch, least, n, k, hist) : wave_select_k<kSelectRegs>(scratch, least, n, k, hist);
+        };
+        if (all >= 0.0f) t = pick([list](int idx) { return list[idx]; });
+        else t = pick([list, tile_err](int idx) { const uint64_t key = list[idx]; return make_key(key_score(key) - tile_err[key_id(key) / kBM], key_id(key)); });
+        *base = fmaxf(*base, all >= 0.0f ? t - all : t);
     }
-    *thr = *base - e;
+    const float thr = *base - all;
     int out = 0;
     for (int i0 = 0; i0 < n; i0 += kWave) {              // in place: a chunk is read before anything of it is overwritten
         const uint64_t key = i0 + lane < n ? list[i0 + lane] : kKeySentinel;
-        const bool keep = i0 + lane < n && key_score(key) >= *thr;
+        bool keep = i0 + lane < n;
+        if (all >= 0.0f) keep = keep && key_score(key) >= thr;
+        else if (keep) keep = key_score(key) + tile_err[key_id(key) / kBM] >= *base;
         const uint64_t bal = __ballot(keep);
         if (keep) list[out + __popcll(bal & lanemask_lt())] = key;
         out += __popcll(bal);
@@ -149,15 +185,15 @@ __device__ int half_prune(uint64_t* list, int n, int k, float e, float* base, fl
 }
 
 __global__ __launch_bounds__(256)
-void half_select_kernel(uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt, uint32_t* __restrict__ tau_g, float4* __restrict__ zpar,
-                        const uint32_t* __restrict__ stats, int32_t* __restrict__ over, int64_t Zq, int glist_cap, int k, int d) {
+void half_select_kernel(uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt, uint32_t* __restrict__ tau_g, const float2* __restrict__ zpar,
+                        const float* __restrict__ tile_err, const uint32_t* __restrict__ range, int32_t* __restrict__ over, int64_t Zq, int glist_cap, int k) {
     __shared__ int hist[4][256];
     __shared__ uint64_t scratch[4][XC_MAX_K_MINE];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + wave;
     if (q >= Zq) return;                                 // wave-uniform; no workgroup barrier below
-    const float4 zp = zpar[q];
-    if (zp.w != kHalfPlain) return;
+    const float2 zp = zpar[q];
+    if (zp.y != kHalfPlain) return;
     const int n = gcnt[q];
     if (n > glist_cap || __builtin_amdgcn_readfirstlane(over[1 + q / kBN]) != 0) {       // given up: nothing reaches it any more
         if (lane == 0) {
@@ -167,9 +203,9 @@ void half_select_kernel(uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt
         }
         return;
     }
-    float base = zp.y, thr;
-    const int left = half_prune(glist + static_cast<size_t>(q) * glist_cap, n, k, half_query_error(zp, stats, d), &base, &thr, hist[wave], scratch[wave]);
-    if (lane == 0) { gcnt[q] = left; tau_g[q] = float_to_ordered(thr); zpar[q].y = base; }
+    float base = ordered_to_float(tau_g[q]);
+    const int left = half_prune(glist + static_cast<size_t>(q) * glist_cap, n, k, tile_err, half_error_of_all(range), &base, hist[wave], scratch[wave]);
+    if (lane == 0) { gcnt[q] = left; tau_g[q] = float_to_ordered(base); }
 }
 
 // The fp32 scores of what is left, 16 rows by one query as in the few-query search, and the best k.  Bound: random rows from HBM or the
@@ -179,8 +215,8 @@ void half_select_kernel(uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt
 template <int WQ>
 __global__ __launch_bounds__(256)
 void half_finish_kernel(const unsigned char* __restrict__ Z, const unsigned char* __restrict__ W, int row_bytes,
-                        uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt, uint32_t* __restrict__ tau_g, const float4* __restrict__ zpar,
-                        const uint32_t* __restrict__ stats, int32_t* __restrict__ over, int glist_cap, int k,
+                        uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt, uint32_t* __restrict__ tau_g, const float2* __restrict__ zpar,
+                        const float* __restrict__ tile_err, const uint32_t* __restrict__ range, int32_t* __restrict__ over, int glist_cap, int k,
                         int64_t Zq, int32_t* __restrict__ shortlist, float* __restrict__ scores) {
     extern __shared__ uint4 zops[];                      // [4 / WQ] queries as operands, whole steps of 64 bytes
     __shared__ int hists[4 / WQ][256];
@@ -200,13 +236,13 @@ void half_finish_kernel(const unsigned char* __restrict__ Z, const unsigned char
         if (WQ > 1) __syncthreads();
         else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
     };
-    const float4 zp = zpar[q];
+    const float2 zp = zpar[q];
     int n = gcnt[q];
-    if (stats[1] != 0u || zp.w == kHalfBad || (zp.w == kHalfPlain && n > glist_cap)) {       // uniform (nothing writes these here)
+    if (zp.y == kHalfBad || (zp.y == kHalfZero && range[0] == __float_as_uint(INFINITY)) || (zp.y == kHalfPlain && n > glist_cap)) {      // uniform (nothing writes these here)
         if (tid == 0) { over[0] = 1; over[1 + q / kBN] = 1; }
         return;
     }
-    if (zp.w == kHalfZero) {                             // all scores are zero: the first k labels
+    if (zp.y == kHalfZero) {                             // all scores are zero: the first k labels
         for (int i = tid; i < k; i += WQ * kWave) {
             shortlist[q * k + i] = i;
             if (scores) scores[q * k + i] = 0.0f;
@@ -222,18 +258,18 @@ void half_finish_kernel(const unsigned char* __restrict__ Z, const unsigned char
         v = FewMma<float>::operand(v);
         if ((lane & 15) == 0) zop[c] = v;
     }
-    float base = zp.y;
+    float base = ordered_to_float(tau_g[q]);             // (wave 0's, which also writes tau_g below)
     if (wave == 0) {
         // The other queries' workgroups set the tile's word meanwhile: what one wave reads holds for all of them (two waves that read
         // for themselves could part here, one gone and one at the barrier with an n that nobody wrote).
-        float thr;
         n = __builtin_amdgcn_readfirstlane(over[1 + q / kBN]) != 0
-                ? 0 : half_prune(list, n, k, half_query_error(zp, stats, row_bytes / 4), &base, &thr, hist, srt);
+                ? 0 : half_prune(list, n, k, tile_err, half_error_of_all(range), &base, hist, srt);
         if (WQ > 1 && lane == 0) { n_sh = n; base_sh = base; }
     }
     meet();
     if (WQ > 1) { n = n_sh; base = base_sh; }
-    base = base / zp.z;                                  // (a power of two)
+    base = base / zp.x;
+    base -= 1e-6f * fabsf(base);                         // (rounded; the errors have a hundredth to spare)
     if (n < k) {                                         // uniform
         if (tid == 0) { over[0] = 1; over[1 + q / kBN] = 1; }
         return;
@@ -255,7 +291,8 @@ void half_finish_kernel(const unsigned char* __restrict__ Z, const unsigned char
             const float v = (r & 2) ? ((r & 1) ? acc[u][3] : acc[u][2]) : ((r & 1) ? acc[u][1] : acc[u][0]);
             const int32_t lab = __shfl(id[u], 4 * g + (r & 3), kWave);
             const int e = 16 * (b + WQ * u) + 4 * g + r;
-            if (r < 4 && e < n) list[e] = make_key(v + 0.0f, lab);
+            // (a score that is no number comes last.  The label stays: another block's lanes past the list's end may read it here)
+            if (r < 4 && e < n) list[e] = v == v ? make_key(v + 0.0f, lab) : (0xffffffffull << 32) | static_cast<uint32_t>(lab);
         }
     }
     meet();

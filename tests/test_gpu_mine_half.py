@@ -11,13 +11,19 @@ DEV = "cuda:0"
 
 
 def _check(monkeypatch, Z, W, k):
+    """A search from scratch, bit for bit the fp32 kernels'.  Returns the workspace's first word: 1 if the fp32 kernels had to take some
+    query tile of a sweep on fp16 copies, 0 if none, -1 if there was no such sweep."""
     import paper_2409_20156_amd as xc
-    ids, sc = (t.clone() for t in xc.mine_negatives(Z, W, k, want_scores=True))
+    ws = torch.empty(xc.mine_workspace(Z.shape[0], W.shape[0], Z.shape[1], k, xc.XC_F32), dtype=torch.uint8, device=DEV)
+    ws[:4].fill_(0xff)
+    ids, sc = (t.clone() for t in xc.mine_negatives(Z, W, k, want_scores=True, workspace=ws))
+    repeats = int(ws[:4].view(torch.int32).item())
     monkeypatch.setenv("XC_MINE_GENERAL", "1")
     want, want_sc = xc.mine_negatives(Z, W, k, want_scores=True)
     monkeypatch.delenv("XC_MINE_GENERAL")
     assert torch.equal(ids, want)
     assert torch.equal(sc.view(torch.int32), want_sc.view(torch.int32))
+    return repeats
 
 
 def _inputs(Zq, L, d):
@@ -106,8 +112,36 @@ def _thresholds(monkeypatch, Z, W, k, margin):
 ])
 def test_many_queries(monkeypatch, Zq, L, d, k):
     Z, W = _inputs(Zq, L, d)
-    _check(monkeypatch, Z, W, k)
+    assert _check(monkeypatch, Z, W, k) == 0
     _thresholds(monkeypatch, Z, W, k, 0.1)
+
+
+@pytest.mark.parametrize("Zq,L,d,k", [
+    (2560, 40011, 128, 32), (8300, 40010, 128, 16), (4100, 30010, 252, 100),       # the row kernel, items of 256 and 512 queries
+    (2560, 40011, 320, 32), (4097, 20010, 260, 100), (2300, 4300000, 60, 16),       # the general kernel; copies of more than one chunk
+])
+@pytest.mark.parametrize("rows", ["element", "far element", "row", "rows", "norms", "inf", "nan", "zero rows"])
+def test_rows_that_stand_out_cost_their_own_tile(monkeypatch, Zq, L, d, k, rows):
+    """A few rows far longer than the others, beyond fp16 or no numbers: no query tile is left to the fp32 kernels for them."""
+    Z, W = _inputs(Zq, L, d)
+    if rows == "element":
+        W[L // 3, 5] = 2000.0
+    elif rows == "far element":
+        W[77, 5] = -3e9
+    elif rows == "row":
+        W[L // 3] *= 100.0
+    elif rows == "rows":
+        W[100:110] *= 30.0
+        W[L - 1] *= 1000.0
+    elif rows == "norms":
+        W *= torch.exp(0.7 * torch.randn((L, 1), device=DEV, generator=torch.Generator(device=DEV).manual_seed(1)))
+    elif rows == "inf":
+        W[L // 2, 3] = float("inf")
+    elif rows == "nan":
+        W[L - 3] = float("nan")
+    else:
+        W[torch.arange(L, device=DEV) // 300 % 4 == 1] = 0.0         # whole tiles among them
+    assert _check(monkeypatch, Z, W, k) == 0
 
 
 @pytest.mark.parametrize("rows", ["zero", "mostly zero", "equal", "pairs", "large", "tiny", "wide", "inf", "nan", "rising", "queries"])
