@@ -139,14 +139,41 @@ __device__ __forceinline__ void score_rows(const unsigned char* const (&wrow)[kS
 }
 
 // ---- scores of fp32 rows from fp16 copies (few_half_kernel, xc_mine_half.h)
-// Powers of two keep fp16's range out of it: a query is scaled by its largest element, W by kHalfScale.
-constexpr float kHalfScale = 64.0f;
+// Powers of two keep fp16's range out of it: a query is scaled by its own size, W by a scale S that brings the middle one of sixteen rows'
+// largest elements to [8, 16).  Elements up to 4000 times that are held, and those below 2^-17 of it lose bits.
+constexpr int kHalfSample = 16;
 constexpr float kHalfLeast = 1e-15f, kHalfMost = 1e15f;      // largest elements of a query that scaling and norm cover (or all zero)
 
-// |score - 16-bit score| <= this |z| |w| + 2^-20 sqrt(d) |z|: two roundings of 2^-11, what fp32 sums of d products lose on both sides, a
-// hundredth of that to spare; the second term is what elements of W below fp16's normal range can lose.
+// |score - 16-bit score| <= half_error |z| |w| + half_error_small / S |z|: two roundings of 2^-11, what fp32 sums of d products lose on both
+// sides, a hundredth of that to spare; the second term, 1.05 * 2^-14 sqrt(d), is what elements of W below fp16's normal range can lose.
 __device__ __forceinline__ float half_error(int d) { return (2.0f / 2048.0f) * 1.01f + 6.0f * static_cast<float>(d) * 5.97e-8f; }
-__device__ __forceinline__ float half_error_small(int d) { return 1.0e-6f * sqrtf(static_cast<float>(d)); }
+__device__ __forceinline__ float half_error_small(int d) { return 6.41e-5f * sqrtf(static_cast<float>(d)); }
+
+// Row i of the sample, and the scale from the rows' largest elements (lane i < 16 of the wave: that of row i as bits, 0 if it has none; the
+// same in all waves that ask).
+__device__ __forceinline__ int64_t half_sample_row(int i, int64_t L) { return (2 * i + 1) * L / (2 * kHalfSample); }
+__device__ __forceinline__ uint32_t half_sample_bits(const uint4& v) {       // of four elements; those that are no finite numbers do not count
+    uint32_t m = 0;
+    const uint32_t u[4] = {v.x & 0x7fffffffu, v.y & 0x7fffffffu, v.z & 0x7fffffffu, v.w & 0x7fffffffu};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) m = u[i] < 0x7f800000u && u[i] > m ? u[i] : m;
+    return m;
+}
+__device__ __forceinline__ float half_scale(uint32_t bits) {
+    const bool have = lane_id() < kHalfSample && bits != 0u;
+    int rank = 0;
+#pragma unroll
+    for (int j = 0; j < kHalfSample; ++j) {
+        const uint32_t o = __builtin_amdgcn_readlane(bits, j);
+        rank += o != 0u && (o < bits || (o == bits && j < lane_id())) ? 1 : 0;
+    }
+    const int n = __popcll(__ballot(have));
+    const uint64_t middle = __ballot(have && rank == n / 2);
+    if (middle == 0ull) return 64.0f;                // nothing but zeros
+    int e = 3 - (static_cast<int>(__builtin_amdgcn_readlane(bits, __ffsll(static_cast<long long>(middle)) - 1) >> 23) - 127);
+    e = e < -47 ? -47 : e > 53 ? 53 : e;
+    return __uint_as_float(static_cast<uint32_t>(e + 127) << 23);
+}
 
 // The errors of the tiles' scores from fp16 copies: range holds the bits of the largest and of the smallest that is not zero (of any wave's share
 // of a tile).  Within four of each other the largest stands for all: returned.  Else -1: each tile has its own.

@@ -1680,6 +1680,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         float2* zpar = reinterpret_cast<float2*>(hw + hp.off_zpar);
         float* tile_err = reinterpret_cast<float*>(hw + hp.off_err);
         uint32_t* range = reinterpret_cast<uint32_t*>(hw + hp.off_range);
+        float* scale = reinterpret_cast<float*>(range) + 32;         // of W's copies
         int32_t* over = flag;
         const int row_bytes = static_cast<int>(a.row_bytes), pitch = static_cast<int>(hp.pitch);
         int LG = 8;
@@ -1702,13 +1703,13 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             const int unit = n_rows >= (1 << 16) ? 128 : 64;
             const int64_t blocks = n_rows / unit;
             half_rows_kernel<<<static_cast<unsigned>(blocks < 2048 ? blocks : 2048), 256, 0, st>>>(
-                exact.W + lo * kBM * row_bytes, n_lab, n_rows, row_bytes, pitch, LG, unit, rows, tile_err + lo);
+                exact.W + lo * kBM * row_bytes, n_lab, n_rows, row_bytes, pitch, LG, unit, rows, tile_err + lo, scale);
             XC_HIP_CHECK(hipGetLastError());
             a.W = reinterpret_cast<const unsigned char*>(reinterpret_cast<uintptr_t>(rows) - static_cast<uintptr_t>(lo * kBM * pitch));    // (row numbers count from 0)
             a.w_rows = chunk_end * kBM;
             return XC_OK;
         };
-        half_queries_kernel<<<static_cast<unsigned>(nq / 4), 256, 0, st>>>(exact.Z, Zq, nq, row_bytes, pitch, hw + hp.off_z, zpar, tile_err, p.nLT);
+        half_queries_kernel<<<static_cast<unsigned>(nq / 4 + 1), 256, 0, st>>>(exact.Z, Zq, nq, row_bytes, pitch, hw + hp.off_z, zpar, tile_err, p.nLT, exact.W, L, scale);
         XC_HIP_CHECK(hipGetLastError());
         int rch = convert();
         if (rch != XC_OK) return rch;
@@ -1724,7 +1725,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             dense_select(n0);
             XC_HIP_CHECK(hipGetLastError());
         }
-        half_start_kernel<<<static_cast<unsigned>((nq + 256) / 256 + 1), 256, 0, st>>>(warm ? 2 : n0 > 0 ? 1 : 0, rel_margin, tau_g, a.gcnt, zpar, over, nq, Zq, tile_err, chunk_end, range);
+        half_start_kernel<<<static_cast<unsigned>((nq + 256) / 256 + 1), 256, 0, st>>>(warm ? 2 : n0 > 0 ? 1 : 0, rel_margin, tau_g, a.gcnt, zpar, over, nq, Zq, tile_err, chunk_end, range, scale);
         XC_HIP_CHECK(hipGetLastError());
         const int slices = slices_cap(p.kcap);
         int64_t seen = n0;                                   // labels behind the thresholds
@@ -1760,10 +1761,10 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         const size_t zop = static_cast<size_t>((row_bytes + 63) / 64 * 64);
         if (Zq >= kHalfWaveQueries)
             XC_LAUNCH(K_MINE_SELECT, st, (half_finish_kernel<1><<<select_grid, 256, 4 * zop, st>>>(
-                exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, tile_err, range, over, p.glist_cap, k_h, Zq, shortlist, scores)));
+                exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, tile_err, range, scale, over, p.glist_cap, k_h, Zq, shortlist, scores)));
         else
             XC_LAUNCH(K_MINE_SELECT, st, (half_finish_kernel<4><<<static_cast<unsigned>(Zq), 256, zop, st>>>(
-                exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, tile_err, range, over, p.glist_cap, k_h, Zq, shortlist, scores)));
+                exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, tile_err, range, scale, over, p.glist_cap, k_h, Zq, shortlist, scores)));
         XC_HIP_CHECK(hipGetLastError());
         a = exact;
         mine_init_kernel<<<init_grid, 256, 0, st>>>(tau_g, a.gcnt, nq, zeros32, over);

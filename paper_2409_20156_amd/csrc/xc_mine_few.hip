@@ -60,7 +60,7 @@ struct FewArgs {
     uint64_t* part;              // [Zq][n_split][kPartKeys] their candidates
     int32_t* part_n;             // [Zq][n_split]
     int32_t* done;               // [Zq] how many of them are through (cleared by the first kernel)
-    float* gnorm;                // 16-bit maxima: [n_groups] largest |w| of the group
+    float* gerr;                 // 16-bit maxima: [n_groups] times |z| is the error of the group's maximum
     int32_t* redo_any;           // 16-bit maxima: 1 if any query has to be searched again in fp32 (cleared by the first kernel),
     int32_t* redo;               // [Zq] 1 if q has
     int again;                   // 1: this is that search: only queries with redo[q]
@@ -569,8 +569,8 @@ void few_wide_kernel(const FewArgs a) {
 // w rounded to 11 bits each a score is off by at most half_error() |z| |w|, a thousandth, about a thirtieth of the scores'
 // spread at 1024 elements.  The second kernel forms the scores of the k best groups in fp32 as ever, and then of every other group whose
 // maximum plus its error reaches the k-th of them: the answer is that of the fp32 search, bit for bit.
-// Powers of two keep fp16's range out of it: a query is scaled by its largest element, W by kHalfScale.  Elements of W beyond
-// 1023 become infinite, and so does their group's norm: such a group is always looked at.  Where too many groups are
+// Powers of two keep fp16's range out of it: a query is scaled by its largest element, W by that of a sample (half_scale).  Elements of W
+// beyond fp16 become infinite, and so does their group's error: such a group is always looked at.  Where too many groups are
 // (equal rows by the thousand, odd numbers), the query is searched again by the fp32 kernels, whose launches return at once otherwise.
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 constexpr int kHalfRing = 4;             // steps of 32 elements in flight per wave (two rows of 32 B per lane each: 16 KiB)
@@ -590,7 +590,7 @@ __device__ __forceinline__ f16x8 to_half8(const uint4& a, const uint4& b, float 
 template <int NB, bool KTAIL>
 __global__ __launch_bounds__(kFewThreads)
 void few_half_kernel(const FewArgs a) {
-    extern __shared__ __align__(16) unsigned char zlds[];       // [ks][NB] operands of 1 KiB, then a factor per query
+    extern __shared__ __align__(16) unsigned char zlds[];       // [ks][NB] operands of 1 KiB, then a factor per query, then the sample's rows
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -609,6 +609,11 @@ void few_half_kernel(const FewArgs a) {
     const int64_t n_units = (n_tiles + comb - 1) / comb;
     const int64_t u_step = static_cast<int64_t>(n_wg) * kFewWaves;
     int64_t unit = static_cast<int64_t>(wg) * kFewWaves + wave;
+
+    // ---- W's scale, from 32 chunks of each of the sample's rows (the same in every workgroup)
+    uint32_t* most = reinterpret_cast<uint32_t*>(back + NB * 16);            // [kHalfSample]
+    const uint4 sample = *reinterpret_cast<const uint4*>(a.W + half_sample_row(tid >> 5, a.L) * a.row_bytes + (tid & 31) * (a.row_bytes / 16) / 32 * 16);
+    static_assert(kFewThreads == 32 * kHalfSample, "");
 
     // ---- the load stream, begun before the queries are laid out
     int64_t ld_unit = unit < n_units ? unit : n_units - 1;
@@ -641,6 +646,12 @@ void few_half_kernel(const FewArgs a) {
 #pragma unroll
     for (int j = 0; j < kHalfRing; ++j) load_step(j);
 
+    {
+        uint32_t m = half_sample_bits(sample);
+#pragma unroll
+        for (int off = 16; off > 0; off >>= 1) { const uint32_t o = __shfl_xor(m, off, kWave); m = o > m ? o : m; }
+        if ((tid & 31) == 0) most[tid >> 5] = m;
+    }
     // ---- the queries, 512 / (16 NB) neighbouring lanes for each: the largest element, then the scaled row
     {
         constexpr int TQ = kFewThreads / (NB * 16);
@@ -662,7 +673,7 @@ void few_half_kernel(const FewArgs a) {
         const bool ok = m == 0 || (mf >= kHalfLeast && mf <= kHalfMost);        // (else the second kernel has it searched again)
         const int e = m == 0 || !ok ? 0 : 14 - (static_cast<int>(m >> 23) - 127);            // largest element to [2^14, 2^15)
         const float up = ldexpf(1.0f, e);
-        if (sub == 0) back[i] = ldexpf(1.0f / kHalfScale, -e);
+        if (sub == 0) back[i] = ldexpf(1.0f, -e);
 #pragma unroll 8
         for (int c = sub; c < KS * 8; c += TQ) {                // chunk c: elements 4 c .. 4 c + 3
             uint4 v = make_uint4(0, 0, 0, 0);
@@ -680,9 +691,12 @@ void few_half_kernel(const FewArgs a) {
     }
     __syncthreads();
     if (unit >= n_units) return;                                // (no barrier below)
+    const float scale = half_scale(most[lane & (kHalfSample - 1)]), unscale = 1.0f / scale;        // (powers of two)
+    const float he = half_error(static_cast<int>(a.row_bytes / 4)) * 1.001f * unscale;             // (rounded elements are up to 2^-11 smaller)
+    const float hs = half_error_small(static_cast<int>(a.row_bytes / 4)) * unscale;
     float bk[NB];
 #pragma unroll
-    for (int n = 0; n < NB; ++n) bk[n] = back[n * 16 + r];
+    for (int n = 0; n < NB; ++n) bk[n] = back[n * 16 + r] * unscale;
 
     // this lane's chunks of the last step that lie past the row's end
     const bool tail0 = static_cast<int64_t>(KS - 1) * 128 + g * 16 >= a.row_bytes, tail1 = static_cast<int64_t>(KS - 1) * 128 + g * 16 + 64 >= a.row_bytes;
@@ -713,7 +727,7 @@ void few_half_kernel(const FewArgs a) {
                 if (tail0) { ra[j][0] = make_uint4(0, 0, 0, 0); ra[j][2] = make_uint4(0, 0, 0, 0); }
                 if (tail1) { ra[j][1] = make_uint4(0, 0, 0, 0); ra[j][3] = make_uint4(0, 0, 0, 0); }
             }
-            const f16x8 a0 = to_half8(ra[j][0], ra[j][1], kHalfScale), a1 = to_half8(ra[j][2], ra[j][3], kHalfScale);
+            const f16x8 a0 = to_half8(ra[j][0], ra[j][1], scale), a1 = to_half8(ra[j][2], ra[j][3], scale);
             if (norms) {                                        // uniform
 #pragma unroll
                 for (int u = 0; u < 4; ++u) any |= (ra[j][u].x | ra[j][u].y | ra[j][u].z | ra[j][u].w) << 1;
@@ -751,18 +765,18 @@ void few_half_kernel(const FewArgs a) {
                         if (a.gshift >= 0) v = fmaxf(v, __shfl_xor(v, 8, kWave));
                         sq[b] = v;
                     }
-                    constexpr float kBack = 1.001f / kHalfScale;        // (rounded elements are up to 2^-11 smaller)
+                    auto error = [he, hs](float v) { return v == 0.0f ? 0.0f : sqrtf(v) * he + hs; };
                     if (a.gshift <= 0) {
                         const int per = a.gshift < 0 ? 4 : 2;   // groups of a tile: lanes 0, 8, 16, 24 of it, or 0, 16
                         const int grp = a.gshift < 0 ? (lane >> 3) : (lane >> 4);
                         const float v = (a.gshift < 0 ? grp >> 1 : grp) == 0 ? sq[0] : sq[1];
                         // (of block 1 the lanes 16.. hold the values of their r as well: rows 0..7 in lanes r < 8, 8..15 in r >= 8)
                         if (grp < per && (lane & (a.gshift < 0 ? 7 : 15)) == 0 && tile * per + grp < a.n_groups)
-                            a.gnorm[tile * per + grp] = sqrtf(v) * kBack;
+                            a.gerr[tile * per + grp] = error(v);
                     } else {
                         run_sq = fmaxf(run_sq, fmaxf(sq[0], sq[1]));
                         if (unit_done) {
-                            if (lane == 0) a.gnorm[unit] = sqrtf(run_sq) * kBack;
+                            if (lane == 0) a.gerr[unit] = error(run_sq);
                             run_sq = 0.0f;
                         }
                     }
@@ -906,7 +920,7 @@ void few_finish_kernel(const FewArgs a) {
         }
     };
     if (tid == 0) { n_sel = 0; n_key = 0; tau_sh = 0xffffffffu; }
-    // the query's norm, and what a group's norm is multiplied with to give the error of its maximum
+    // the query's norm
     float zn = 0.0f;
     auto redo = [&]() {                                        // (every thread that gets here writes the same)
         a.redo_any[0] = 1;
@@ -925,10 +939,9 @@ void few_finish_kernel(const FewArgs a) {
         if (!(s2 < INFINITY) || (zmax != 0.0f && zmax < kHalfLeast)) { redo(); return; }      // uniform over the workgroup: every wave sees the whole row
         zn = sqrtf(s2) * 1.001f;
     }
-    const float he = HALF ? half_error(static_cast<int>(a.row_bytes / 4)) : 0.0f, hs = HALF ? half_error_small(static_cast<int>(a.row_bytes / 4)) : 0.0f;
     auto group_error = [&](int64_t i) {
-        const float w = a.gnorm[i];
-        return w == 0.0f ? 0.0f : zn * (w * he + hs);
+        const float e = a.gerr[i];
+        return e == 0.0f ? 0.0f : zn * e;
     };
     uint32_t prefix = 0;           // the digits found so far
     int bits = 32;                 // bits below them
@@ -1314,8 +1327,8 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
     if (f32 && Zq > kHalfFrom && 2e-9 * p->n_qb * p->nb * 16 * L * (row_bytes / 4) > kHalfGflop) {
         p->hks = static_cast<int>((row_bytes + 127) / 128);
         int hnb = 2;
-        while (hnb < 8 && hnb * 16 < Zq && static_cast<size_t>(2 * hnb * p->hks) * 1024 + 2 * hnb * 64 <= kFewLds) hnb <<= 1;
-        p->hlds = static_cast<size_t>(hnb) * p->hks * 1024 + hnb * 64;
+        while (hnb < 8 && hnb * 16 < Zq && static_cast<size_t>(2 * hnb * p->hks) * 1024 + 2 * hnb * 64 + kHalfSample * 4 <= kFewLds) hnb <<= 1;
+        p->hlds = static_cast<size_t>(hnb) * p->hks * 1024 + hnb * 64 + kHalfSample * 4;
         p->hn_qb = static_cast<int>((Zq + hnb * 16 - 1) / (hnb * 16));
         p->hgshift = gs == 0 ? -1 : gs;
         p->hn_groups = gs == 0 ? (L + 7) / 8 : p->n_groups;
@@ -1458,7 +1471,7 @@ int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int
     a.part = reinterpret_cast<uint64_t*>(s); s += static_cast<size_t>(Zq) * p.n_split * kPartKeys * 8;
     a.part_n = reinterpret_cast<int32_t*>(s); s += round_up(static_cast<size_t>(Zq) * p.n_split * 4, 256);
     a.done = reinterpret_cast<int32_t*>(s); s += round_up(static_cast<size_t>(Zq) * 4, 256);
-    a.gnorm = reinterpret_cast<float*>(s); s += round_up(static_cast<size_t>(most_groups) * 4, 256);     // (these two only with 16-bit maxima)
+    a.gerr = reinterpret_cast<float*>(s); s += round_up(static_cast<size_t>(most_groups) * 4, 256);     // (these two only with 16-bit maxima)
     a.redo = reinterpret_cast<int32_t*>(s);
     if (t == XC_BF16) return launch_few<bf16_t>(p, a, st);
     return p.hnb > 0 ? launch_half(p, a, st) : launch_few<float>(p, a, st);

@@ -31,16 +31,33 @@ struct HalfPlan {
     size_t off_rows, off_z, off_zpar, off_err, off_range, bytes;      // within its part of the workspace
 };
 
-// The copies: queries to a norm of kHalfNorm, W by kHalfScale.  A score's error then depends on the label alone: tile_err[l / kBM] at most.
+// The copies: queries to a norm of kHalfNorm, W by a scale for all.  A score's error then depends on the label alone: tile_err[l / kBM] at most.
+// The last workgroup finds the scale.  zpar: (scale of the query, kind)
 constexpr float kHalfNorm = 16384.0f;
-// zpar: (scale of a query's scores, kind)
 __global__ __launch_bounds__(256)
 void half_queries_kernel(const unsigned char* __restrict__ Z, int64_t Zq, int64_t nq, int row_bytes, int pitch,
                          unsigned char* __restrict__ out, float2* __restrict__ zpar,
-                         float* __restrict__ tile_err, int64_t nLT) {
+                         float* __restrict__ tile_err, int64_t nLT, const unsigned char* __restrict__ W, int64_t L, float* __restrict__ scale) {
     const int lane = lane_id();
+    if (blockIdx.x == gridDim.x - 1) {
+        __shared__ uint32_t most[kHalfSample];
+        const int i = threadIdx.x >> 4;                  // sixteen lanes to a row
+        const unsigned char* wr = W + half_sample_row(i, L) * row_bytes;
+        uint32_t m = 0;
+        for (int c = threadIdx.x & 15; c * 16 < row_bytes; c += 16) {
+            const uint32_t b = half_sample_bits(*reinterpret_cast<const uint4*>(wr + c * 16));
+            m = b > m ? b : m;
+        }
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) { const uint32_t o = __shfl_xor(m, off, kWave); m = o > m ? o : m; }
+        if ((threadIdx.x & 15) == 0) most[i] = m;
+        __syncthreads();
+        const float s = half_scale(most[lane & (kHalfSample - 1)]);
+        if (threadIdx.x == 0) scale[0] = s;
+        return;
+    }
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < nLT; i += static_cast<int64_t>(gridDim.x) * 256) tile_err[i] = 0.0f;
+    for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < nLT; i += static_cast<int64_t>(gridDim.x - 1) * 256) tile_err[i] = 0.0f;
     if (q >= nq) return;
     const float* zr = reinterpret_cast<const float*>(Z + (q < Zq ? q : 0) * row_bytes);
     const int d = q < Zq ? row_bytes / 4 : 0;
@@ -56,19 +73,20 @@ void half_queries_kernel(const unsigned char* __restrict__ Z, int64_t Zq, int64_
     const float up = m == 0.0f || bad ? 0.0f : kHalfNorm / sqrtf(s2);
     for (int i = lane; i < pitch / 2; i += kWave)
         reinterpret_cast<_Float16*>(out + q * pitch)[i] = static_cast<_Float16>(i < d && !bad ? zr[i] * up : 0.0f);
-    if (lane == 0) zpar[q] = make_float2(up * kHalfScale, q >= Zq || m == 0.0f ? kHalfZero : bad ? kHalfBad : kHalfPlain);
+    if (lane == 0) zpar[q] = make_float2(up, q >= Zq || m == 0.0f ? kHalfZero : bad ? kHalfBad : kHalfPlain);
 }
 
 // Rows [0, n_lab) of the chunk, LG lanes (a power of two) to a row; rows up to n_rows are zeros.  Bound: HBM (6 bytes per element).
 __global__ __launch_bounds__(256)
 void half_rows_kernel(const unsigned char* __restrict__ W, int64_t n_lab, int64_t n_rows, int row_bytes, int pitch, int LG, int unit,
-                      unsigned char* __restrict__ out, float* __restrict__ tile_err /* of the chunk's first tile */) {
+                      unsigned char* __restrict__ out, float* __restrict__ tile_err /* of the chunk's first tile */, const float* __restrict__ w_scale) {
     const int wave_rows = unit / 4;                      // one after the other, of one tile
-    const uint32_t far = __float_as_uint(65504.0f / kHalfScale);
+    const float scale = w_scale[0];                      // (a power of two)
+    const uint32_t far = __float_as_uint(65504.0f / scale);
     const int lane = lane_id(), wave = threadIdx.x >> 6;
     const int per = kWave / LG, l = lane & (LG - 1);
-    constexpr float kUp = kHalfNorm * kHalfScale * 1.002f;           // (both norms are rounded)
-    const float he = half_error(row_bytes / 4) * kUp, hs = half_error_small(row_bytes / 4) * kUp;
+    constexpr float kUp = kHalfNorm * 1.002f;            // (both norms are rounded)
+    const float he = half_error(row_bytes / 4) * kUp * scale, hs = half_error_small(row_bytes / 4) * kUp;
     for (int64_t u0 = static_cast<int64_t>(blockIdx.x) * unit; u0 < n_rows; u0 += static_cast<int64_t>(gridDim.x) * unit) {
         const int64_t w0 = u0 + wave * wave_rows;
         float most = 0.0f;                               // the largest |w|^2
@@ -89,7 +107,7 @@ void half_rows_kernel(const unsigned char* __restrict__ W, int64_t n_lab, int64_
                     s2 = fmaf(f, f, s2);
                     const uint32_t bits = u[i] & 0x7fffffffu;
                     m = bits > m ? bits : m;
-                    h[i] = static_cast<_Float16>(f * kHalfScale);
+                    h[i] = static_cast<_Float16>(f * scale);
                 }
                 if (m >= far) {                          // beyond fp16, or no number: such a row's score is never looked at
 #pragma unroll
@@ -140,7 +158,7 @@ void half_range_kernel(const float* __restrict__ tile_err, int64_t n, uint32_t* 
 __global__ __launch_bounds__(256)
 void half_start_kernel(int from, float rel, uint32_t* __restrict__ tau_g, int32_t* __restrict__ gcnt, const float2* __restrict__ zpar,
                        int32_t* __restrict__ over /* [1 + n / kBN] */, int64_t n, int64_t Zq,
-                       const float* __restrict__ tile_err, int64_t n_tiles, uint32_t* __restrict__ range) {
+                       const float* __restrict__ tile_err, int64_t n_tiles, uint32_t* __restrict__ range, const float* __restrict__ scale) {
     if (blockIdx.x == gridDim.x - 1) { half_range(tile_err, n_tiles, range); return; }
     const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (q <= n / kBN) over[q] = 0;
@@ -149,7 +167,7 @@ void half_start_kernel(int from, float rel, uint32_t* __restrict__ tau_g, int32_
     const float2 zp = zpar[q];
     if (q >= Zq || zp.y != kHalfPlain) tau_g[q] = float_to_ordered(INFINITY);
     else if (from == 0) tau_g[q] = kTauInit;
-    else if (from == 2) { const float t = ordered_to_float(tau_g[q]); tau_g[q] = float_to_ordered((t - rel * fabsf(t)) * zp.x); }
+    else if (from == 2) { const float t = ordered_to_float(tau_g[q]); tau_g[q] = float_to_ordered((t - rel * fabsf(t)) * zp.x * scale[0]); }
 }
 
 // A query's list cut to the labels that can still be among the best k, `base` raised to what k of them are known to reach.  By one wave.
@@ -216,8 +234,8 @@ template <int WQ>
 __global__ __launch_bounds__(256)
 void half_finish_kernel(const unsigned char* __restrict__ Z, const unsigned char* __restrict__ W, int row_bytes,
                         uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt, uint32_t* __restrict__ tau_g, const float2* __restrict__ zpar,
-                        const float* __restrict__ tile_err, const uint32_t* __restrict__ range, int32_t* __restrict__ over, int glist_cap, int k,
-                        int64_t Zq, int32_t* __restrict__ shortlist, float* __restrict__ scores) {
+                        const float* __restrict__ tile_err, const uint32_t* __restrict__ range, const float* __restrict__ scale,
+                        int32_t* __restrict__ over, int glist_cap, int k, int64_t Zq, int32_t* __restrict__ shortlist, float* __restrict__ scores) {
     extern __shared__ uint4 zops[];                      // [4 / WQ] queries as operands, whole steps of 64 bytes
     __shared__ int hists[4 / WQ][256];
     __shared__ uint64_t srts[4 / WQ][XC_MAX_K_MINE];
@@ -268,7 +286,7 @@ void half_finish_kernel(const unsigned char* __restrict__ Z, const unsigned char
     }
     meet();
     if (WQ > 1) { n = n_sh; base = base_sh; }
-    base = base / zp.x;
+    base = base / zp.x / scale[0];
     base -= 1e-6f * fabsf(base);                         // (rounded; the errors have a hundredth to spare)
     if (n < k) {                                         // uniform
         if (tid == 0) { over[0] = 1; over[1 + q / kBN] = 1; }

@@ -43,6 +43,26 @@ def test_sizes(monkeypatch, Zq, L, d, k):
     _check(monkeypatch, *_inputs(Zq, L, d), k)
 
 
+@pytest.mark.parametrize("Zq,L,d,k", [(64, 50021, 768, 5), (1000, 50021, 300, 32), (2560, 40011, 128, 32), (2560, 40011, 320, 32)])
+@pytest.mark.parametrize("scale", [1e-12, 1e-6, 1e-3, 37.0, 3e4, 1e8, 1e14])
+def test_scale_of_the_rows_does_not_matter(monkeypatch, Zq, L, d, k, scale):
+    """fp16's range is brought to W's, whatever that is: no query is left to the fp32 kernels.  Most of the sixteen rows that tell it are
+    ordinary ones here, the others zero, far longer or no numbers."""
+    import paper_2409_20156_amd as xc
+    Z, W = _inputs(Zq, L, d)
+    W *= scale
+    sample = [(2 * i + 1) * L // 32 for i in range(16)]
+    W[sample[0]] = 0.0
+    W[sample[3], 1] = float("nan")
+    W[sample[7]] *= 1000.0
+    ws = torch.empty(xc.mine_workspace(Zq, L, d, k, xc.XC_F32), dtype=torch.uint8, device=DEV)
+    ws[:256].fill_(0xff)
+    xc.mine_negatives(Z, W, k, workspace=ws)
+    words = ws[:256].view(torch.int32).tolist()
+    assert (words[0], words[32]) == ((-1, 0) if Zq <= 1000 else (0, -1))
+    _check(monkeypatch, Z, W, k)
+
+
 @pytest.mark.parametrize("Zq", [40, 600])
 @pytest.mark.parametrize("rows", ["zero", "mostly zero", "equal", "pairs", "large", "tiny", "wide", "inf", "nan", "far", "queries"])
 def test_odd_rows(monkeypatch, Zq, rows):
