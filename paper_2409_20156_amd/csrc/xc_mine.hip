@@ -149,6 +149,7 @@ struct MineArgs {
     const float* tile_err;   // [label tile] the error, for every query
     const uint32_t* err_range;   // the errors' range, see half_error_of_all
     int32_t* over;           // [0] and [1 + qt] are set when query tile qt is given up (a list ran over)
+    const int32_t* skip;     // [qt]: given up before this launch
     const int32_t* items;    // not null (row kernel): only these work items, [0] their number, [1] slices per XCD, [2..] the items
 };
 
@@ -177,6 +178,21 @@ __device__ __noinline__ void issue_stage_slow(const unsigned char* base, int64_t
         if (KTAIL && kb + dc >= static_cast<uint32_t>(row_bytes)) g = zeros;
         lds_dma16(g, __builtin_amdgcn_readfirstlane(dst + t * 1024));
     }
+}
+
+// The nth of the n tiles whose flag is set; their number if there are fewer.  By whole waves.
+__device__ __forceinline__ int flagged_tiles(const int32_t* flag, int64_t n, int nth) {
+    int seen = 0;
+    for (int64_t i0 = 0; i0 < n; i0 += kWave) {
+        uint64_t bal = __ballot(i0 + lane_id() < n && flag[i0 + lane_id()] != 0);
+        const int c = __popcll(bal);
+        if (nth < seen + c) {
+            for (int j = seen; j < nth; ++j) bal &= bal - 1;
+            return __builtin_amdgcn_readfirstlane(static_cast<int>(i0) + __ffsll(static_cast<long long>(bal)) - 1);
+        }
+        seen += c;
+    }
+    return seen;
 }
 
 // DENSE: the first phase, where no threshold exists yet: a work item is one tile, and all its scores are written.
@@ -237,9 +253,18 @@ void mine_tile_kernel(const MineArgs a) {
     const uint32_t voff[2] = {static_cast<uint32_t>(drow * a.row_bytes) + dcol[0],
                               static_cast<uint32_t>((drow + 8) * a.row_bytes) + dcol[1]};
 
+    // a repeat in fp32: the items are those of the tiles that need it, so that a few of them keep as many compute units busy as they can
+    constexpr bool kListed = std::is_same<T, float>::value;
+    if (kListed && a.cond != nullptr) {
+        const int n = flagged_tiles(a.cond + 1, a.nQT, 0x7fffffff);
+        item_end = item_end == 0 ? 0 : a.Qx > 0 ? n : n * a.S;
+    }
+
     for (; item < item_end; item += item_step) {
-        const int64_t qtile = a.Qx > 0 ? item : item / a.S;
-        if (a.cond != nullptr && a.cond[1 + qtile] == 0) continue;     // uniform: this query tile came out complete
+        int64_t qtile = a.Qx > 0 ? item : item / a.S;
+        if (kListed && a.cond != nullptr) qtile = flagged_tiles(a.cond + 1, a.nQT, static_cast<int>(qtile));
+        if (!kListed && a.cond != nullptr && a.cond[1 + qtile] == 0) continue;     // uniform: this query tile came out complete
+        if (kHalf && !DENSE && a.skip[qtile] != 0) continue;           // uniform
         const int slice = a.Qx > 0 ? slice_fixed : static_cast<int>(item % a.S);
         const int64_t t_begin = a.tile_lo + static_cast<int64_t>(slice) * a.tiles_per_slice;
         // tiles of the slice are counted from t_begin in 32 bits (a slice has at most 2^31 / 256 / 8 tiles)
@@ -667,7 +692,9 @@ void mine_rows_kernel(const MineArgs a) {
     uint64_t* my_lists = a.lists + static_cast<size_t>(blockIdx.x) * kBN * kCandCap;
     constexpr int row_bytes = NK * kStageBytes;
     // a query takes part if it exists and, in the repeat of a warm search, if its 256-query tile needs it
-    auto live = [&](int64_t q) { return q < a.Zq && (a.cond == nullptr || a.cond[1 + q / kBN] != 0); };
+    auto live = [&](int64_t q) {
+        return q < a.Zq && (kHalf ? a.skip[q / kBN] == 0 : a.cond == nullptr || a.cond[1 + q / kBN] != 0);
+    };
 
     int item, item_step, item_end;
     int slice_fixed = -1;
@@ -716,6 +743,11 @@ void mine_rows_kernel(const MineArgs a) {
         if (a.cond != nullptr) {                             // uniform: every 256-query tile of the item came out complete
             bool any = false;
             for (int64_t qt = q0 / kBN; qt < (q0 + kQN) / kBN && qt * kBN < a.Zq; ++qt) any = any || a.cond[1 + qt] != 0;
+            if (!any) continue;
+        }
+        if (kHalf) {                                         // the same for tiles given up
+            bool any = false;
+            for (int64_t qt = q0 / kBN; qt < (q0 + kQN) / kBN && qt * kBN < a.Zq; ++qt) any = any || a.skip[qt] == 0;
             if (!any) continue;
         }
         const int slice = a.Qx > 0 ? slice_fixed : static_cast<int>(item % a.S);
@@ -1188,7 +1220,8 @@ template <int R>
 __global__ __launch_bounds__(kSelectWaves * kWave)
 void mine_dense_select_kernel(const float* __restrict__ dense, int dense_ld, uint64_t* __restrict__ glist,
                               int32_t* __restrict__ gcnt, uint32_t* __restrict__ tau_g, int64_t Zq, int glist_cap, int k,
-                              const float* __restrict__ tile_err /* not null: 16-bit scores, to be lowered by their errors */) {
+                              const float* __restrict__ tile_err /* not null: 16-bit scores, to be lowered by their errors */,
+                              const int32_t* __restrict__ cond /* not null: only query tiles qt with cond[1 + qt] != 0 */) {
     static_assert(R % 2 == 0 && R <= kDenseTiles, "");
     __shared__ int hist[kSelectWaves][256];
     __shared__ uint64_t picked[kSelectWaves][kDenseList];
@@ -1196,6 +1229,7 @@ void mine_dense_select_kernel(const float* __restrict__ dense, int dense_ld, uin
     const int wave = threadIdx.x >> 6;
     const int64_t q = static_cast<int64_t>(blockIdx.x) * kSelectWaves + wave;
     if (q >= Zq) return;                               // wave-uniform; no workgroup barrier below
+    if (cond != nullptr && cond[1 + q / kBN] == 0) return;
     uint64_t* list = glist + static_cast<size_t>(q) * glist_cap;
     // label of v[r][j]: 256 r + 4 lane + j; rows past dense_ld do not exist (image 0, as a score that is no number)
     uint32_t v[R][4];
@@ -1252,7 +1286,7 @@ void mine_dense_select_kernel(const float* __restrict__ dense, int dense_ld, uin
             for (int e = lane; e < n; e += kWave) { const uint32_t o = ~static_cast<uint32_t>(keys[e] >> 32); lowest = o < lowest ? o : lowest; }
             for (int off = 32; off > 0; off >>= 1) { const uint32_t o = __shfl_xor(lowest, off, kWave); lowest = o < lowest ? o : lowest; }
         }
-        if (lane == 0) { gcnt[q] = n; if (n == k) tau_g[q] = lowest; }
+        if (lane == 0) { gcnt[q] = n; tau_g[q] = n == k ? lowest : kTauInit; }
         return;
     }
     if (n <= kDenseList) {
@@ -1431,6 +1465,7 @@ static bool rows_wide_items(int64_t Zq) {
 // 19.6 : 3.8; 20 000 x 300 000 x 300, k = 32 33.7 : 5.0; 2500 x 4 M x 64, k = 50 12.1 : 3.2; 60 000 x 9000 x 300, k = 8 4.0 : 2.3; the
 // other way 60 000 x 4096 x 64, k = 100 0.88 : 1.84; 20 000 x 4096 x 300, k = 100 0.95 : 0.74.  Below 2048 labels there is no dense phase to find
 // thresholds with (47 767 x 1292 x 972, k = 89: 1.8 : 3.1).
+constexpr int64_t kBriefStages = 40000;      // 256 x 256 x 32 products in fp32: about 2 ms
 static void plan_half(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, HalfPlan* p) {
     p->pitch = 0;
     p->bytes = 0;
@@ -1453,6 +1488,7 @@ static void plan_half(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype 
     p->off_zpar = take(static_cast<size_t>(nq) * sizeof(float2));
     p->off_err = take(static_cast<size_t>(nLT) * sizeof(float));
     p->off_range = take(256);
+    p->off_skip = take(static_cast<size_t>(nq / kBN) * sizeof(int32_t));
     p->bytes = off;
 }
 
@@ -1544,6 +1580,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     a.dense_ld = 0;
     a.items = nullptr;
     a.over = nullptr;
+    a.skip = nullptr;
     a.tile_err = nullptr;
     a.err_range = nullptr;
     a.z_rows = Zq;
@@ -1658,13 +1695,34 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
     auto dense_select = [&](int n0) {
         if (n0 <= kDenseMin)
             XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<kDenseMin><<<select_grid, kSelectWaves * kWave, 0, st>>>(
-                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h, a.tile_err)));
+                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h, a.tile_err, a.cond)));
         else if (n0 <= 8)
             XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<8><<<select_grid, kSelectWaves * kWave, 0, st>>>(
-                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h, a.tile_err)));
+                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h, a.tile_err, a.cond)));
         else
             XC_LAUNCH(K_MINE_SELECT, st, (mine_dense_select_kernel<kDenseTiles><<<select_grid, kSelectWaves * kWave, 0, st>>>(
-                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h, a.tile_err)));
+                a.dense, a.dense_ld, a.glist, a.gcnt, tau_g, Zq, p.glist_cap, k_h, a.tile_err, a.cond)));
+    };
+
+    auto dense_phase = [&](int n0, const int32_t* cond) -> int {
+        a.nQT = p.nQT;
+        a.tile_lo = 0; a.tile_hi = n0; a.tiles_per_slice = 1;
+        a.S = n0; a.Qx = 0;
+        a.dense = reinterpret_cast<float*>(w8 + p.off_lists);
+        a.dense_ld = n0 * kBM;
+        a.cond = cond;
+        const bool ktail = (a.row_bytes % kStageBytes) != 0;
+        if (t == XC_BF16) {
+            if (ktail) XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<bf16_t, true, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<bf16_t, false, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+        } else {
+            if (ktail) XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, true, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+            else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, false, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
+        }
+        XC_HIP_CHECK(hipGetLastError());
+        dense_select(n0);
+        XC_HIP_CHECK(hipGetLastError());
+        return XC_OK;
     };
 
     auto phase = [&](int64_t lo, int64_t hi, const int32_t* cond, int32_t* short_flag) -> int {
@@ -1682,6 +1740,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         uint32_t* range = reinterpret_cast<uint32_t*>(hw + hp.off_range);
         float* scale = reinterpret_cast<float*>(range) + 32;         // of W's copies
         int32_t* over = flag;
+        int32_t* skip = reinterpret_cast<int32_t*>(hw + hp.off_skip);
         const int row_bytes = static_cast<int>(a.row_bytes), pitch = static_cast<int>(hp.pitch);
         int LG = 8;
         while (LG < kWave && LG * 16 < pitch) LG <<= 1;
@@ -1691,6 +1750,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         a.nkb = pitch / kStageBytes;
         a.z_rows = nq;
         a.over = over;
+        a.skip = skip;
         a.tile_err = tile_err;
         a.err_range = range;
         const RowsKernel* hk = pitch <= kMaxRowKernelBytes ? find_rows_kernel(pitch / kStageBytes, rows_wide_items(Zq) ? 1 : 2, true) : nullptr;
@@ -1709,7 +1769,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             a.w_rows = chunk_end * kBM;
             return XC_OK;
         };
-        half_queries_kernel<<<static_cast<unsigned>(nq / 4 + 1), 256, 0, st>>>(exact.Z, Zq, nq, row_bytes, pitch, hw + hp.off_z, zpar, tile_err, p.nLT, exact.W, L, scale);
+        half_queries_kernel<<<static_cast<unsigned>(nq / 4 + 1), 256, 0, st>>>(exact.Z, Zq, nq, row_bytes, pitch, hw + hp.off_z, zpar, tile_err, p.nLT, over, skip, exact.W, L, scale, zeros32);
         XC_HIP_CHECK(hipGetLastError());
         int rch = convert();
         if (rch != XC_OK) return rch;
@@ -1725,7 +1785,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             dense_select(n0);
             XC_HIP_CHECK(hipGetLastError());
         }
-        half_start_kernel<<<static_cast<unsigned>((nq + 256) / 256 + 1), 256, 0, st>>>(warm ? 2 : n0 > 0 ? 1 : 0, rel_margin, tau_g, a.gcnt, zpar, over, nq, Zq, tile_err, chunk_end, range, scale);
+        half_start_kernel<<<static_cast<unsigned>((nq + 256) / 256 + 1), 256, 0, st>>>(warm ? 2 : n0 > 0 ? 1 : 0, rel_margin, tau_g, a.gcnt, zpar, over, skip, nq, Zq, tile_err, chunk_end, range, scale);
         XC_HIP_CHECK(hipGetLastError());
         const int slices = slices_cap(p.kcap);
         int64_t seen = n0;                                   // labels behind the thresholds
@@ -1746,7 +1806,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             } else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<half_t, false, false><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
             XC_HIP_CHECK(hipGetLastError());
             if (hi < p.nLT) {
-                XC_LAUNCH(K_MINE_SELECT, st, (half_select_kernel<<<select_grid, 256, 0, st>>>(a.glist, a.gcnt, tau_g, zpar, tile_err, range, over, Zq, p.glist_cap, k_h)));
+                XC_LAUNCH(K_MINE_SELECT, st, (half_select_kernel<<<select_grid, 256, 0, st>>>(a.glist, a.gcnt, tau_g, zpar, tile_err, range, over, skip, Zq, p.glist_cap, k_h)));
                 XC_HIP_CHECK(hipGetLastError());
             }
             if (hi == chunk_end && hi < p.nLT) {
@@ -1766,13 +1826,26 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             XC_LAUNCH(K_MINE_SELECT, st, (half_finish_kernel<4><<<static_cast<unsigned>(Zq), 256, zop, st>>>(
                 exact.Z, exact.W, row_bytes, a.glist, a.gcnt, tau_g, zpar, tile_err, range, scale, over, p.glist_cap, k_h, Zq, shortlist, scores)));
         XC_HIP_CHECK(hipGetLastError());
+        // Then the fp32 search for the tiles flagged, as for a pool that takes no copies but for its phases: while it is short, one behind the
+        // dense one (two launches that return at once where nothing is flagged take as long as the second saves)
         a = exact;
-        mine_init_kernel<<<init_grid, 256, 0, st>>>(tau_g, a.gcnt, nq, zeros32, over);
-        XC_HIP_CHECK(hipGetLastError());
-        const int64_t first = p.nLT > 2 * kXcds ? kXcds : p.nLT;
-        rch = phase(0, first, over, nullptr);
-        if (rch == XC_OK && first < p.nLT) rch = phase(first, p.nLT, over, nullptr);
-        return rch;
+        const int m0 = dense_tiles(p.nQT, L / kBM, k_h, p.off_glist - p.off_lists, true);
+        if (m0 == 0) {
+            mine_init_kernel<<<init_grid, 256, 0, st>>>(tau_g, a.gcnt, nq, zeros32, over);
+            XC_HIP_CHECK(hipGetLastError());
+        } else {
+            rch = dense_phase(m0, over);
+            if (rch != XC_OK) return rch;
+        }
+        const bool brief = m0 > 0 && p.nQT * p.nLT * a.nkb <= kBriefStages;
+        for (int64_t lo = m0; lo < p.nLT;) {
+            int64_t hi = brief ? p.nLT : lo + (m0 > 0 ? even_phase_tiles(lo, p.nLT, p.nQT, k_h, slices) : phase_tiles(lo, p.nQT));
+            if (hi > p.nLT || p.nLT - hi < hi / 4) hi = p.nLT;
+            rch = phase(lo, hi, over, nullptr);
+            if (rch != XC_OK) return rch;
+            lo = hi;
+        }
+        return XC_OK;
     }
 
     const int32_t* cond = nullptr;
@@ -1792,23 +1865,8 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
         // the first phase dense, by the general kernel: as many tiles as one or a few full rounds of the compute units take
         const int n0 = dense_tiles(p.nQT, L / kBM, k_h, p.off_glist - p.off_lists, false);
         if (n0 > 0) {
-            a.nQT = p.nQT;
-            a.tile_lo = 0; a.tile_hi = n0; a.tiles_per_slice = 1;
-            a.S = n0; a.Qx = 0;
-            a.dense = reinterpret_cast<float*>(w8 + p.off_lists);
-            a.dense_ld = n0 * kBM;
-            a.cond = nullptr;
-            const bool ktail = (a.row_bytes % kStageBytes) != 0;
-            if (t == XC_BF16) {
-                if (ktail) XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<bf16_t, true, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
-                else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<bf16_t, false, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
-            } else {
-                if (ktail) XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, true, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
-                else XC_LAUNCH(K_MINE_TILE, st, (mine_tile_kernel<float, false, true><<<kMineGrid, kMineThreads, p.lds_tile, st>>>(a)));
-            }
-            XC_HIP_CHECK(hipGetLastError());
-            dense_select(n0);
-            XC_HIP_CHECK(hipGetLastError());
+            const int rcd = dense_phase(n0, nullptr);
+            if (rcd != XC_OK) return rcd;
             lo = n0;
         }
     }

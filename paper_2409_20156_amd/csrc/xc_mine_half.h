@@ -28,7 +28,7 @@ constexpr int64_t kHalfWaveQueries = 2048;           // from so many queries on,
 struct HalfPlan {
     int64_t pitch;                                   // bytes of an fp16 row: whole stages; 0 = not used
     int64_t chunk;                                   // label tiles at a time
-    size_t off_rows, off_z, off_zpar, off_err, off_range, bytes;      // within its part of the workspace
+    size_t off_rows, off_z, off_zpar, off_err, off_range, off_skip, bytes;      // within its part of the workspace
 };
 
 // The copies: queries to a norm of kHalfNorm, W by a scale for all.  A score's error then depends on the label alone: tile_err[l / kBM] at most.
@@ -37,7 +37,7 @@ constexpr float kHalfNorm = 16384.0f;
 __global__ __launch_bounds__(256)
 void half_queries_kernel(const unsigned char* __restrict__ Z, int64_t Zq, int64_t nq, int row_bytes, int pitch,
                          unsigned char* __restrict__ out, float2* __restrict__ zpar,
-                         float* __restrict__ tile_err, int64_t nLT, const unsigned char* __restrict__ W, int64_t L, float* __restrict__ scale) {
+                         float* __restrict__ tile_err, int64_t nLT, int32_t* __restrict__ over, int32_t* __restrict__ skip, const unsigned char* __restrict__ W, int64_t L, float* __restrict__ scale, uint32_t* __restrict__ zeros /* [64] */) {
     const int lane = lane_id();
     if (blockIdx.x == gridDim.x - 1) {
         __shared__ uint32_t most[kHalfSample];
@@ -54,10 +54,12 @@ void half_queries_kernel(const unsigned char* __restrict__ Z, int64_t Zq, int64_
         __syncthreads();
         const float s = half_scale(most[lane & (kHalfSample - 1)]);
         if (threadIdx.x == 0) scale[0] = s;
+        if (threadIdx.x < 64) zeros[threadIdx.x] = 0u;
         return;
     }
     const int64_t q = static_cast<int64_t>(blockIdx.x) * 4 + (threadIdx.x >> 6);
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; i < nLT; i += static_cast<int64_t>(gridDim.x - 1) * 256) tile_err[i] = 0.0f;
+    if (lane == 0 && (q & (kBN - 1)) == 0 && q < nq) { over[1 + q / kBN] = 0; skip[q / kBN] = 0; if (q == 0) over[0] = 0; }
     if (q >= nq) return;
     const float* zr = reinterpret_cast<const float*>(Z + (q < Zq ? q : 0) * row_bytes);
     const int d = q < Zq ? row_bytes / 4 : 0;
@@ -157,14 +159,14 @@ void half_range_kernel(const float* __restrict__ tile_err, int64_t n, uint32_t* 
 // before, lowered by rel |tau| (fp32 scores).  The last workgroup has the errors' range to find.
 __global__ __launch_bounds__(256)
 void half_start_kernel(int from, float rel, uint32_t* __restrict__ tau_g, int32_t* __restrict__ gcnt, const float2* __restrict__ zpar,
-                       int32_t* __restrict__ over /* [1 + n / kBN] */, int64_t n, int64_t Zq,
+                       int32_t* __restrict__ over, int32_t* __restrict__ skip, int64_t n, int64_t Zq,
                        const float* __restrict__ tile_err, int64_t n_tiles, uint32_t* __restrict__ range, const float* __restrict__ scale) {
     if (blockIdx.x == gridDim.x - 1) { half_range(tile_err, n_tiles, range); return; }
     const int64_t q = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (q <= n / kBN) over[q] = 0;
     if (q >= n) return;
     gcnt[q] = 0;
     const float2 zp = zpar[q];
+    if (q < Zq && zp.y == kHalfBad) { over[0] = 1; over[1 + q / kBN] = 1; skip[q / kBN] = 1; }       // the tile is not swept at all
     if (q >= Zq || zp.y != kHalfPlain) tau_g[q] = float_to_ordered(INFINITY);
     else if (from == 0) tau_g[q] = kTauInit;
     else if (from == 2) { const float t = ordered_to_float(tau_g[q]); tau_g[q] = float_to_ordered((t - rel * fabsf(t)) * zp.x * scale[0]); }
@@ -204,7 +206,7 @@ __device__ int half_prune(uint64_t* list, int n, int k, const float* __restrict_
 
 __global__ __launch_bounds__(256)
 void half_select_kernel(uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt, uint32_t* __restrict__ tau_g, const float2* __restrict__ zpar,
-                        const float* __restrict__ tile_err, const uint32_t* __restrict__ range, int32_t* __restrict__ over, int64_t Zq, int glist_cap, int k) {
+                        const float* __restrict__ tile_err, const uint32_t* __restrict__ range, int32_t* __restrict__ over, int32_t* __restrict__ skip, int64_t Zq, int glist_cap, int k) {
     __shared__ int hist[4][256];
     __shared__ uint64_t scratch[4][XC_MAX_K_MINE];
     const int lane = lane_id(), wave = threadIdx.x >> 6;
@@ -216,6 +218,7 @@ void half_select_kernel(uint64_t* __restrict__ glist, int32_t* __restrict__ gcnt
     if (n > glist_cap || __builtin_amdgcn_readfirstlane(over[1 + q / kBN]) != 0) {       // given up: nothing reaches it any more
         if (lane == 0) {
             over[0] = 1; over[1 + q / kBN] = 1;
+            skip[q / kBN] = 1;
             gcnt[q] = 0;
             tau_g[q] = float_to_ordered(INFINITY);
         }
