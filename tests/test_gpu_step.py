@@ -283,9 +283,8 @@ def test_step_wide_keys_in_a_narrow_label_range():
     (683, 2, 4200000), (64, 63, 4200000), (241, 16, 4200000),                   # 2049, 4096, 4097 pairs with wide keys
 ])
 def test_step_small_pair_sort(B, n_neg, L):
-    """Steps of up to 2048 pairs, with keys of more than 22 bits up to 4096, sort them in one workgroup: both element
-    widths, one to four elements per thread, a last one partly filled, masked pairs among them; labels with one and with
-    many pairs; and the sizes just behind these lines."""
+    """Steps of up to 4096 pairs sort them in one workgroup: both element widths, one to four elements per thread, a last
+    one partly filled, masked pairs among them; labels with one and with many pairs; and the sizes just behind that line."""
     print("case", B, n_neg, L, flush=True)
     Z, W, pos, neg, logq, Z64, W64 = _inputs(31, B, L, 8, torch.float32, 1, 0, n_neg)
     neg[0, n_neg // 2] = -1
