@@ -1762,14 +1762,15 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             // rows a workgroup converts at a time: 131 072 x 768 64 rows 111 us, 128 103, 256 154; 131 072 x 256 43, 37 and 45
             const int unit = n_rows >= (1 << 16) ? 128 : 64;
             const int64_t blocks = n_rows / unit;
-            half_rows_kernel<<<static_cast<unsigned>(blocks < 2048 ? blocks : 2048), 256, 0, st>>>(
-                exact.W + lo * kBM * row_bytes, n_lab, n_rows, row_bytes, pitch, LG, unit, rows, tile_err + lo, scale);
+            XC_LAUNCH(K_MINE_TILE, st, (half_rows_kernel<<<static_cast<unsigned>(blocks < 2048 ? blocks : 2048), 256, 0, st>>>(
+                exact.W + lo * kBM * row_bytes, n_lab, n_rows, row_bytes, pitch, LG, unit, rows, tile_err + lo, scale)));
             XC_HIP_CHECK(hipGetLastError());
             a.W = reinterpret_cast<const unsigned char*>(reinterpret_cast<uintptr_t>(rows) - static_cast<uintptr_t>(lo * kBM * pitch));    // (row numbers count from 0)
             a.w_rows = chunk_end * kBM;
             return XC_OK;
         };
-        half_queries_kernel<<<static_cast<unsigned>(nq / 4 + 1), 256, 0, st>>>(exact.Z, Zq, nq, row_bytes, pitch, hw + hp.off_z, zpar, tile_err, p.nLT, over, skip, exact.W, L, scale, zeros32);
+        XC_LAUNCH(K_MINE_TILE, st, (half_queries_kernel<<<static_cast<unsigned>(nq / 4 + 1), 256, 0, st>>>(
+            exact.Z, Zq, nq, row_bytes, pitch, hw + hp.off_z, zpar, tile_err, p.nLT, over, skip, exact.W, L, scale, zeros32)));
         XC_HIP_CHECK(hipGetLastError());
         int rch = convert();
         if (rch != XC_OK) return rch;
@@ -1785,7 +1786,8 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             dense_select(n0);
             XC_HIP_CHECK(hipGetLastError());
         }
-        half_start_kernel<<<static_cast<unsigned>((nq + 256) / 256 + 1), 256, 0, st>>>(warm ? 2 : n0 > 0 ? 1 : 0, rel_margin, tau_g, a.gcnt, zpar, over, skip, nq, Zq, tile_err, chunk_end, range, scale);
+        XC_LAUNCH(K_MINE_SELECT, st, (half_start_kernel<<<static_cast<unsigned>((nq + 256) / 256 + 1), 256, 0, st>>>(
+            warm ? 2 : n0 > 0 ? 1 : 0, rel_margin, tau_g, a.gcnt, zpar, over, skip, nq, Zq, tile_err, chunk_end, range, scale)));
         XC_HIP_CHECK(hipGetLastError());
         const int slices = slices_cap(p.kcap);
         int64_t seen = n0;                                   // labels behind the thresholds
@@ -1812,7 +1814,7 @@ static int run_mine(const void* Z, const void* W, int64_t Zq, int64_t L, int d, 
             if (hi == chunk_end && hi < p.nLT) {
                 rch = convert();
                 if (rch != XC_OK) return rch;
-                half_range_kernel<<<1, 256, 0, st>>>(tile_err, chunk_end, range);
+                XC_LAUNCH(K_MINE_SELECT, st, (half_range_kernel<<<1, 256, 0, st>>>(tile_err, chunk_end, range)));
                 XC_HIP_CHECK(hipGetLastError());
             }
             lo = hi;

@@ -1430,7 +1430,8 @@ static int launch_few(const FewPlan& p, const FewArgs& a, hipStream_t st) {
     return XC_OK;
 }
 
-// 16-bit maxima; then the fp32 kernels for the queries that these did not settle (without any, they return at once).
+// 16-bit maxima; then the fp32 kernels for the queries that these did not settle (without any, they return at once).  The event timing counts
+// all behind the maxima as one selection.
 static int launch_half(const FewPlan& p, const FewArgs& exact, hipStream_t st) {
     FewArgs a = exact;
     a.ks = p.hks; a.n_qb = p.hn_qb; a.gshift = p.hgshift; a.n_groups = p.hn_groups;
@@ -1438,17 +1439,22 @@ static int launch_half(const FewPlan& p, const FewArgs& exact, hipStream_t st) {
     const dim3 grid = few_grid(p.hlds, p.hn_qb, a.L);
     XC_LAUNCH(K_MINE_TILE, st, (fn<<<grid, kFewThreads, p.hlds, st>>>(a)));
     XC_HIP_CHECK(hipGetLastError());
-    XC_LAUNCH(K_MINE_SELECT, st, (launch_finish<float, true>(a, st)));
-    XC_HIP_CHECK(hipGetLastError());
-    a = exact;
-    a.again = 1;
-    a.flag = nullptr;
-    const FewFn again = few_kernel<float>(p.nb, a.row_bytes % 64 != 0);
-    again<<<few_grid(p.lds, p.n_qb, a.L), kFewThreads, p.lds, st>>>(a);
-    XC_HIP_CHECK(hipGetLastError());
-    launch_finish<float, false>(a, st);
-    XC_HIP_CHECK(hipGetLastError());
-    return XC_OK;
+    auto rest = [&]() -> int {
+        launch_finish<float, true>(a, st);
+        XC_HIP_CHECK(hipGetLastError());
+        a = exact;
+        a.again = 1;
+        a.flag = nullptr;
+        const FewFn again = few_kernel<float>(p.nb, a.row_bytes % 64 != 0);
+        again<<<few_grid(p.lds, p.n_qb, a.L), kFewThreads, p.lds, st>>>(a);
+        XC_HIP_CHECK(hipGetLastError());
+        launch_finish<float, false>(a, st);
+        XC_HIP_CHECK(hipGetLastError());
+        return XC_OK;
+    };
+    int rc = XC_OK;
+    XC_LAUNCH(K_MINE_SELECT, st, rc = rest());
+    return rc;
 }
 
 int run_mine_few(const FewPlan& p, const void* Z, const void* W, int64_t Zq, int64_t L, int64_t row_bytes, int k,

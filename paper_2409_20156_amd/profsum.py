@@ -25,7 +25,10 @@ from collections import defaultdict
 
 # kernel function name -> name used by the benchmark
 KERNELS = {"mine_tile_kernel": "mine_tile", "mine_rows_kernel": "mine_tile", "mine_select_kernel": "mine_select",
-           "few_max_kernel": "mine_tile", "few_wide_kernel": "mine_tile", "q8_rows_kernel": "mine_tile", "mine_q8_kernel": "mine_tile",
+           "few_max_kernel": "mine_tile", "few_wide_kernel": "mine_tile", "few_line_kernel": "mine_tile", "few_half_kernel": "mine_tile",
+           "half_queries_kernel": "mine_queries", "half_rows_kernel": "mine_copies", "half_start_kernel": "mine_select",
+           "half_range_kernel": "mine_select", "half_select_kernel": "mine_select", "half_finish_kernel": "mine_select",
+           "q8_rows_kernel": "mine_tile", "mine_q8_kernel": "mine_tile",
            "few_finish_kernel": "mine_select", "q8_rescore_kernel": "mine_select",
            "mine_dense_select_kernel": "mine_select", "q8_queries_kernel": "mine_queries", "sort_small_kernel": "bucket_sort",
            "mine_init_kernel": "mine_init", "mine_warm_init_kernel": "mine_warm_init",
