@@ -263,7 +263,6 @@ void few_line_kernel(const FewArgs a) {
     const int wg = (id % 8) + 8 * (id / (8 * a.n_qb));
     const int n_wg = gridDim.x / a.n_qb;                        // (a multiple of 8, see the launch)
     const int64_t q0 = static_cast<int64_t>(qb) * NB * 16;
-    if (a.again && !few_again(a, q0, NB * 16)) return;          // uniform
 
     // a unit is the tiles whose maxima one wave combines: a tile of two groups (gshift 0), or 2^(gshift-1) tiles of one
     const int comb = a.gshift > 0 ? 1 << (a.gshift - 1) : 1;
