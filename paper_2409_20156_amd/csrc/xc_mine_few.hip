@@ -1264,8 +1264,10 @@ static double others_us(int64_t Zq, int64_t L, int64_t row_bytes, int k, bool f3
 }
 
 // The same where both have fp16 copies (fp32 rows, more than 256 queries): least squares over 70 searches of 128 to 2048 queries, 5000 to
-// 4 million rows of 64 to 768 elements, k = 5 to 100, within a tenth for half of them; choosing by these costs 1.2 % over always choosing
-// right, 38 % at worst.
+// 4 million rows of 64 to 768 elements, k = 5 to 100, within a tenth for half of them; over 473 others of 257 to 2048 queries, 3000 to 10 million rows
+// of 64 to 1024 elements, choosing by these costs 4 % over always choosing right (always one or the other 29 % and more).  Searches of too few products
+// for 16-bit maxima are held against the copies by few_us: few queries : copies, us, 264 x 10 771 x 256, k = 20 58 : 158; 560 x 8264 x 256, k = 5 61 : 121;
+// 910 x 6435 x 200, k = 20 77 : 147; 293 x 4253 x 768, k = 100 335 : 199 (of 34 such searches three take the slower, by 1.3 at most).
 static double few_half_us(const FewPlan& p, int64_t Zq, int64_t L, int64_t row_bytes, int k) {
     const double slots = static_cast<double>(few_slots(p.hlds)), wgs = static_cast<double>(few_ranges(p.hlds, p.hn_qb) * p.hn_qb);
     const double gflop = 2e-9 * p.hn_qb * p.hnb * 16 * L * (row_bytes / 4) * slots * ceil(wgs / slots) / wgs;
@@ -1333,7 +1335,10 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
         p->hn_groups = gs == 0 ? (L + 7) / 8 : p->n_groups;
         if (p->hlds <= kFewLds && few_bytes(q, p->hn_groups, ns) + few_half_bytes(q, p->hn_groups) <= scratch) p->hnb = hnb;
     }
-    if (!always && f32 && half && (p->hnb == 0 || few_half_us(*p, Zq, L, row_bytes, k) >= others_half_us(Zq, L, row_bytes, k))) return false;
+    if (!always && f32 && half) {
+        const double here = p->hnb > 0 ? few_half_us(*p, Zq, L, row_bytes, k) : few_us(*p, Zq, L, row_bytes, k, true);
+        if (here >= others_half_us(Zq, L, row_bytes, k)) return false;
+    }
     return true;
 }
 

@@ -123,6 +123,10 @@ def test_few_queries_score_as_the_other_kernels_do_bf16(monkeypatch, Zq, L, d, k
     (256, 100000, 768, torch.float32, 50, True, True),            # fp32 up to 256 queries
     (1024, 60000, 300, torch.float32, 32, False, True),
     (1024, 70000, 2304, torch.float32, 5, False, False),
+    (264, 10771, 256, torch.float32, 20, False, True),            # too few products for 16-bit maxima, against copies
+    (560, 8264, 256, torch.float32, 5, False, True),
+    (910, 6435, 200, torch.float32, 20, False, True),
+    (293, 4253, 768, torch.float32, 100, False, False),
 ])
 def test_searches_take_the_faster_route(monkeypatch, Zq, L, d, dtype, k, warm, few):
     """Either side of the lines between the search of few queries and the others; the result is the same."""
