@@ -573,7 +573,11 @@ void few_wide_kernel(const FewArgs a) {
 // (equal rows by the thousand, odd numbers), the query is searched again by the fp32 kernels, whose launches return at once otherwise.
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 constexpr int kHalfRing = 4;             // steps of 32 elements in flight per wave (two rows of 32 B per lane each: 16 KiB)
-constexpr int kMoreGroups = 512;         // groups beside the k best that the second kernel looks at
+// Groups beside the k best that the second kernel looks at.  108 searches of nine shapes on rows of eleven kinds (a common part of up to three times the
+// rest, clusters, long tails, few dimensions) needed 16 to 192 of them; rows that lie in hundreds of copies each settle with none, and
+// what is read in vain comes on top.  1000 queries x 50 021 x 300, 100 different rows, 512 : 256 groups 1002 : 491 us (fp32 alone 370); with rows
+// in 300 copies 724 (396), in 50 copies 213 (431).
+constexpr int kMoreGroups = 256;
 __device__ __forceinline__ f16x8 to_half8(const uint4& a, const uint4& b, float scale) {
     const float f[8] = {__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(a.z), __uint_as_float(a.w),
                         __uint_as_float(b.x), __uint_as_float(b.y), __uint_as_float(b.z), __uint_as_float(b.w)};
