@@ -11,19 +11,19 @@ DEV = "cuda:0"
 
 
 def _check(monkeypatch, Z, W, k):
-    """A search from scratch, bit for bit the fp32 kernels'.  Returns the workspace's first word: 1 if the fp32 kernels had to take some
-    query tile of a sweep on fp16 copies, 0 if none, -1 if there was no such sweep."""
+    """A search from scratch, bit for bit the fp32 kernels'.  Returns what its workspace says of the route, (many, few): 1 if the fp32 kernels
+    had to take some query tile of a sweep on fp16 copies, or some query of 16-bit maxima; 0 if none; -1 if there was no such search."""
     import paper_2409_20156_amd as xc
     ws = torch.empty(xc.mine_workspace(Z.shape[0], W.shape[0], Z.shape[1], k, xc.XC_F32), dtype=torch.uint8, device=DEV)
-    ws[:4].fill_(0xff)
+    ws[:256].fill_(0xff)
     ids, sc = (t.clone() for t in xc.mine_negatives(Z, W, k, want_scores=True, workspace=ws))
-    repeats = int(ws[:4].view(torch.int32).item())
+    words = ws[:256].view(torch.int32).tolist()
     monkeypatch.setenv("XC_MINE_GENERAL", "1")
     want, want_sc = xc.mine_negatives(Z, W, k, want_scores=True)
     monkeypatch.delenv("XC_MINE_GENERAL")
     assert torch.equal(ids, want)
     assert torch.equal(sc.view(torch.int32), want_sc.view(torch.int32))
-    return repeats
+    return words[0], words[32] if Z.shape[0] <= 2048 else -1          # (of more queries the word is a tile's)
 
 
 def _inputs(Zq, L, d):
@@ -40,7 +40,9 @@ def _inputs(Zq, L, d):
     (513, 30011, 100, 50), (1025, 20001, 300, 32),  # 256 threads per query at the end
 ])
 def test_sizes(monkeypatch, Zq, L, d, k):
-    _check(monkeypatch, *_inputs(Zq, L, d), k)
+    many, few = _check(monkeypatch, *_inputs(Zq, L, d), k)
+    fp32 = (Zq, L) in ((17, 4096), (100, 20000), (200, 130))
+    assert (many, few) == (-1, -1 if fp32 else 0)
 
 
 @pytest.mark.parametrize("Zq,L,d,k", [(64, 50021, 768, 5), (1000, 50021, 300, 32), (2560, 40011, 128, 32), (2560, 40011, 320, 32)])
@@ -60,11 +62,11 @@ def test_scale_of_the_rows_does_not_matter(monkeypatch, Zq, L, d, k, scale):
     xc.mine_negatives(Z, W, k, workspace=ws)
     words = ws[:256].view(torch.int32).tolist()
     assert (words[0], words[32]) == ((-1, 0) if Zq <= 1000 else (0, -1))
-    _check(monkeypatch, Z, W, k)
+    assert _check(monkeypatch, Z, W, k) == (words[0], words[32])
 
 
 @pytest.mark.parametrize("Zq", [40, 600])
-@pytest.mark.parametrize("rows", ["zero", "mostly zero", "equal", "pairs", "large", "tiny", "wide", "inf", "nan", "far", "queries"])
+@pytest.mark.parametrize("rows", ["zero", "mostly zero", "equal", "pairs", "large", "tiny", "wide", "inf", "nan", "far", "common", "queries"])
 def test_odd_rows(monkeypatch, Zq, rows):
     L, d, k = 20011 if Zq > 100 else 200011, 100, 32
     Z, W = _inputs(Zq, L, d)
@@ -93,6 +95,9 @@ def test_odd_rows(monkeypatch, Zq, rows):
         W[20000, 99] = float("nan")
     elif rows == "far":                              # as many large maxima side by side as there are threads
         W[:3000] *= 4.0
+    elif rows == "common":                           # a part of all rows that is three times the rest
+        W += 3.0 * d ** -0.5
+        Z += 3.0 * d ** -0.5
     else:
         Z[0] = 0.0
         Z[1] *= 1e20
@@ -101,7 +106,9 @@ def test_odd_rows(monkeypatch, Zq, rows):
         Z[4, 6] = float("nan")
         Z[5] *= -1e30
         Z[6, 1:] = 0.0
-    _check(monkeypatch, Z, W, k)
+    # some query is left to the fp32 kernels: ties by the thousand, rows of all sizes, a group in six beyond fp16, queries out of its range
+    left = rows in ("mostly zero", "equal", "large", "wide", "queries")
+    assert _check(monkeypatch, Z, W, k) == (-1, 1 if left else 0)
 
 
 # ---- many queries: the sweep runs on fp16 copies, what it leaves is scored in fp32
@@ -132,7 +139,7 @@ def _thresholds(monkeypatch, Z, W, k, margin):
 ])
 def test_many_queries(monkeypatch, Zq, L, d, k):
     Z, W = _inputs(Zq, L, d)
-    assert _check(monkeypatch, Z, W, k) == 0
+    assert _check(monkeypatch, Z, W, k) == (0, -1)
     _thresholds(monkeypatch, Z, W, k, 0.1)
 
 
@@ -161,12 +168,15 @@ def test_rows_that_stand_out_cost_their_own_tile(monkeypatch, Zq, L, d, k, rows)
         W[L - 3] = float("nan")
     else:
         W[torch.arange(L, device=DEV) // 300 % 4 == 1] = 0.0         # whole tiles among them
-    assert _check(monkeypatch, Z, W, k) == 0
+    assert _check(monkeypatch, Z, W, k) == (0, -1)
 
 
 @pytest.mark.parametrize("rows", ["zero", "mostly zero", "equal", "pairs", "large", "tiny", "wide", "inf", "nan", "rising", "queries"])
-def test_many_queries_odd_rows(monkeypatch, rows):
-    Zq, L, d, k = 2560, 40011, 320, 32
+@pytest.mark.parametrize("Zq,L,d,k", [
+    (2560, 40011, 320, 32),                         # the general kernel
+    (2560, 40011, 128, 32), (8300, 40011, 252, 32),   # the row kernel, items of 256 and 512 queries
+])
+def test_many_queries_odd_rows(monkeypatch, Zq, L, d, k, rows):
     Z, W = _inputs(Zq, L, d)
     if rows == "zero":
         W.zero_()
@@ -202,7 +212,9 @@ def test_many_queries_odd_rows(monkeypatch, rows):
         Z[800, 5] = float("inf")
         Z[1400, 6] = float("nan")
         Z[2500, 1:] = 0.0
-    _check(monkeypatch, Z, W, k)
+    # some query tile is left to the fp32 kernels: more labels than a list holds pass, or a query is out of fp16's range
+    left = rows in ("zero", "mostly zero", "equal", "large", "wide", "rising", "queries")
+    assert _check(monkeypatch, Z, W, k) == (1 if left else 0, -1)
 
 
 def test_thresholds_too_high_are_repeated(monkeypatch):
@@ -232,3 +244,20 @@ def test_unsettled_queries_beside_settled_ones(monkeypatch, Zq):
         monkeypatch.delenv("XC_MINE_GENERAL")
         assert torch.equal(ids, want)
         assert torch.equal(sc.view(torch.int32), want_sc.view(torch.int32))
+
+
+@pytest.mark.parametrize("Zq,L,d,k", [(2560, 40011, 320, 32), (4100, 30010, 128, 100)])
+def test_workspace_without_room_for_copies(monkeypatch, Zq, L, d, k):
+    """A byte less than the copies need: the fp32 kernels search, with the same answer, from scratch and from thresholds."""
+    import paper_2409_20156_amd as xc
+    Z, W = _inputs(Zq, L, d)
+    need = xc.mine_workspace(Zq, L, d, k, xc.XC_F32)
+    full, less = (torch.empty(n, dtype=torch.uint8, device=DEV) for n in (need, need - 1))
+    for margin in (None, 0.05):
+        full[:4].fill_(0xff)
+        less[:4].fill_(0xff)
+        ids, sc = (t.clone() for t in xc.mine_negatives(Z, W, k, want_scores=True, workspace=full, warm_margin=margin))
+        l_ids, l_sc = xc.mine_negatives(Z, W, k, want_scores=True, workspace=less, warm_margin=margin)
+        assert torch.equal(ids, l_ids) and torch.equal(sc.view(torch.int32), l_sc.view(torch.int32))
+        assert int(full[:4].view(torch.int32).item()) == 0                              # on copies
+        assert int(less[:4].view(torch.int32).item()) == (-1 if margin is None else 0)   # a search from scratch in fp32 leaves the word alone
