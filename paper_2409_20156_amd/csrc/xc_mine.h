@@ -271,6 +271,8 @@ struct FewPlan {
     int64_t n_groups;
     int n_split;             // workgroups per query in the second kernel
     size_t lds;              // bytes of the query block in LDS
+    bool lines;              // W read by whole lines, with a stage per wave beside the query block: line_lds bytes
+    size_t line_lds;
     // fp32 with group maxima from 16-bit products (hnb 0: not used)
     int hnb, hn_qb, hks, hgshift;
     int64_t hn_groups;

@@ -1239,6 +1239,24 @@ static int64_t few_ranges(size_t lds, int n_qb) {
     return n < 8 ? 8 : n;
 }
 
+// The share of the slots' time that such workgroups use.
+static double few_used(size_t lds, int n_qb) {
+    const double slots = static_cast<double>(few_slots(lds)), wgs = static_cast<double>(few_ranges(lds, n_qb) * n_qb);
+    return wgs / (slots * ceil(wgs / slots));
+}
+
+// Whether W is read by whole lines (few_line_kernel) where the rows have them and the stages fit LDS beside the queries, or 64 bytes of 16 rows at a
+// time (few_max_kernel).  Lines are the better way but for two things.  Short rows that end within a line share it with their neighbours, and where
+// several blocks of queries read them from memory that costs more than lines gain: halves : lines, us, 127 x 8.2 M x 96 bf16 784 : 905, 459 x
+// 8.1 M x 96 2062 : 2550, 328 x 3.8 M x 200 1923 : 2298; the other way 128 x 300 000 x 96 50 : 47, 256 x 300 000 x 200 120 : 112.  And a
+// stage's LDS may leave one workgroup to a compute unit where two would fit, and a last round mostly empty: 1120 x 192 228 x 504 559 : 661.
+// Over 2250 searches of 97 to 2048 queries this is 0.3 % off the better of both, 19 % at worst (always lines 0.6 and 26).
+static bool few_lines(const FewPlan& p, int64_t L, int64_t row_bytes, bool f32) {
+    if ((f32 && p.nb > 1) || row_bytes < 128 || p.line_lds > kLineLds) return false;
+    if (row_bytes % 128 != 0 && row_bytes < 512 && L * row_bytes >= (192ll << 20) && p.n_qb >= (row_bytes < 256 ? 2 : 5)) return false;
+    return few_used(p.line_lds, p.n_qb) >= 0.75 * few_used(p.lds, p.n_qb);
+}
+
 // Estimated time of this search, and of the other kernels' where it can be the smaller one, in us: least squares over 870
 // searches of 97 to 2048 queries, 5000 to 30 million rows of 128 to 9216 bytes, k = 5, 50 and 100, W from memory.  Half of the estimates are
 // within a tenth, nine in ten within a quarter; choosing by them costs 0.6 % over always choosing right (bf16; fp32 0.6 %
@@ -1312,6 +1330,8 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
     p->nb = nb;
     p->n_qb = static_cast<int>((Zq + nb * 16 - 1) / (nb * 16));
     p->lds = static_cast<size_t>(nb) * ks * 1024;
+    p->line_lds = static_cast<size_t>(nb) * ((ks + 1) & ~1) * 1024 + kFewWaves * kFewStage;
+    p->lines = few_lines(*p, L, row_bytes, f32);
     // groups of 16 labels (least to compute again) while a query has at most 2^17 of them
     int gs = 0;
     while (gs < 4 && (L >> (4 + gs)) > (1 << 17)) ++gs;
@@ -1425,11 +1445,8 @@ static int line_way(const FewArgs& a, int n_qb) {
 
 template <typename T>
 static int launch_few(const FewPlan& p, const FewArgs& a, hipStream_t st) {
-    // lines of W where the rows have them, and the stages fit LDS beside the queries
-    const size_t line_lds = static_cast<size_t>(p.nb) * ((p.ks + 1) & ~1) * 1024 + kFewWaves * kFewStage;
-    const bool lines = line_kernel<T>(p.nb, 0) != nullptr && a.row_bytes >= 128 && line_lds <= kLineLds;
-    const FewFn fn = lines ? line_kernel<T>(p.nb, line_way(a, p.n_qb)) : few_kernel<T>(p.nb, a.row_bytes % 64 != 0);
-    const size_t lds = lines ? line_lds : p.lds;
+    const FewFn fn = p.lines ? line_kernel<T>(p.nb, line_way(a, p.n_qb)) : few_kernel<T>(p.nb, a.row_bytes % 64 != 0);
+    const size_t lds = p.lines ? p.line_lds : p.lds;
     const dim3 grid = few_grid(lds, p.n_qb, a.L);
     XC_LAUNCH(K_MINE_TILE, st, (fn<<<grid, kFewThreads, lds, st>>>(a)));
     XC_HIP_CHECK(hipGetLastError());

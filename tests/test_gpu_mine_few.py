@@ -105,6 +105,8 @@ def test_few_queries_warm_call_needs_no_repeat():
     (64, 30011, 768, 20, torch.bfloat16), (8, 5003, 2304, 20, torch.bfloat16),                     # no room for the stages; one block of queries
     (20, 2200003, 64, 100, torch.bfloat16), (3, 400011, 384, 9, torch.bfloat16),                   # read past the caches, groups of 32 labels
     (1, 4099, 32, 5, torch.float32), (16, 5003, 100, 60, torch.float32), (9, 150001, 512, 20, torch.float32),
+    (100, 1048577, 96, 20, torch.bfloat16), (100, 1048575, 96, 20, torch.bfloat16),                # either side of the line to half lines
+    (257, 503317, 200, 20, torch.bfloat16), (1100, 20011, 504, 9, torch.bfloat16),                 # ... of five blocks; of LDS that leaves slots idle
 ])
 @pytest.mark.parametrize("shift", [0, 8])
 def test_rows_read_by_lines(monkeypatch, Zq, L, d, k, dtype, shift):
