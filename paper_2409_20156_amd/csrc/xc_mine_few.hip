@@ -1228,7 +1228,7 @@ constexpr int64_t kHalfFrom = 16;            // fp32: more queries than this tak
 // maxima: 20 queries x 4096 x 64 19 and 27, 250 x 10 000 x 128 33 and 38, 100 x 20 000 x 256 43 and 47, 128 x 40 000 x 256 65 and 51, 250 x 20 000 x 256 70 and 48
 constexpr double kHalfGflop = 2.5;
 constexpr int64_t kFewAlways = 96;           // up to so many queries always
-constexpr int64_t kFewQueries = 256;         // up to so many without limits on the work (one query tile of the other kernels)
+constexpr int64_t kFewQueries = 256;         // one query tile of the other kernels: up to so many usually
 constexpr int64_t kFewMaxQueries = 2048;     // beyond that never
 
 // Workgroups of the first kernel: as many label ranges per block of queries as fit the chip (two workgroups per compute unit
@@ -1257,32 +1257,33 @@ static bool few_lines(const FewPlan& p, int64_t L, int64_t row_bytes, bool f32) 
     return few_used(p.line_lds, p.n_qb) >= 0.75 * few_used(p.lds, p.n_qb);
 }
 
-// Estimated time of this search, and of the other kernels' where it can be the smaller one, in us: least squares over 870
-// searches of 97 to 2048 queries, 5000 to 30 million rows of 128 to 9216 bytes, k = 5, 50 and 100, W from memory.  Half of the estimates are
-// within a tenth, nine in ten within a quarter; choosing by them costs 0.6 % over always choosing right (bf16; fp32 0.6 %
-// with the fifth below).  This search: products per block of 16, 32 or 64 queries, with what the last round of workgroups
-// leaves idle; rows read again by the second kernel; maxima (stored four bytes at a time, dearer where 64 MB of them are
-// under way).  The others: products, W, what passes (more per query tile, and
+// Estimated time of this search, and of the other kernels' where it can be the smaller one, in us.  bf16: least squares over 2650
+// searches of 97 to 2048 queries, 3000 to 30 million rows of 128 to 9216 bytes, k = 5 to 100, W from memory.  Half of the estimates are
+// within an eighth, nine in ten within two fifths; choosing by them costs 1.7 % over always choosing right (beyond 256 queries 2.8 %; the line at six
+// tiles of 256 x 256 per compute unit that was fitted to half lines, with all that the row kernel takes on this side of it, cost 28 %, and
+// 9 of 1600 searches took a better way there, by a third at most).  fp32: 870 searches, 0.6 % with the fifth below.  This search: scores and their products per block of 16, 32 or 64 queries, with
+// what the last round of workgroups leaves idle; rows read again by the second kernel; maxima (stored four bytes at a time, dearer
+// where 64 MB of them are under way); W.  The others: products, W, what passes (more per query tile, and
 // much more where k > 64), the phases' start-up; rows that are no multiple of a stage load slowly.
 static double few_us(const FewPlan& p, int64_t Zq, int64_t L, int64_t row_bytes, int k, bool f32) {
-    const double slots = static_cast<double>(few_slots(p.lds)), wgs = static_cast<double>(few_ranges(p.lds, p.n_qb) * p.n_qb);
     const double padded = static_cast<double>(p.n_qb) * p.nb * 16;
-    const double gflop = 2e-9 * padded * L * (row_bytes / (f32 ? 4 : 2)) * slots * ceil(wgs / slots) / wgs;
-    const double per = f32 ? (p.nb == 1 ? 13.9 : p.nb == 2 ? 8.4 : 8.2) : (p.nb == 1 ? 7.3 : p.nb == 2 ? 3.8 : 2.2);
-    const double maxima = 1e-6 * padded * p.n_groups;
-    return 22.0 + gflop * per + 0.16e-6 * Zq * k * (16 << p.gshift) * row_bytes + maxima * (maxima < 16.0 ? 5.1 : 12.0);
+    const double gflop = 2e-9 * padded * L * (row_bytes / (f32 ? 4 : 2)) / few_used(p.lines ? p.line_lds : p.lds, p.n_qb);
+    const double maxima = 1e-6 * padded * p.n_groups, rows = 1e-6 * Zq * k * (16 << p.gshift) * row_bytes;
+    if (f32) return 22.0 + gflop * (p.nb == 1 ? 13.9 : p.nb == 2 ? 8.4 : 8.2) + 0.16 * rows + maxima * (maxima < 16.0 ? 5.1 : 12.0);
+    const double per = p.nb == 1 ? 3.4 : p.nb == 2 ? (p.lines ? 1.5 : 3.2) : (p.lines ? 0.88 : 1.4);
+    return 15.0 + 79e-9 * padded * L + gflop * per + 0.125 * rows + 4.5 * maxima + (maxima > 16.0 ? 4.3 * (maxima - 16.0) : 0.0) + 0.27e-6 * L * row_bytes;
 }
 static double others_us(int64_t Zq, int64_t L, int64_t row_bytes, int k, bool f32, bool row_kernel, bool warm) {
-    const double mlab = 1e-6 * L, kb = 1e-3 * row_bytes, long_list = k > 64 ? 1.0 : 0.0;
+    const double mlab = 1e-6 * L, kb = 1e-3 * row_bytes, long_list = k > 64 ? 1.0 : 0.0, zk = 1e-3 * Zq * k;
+    const bool tail = row_bytes % kStageBytes != 0;
     if (Zq <= kBN) {
-        if (row_kernel) return 56.0 + 625.0 * mlab * kb + 12.0 * kb + long_list * (22.0 + 217.0 * mlab);
-        return warm ? 37.0 + 920.0 * mlab * kb + 24.0 * kb + long_list * (17.0 + 1040.0 * mlab)
-                    : 36.0 + 980.0 * mlab * kb + 26.0 * kb + long_list * (41.0 + 1090.0 * mlab);
+        if (row_kernel) return 45.0 + mlab * (kb * (541.0 + long_list * 636.0) + 9.0 + 0.44 * k) + 21.0 * kb + 1.28 * zk;
+        return (warm ? 37.0 + 17.0 * kb : 58.0 + 30.0 * kb) + mlab * (kb * (860.0 + (tail ? 280.0 : 0.0) + long_list * 820.0) + 90.0 + long_list * 190.0) + 0.77 * zk;
     }
     const double qt = static_cast<double>((Zq + kBN - 1) / kBN), gflop = 2e-9 * qt * kBN * L * (row_bytes / (f32 ? 4 : 2));
-    const bool tail = row_bytes % kStageBytes != 0;
-    return f32 ? 84.0 + gflop * (tail ? 5.2 : 2.3) + 2960.0 * mlab * kb + 19.0 * qt * mlab + 100.0 * kb + long_list * 1190.0 * mlab
-               : 44.0 + gflop * (tail ? 0.84 : 0.22) + 556.0 * mlab * kb + 147.0 * qt * mlab + 34.0 * kb + long_list * 1300.0 * mlab;
+    if (f32) return 84.0 + gflop * (tail ? 5.2 : 2.3) + 2960.0 * mlab * kb + 19.0 * qt * mlab + 100.0 * kb + long_list * 1190.0 * mlab;
+    if (row_kernel) return 245.0 + 0.99 * gflop + mlab * (102.0 + 46.0 * kb + 1.3 * qt + long_list * 279.0) + 1.09 * zk + 0.0124 * Zq;
+    return 63.0 + 0.62 * gflop + mlab * ((tail ? 825.0 : 537.0) * kb + 55.0 * qt + long_list * 666.0) + 0.124 * zk + 28.0 * kb;
 }
 
 // The same where both have fp16 copies (fp32 rows, more than 256 queries): least squares over 70 searches of 128 to 2048 queries, 5000 to
@@ -1306,21 +1307,23 @@ static size_t few_bytes(size_t q, int64_t groups, int ns) { return round_up(q * 
 static size_t few_half_bytes(size_t q, int64_t groups) { return 256 + round_up(static_cast<size_t>(groups) * 4, 256) + q * 4; }
 
 // Which searches come here.  Up to 96 queries (less than half of a query tile of the general kernel) all whose query block fits LDS:
-// 131 072 x 768 bf16, k = 5: 71 us against 408 at 64 queries; 4 M x 256 bf16, k = 50: 0.65 ms against 1.57.  More queries
+// 131 072 x 768 bf16, k = 5: 54 us against 408 at 64 queries; 4 M x 256 bf16, k = 50: 0.57 ms against 1.57.  More queries
 // cost this path time in proportion (it multiplies W once per block of at most 64), the others almost nothing until their tiles of
-// 256 x 256 fill the chip several times over.  Up to 2048 queries, 6 tiles per compute unit (fp32: 16) and 1.3 GB of rows read
-// again - no limits up to 256 - all searches whose alternative starts in phases too short to fill the chip: from scratch
-// where that is the row kernel (1024 x 98 304 x 256, k = 64 212 against 624 us; 2048 x 49 152 276 and 685), fp32 up to 256
-// queries (256 x 1 M x 128, k = 100 639 and 4302).  Of the rest the estimates choose, in fp32 with a fifth in favour of this
-// path, up to 256 queries on long bf16 rows with a twentieth against it (where the estimates err, by these parts).  Here and there: 1024 x 98 301 x 768 bf16, k = 50 499 and 250 us; 2048 x 49 149 x 2304, k = 5 1679 and 549; 512 x 98 301 x 768, k
-// = 5 199 and 214; from thresholds 256 x 4 M x 128, k = 5 1036 and 722, 256 x 4 M x 64, k = 100 710 and 1405; 256 x 5000 x
-// 2304, k = 100 316 and 249; 1024 x 262 141 x 768 fp32 3480 and 3100, 1024 x 78 589 x 300 445 and 590.
+// 256 x 256 fill the chip several times over.  Up to 256 queries also all whose alternative has phases too short to fill the chip: fp32
+// (256 x 1 M x 128, k = 100 639 and 4302), and bf16 from scratch, rows that leave LDS room for 64 queries (of 400 searches
+// the other way was better in three, by 6 % at most).  Of the rest up to 2048 queries the estimates choose: up to 256 queries (from thresholds) with a
+// seventh in favour of this path against the row kernel, beyond with a twentieth against it, and a quarter where there are more than six tiles of 256 x
+// 256 per compute unit (where the estimates err by these parts); in fp32 with a fifth in favour, up to 16 tiles of
+// 256 x 256 per compute unit and 1.3 GB of rows read again.  Here and there, us, bf16: 1257 x 118 938 x 256, k = 100 291 and 640;
+// 276 x 652 935 x 1024, k = 20 692 and 1363; 643 x 361 318 x 128, k = 20 240 and 478; the other way 690 x 793 300 x 1024, k =
+// 20 2124 and 1702; from thresholds 256 x 10 M x 128, k = 50 1293 and 1601, 256 x 4 M x 128, k = 5 866 and 643, 256 x 4 M x 64 688 and 383; fp32
+// 1024 x 262 141 x 768 3480 and 3100, 1024 x 78 589 x 300 445 and 590.
 bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool warm, bool half, size_t scratch, FewPlan* p) {
     const bool f32 = t == XC_F32;
+    const int64_t tiles = ((Zq + 255) / 256) * ((L + 255) / 256);
     if (Zq > kFewQueries) {
-        const int64_t tiles = ((Zq + 255) / 256) * ((L + 255) / 256);
-        if (Zq > kFewMaxQueries || tiles > (f32 ? 16 : 6) * 256) return false;
-        if (static_cast<double>(Zq) * k * 16.0 * static_cast<double>(row_bytes) > 1.3e9) return false;
+        if (Zq > kFewMaxQueries || (f32 && tiles > 16 * 256)) return false;
+        if (f32 && static_cast<double>(Zq) * k * 16.0 * static_cast<double>(row_bytes) > 1.3e9) return false;
     }
     const int64_t ks = (row_bytes + 63) / 64;
     if (ks * 1024 > static_cast<int64_t>(kFewLds)) return false;
@@ -1338,8 +1341,8 @@ bool plan_few(int64_t Zq, int64_t L, int64_t row_bytes, int k, xc_dtype t, bool 
     p->gshift = gs;
     p->n_groups = (L + (16LL << gs) - 1) / (16LL << gs);
     const bool row_kernel = !f32 && row_bytes % kStageBytes == 0 && row_bytes <= kMaxRowKernelBytes;
-    const bool always = Zq <= kFewAlways || (f32 ? Zq <= kFewQueries : row_kernel && !warm);
-    const double favour = f32 ? 1.2 : Zq <= kFewQueries && !row_kernel ? 0.95 : 1.0;
+    const bool always = Zq <= kFewAlways || (Zq <= kFewQueries && (f32 || (!warm && nb == 4)));
+    const double favour = f32 ? 1.2 : Zq <= kFewQueries ? (row_kernel ? 1.15 : 1.0) : tiles <= 6 * 256 ? 0.95 : 0.75;
     // (the choice among the fp16 forms of both is made below)
     if (!always && !(f32 && half) && few_us(*p, Zq, L, row_bytes, k, f32) >= favour * others_us(Zq, L, row_bytes, k, f32, row_kernel, warm)) return false;
     // the second kernel: as many workgroups per query as give each wave one block of 16 labels, within what the chip holds

@@ -120,6 +120,12 @@ def test_few_queries_score_as_the_other_kernels_do_bf16(monkeypatch, Zq, L, d, k
     (512, 60000, 768, torch.bfloat16, 5, False, True),
     (1024, 98301, 768, torch.bfloat16, 50, False, False),         # enough tiles for the general kernel
     (2048, 24573, 2304, torch.bfloat16, 5, False, False),         # two blocks of queries in LDS only
+    (1257, 118938, 256, torch.bfloat16, 100, False, True),        # more tiles than six per compute unit: by the estimates all the same
+    (276, 652935, 1024, torch.bfloat16, 20, False, True),
+    (643, 361318, 128, torch.bfloat16, 20, False, True),
+    (690, 793300, 1024, torch.bfloat16, 20, False, False),
+    (235, 1200071, 96, torch.bfloat16, 50, False, True),          # up to 256 queries from scratch
+    (256, 10000000, 128, torch.bfloat16, 50, True, True),         # from thresholds, long label ranges
     (256, 100000, 768, torch.float32, 50, True, True),            # fp32 up to 256 queries
     (1024, 60000, 300, torch.float32, 32, False, True),
     (1024, 70000, 2304, torch.float32, 5, False, False),
