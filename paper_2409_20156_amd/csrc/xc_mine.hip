@@ -1460,7 +1460,8 @@ static bool rows_wide_items(int64_t Zq) {
 // Which fp32 searches run on fp16 copies, of those that the search of few queries does not take: by estimates of both times in us,
 // least squares over 150 searches of 416 to 65 536 queries, 1100 to 300 000 rows of 16 to 972 elements, k = 5 to 128 (within a
 // seventh for half of them).  What the copies save is fp32 products; what they cost is per query: thresholds, lists, scores formed
-// again.  With a sixth in favour of the fp32 kernels no search is slower than with them (of the 150), and 4 % are lost over always choosing right.
+// again.  With a sixth in favour of the fp32 kernels none of the 150 is slower than with them, and 4 % are lost over always choosing right;
+// rows that make most lists run over pay for both (all rows equal 1.05 to 1.1 times the fp32 kernels' time, in hundreds of copies each 1.7).
 // fp32 : copies in ms, 10 240 queries x 131 072 x 768, k = 64 15.1 : 3.0, from thresholds 14.4 : 2.6; 4096 x 1.3 M x 256, k = 100
 // 19.6 : 3.8; 20 000 x 300 000 x 300, k = 32 33.7 : 5.0; 2500 x 4 M x 64, k = 50 12.1 : 3.2; 60 000 x 9000 x 300, k = 8 4.0 : 2.3; the
 // other way 60 000 x 4096 x 64, k = 100 0.88 : 1.84; 20 000 x 4096 x 300, k = 100 0.95 : 0.74.  Below 2048 labels there is no dense phase to find

@@ -1,7 +1,7 @@
 // The search for few queries: the same exact top-k as xc_mine.hip (score of Sec. 2.1) where the work is
 // reading W once, not the products.  Inference over a handful of queries, small pools.
 //
-//   few_line_kernel    streams W once (few_max_kernel rows of under 128 bytes and very long ones; few_half_kernel
+//   few_line_kernel    streams W once (few_max_kernel where rows are short or LDS is, see few_lines; few_half_kernel
 //       more than 16 fp32 queries).  A wave multiplies 32 labels with all queries of the workgroup, whose rows
 //       lie in LDS as MFMA operands, and keeps of every group of 16 << gshift labels the largest score per
 //       query: the only thing written, 1 / (16 << gshift) of the score matrix.
